@@ -5,22 +5,20 @@
 // the layout the INT8 matrix instructions want: every lane supplies 16 consecutive bytes of one row.
 //
 // Two kernels, same results (integer accumulation is exact, so tiling and order cannot matter):
-//   - gemm_i8_ring_kernel, the fast path: 16-byte aligned operands, K a multiple of 128, any T (edge tiles
-//     read clamped rows and drop the surplus outputs).  512 threads = 8 waves in a 2 x 4 arrangement, each
-//     wave owning 128 x 64 = 8 x 4 MFMA tiles of 16 x 16 (128 accumulator registers); operands go from
-//     global memory straight into a five-slot LDS ring (described at the kernel); one block per CU walks over
+//   - gemm_i8_ring_kernel, here, for layers that fill the chip with large tiles: 16-byte aligned operands, K a
+//     multiple of 128, any T (edge tiles read clamped rows and drop the surplus outputs).  512 threads = 8 waves in a
+//     2 x 4 arrangement, each wave owning 128 x 64 = 8 x 4 MFMA tiles of 16 x 16 (128 accumulator registers); operands go
+//     from global memory straight into a five-slot LDS ring (described at the kernel); one block per CU walks over
 //     several tiles, requesting the next tile's first operands before it scales and stores the current one, and
 //     the results leave straight from the accumulator registers (8 bytes per lane, whole 128-byte lines per
 //     16 lanes); a last round of tiles that is at most half full runs as 256 x 128 half tiles;
-//   - gemm_i8_kernel<true>, any shape and alignment: 256 threads = 4 waves in a 2 x 2 arrangement
-//     (128 x 128 per wave), two LDS stages of (256 + 256) rows x 128 B = 128 KiB; the next K step
-//     is fetched into registers (bounds-checked) while the current one is multiplied, then stored
-//     to the other stage: one barrier per K step.
-// Common to both:
+//   - gemm_i8_staged_kernel (cq_gemm_staged.hip): smaller tiles with the contraction split inside a block, for few
+//     tokens or small outputs, and any shape and alignment.
+// The ring kernel:
 //   - block tile 256 x 256, K step 128 bytes;
 //   - LDS rows are 128 B = 8 chunks of 16 B, stored at chunk ^ ((row >> 1) & 7) so that the 16
 //     rows a quarter-wave reads (and the row pairs it writes) fall in 16 distinct bank groups of the
-//     64-bank LDS (the ring kernel's weight tile differs in one detail, see its loader);
+//     64-bank LDS (the weight tile differs in one detail, see its loader);
 //   - block -> tile mapping: consecutive block ids land on different XCDs, so ids are first
 //     de-interleaved by XCD (each XCD gets a contiguous range of tiles, hence its own L2 sees a
 //     compact patch), then walked in groups of 4 tile-rows so that concurrently resident tiles
@@ -34,149 +32,6 @@ namespace cq {
 namespace {
 
 constexpr int BK = 128;
-constexpr int kThreads = 256;
-constexpr int kStageBytes = (BM + BN) * BK;       // 64 KiB
-constexpr int kLdsBytes = 2 * kStageBytes;         // 128 KiB
-
-__device__ __forceinline__ int swz(int row, int chunk) { return (chunk ^ ((row >> 1) & 7)) * 16; }
-
-// one 16-byte chunk of row `row`, bytes [kb, kb+16) of an int8 matrix with `ld` = I bytes per row
-template <bool GENERIC>
-__device__ __forceinline__ v4i load_chunk(const int8_t* __restrict__ base, int row, int nrows, int kb, int I,
-                                          bool vec) {
-    v4i v = {0, 0, 0, 0};
-    if (!GENERIC) {
-        v = *reinterpret_cast<const v4i*>(base + (int64_t)row * I + kb);
-    } else if (row < nrows && kb < I) {
-        const int8_t* p = base + (int64_t)row * I + kb;
-        if (vec && kb + 16 <= I) {
-            v = *reinterpret_cast<const v4i*>(p);
-        } else {
-            uint32_t w[4] = {0u, 0u, 0u, 0u};
-            for (int e = 0; e < 16; ++e)
-                if (kb + e < I) w[e >> 2] |= (uint32_t)(uint8_t)p[e] << (8 * (e & 3));
-            v = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-        }
-    }
-    return v;
-}
-
-template <bool GENERIC>
-__global__ void __launch_bounds__(kThreads)
-gemm_i8_kernel(const int8_t* __restrict__ qx, const float* __restrict__ row_scale, const int8_t* __restrict__ qw,
-               const float* __restrict__ w_scale, int T, int I, int O, uint16_t* __restrict__ Y, int64_t ldy,
-               int32_t* __restrict__ acc_debug, int tiles_m, int tiles_n, bool vec) {
-    extern __shared__ __align__(16) int8_t lds[];
-
-    // ---- block id -> tile
-    const int total = tiles_m * tiles_n;
-    const int per_xcd = (total + kXcds - 1) / kXcds;
-    const int L = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-    if (L >= total) return;                        // whole block leaves before any barrier
-    const int group_sz = kGroupM * tiles_n;
-    const int g = L / group_sz;
-    const int gm = min(kGroupM, tiles_m - g * kGroupM);
-    const int in_g = L - g * group_sz;
-    const int tile_m = g * kGroupM + in_g % gm;
-    const int tile_n = in_g / gm;
-    const int m0 = tile_m * BM, n0 = tile_n * BN;
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-
-    // ---- global -> LDS staging: thread handles chunk (tid & 7) of rows (tid >> 3) + 32 * i
-    const int ld_chunk = tid & 7;
-    const int ld_row = tid >> 3;
-    const int nk = (I + BK - 1) / BK;
-
-    v4i ga[8], gb[8];
-    auto fetch = [&](int kt) {
-        const int kb = kt * BK + ld_chunk * 16;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int r = ld_row + 32 * i;
-            ga[i] = load_chunk<GENERIC>(qx, m0 + r, T, kb, I, vec);
-            gb[i] = load_chunk<GENERIC>(qw, n0 + r, O, kb, I, vec);
-        }
-    };
-    auto stash = [&](int stage) {
-        int8_t* As = lds + stage * kStageBytes;
-        int8_t* Bs = As + BM * BK;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int r = ld_row + 32 * i;
-            *reinterpret_cast<v4i*>(As + r * BK + swz(r, ld_chunk)) = ga[i];
-            *reinterpret_cast<v4i*>(Bs + r * BK + swz(r, ld_chunk)) = gb[i];
-        }
-    };
-
-    v16i acc[4][4];
-#pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < 4; ++ni)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0;
-
-    fetch(0);
-    stash(0);
-    __syncthreads();
-
-    const int frag_row = lane & 31;     // row of the 32-row MFMA tile this lane supplies
-    const int frag_half = lane >> 5;    // which 16-byte half of the 32-byte K slab
-
-    for (int kt = 0; kt < nk; ++kt) {
-        const bool more = (kt + 1 < nk);
-        if (more) fetch(kt + 1);
-        const int8_t* As = lds + (kt & 1) * kStageBytes;
-        const int8_t* Bs = As + BM * BK;
-#pragma unroll
-        for (int ks = 0; ks < BK / 32; ++ks) {
-            v4i af[4], bf[4];
-            const int chunk = ks * 2 + frag_half;
-#pragma unroll
-            for (int mi = 0; mi < 4; ++mi) {
-                const int r = wm * 128 + mi * 32 + frag_row;
-                af[mi] = *reinterpret_cast<const v4i*>(As + r * BK + swz(r, chunk));
-            }
-#pragma unroll
-            for (int ni = 0; ni < 4; ++ni) {
-                const int r = wn * 128 + ni * 32 + frag_row;
-                bf[ni] = *reinterpret_cast<const v4i*>(Bs + r * BK + swz(r, chunk));
-            }
-#pragma unroll
-            for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < 4; ++ni)
-                    acc[mi][ni] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[mi], bf[ni], acc[mi][ni], 0, 0, 0);
-        }
-        if (more) stash((kt + 1) & 1);
-        __syncthreads();
-    }
-
-    // ---- epilogue: accumulator register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32
-#pragma unroll
-    for (int mi = 0; mi < 4; ++mi) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = m0 + wm * 128 + mi * 32 + 8 * (r >> 2) + 4 * frag_half + (r & 3);
-            if (GENERIC && row >= T) continue;
-            const float a = row_scale[row];
-#pragma unroll
-            for (int ni = 0; ni < 4; ++ni) {
-                const int col = n0 + wn * 128 + ni * 32 + frag_row;
-                if (GENERIC && col >= O) continue;
-                const int v = acc[mi][ni][r];
-                float y = (float)v * a;
-                y = rounded_f32(y * w_scale[col]);
-                Y[(int64_t)row * ldy + col] = (uint16_t)f2h(y);
-                if (acc_debug) acc_debug[(int64_t)row * O + col] = v;
-            }
-        }
-    }
-}
-
 
 // ---------------------------------------------------------------------------------------------
 // Fast path (full tiles, 16-byte aligned operands): global -> LDS loads that bypass registers.
@@ -550,52 +405,47 @@ hipError_t launch_w8a8_linear(const int8_t* qx, const float* row_scale, const in
     const int tiles_m = (T + BM - 1) / BM, tiles_n = (O + BN - 1) / BN;
     if (!grid_fits((int64_t)tiles_m * tiles_n + kXcds, 512)) return hipErrorInvalidValue;
     const int total = tiles_m * tiles_n;
-    const int per_xcd = (total + kXcds - 1) / kXcds;
-    const dim3 grid((unsigned)(per_xcd * kXcds)), block(kThreads);
-    const bool vec = (reinterpret_cast<uintptr_t>(qx) % 16 == 0) && (reinterpret_cast<uintptr_t>(qw) % 16 == 0) &&
-                     (I % 16 == 0);
+    int n_cu = 0, dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
+        n_cu = 256;
+    // One block fills a CU, so the tiles run in rounds of n_cu.  A last round that is at most half full is
+    // run as half tiles (256 x 128) instead, which spreads it over twice as many CUs: 2048 x 4096 x 11008
+    // has 344 tiles = 1.34 rounds of 256 and took 2 tile times; the 88 tiles of its last round now take
+    // 176 CUs for about 0.6 of a tile time.
+    const int rem = total % n_cu;
+    const int n_main = (rem > 0 && 2 * rem <= n_cu) ? total - rem : total;
     auto al16 = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
-    // fast path: K a multiple of the K step and everything the vector loads/stores touch aligned to 16
+    // ring kernel: K a multiple of the K step and everything the vector loads/stores touch aligned to 16
     // bytes (any T; O a multiple of 8)
-    // (the fast path's epilogue addresses a wave's 128 output rows with 32-bit byte offsets)
-    const bool full = vec && (I % BK == 0) && (O % 8 == 0) && al16(Y) && (ldy % 8 == 0) && al16(w_scale) &&
-                      al16(acc_debug) && ldy < ((int64_t)1 << 22);
-    hipError_t e;
-    if (full) {
-        // four instances: with or without the raw accumulators, Y streamed to memory or left in the caches
-        using kernel_t = void (*)(const int8_t*, const float*, const int8_t*, const float*, int, int, int, uint16_t*,
-                                  int64_t, int32_t*, int, int, int);
-        static const kernel_t kernels[4] = {&gemm_i8_ring_kernel<false, false>, &gemm_i8_ring_kernel<false, true>,
-                                            &gemm_i8_ring_kernel<true, false>, &gemm_i8_ring_kernel<true, true>};
-        static std::atomic<uint64_t> lds_allowed[4];
-        const int which = (acc_debug ? 2 : 0) + (y_stays_cached(T, O) ? 0 : 1);
-        const kernel_t kernel = kernels[which];
-        e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), kRingLds, lds_allowed[which]);
-        if (e != hipSuccess) return e;
-        // One block fills a CU, so the tiles run in rounds of n_cu.  A last round that is at most half full is
-        // run as half tiles (256 x 128) instead, which spreads it over twice as many CUs: 2048 x 4096 x 11008
-        // has 344 tiles = 1.34 rounds of 256 and took 2 tile times; the 88 tiles of its last round now take
-        // 176 CUs for about 0.6 of a tile time.
-        int n_cu = 0, dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
-            n_cu = 256;
-        const int rem = total % n_cu;
-        const int n_main = (rem > 0 && 2 * rem <= n_cu) ? total - rem : total;
-        const int main_blocks = ((n_main + kXcds - 1) / kXcds) * kXcds;
-        const int half_blocks = ((2 * (total - n_main) + kXcds - 1) / kXcds) * kXcds;
-        // one block per CU (a multiple of the XCD count), fewer when there are fewer tiles than that
-        const int cu_blocks = n_cu >= kXcds ? n_cu / kXcds * kXcds : kXcds;
-        const int blocks = std::min(cu_blocks, std::max(main_blocks, half_blocks));
-        kernel<<<dim3((unsigned)blocks), dim3(512), kRingLds, stream>>>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy,
-                                                                        acc_debug, tiles_m, tiles_n, n_main);
-    } else {
-        static std::atomic<uint64_t> lds_allowed{0};
-        e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_i8_kernel<true>), kLdsBytes, lds_allowed);
-        if (e != hipSuccess) return e;
-        gemm_i8_kernel<true><<<grid, block, kLdsBytes, stream>>>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy,
-                                                                 acc_debug, tiles_m, tiles_n, vec);
-    }
+    // (the epilogue addresses a wave's 128 output rows with 32-bit byte offsets)
+    const bool ring_ok = al16(qx) && al16(qw) && (I % BK == 0) && (O % 8 == 0) && al16(Y) && (ldy % 8 == 0) && al16(w_scale) &&
+                         al16(acc_debug) && ldy < ((int64_t)1 << 22);
+    // The smaller tiles of cq_gemm_staged.hip where they cover the layer in less of their own measure (rounds x rows a
+    // CU takes in per step): a round of half tiles counts as 240 there, one of whole tiles as 500.  At the line, us:
+    // 128 x 8192 x 28672 (256 : 240) 57.3 against 61.4 for the ring, 1024 x 4096 x 4096 (256 : 240) 26.3 : 24.8,
+    // 512 x 4096 x 4096 (192 : 240) 16.1 : 24.0, 64 x 8192 x 28672 (192 : 240) 53.5 : 60.6, 256 x 4096 x 11008 (256 : 240)
+    // 24.6 : 23.5.
+    const int64_t ring_cost = (int64_t)((n_main + n_cu - 1) / n_cu) * 500 + (n_main < total ? 240 : 0);
+    if (!ring_ok || w8a8_staged_cost(qx, qw, T, I, O, n_cu) < ring_cost)
+        return launch_w8a8_staged(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, n_cu, stream);
+    // four instances: with or without the raw accumulators, Y streamed to memory or left in the caches
+    using kernel_t = void (*)(const int8_t*, const float*, const int8_t*, const float*, int, int, int, uint16_t*,
+                              int64_t, int32_t*, int, int, int);
+    static const kernel_t kernels[4] = {&gemm_i8_ring_kernel<false, false>, &gemm_i8_ring_kernel<false, true>,
+                                        &gemm_i8_ring_kernel<true, false>, &gemm_i8_ring_kernel<true, true>};
+    static std::atomic<uint64_t> lds_allowed[4];
+    const int which = (acc_debug ? 2 : 0) + (y_stays_cached(T, O) ? 0 : 1);
+    const kernel_t kernel = kernels[which];
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), kRingLds, lds_allowed[which]);
+    if (e != hipSuccess) return e;
+    const int main_blocks = ((n_main + kXcds - 1) / kXcds) * kXcds;
+    const int half_blocks = ((2 * (total - n_main) + kXcds - 1) / kXcds) * kXcds;
+    // one block per CU (a multiple of the XCD count), fewer when there are fewer tiles than that
+    const int cu_blocks = n_cu >= kXcds ? n_cu / kXcds * kXcds : kXcds;
+    const int blocks = std::min(cu_blocks, std::max(main_blocks, half_blocks));
+    kernel<<<dim3((unsigned)blocks), dim3(512), kRingLds, stream>>>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug,
+                                                                    tiles_m, tiles_n, n_main);
     return hipGetLastError();
 }
 

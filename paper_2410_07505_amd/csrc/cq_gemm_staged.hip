@@ -1,0 +1,358 @@
+// W8A8 linear layer for few tokens, small outputs and any layout: output tiles from 16 x 16 to 128 x 128 whose
+// contraction is split over the waves of a block.
+//
+// The ring kernel (cq_gemm.hip) works on 256 x 256 tiles: at 16 tokens it multiplies 240 rows of padding, and a
+// 256 x 4096 output gives it 32 half tiles for 256 CUs.  Here a block's 8 waves are WM x WN wave tiles of 16 MT tokens x
+// 16 NT channels times WK shares of the contraction; the WK partial sums (int32, so their order cannot matter) meet in
+// LDS at the end.  The tile is chosen so that one round of blocks covers the chip (launch_w8a8_staged).
+// What bounds it: a CU takes in about 28 bytes per clock from its L2, whatever is in flight (128 x 128 tiles with a
+// 3-slot and a 4-slot ring run alike; 64 and 256 active CUs run alike), so a step costs (TM + TN) x 128 bytes of that;
+// a decode step of a large layer is bound by the weights' way from HBM.
+#include <algorithm>
+
+#include "cq_gemm_common.h"
+
+namespace cq {
+namespace {
+
+constexpr int kSplitWaves = 8;
+
+// 16 bytes at p, any alignment
+__device__ __forceinline__ v4i load16(const int8_t* p) {
+    v4i v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+// bytes [kb, kb + 16) of a row of I >= 16 bytes, bytes past the row's end as zero; nothing outside the row is read
+__device__ __forceinline__ v4i load16_tail(const int8_t* row, int kb, int I) {
+    const int at = min(kb, I - 16), sh = kb - at;
+    unsigned __int128 w = __builtin_bit_cast(unsigned __int128, load16(row + at));
+    w = sh >= 16 ? 0 : w >> (8 * (sh & 15));
+    return __builtin_bit_cast(v4i, w);
+}
+
+// The end of a tile: the WK partial sums of every accumulator meet in LDS (parts: [wk][wm][wn][mi][ni][lane]), are
+// scaled and stored.  Weight tile ni of a wave holds the channels NT fr + ni (fr = lane & 15) of the wave's 16 NT.
+// vec_out: every lane's NT channels exist or not together and their 2 NT bytes of Y are aligned.
+template <int MT, int NT, int WM, int WN, int WK>
+__device__ __forceinline__ void sum_and_store(const v4i (&acc)[MT][NT], v4i* parts, int wave, int lane,
+                                              const float* __restrict__ row_scale, const float* __restrict__ w_scale, int T,
+                                              int O, uint16_t* __restrict__ Y, int64_t ldy, int32_t* __restrict__ acc_debug,
+                                              int m0, int n0, bool vec_out) {
+#pragma unroll
+    for (int mi = 0; mi < MT; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NT; ++ni) parts[((wave * MT + mi) * NT + ni) * 64 + lane] = acc[mi][ni];
+    __syncthreads();
+    // A unit is two tokens x NT channels: accumulator registers 2 h, 2 h + 1 of lane l of the tiles (mi, 0 .. NT - 1) of
+    // wave position w.  Lane l holds channel l & 15 of a weight tile and, in register r, token 4 (l >> 4) + r.
+    constexpr int kUnits = WM * WN * MT * 64 * 2;
+    for (int u = threadIdx.x; u < kUnits; u += 64 * kSplitWaves) {
+        const int l = u & 63, h = (u >> 6) & 1, mi = (u >> 7) % MT, w = (u >> 7) / MT;
+        int2 sum[NT];
+#pragma unroll
+        for (int ni = 0; ni < NT; ++ni) sum[ni] = make_int2(0, 0);
+#pragma unroll
+        for (int p = 0; p < WK; ++p)
+#pragma unroll
+            for (int ni = 0; ni < NT; ++ni) {
+                const int2 v = *reinterpret_cast<const int2*>(
+                    reinterpret_cast<const int8_t*>(parts + (((p * WM * WN + w) * MT + mi) * NT + ni) * 64 + l) + 8 * h);
+                sum[ni].x += v.x;
+                sum[ni].y += v.y;
+            }
+        const int col = n0 + ((w % WN) * 16 + (l & 15)) * NT;
+        const int row = m0 + (w / WN) * 16 * MT + 16 * mi + 4 * (l >> 4) + 2 * h;
+        if (col >= O) continue;
+        float s[NT];
+#pragma unroll
+        for (int ni = 0; ni < NT; ++ni) s[ni] = w_scale[min(col + ni, O - 1)];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            if (row + r >= T) break;
+            const float a = row_scale[row + r];
+            float y[NT];
+#pragma unroll
+            for (int ni = 0; ni < NT; ++ni) {
+                y[ni] = (float)(r ? sum[ni].y : sum[ni].x) * a;
+                y[ni] = rounded_f32(y[ni] * s[ni]);
+            }
+            uint16_t* dst = Y + (int64_t)(row + r) * ldy + col;
+            if (NT == 4 && vec_out) {
+                *reinterpret_cast<uint2*>(dst) = make_uint2(pack_half2(y[0], y[1]), pack_half2(y[NT - 2], y[NT - 1]));
+            } else if (NT == 2 && vec_out) {
+                *reinterpret_cast<uint32_t*>(dst) = pack_half2(y[0], y[NT - 1]);
+            } else {
+#pragma unroll
+                for (int ni = 0; ni < NT; ++ni)
+                    if (col + ni < O) dst[ni] = (uint16_t)f2h(y[ni]);
+            }
+            if (acc_debug) {
+#pragma unroll
+                for (int ni = 0; ni < NT; ++ni)
+                    if (col + ni < O) acc_debug[(int64_t)(row + r) * O + col + ni] = r ? sum[ni].y : sum[ni].x;
+            }
+        }
+    }
+}
+
+// A step is 64 WK contraction bytes; wave share wk multiplies slab wk of it.  A slot holds one step:
+// [WK / 2][TM + TN rows][128 bytes], chunk c of row R at chunk c ^ ((R >> 1) & 7), so that the 16 rows a fragment read
+// covers fall on distinct banks.  LDS row 16 ni + f of a wave's weight rows holds its channel NT f + ni (the loader picks
+// the rows; a request covers whole 128-byte lines of 8 rows).
+// At step kt the fragments of kt are in registers; behind the step's barrier slot kt % S is free (step kt + S is
+// requested into it) and step kt + 1 has landed (its fragments are read while kt is multiplied): one barrier a step.
+// DMA: operands aligned to 16 bytes with I % 16 == 0 go straight to LDS; pieces past a row's end come from a zero
+// block.  Otherwise (I >= 16) they pass through registers, loaded unaligned one step before they are stored: 512 x 2752 x
+// 4096 takes 14.3 us in the first form, and 19.8 to 21.2 us with I = 2760, 2756, 2754, 2753 in the second.
+__device__ const uint4 g_zero_piece = {0u, 0u, 0u, 0u};
+
+// One request: every lane's 16 bytes at src go to LDS at dst + 16 * lane, counted by vmcnt.  (Inline assembly, as in the
+// FP6 kernel: after the compiler's builtin every LDS read waits for all such requests.)
+__device__ __forceinline__ void request_1k(const int8_t* src, const int8_t* dst) {
+    const uint32_t lds_off = (uint32_t)(uintptr_t)((lptr_t)dst);     // wave-uniform
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc0" : : "v"(src), "s"(lds_off) : "m0");
+}
+
+template <int MT, int NT, int WM, int WN, int WK, int S, bool DMA>
+__global__ void __launch_bounds__(64 * kSplitWaves)
+gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ row_scale, const int8_t* __restrict__ qw,
+                      const float* __restrict__ w_scale, int T, int I, int O, uint16_t* __restrict__ Y, int64_t ldy,
+                      int32_t* __restrict__ acc_debug, int tiles_m, int total, bool vec_out) {
+    static_assert(WM * WN * WK == kSplitWaves && WK % 2 == 0, "8 waves, whole 128-byte lines");
+    constexpr int TM = 16 * MT * WM, TN = 16 * NT * WN, kRows = TM + TN;
+    constexpr int kStepK = 64 * WK, kSlot = kRows * kStepK;
+    constexpr int N = kSlot / 1024 / kSplitWaves;             // 1 KiB requests per wave and step
+    static_assert(N * 1024 * kSplitWaves == kSlot, "the waves share a step evenly");
+    extern __shared__ __align__(16) int8_t lds[];
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = wave % (WM * WN), wk = wave / (WM * WN);
+    const int wm = w / WN, wn = w % WN;
+    const int fr = lane & 15, chunk = lane >> 4;
+    const int nk = (I + kStepK - 1) / kStepK;
+    // A request holds its wave for about 100 cycles: waves 0-3 (one per SIMD) request before they multiply and
+    // waves 4-7 after, so that one wave of every SIMD multiplies meanwhile.
+    const bool early = wave < 4;
+
+    const int per_xcd = (total + kXcds - 1) / kXcds;
+    for (int i = blockIdx.x / kXcds; i < per_xcd; i += gridDim.x / kXcds) {
+        const int L = (blockIdx.x % kXcds) * per_xcd + i;
+        if (L >= total) break;                                // block-uniform
+        const int tile_n = L / tiles_m;
+        const int m0 = (L - tile_n * tiles_m) * TM, n0 = tile_n * TN;
+
+        // request n of this wave fills LDS rows 8 g .. 8 g + 7 of a slot, g = wave N + n; lane l's 16 bytes are physical
+        // chunk l & 7 of row 8 g + (l >> 3)
+        const int8_t* src[N];
+        int kb[N];                                            // first contraction byte of the lane's piece in step 0
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            const int g = wave * N + n, R_all = 8 * g + (lane >> 3);
+            const int sub = R_all / kRows, R = R_all % kRows;
+            kb[n] = sub * 128 + (((lane & 7) ^ ((R >> 1) & 7)) * 16);
+            if (R < TM) {
+                src[n] = qx + (int64_t)min(m0 + R, T - 1) * I;
+            } else {
+                const int b = R - TM, grp = b / (16 * NT), in = b % (16 * NT);
+                src[n] = qw + (int64_t)min(n0 + grp * 16 * NT + NT * (in & 15) + (in >> 4), O - 1) * I;
+            }
+        }
+        v4i reg[DMA ? 1 : N];
+        auto request = [&](int kt, int slot) {                // DMA: straight to LDS; else into registers
+#pragma unroll
+            for (int n = 0; n < N; ++n) {
+                const int at = kt * kStepK + kb[n];
+                if (DMA) {
+                    const int8_t* p = at < I ? src[n] + at : reinterpret_cast<const int8_t*>(&g_zero_piece);
+                    request_1k(p, lds + slot * kSlot + (wave * N + n) * 1024);
+                } else if ((kt + 1) * kStepK <= I) {
+                    reg[DMA ? 0 : n] = load16(src[n] + at);
+                } else {
+                    reg[DMA ? 0 : n] = load16_tail(src[n], at, I);
+                }
+            }
+        };
+        auto commit = [&](int slot) {
+            if (DMA) return;
+#pragma unroll
+            for (int n = 0; n < N; ++n)
+                *reinterpret_cast<v4i*>(lds + slot * kSlot + (wave * N + n) * 1024 + lane * 16) = reg[DMA ? 0 : n];
+        };
+
+        struct Frags {
+            v4i a[MT], b[NT];
+        };
+        const int sub_base = (wk >> 1) * kRows * 128;
+        const int sw = (((wk & 1) * 4 + chunk) ^ ((fr >> 1) & 7)) * 16;
+        const int a_off = sub_base + (wm * 16 * MT + fr) * 128 + sw, b_off = sub_base + (TM + wn * 16 * NT + fr) * 128 + sw;
+        auto read = [&](Frags& f, int slot) {
+#pragma unroll
+            for (int ni = 0; ni < NT; ++ni) f.b[ni] = *reinterpret_cast<const v4i*>(lds + slot * kSlot + b_off + ni * 2048);
+#pragma unroll
+            for (int mi = 0; mi < MT; ++mi) f.a[mi] = *reinterpret_cast<const v4i*>(lds + slot * kSlot + a_off + mi * 2048);
+        };
+        v4i acc[MT][NT];
+#pragma unroll
+        for (int mi = 0; mi < MT; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NT; ++ni) acc[mi][ni] = v4i{0, 0, 0, 0};
+
+        // prologue: steps 0 .. S - 1 requested (register form: steps 0 .. S - 1 stored, step S in the registers)
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+            if (s < nk) {
+                request(s, s);
+                commit(s);
+            }
+        if (!DMA && S < nk) request(S, 0);
+        if (DMA) {
+            if (nk >= S) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 1) * N, 15));      // step 0 has landed
+            else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
+        } else {
+            __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
+        }
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        Frags f0, f1;
+        read(f0, 0);
+
+        int slot = 0;                                         // slot of step kt
+        auto step = [&](int kt, Frags& cur, Frags& nxt) {
+            // this wave's reads of step kt are done and its share of step kt + 1 has landed (steps kt + 2 .. kt + S - 1
+            // may still be in flight; near the end, where there are fewer, all of them)
+            if (DMA && kt + S - 1 < nk) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 2) * N, 0));
+            else if (DMA) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+            else __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            auto fetch = [&]() {
+                if (kt + S < nk) {
+                    if (DMA) {
+                        request(kt + S, slot);
+                    } else {
+                        commit(slot);
+                        if (kt + S + 1 < nk) request(kt + S + 1, 0);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            const int next_slot = slot + 1 == S ? 0 : slot + 1;
+            if (early) fetch();
+            if (kt + 1 < nk) read(nxt, next_slot);
+#pragma unroll
+            for (int mi = 0; mi < MT; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < NT; ++ni)
+                    acc[mi][ni] = __builtin_amdgcn_mfma_i32_16x16x64_i8(cur.a[mi], cur.b[ni], acc[mi][ni], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!early) fetch();
+            slot = next_slot;
+        };
+        for (int kt = 0; kt < nk; kt += 2) {
+            step(kt, f0, f1);
+            if (kt + 1 < nk) step(kt + 1, f1, f0);
+        }
+        __syncthreads();                                      // the ring is free: it holds the partial sums now
+        sum_and_store<MT, NT, WM, WN, WK>(acc, reinterpret_cast<v4i*>(lds), wave, lane, row_scale, w_scale, T, O, Y, ldy,
+                                          acc_debug, m0, n0, vec_out);
+        __syncthreads();
+    }
+}
+
+template <int MT, int NT, int WM, int WN, int WK, int S, bool DMA>
+hipError_t launch_staged(const int8_t* qx, const float* row_scale, const int8_t* qw, const float* w_scale, int T, int I,
+                         int O, uint16_t* Y, int64_t ldy, int32_t* acc_debug, hipStream_t stream) {
+    constexpr int TM = 16 * MT * WM, TN = 16 * NT * WN;
+    constexpr int kRing = S * (TM + TN) * 64 * WK, kParts = kSplitWaves * MT * NT * 64 * 16, kLds = kRing > kParts ? kRing : kParts;
+    const int tiles_m = (T + TM - 1) / TM;
+    const int64_t total = (int64_t)tiles_m * ((O + TN - 1) / TN);
+    if (total >= (int64_t)1 << 31) return hipErrorInvalidValue;
+    const bool vec_out = O % NT == 0 && ldy % NT == 0 && reinterpret_cast<uintptr_t>(Y) % (2 * NT) == 0;
+    static std::atomic<uint64_t> allowed{0};
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_i8_staged_kernel<MT, NT, WM, WN, WK, S, DMA>), kLds, allowed);
+    if (e != hipSuccess) return e;
+    const int64_t blocks = std::min<int64_t>((total + kXcds - 1) / kXcds * kXcds, (int64_t)1 << 20);
+    gemm_i8_staged_kernel<MT, NT, WM, WN, WK, S, DMA><<<dim3((unsigned)blocks), dim3(64 * kSplitWaves), kLds, stream>>>(
+        qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, tiles_m, (int)total, vec_out);
+    return hipGetLastError();
+}
+
+// Contractions shorter than one 16-byte piece: a thread per output.
+__global__ void __launch_bounds__(256)
+gemm_i8_short_kernel(const int8_t* __restrict__ qx, const float* __restrict__ row_scale, const int8_t* __restrict__ qw,
+                     const float* __restrict__ w_scale, int T, int I, int O, uint16_t* __restrict__ Y, int64_t ldy,
+                     int32_t* __restrict__ acc_debug) {
+    const int64_t n = (int64_t)T * O;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const int64_t r = i / O, k = i - r * O;
+        int v = 0;
+        for (int j = 0; j < I; ++j) v += (int)qx[r * I + j] * (int)qw[k * I + j];
+        float y = (float)v * row_scale[r];
+        y = rounded_f32(y * w_scale[k]);
+        Y[r * ldy + k] = (uint16_t)f2h(y);
+        if (acc_debug) acc_debug[i] = v;
+    }
+}
+
+}  // namespace
+
+// Tile kinds by what a CU has to take in for one 128-byte step of one tile (TM + TN rows).  The cost of a launch is the
+// rounds of tiles over the CUs times that; of equal ones the smaller tile is taken.  Measured at I = 4096 (us, best kind
+// first): 16 x 4096 5.5 (16 x 16), 6.3 (32 x 32), 8.4 (32 x 64); 64 x 4096 7.3 (32 x 32), 8.7 (32 x 64), 10.1 (64 x 64);
+// 64 x 11008 11.3 (64 x 64), 12.8 (32 x 64), 17.1 (32 x 32); 256 x 4096 10.9 (64 x 64), 12.1 (32 x 64), 14.8 (64 x 128);
+// 512 x 4096 16.1 (64 x 128), 19.8 (64 x 64), 23.3 (128 x 128); the rule picks the first of each.
+static const int kKinds[][2] = {{16, 16}, {32, 32}, {32, 64}, {64, 64}, {64, 128}, {128, 128}};
+constexpr int kNumKinds = 6;
+
+static bool staged_dma(const int8_t* qx, const int8_t* qw, int I) {
+    return reinterpret_cast<uintptr_t>(qx) % 16 == 0 && reinterpret_cast<uintptr_t>(qw) % 16 == 0 && I % 16 == 0;
+}
+
+static int best_kind(bool dma, int T, int O, int n_cu, int64_t* cost) {
+    int best = -1;
+    for (int k = 0; k < kNumKinds; ++k) {
+        if (k == 2 && !dma) continue;             // through registers this tile loses to its neighbours (512 x 2756 x 4096: 39 against 20 us)
+        const int tm = kKinds[k][0], tn = kKinds[k][1];
+        const int64_t tiles = (int64_t)((T + tm - 1) / tm) * ((O + tn - 1) / tn);
+        const int64_t c = (tiles + n_cu - 1) / n_cu * (tm + tn);
+        if (best < 0 || c < *cost) {
+            best = k;
+            *cost = c;
+        }
+    }
+    return best;
+}
+
+int64_t w8a8_staged_cost(const int8_t* qx, const int8_t* qw, int T, int I, int O, int n_cu) {
+    int64_t cost = 0;
+    best_kind(staged_dma(qx, qw, I), T, O, n_cu, &cost);
+    return cost;
+}
+
+hipError_t launch_w8a8_staged(const int8_t* qx, const float* row_scale, const int8_t* qw, const float* w_scale, int T, int I,
+                              int O, uint16_t* Y, int64_t ldy, int32_t* acc_debug, int n_cu, hipStream_t stream) {
+    if (I < 16) {
+        const int64_t blocks = std::min<int64_t>(((int64_t)T * O + 255) / 256, (int64_t)1 << 20);
+        gemm_i8_short_kernel<<<dim3((unsigned)blocks), dim3(256), 0, stream>>>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug);
+        return hipGetLastError();
+    }
+    const bool dma = staged_dma(qx, qw, I);
+    int64_t cost;
+    // the steps and slots of a kind: as much of the contraction per barrier, and as many slots, as the LDS allows
+    // (through registers shorter steps, which leave registers free, are better: 512 x 2752 x 4096 with 64 x 128 tiles,
+    // WK 2 against 4: 14.3 and 14.3 us straight to LDS, 20.9 and 83 us through registers)
+#define CQ_STAGED(MT, NT, WM, WN, WK, S, DMA) \
+    launch_staged<MT, NT, WM, WN, WK, S, DMA>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream)
+    switch (best_kind(dma, T, O, n_cu, &cost)) {
+        case 0: return dma ? CQ_STAGED(1, 1, 1, 1, 8, 4, true) : CQ_STAGED(1, 1, 1, 1, 8, 4, false);
+        case 1: return dma ? CQ_STAGED(2, 2, 1, 1, 8, 4, true) : CQ_STAGED(2, 2, 1, 1, 8, 4, false);
+        case 2: return CQ_STAGED(2, 2, 1, 2, 4, 3, true);
+        case 3: return dma ? CQ_STAGED(2, 4, 2, 1, 4, 4, true) : CQ_STAGED(2, 2, 2, 2, 2, 4, false);
+        case 4: return dma ? CQ_STAGED(4, 4, 1, 2, 4, 3, true) : CQ_STAGED(2, 4, 2, 2, 2, 4, false);
+        default: return dma ? CQ_STAGED(4, 4, 2, 2, 2, 3, true) : CQ_STAGED(4, 4, 2, 2, 2, 3, false);
+    }
+#undef CQ_STAGED
+}
+
+}  // namespace cq

@@ -132,6 +132,11 @@ hipError_t launch_w8a8_linear(const int8_t* qx, const float* row_scale, const in
                               const float* w_scale, int T, int I, int O, uint16_t* Y, int64_t ldy,
                               int32_t* acc_debug, hipStream_t stream);
 
+// The small-tile form of it, any layout; its cost in the measure launch_w8a8_linear compares (see there).
+int64_t w8a8_staged_cost(const int8_t* qx, const int8_t* qw, int T, int I, int O, int n_cu);
+hipError_t launch_w8a8_staged(const int8_t* qx, const float* row_scale, const int8_t* qw, const float* w_scale, int T, int I,
+                              int O, uint16_t* Y, int64_t ldy, int32_t* acc_debug, int n_cu, hipStream_t stream);
+
 // CrossQuant step inside the GEMM's activation load (X binary16 -> Y, no codes in memory); a, b receive the factors.
 hipError_t launch_quantize_linear(const uint16_t* X, int T, int I, int64_t ldx, const float* t, const float* c,
                                   float alpha, int bits, float* a, float* b, const int8_t* qw, const float* w_scale,

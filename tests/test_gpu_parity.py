@@ -1006,6 +1006,64 @@ def test_linear_blocks_walk_several_tiles(cq, T, I, O):
     assert np.array_equal(host(acc), acc_ref) and np.array_equal(bits16(host(Y2)), bits16(Y_ref))
 
 
+# (T, O) for which the launcher takes, on 256 CUs, tiles of 16 x 16, 32 x 32, 32 x 64 (32 x 32 through registers), 64 x 64,
+# 64 x 128 and 128 x 128, one short of or past a tile's edge; I: operands straight to LDS (multiples of 16: one short
+# step, several with a partial last one) and through registers (odd: one step, a last piece of 1, 3 and 15 bytes); and
+# contractions shorter than a piece.
+@pytest.mark.parametrize("I", [5, 16, 17, 1040, 2595, 2639])
+@pytest.mark.parametrize("T,O", [(15, 4093), (63, 4090), (127, 4096), (250, 4081), (505, 4088), (1000, 4100)])
+def test_linear_tiles_that_split_the_contraction(cq, T, O, I):
+    import torch
+    say("linear, split contraction: T=%d I=%d O=%d" % (T, I, O))
+    qx, qw = workloads.int8_codes(T, I, seed=T + I), workloads.int8_codes(O, I, seed=O + I)
+    rng = np.random.default_rng(T + O + I)
+    a = rng.uniform(1e-3, 1e-1, T).astype(np.float32)
+    s = rng.uniform(1e-5, 1e-3, O).astype(np.float32)
+    Y_ref, acc_ref = oracle.w8a8_linear(qx, a, qw, s)
+    gx, ga, gw, gs = gpu(qx), gpu(a), gpu(qw), gpu(s)
+    for ldy in (O, O + 3):                         # aligned rows where O is; never aligned
+        buf = torch.full((T + 2, ldy), 7.0, dtype=torch.float16, device="cuda")
+        accbuf = torch.full((T + 2, O), -5, dtype=torch.int32, device="cuda")
+        cq.crossquant_w8a8_linear(gx, ga, gw, gs, Y=buf[:T, :O], acc_debug=accbuf[:T])
+        out, acc = host(buf), host(accbuf)
+        assert np.array_equal(acc[:T], acc_ref) and np.all(acc[T:] == -5)
+        assert np.array_equal(bits16(out[:T, :O]), bits16(Y_ref))
+        assert np.all(out[:T, O:] == 7.0) and np.all(out[T:] == 7.0)
+
+
+def test_linear_operands_that_start_off_a_16_byte_boundary(cq):
+    """Codes that begin one byte into their buffer: rows of 256 bytes, none of them aligned."""
+    import torch
+    T, I, O = 70, 256, 520
+    qx, qw = workloads.int8_codes(T, I, seed=31), workloads.int8_codes(O, I, seed=32)
+    a, s = np.full(T, 0.01, np.float32), np.full(O, 0.001, np.float32)
+    Y_ref, acc_ref = oracle.w8a8_linear(qx, a, qw, s)
+
+    def shifted(m):
+        flat = torch.zeros(m.size + 1, dtype=torch.int8, device="cuda")
+        flat[1:] = gpu(m).flatten()
+        return flat[1:].view(m.shape)
+    Y, acc = cq.crossquant_w8a8_linear(shifted(qx), gpu(a), shifted(qw), gpu(s), want_acc=True)
+    assert np.array_equal(host(acc), acc_ref) and np.array_equal(bits16(host(Y)), bits16(Y_ref))
+
+
+@pytest.mark.parametrize("T,I,O", [(1100, 128, 4104),      # 85 tiles run as halves; the last tile column is 8 wide, its second halves empty
+                                   (700, 256, 7176)])      # 87 tiles, ragged on both edges
+def test_linear_ring_kernel_on_ragged_half_tiles(cq, T, I, O):
+    import torch
+    say("linear, ragged half tiles: T=%d I=%d O=%d" % (T, I, O))
+    qx, qw = workloads.int8_codes(T, I, seed=T), workloads.int8_codes(O, I, seed=O)
+    rng = np.random.default_rng(T + O)
+    a = rng.uniform(1e-3, 1e-1, T).astype(np.float32)
+    s = rng.uniform(1e-5, 1e-3, O).astype(np.float32)
+    Y_ref, acc_ref = oracle.w8a8_linear(qx, a, qw, s)
+    buf = torch.full((T + 20, O + 8), 7.0, dtype=torch.float16, device="cuda")
+    cq.crossquant_w8a8_linear(gpu(qx), gpu(a), gpu(qw), gpu(s), Y=buf[:T, :O])
+    out = host(buf)
+    assert np.array_equal(bits16(out[:T, :O]), bits16(Y_ref))
+    assert np.all(out[:T, O:] == 7.0) and np.all(out[T:] == 7.0)
+
+
 def test_linear_extreme_accumulators(cq):
     say("linear extremes")
     T, I, O = 256, 8192, 256
