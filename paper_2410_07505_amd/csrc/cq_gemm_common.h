@@ -140,5 +140,89 @@ __device__ __forceinline__ void epilogue16_store(ACC (&acc)[8][G], float* a_lds,
     }
 }
 
+// ---- Pieces of the kernels with small tiles (8 waves whose contraction shares meet in LDS).
+constexpr int kSplitWaves = 8;
+
+// what requests for pieces past the contraction's end read
+__device__ const uint4 g_zero_piece = {0u, 0u, 0u, 0u};
+
+// One request: every lane's 16 bytes at src go to LDS at dst + 16 * lane (1 KiB per wave), without passing through
+// registers; completion is counted by vmcnt.  Written as inline assembly rather than with the compiler's builtin: for
+// the builtin the compiler makes every later LDS read wait until all such requests have landed (it cannot tell that the
+// ring's slots differ), which would serialise requests made steps ahead with the reads of the current step.  The kernels
+// order reads and in-flight writes themselves (slot discipline, explicit vmcnt waits, barriers).
+__device__ __forceinline__ void request_1k(const void* src, const int8_t* dst) {
+    const uint32_t lds_off = (uint32_t)(uintptr_t)((lptr_t)dst);     // wave-uniform
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc0" : : "v"(src), "s"(lds_off) : "m0");
+}
+
+// The end of a tile: the WK partial sums of every accumulator meet in LDS (parts: [wk][wm][wn][mi][ni][lane]), are
+// scaled and stored.  Weight tile ni of a wave holds the channels NT fr + ni (fr = lane & 15) of the wave's 16 NT.
+// vec_out: every lane's NT channels exist or not together and their 2 NT bytes of Y are aligned.
+// V: four int32 or four binary32 values (sums of the FP6 products are integers below 2^24, exact in any order).
+template <int MT, int NT, int WM, int WN, int WK, typename V>
+__device__ __forceinline__ void sum_and_store(const V (&acc)[MT][NT], V* parts, int wave, int lane,
+                                              const float* __restrict__ row_scale, const float* __restrict__ w_scale, int T,
+                                              int O, uint16_t* __restrict__ Y, int64_t ldy, int32_t* __restrict__ acc_debug,
+                                              int m0, int n0, bool vec_out) {
+#pragma unroll
+    for (int mi = 0; mi < MT; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NT; ++ni) parts[((wave * MT + mi) * NT + ni) * 64 + lane] = acc[mi][ni];
+    __syncthreads();
+    // A unit is two tokens x NT channels: accumulator registers 2 h, 2 h + 1 of lane l of the tiles (mi, 0 .. NT - 1) of
+    // wave position w.  Lane l holds channel l & 15 of a weight tile and, in register r, token 4 (l >> 4) + r.
+    constexpr int kUnits = WM * WN * MT * 64 * 2;
+    for (int u = threadIdx.x; u < kUnits; u += 64 * kSplitWaves) {
+        const int l = u & 63, h = (u >> 6) & 1, mi = (u >> 7) % MT, w = (u >> 7) / MT;
+        typedef decltype(acc[0][0][0] + acc[0][0][0]) elem;
+        elem sum[NT][2];
+#pragma unroll
+        for (int ni = 0; ni < NT; ++ni) sum[ni][0] = sum[ni][1] = 0;
+#pragma unroll
+        for (int p = 0; p < WK; ++p)
+#pragma unroll
+            for (int ni = 0; ni < NT; ++ni) {
+                typedef elem pair __attribute__((ext_vector_type(2)));
+                const pair v = *reinterpret_cast<const pair*>(
+                    reinterpret_cast<const int8_t*>(parts + (((p * WM * WN + w) * MT + mi) * NT + ni) * 64 + l) + 8 * h);
+                sum[ni][0] += v.x;
+                sum[ni][1] += v.y;
+            }
+        const int col = n0 + ((w % WN) * 16 + (l & 15)) * NT;
+        const int row = m0 + (w / WN) * 16 * MT + 16 * mi + 4 * (l >> 4) + 2 * h;
+        if (col >= O) continue;
+        float s[NT];
+#pragma unroll
+        for (int ni = 0; ni < NT; ++ni) s[ni] = w_scale[min(col + ni, O - 1)];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            if (row + r >= T) break;
+            const float a = row_scale[row + r];
+            float y[NT];
+#pragma unroll
+            for (int ni = 0; ni < NT; ++ni) {
+                y[ni] = (float)sum[ni][r] * a;
+                y[ni] = rounded_f32(y[ni] * s[ni]);
+            }
+            uint16_t* dst = Y + (int64_t)(row + r) * ldy + col;
+            if (NT == 4 && vec_out) {
+                *reinterpret_cast<uint2*>(dst) = make_uint2(pack_half2(y[0], y[1]), pack_half2(y[NT - 2], y[NT - 1]));
+            } else if (NT == 2 && vec_out) {
+                *reinterpret_cast<uint32_t*>(dst) = pack_half2(y[0], y[NT - 1]);
+            } else {
+#pragma unroll
+                for (int ni = 0; ni < NT; ++ni)
+                    if (col + ni < O) dst[ni] = (uint16_t)f2h(y[ni]);
+            }
+            if (acc_debug) {
+#pragma unroll
+                for (int ni = 0; ni < NT; ++ni)
+                    if (col + ni < O) acc_debug[(int64_t)(row + r) * O + col + ni] = (int)sum[ni][r];
+            }
+        }
+    }
+}
+
 }  // namespace
 }  // namespace cq

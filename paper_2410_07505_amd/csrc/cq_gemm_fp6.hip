@@ -100,21 +100,6 @@ __global__ void pack_fp6_kernel(const uint8_t* __restrict__ src, int R, int K, u
     *reinterpret_cast<uint2*>(f + kFragLo + lane * 8) = make_uint2(w[4], w[5]);
 }
 
-// ---- global -> LDS ------------------------------------------------------------------------------
-// One request: every lane's 16 bytes at `src` go to LDS at dst + 16 * lane (1 KiB per wave), without
-// passing through registers; completion is counted by vmcnt.  Written as inline assembly rather
-// than with the compiler's builtin: for the builtin the compiler makes every later LDS read wait
-// until all such requests have landed (it cannot tell that the ring's slots differ), which would
-// serialise the requests made two and three steps ahead with the reads of the current step.  The
-// kernel orders reads and in-flight writes itself (slot discipline, explicit vmcnt waits, barriers).
-__device__ __forceinline__ void dma_1k(const uint8_t* src, const int8_t* dst) {
-    const uint32_t lds_off = (uint32_t)(uintptr_t)((lptr_t)dst);     // wave-uniform
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc0"
-                 :
-                 : "v"(src), "s"(lds_off)
-                 : "m0");
-}
-
 // s_waitcnt vmcnt(n), lgkmcnt(0) for a wave-uniform n in [0, 12] (the instruction takes an immediate)
 __device__ __forceinline__ void wait_vmcnt_upto(int n) {
     switch (n) {
@@ -279,17 +264,17 @@ __device__ __forceinline__ void f6_tile(const uint8_t* __restrict__ qx6, const f
         int8_t* dst = lds + slot * kF6Slot + lw * (6 * 1024);
         const int64_t koff = (int64_t)kt * (2 * kFragBytes);
 #pragma unroll
-        for (int ii = 0; ii < 6; ++ii) dma_1k(src_b[ii] + koff, dst + ii * 1024);
+        for (int ii = 0; ii < 6; ++ii) request_1k(src_b[ii] + koff, dst + ii * 1024);
     };
     auto issue_a = [&](int kt, int slot) {        // all waves, n_a instructions each
         int8_t* dst = lds + slot * kF6Slot + a_first * 1024;
         const int64_t koff = (int64_t)kt * (2 * kFragBytes);
         if (late) {
 #pragma unroll
-            for (int ii = 0; ii < kLateA; ++ii) dma_1k(src_a[ii] + koff, dst + ii * 1024);
+            for (int ii = 0; ii < kLateA; ++ii) request_1k(src_a[ii] + koff, dst + ii * 1024);
         } else {
 #pragma unroll
-            for (int ii = 0; ii < kEarlyA; ++ii) dma_1k(src_a[ii] + koff, dst + ii * 1024);
+            for (int ii = 0; ii < kEarlyA; ++ii) request_1k(src_a[ii] + koff, dst + ii * 1024);
         }
     };
     // requests of this wave that may still be in flight when tile kt+1 has to be complete: its share
@@ -469,6 +454,142 @@ gemm_f6_ring_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ r
     }
 }
 
+// ---------------------------------------------------------------------------------------------------------------
+// Smaller tiles for few tokens and small outputs, as in the INT8 path (gemm_i8_staged_kernel, whose schedule this is):
+// 8 waves = WM x WN wave tiles of 16 MT tokens x 64 channels times WK shares of the contraction, whose partial sums
+// meet in LDS.  A step is 128 WK elements; a slot holds [WK][(TM + TN) / 32 row blocks][two fragments along K].  Bound, as
+// there, by the 28 bytes per clock a CU takes in from its L2, and for a decode step by the weights' way from HBM.
+// ---------------------------------------------------------------------------------------------------------------
+template <int MT, int WM, int WN, int WK, int S>
+__global__ void __launch_bounds__(64 * kSplitWaves)
+gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ row_scale,
+                      const uint8_t* __restrict__ qw6, const float* __restrict__ w_scale, int T, int I, int O,
+                      uint16_t* __restrict__ Y, int64_t ldy, int32_t* __restrict__ acc_debug, int tiles_m, int total) {
+    static_assert(WM * WN * WK == kSplitWaves && MT % 2 == 0, "8 waves, whole row blocks");
+    constexpr int NT = 4, TM = 16 * MT * WM, TN = 64 * WN;
+    constexpr int kRbA = TM / 32, kRb = (TM + TN) / 32, kPair = 2 * kFragBytes;
+    constexpr int kSlot = WK * kRb * kPair, kRequests = kSlot / 1024;
+    constexpr int N = (kRequests + kSplitWaves - 1) / kSplitWaves;        // per wave and step (the last one may be made twice)
+    extern __shared__ __align__(16) int8_t lds[];
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = wave % (WM * WN), wk = wave / (WM * WN);
+    const int wm = w / WN, wn = w % WN;
+    const int64_t row_bytes = (int64_t)(I / 64) * kFragBytes;             // a row block's fragments
+    const int nk128 = I / 128, nk = (nk128 + WK - 1) / WK;
+    const bool early = wave < 4;                                         // see gemm_i8_staged_kernel
+    const FragLane fl = frag_lane(lane);
+
+    const int per_xcd = (total + kXcds - 1) / kXcds;
+    for (int i = blockIdx.x / kXcds; i < per_xcd; i += gridDim.x / kXcds) {
+        const int L = (blockIdx.x % kXcds) * per_xcd + i;
+        if (L >= total) break;                                           // block-uniform
+        const int tile_n = L / tiles_m;
+        const int m0 = (L - tile_n * tiles_m) * TM, n0 = tile_n * TN;
+
+        // request id = wave N + n of a step: KiB id % 3 of the pair of fragments of row block (id / 3) % kRb, share
+        // id / (3 kRb).  Row blocks past the end are replaced by the last one (its outputs are dropped).
+        const uint8_t* src[N];
+        int share[N];
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            const int id = min(wave * N + n, kRequests - 1), rb = (id / 3) % kRb;
+            share[n] = id / (3 * kRb);
+            const int pair_offset = (id % 3) * 1024 + lane * 16;
+            const int frag = pair_offset >= kFragBytes ? 1 : 0;
+            const uint8_t* base = rb < kRbA ? qx6 + min(m0 / 32 + rb, (T + 31) / 32 - 1) * row_bytes
+                                            : qw6 + min(n0 / 32 + rb - kRbA, 2 * ((O + 63) / 64) - 1) * row_bytes;
+            src[n] = base + frag * kFragBytes + lds_place(pair_offset - frag * kFragBytes) + share[n] * kPair;
+        }
+        auto request = [&](int kt, int slot) {
+            const int8_t* dst = lds + slot * kSlot;
+            const int64_t koff = (int64_t)kt * (WK * kPair);
+            if ((kt + 1) * WK <= nk128) {
+#pragma unroll
+                for (int n = 0; n < N; ++n) request_1k(src[n] + koff, dst + min(wave * N + n, kRequests - 1) * 1024);
+            } else {                                                     // shares past the end read zeros
+#pragma unroll
+                for (int n = 0; n < N; ++n)
+                    request_1k(kt * WK + share[n] < nk128 ? static_cast<const void*>(src[n] + koff) : static_cast<const void*>(&g_zero_piece),
+                               dst + min(wave * N + n, kRequests - 1) * 1024);
+            }
+        };
+        struct Frags {
+            frag6 a[MT], b[NT];
+        };
+        const int share_base = wk * kRb * kPair;
+        auto read = [&](Frags& f, int slot) {
+            const int8_t* s = lds + slot * kSlot + share_base;
+#pragma unroll
+            for (int ni = 0; ni < NT; ++ni) f.b[ni] = read_tile(s, kRbA + 2 * wn, ni, fl);
+#pragma unroll
+            for (int mi = 0; mi < MT; ++mi) f.a[mi] = read_tile(s, wm * MT / 2, mi, fl);
+        };
+        v4f acc[MT][NT];
+#pragma unroll
+        for (int mi = 0; mi < MT; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NT; ++ni) acc[mi][ni] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+            if (s < nk) request(s, s);
+        if (nk >= S) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 1) * N, 15));           // step 0 has landed
+        else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        Frags f0, f1;
+        read(f0, 0);
+
+        int slot = 0;                                                    // slot of step kt
+        auto step = [&](int kt, Frags& cur, Frags& nxt) {
+            if (kt + S - 1 < nk) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 2) * N, 0));
+            else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            const int next_slot = slot + 1 == S ? 0 : slot + 1;
+            if (early && kt + S < nk) request(kt + S, slot);
+            __builtin_amdgcn_sched_barrier(0);
+            if (kt + 1 < nk) read(nxt, next_slot);
+#pragma unroll
+            for (int mi = 0; mi < MT; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < NT; ++ni) acc[mi][ni] = mfma6(cur.a[mi], cur.b[ni], acc[mi][ni]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!early && kt + S < nk) request(kt + S, slot);
+            __builtin_amdgcn_sched_barrier(0);
+            slot = next_slot;
+        };
+        for (int kt = 0; kt < nk; kt += 2) {
+            step(kt, f0, f1);
+            if (kt + 1 < nk) step(kt + 1, f1, f0);
+        }
+        __syncthreads();                                                 // the ring is free: it holds the partial sums now
+        sum_and_store<MT, NT, WM, WN, WK>(acc, reinterpret_cast<v4f*>(lds), wave, lane, row_scale, w_scale, T, O, Y, ldy,
+                                          acc_debug, m0, n0, true);
+        __syncthreads();
+    }
+}
+
+template <int MT, int WM, int WN, int WK, int S>
+hipError_t launch_f6_staged(const uint8_t* qx6, const float* row_scale, const uint8_t* qw6, const float* w_scale, int T, int I,
+                            int O, uint16_t* Y, int64_t ldy, int32_t* acc_debug, hipStream_t stream) {
+    constexpr int TM = 16 * MT * WM, TN = 64 * WN;
+    constexpr int kRing = S * WK * (TM + TN) / 32 * 2 * kFragBytes, kParts = kSplitWaves * MT * 4 * 64 * 16;
+    constexpr int kLds = kRing > kParts ? kRing : kParts;
+    static_assert(kLds <= 160 * 1024, "LDS budget of a gfx950 CU");
+    const int tiles_m = (T + TM - 1) / TM;
+    const int64_t total = (int64_t)tiles_m * ((O + TN - 1) / TN);
+    if (total >= (int64_t)1 << 31) return hipErrorInvalidValue;
+    static std::atomic<uint64_t> allowed{0};
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_f6_staged_kernel<MT, WM, WN, WK, S>), kLds, allowed);
+    if (e != hipSuccess) return e;
+    const int64_t blocks = std::min<int64_t>((total + kXcds - 1) / kXcds * kXcds, (int64_t)1 << 20);
+    gemm_f6_staged_kernel<MT, WM, WN, WK, S><<<dim3((unsigned)blocks), dim3(64 * kSplitWaves), kLds, stream>>>(
+        qx6, row_scale, qw6, w_scale, T, I, O, Y, ldy, acc_debug, tiles_m, (int)total);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 int64_t fp6_packed_bytes(int64_t R, int64_t K) { return ((R + 31) / 32) * (K / 64) * (int64_t)kFragBytes; }
@@ -499,6 +620,36 @@ hipError_t launch_w4a4_linear(const void* qx6, const float* row_scale, const voi
     if (ldy >= ((int64_t)1 << 22)) return hipErrorInvalidValue;      // the epilogue's 32-bit byte offsets
     const int total = tiles_m * tiles_n;
     const int per_xcd = (total + kXcds - 1) / kXcds;
+    int n_cu = 0, dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
+        n_cu = 256;
+    const uint8_t* qx = static_cast<const uint8_t*>(qx6);
+    const uint8_t* qw = static_cast<const uint8_t*>(qw6);
+    // Small tiles where they cover the layer in less of their own measure: rounds of tiles over the CUs times the rows
+    // (TM + TN) a CU takes in per step; a round of the ring kernel's 256 x 256 tiles counts as 400 there.  Of equal ones
+    // the larger tile.  Measured at I = 4096 (us; ring first, then 32 x 64, 64 x 64, 64 x 128, 128 x 128): 32 x 4096 27.7 :
+    // 8.8 8.5 12.2 15.9; 256 x 4096 27.3 : 15.6 9.0 12.6 17.1; 512 x 4096 27.5 : 29.2 16.2 13.4 17.6; 1024 x 4096 28.9 :
+    // 56.6 31.1 25.4 19.9; 2048 x 4096 (two rounds of the last) 31.3 : 122 77 53 39; and 32 x 5120 x 20480 34.7 : 21.8 20.6
+    // 15.8 19.0.
+    static const int kinds[4][2] = {{128, 128}, {64, 128}, {64, 64}, {32, 64}};
+    int64_t cost = (int64_t)((total + n_cu - 1) / n_cu) * 400;
+    int kind = -1;
+    for (int k = 0; k < 4; ++k) {
+        const int tm = kinds[k][0], tn = kinds[k][1];
+        const int64_t tiles = (int64_t)((T + tm - 1) / tm) * ((O + tn - 1) / tn), c = (tiles + n_cu - 1) / n_cu * (tm + tn);
+        if (c < cost) {
+            cost = c;
+            kind = k;
+        }
+    }
+    switch (kind) {
+        case 0: return launch_f6_staged<4, 2, 2, 2, 3>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
+        case 1: return launch_f6_staged<2, 2, 2, 2, 4>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
+        case 2: return launch_f6_staged<2, 2, 1, 4, 3>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
+        case 3: return launch_f6_staged<2, 1, 1, 8, 2>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
+        default: break;
+    }
     // four instances: with or without the raw accumulators, Y streamed to memory or left in the caches
     using kernel_t = void (*)(const uint8_t*, const float*, const uint8_t*, const float*, int, int, int, uint16_t*, int64_t,
                               int32_t*, int, int);
@@ -509,15 +660,10 @@ hipError_t launch_w4a4_linear(const void* qx6, const float* row_scale, const voi
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernels[which]), kF6Lds, lds_allowed[which]);
     if (e != hipSuccess) return e;
     // one block per CU (a multiple of the XCD count), fewer when there are fewer tiles than that
-    int n_cu = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
-        n_cu = 256;
     const int cu_blocks = n_cu >= kXcds ? n_cu / kXcds * kXcds : kXcds;
     const int blocks = std::min(cu_blocks, per_xcd * kXcds);
     kernels[which]<<<dim3((unsigned)blocks), dim3(512), kF6Lds, stream>>>(
-        static_cast<const uint8_t*>(qx6), row_scale, static_cast<const uint8_t*>(qw6), w_scale, T, I, O, Y, ldy,
-        acc_debug, tiles_m, tiles_n);
+        qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, tiles_m, tiles_n);
     return hipGetLastError();
 }
 

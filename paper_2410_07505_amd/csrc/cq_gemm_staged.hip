@@ -15,8 +15,6 @@
 namespace cq {
 namespace {
 
-constexpr int kSplitWaves = 8;
-
 // 16 bytes at p, any alignment
 __device__ __forceinline__ v4i load16(const int8_t* p) {
     v4i v;
@@ -31,71 +29,6 @@ __device__ __forceinline__ v4i load16_tail(const int8_t* row, int kb, int I) {
     return __builtin_bit_cast(v4i, w);
 }
 
-// The end of a tile: the WK partial sums of every accumulator meet in LDS (parts: [wk][wm][wn][mi][ni][lane]), are
-// scaled and stored.  Weight tile ni of a wave holds the channels NT fr + ni (fr = lane & 15) of the wave's 16 NT.
-// vec_out: every lane's NT channels exist or not together and their 2 NT bytes of Y are aligned.
-template <int MT, int NT, int WM, int WN, int WK>
-__device__ __forceinline__ void sum_and_store(const v4i (&acc)[MT][NT], v4i* parts, int wave, int lane,
-                                              const float* __restrict__ row_scale, const float* __restrict__ w_scale, int T,
-                                              int O, uint16_t* __restrict__ Y, int64_t ldy, int32_t* __restrict__ acc_debug,
-                                              int m0, int n0, bool vec_out) {
-#pragma unroll
-    for (int mi = 0; mi < MT; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < NT; ++ni) parts[((wave * MT + mi) * NT + ni) * 64 + lane] = acc[mi][ni];
-    __syncthreads();
-    // A unit is two tokens x NT channels: accumulator registers 2 h, 2 h + 1 of lane l of the tiles (mi, 0 .. NT - 1) of
-    // wave position w.  Lane l holds channel l & 15 of a weight tile and, in register r, token 4 (l >> 4) + r.
-    constexpr int kUnits = WM * WN * MT * 64 * 2;
-    for (int u = threadIdx.x; u < kUnits; u += 64 * kSplitWaves) {
-        const int l = u & 63, h = (u >> 6) & 1, mi = (u >> 7) % MT, w = (u >> 7) / MT;
-        int2 sum[NT];
-#pragma unroll
-        for (int ni = 0; ni < NT; ++ni) sum[ni] = make_int2(0, 0);
-#pragma unroll
-        for (int p = 0; p < WK; ++p)
-#pragma unroll
-            for (int ni = 0; ni < NT; ++ni) {
-                const int2 v = *reinterpret_cast<const int2*>(
-                    reinterpret_cast<const int8_t*>(parts + (((p * WM * WN + w) * MT + mi) * NT + ni) * 64 + l) + 8 * h);
-                sum[ni].x += v.x;
-                sum[ni].y += v.y;
-            }
-        const int col = n0 + ((w % WN) * 16 + (l & 15)) * NT;
-        const int row = m0 + (w / WN) * 16 * MT + 16 * mi + 4 * (l >> 4) + 2 * h;
-        if (col >= O) continue;
-        float s[NT];
-#pragma unroll
-        for (int ni = 0; ni < NT; ++ni) s[ni] = w_scale[min(col + ni, O - 1)];
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            if (row + r >= T) break;
-            const float a = row_scale[row + r];
-            float y[NT];
-#pragma unroll
-            for (int ni = 0; ni < NT; ++ni) {
-                y[ni] = (float)(r ? sum[ni].y : sum[ni].x) * a;
-                y[ni] = rounded_f32(y[ni] * s[ni]);
-            }
-            uint16_t* dst = Y + (int64_t)(row + r) * ldy + col;
-            if (NT == 4 && vec_out) {
-                *reinterpret_cast<uint2*>(dst) = make_uint2(pack_half2(y[0], y[1]), pack_half2(y[NT - 2], y[NT - 1]));
-            } else if (NT == 2 && vec_out) {
-                *reinterpret_cast<uint32_t*>(dst) = pack_half2(y[0], y[NT - 1]);
-            } else {
-#pragma unroll
-                for (int ni = 0; ni < NT; ++ni)
-                    if (col + ni < O) dst[ni] = (uint16_t)f2h(y[ni]);
-            }
-            if (acc_debug) {
-#pragma unroll
-                for (int ni = 0; ni < NT; ++ni)
-                    if (col + ni < O) acc_debug[(int64_t)(row + r) * O + col + ni] = r ? sum[ni].y : sum[ni].x;
-            }
-        }
-    }
-}
-
 // A step is 64 WK contraction bytes; wave share wk multiplies slab wk of it.  A slot holds one step:
 // [WK / 2][TM + TN rows][128 bytes], chunk c of row R at chunk c ^ ((R >> 1) & 7), so that the 16 rows a fragment read
 // covers fall on distinct banks.  LDS row 16 ni + f of a wave's weight rows holds its channel NT f + ni (the loader picks
@@ -105,15 +38,6 @@ __device__ __forceinline__ void sum_and_store(const v4i (&acc)[MT][NT], v4i* par
 // DMA: operands aligned to 16 bytes with I % 16 == 0 go straight to LDS; pieces past a row's end come from a zero
 // block.  Otherwise (I >= 16) they pass through registers, loaded unaligned one step before they are stored: 512 x 2752 x
 // 4096 takes 14.3 us in the first form, and 19.8 to 21.2 us with I = 2760, 2756, 2754, 2753 in the second.
-__device__ const uint4 g_zero_piece = {0u, 0u, 0u, 0u};
-
-// One request: every lane's 16 bytes at src go to LDS at dst + 16 * lane, counted by vmcnt.  (Inline assembly, as in the
-// FP6 kernel: after the compiler's builtin every LDS read waits for all such requests.)
-__device__ __forceinline__ void request_1k(const int8_t* src, const int8_t* dst) {
-    const uint32_t lds_off = (uint32_t)(uintptr_t)((lptr_t)dst);     // wave-uniform
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc0" : : "v"(src), "s"(lds_off) : "m0");
-}
-
 template <int MT, int NT, int WM, int WN, int WK, int S, bool DMA>
 __global__ void __launch_bounds__(64 * kSplitWaves)
 gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ row_scale, const int8_t* __restrict__ qw,
@@ -152,24 +76,28 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
             const int sub = R_all / kRows, R = R_all % kRows;
             kb[n] = sub * 128 + (((lane & 7) ^ ((R >> 1) & 7)) * 16);
             if (R < TM) {
-                src[n] = qx + (int64_t)min(m0 + R, T - 1) * I;
+                src[n] = qx + (int64_t)min(m0 + R, T - 1) * I + kb[n];
             } else {
                 const int b = R - TM, grp = b / (16 * NT), in = b % (16 * NT);
-                src[n] = qw + (int64_t)min(n0 + grp * 16 * NT + NT * (in & 15) + (in >> 4), O - 1) * I;
+                src[n] = qw + (int64_t)min(n0 + grp * 16 * NT + NT * (in & 15) + (in >> 4), O - 1) * I + kb[n];
             }
         }
         v4i reg[DMA ? 1 : N];
         auto request = [&](int kt, int slot) {                // DMA: straight to LDS; else into registers
+            const int koff = kt * kStepK;
+            const int8_t* dst = lds + slot * kSlot + wave * N * 1024;
+            if (koff + kStepK <= I) {
 #pragma unroll
-            for (int n = 0; n < N; ++n) {
-                const int at = kt * kStepK + kb[n];
-                if (DMA) {
-                    const int8_t* p = at < I ? src[n] + at : reinterpret_cast<const int8_t*>(&g_zero_piece);
-                    request_1k(p, lds + slot * kSlot + (wave * N + n) * 1024);
-                } else if ((kt + 1) * kStepK <= I) {
-                    reg[DMA ? 0 : n] = load16(src[n] + at);
-                } else {
-                    reg[DMA ? 0 : n] = load16_tail(src[n], at, I);
+                for (int n = 0; n < N; ++n) {
+                    if (DMA) request_1k(src[n] + koff, dst + n * 1024);
+                    else reg[DMA ? 0 : n] = load16(src[n] + koff);
+                }
+            } else {
+#pragma unroll
+                for (int n = 0; n < N; ++n) {
+                    if (DMA) request_1k(koff + kb[n] < I ? static_cast<const void*>(src[n] + koff) : static_cast<const void*>(&g_zero_piece),
+                                        dst + n * 1024);
+                    else reg[DMA ? 0 : n] = load16_tail(src[n] - kb[n], koff + kb[n], I);
                 }
             }
         };

@@ -1475,6 +1475,30 @@ def test_w4a4_linear_fp6(cq, T, I, O):
     assert np.array_equal(bits16(host(Y8)), bits16(host(Y)))
 
 
+# (T, O) for which the launcher takes, on 256 CUs, tiles of 32 x 64, 64 x 64, 64 x 128, 128 x 128 and 256 x 256, ragged on
+# both edges; I: one step shared by all, several with shares past the end, and more steps than LDS slots
+@pytest.mark.parametrize("I", [128, 384, 2688])
+@pytest.mark.parametrize("T,O", [(1, 8), (30, 4088), (250, 4088), (505, 4088), (1000, 4088), (2100, 4104)])
+def test_w4a4_linear_tiles_that_split_the_contraction(cq, T, O, I):
+    import torch
+    say("w4a4, split contraction: T=%d I=%d O=%d" % (T, I, O))
+    qx, qw = workloads.int8_codes(T, I, seed=T + I, lo=-7, hi=7), workloads.int8_codes(O, I, seed=O + I, lo=-7, hi=7)
+    rng = np.random.default_rng(T + O + I)
+    a = rng.uniform(1e-3, 1e-1, T).astype(np.float32)
+    s = rng.uniform(1e-5, 1e-3, O).astype(np.float32)
+    Y_ref, acc_ref = oracle.w8a8_linear(qx, a, qw, s)
+    px, pw = cq.crossquant_pack_fp6(gpu(qx)), cq.crossquant_pack_fp6_weights(gpu(qw))
+    buf = torch.full((T + 2, O + 8), 7.0, dtype=torch.float16, device="cuda")
+    accbuf = torch.full((T + 2, O), -5, dtype=torch.int32, device="cuda")
+    cq.crossquant_w4a4_linear(px, gpu(a), pw, gpu(s), T, I, O, Y=buf[:T, :O], acc_debug=accbuf[:T])
+    out, acc = host(buf), host(accbuf)
+    assert np.array_equal(acc[:T], acc_ref) and np.all(acc[T:] == -5)
+    assert np.array_equal(bits16(out[:T, :O]), bits16(Y_ref))
+    assert np.all(out[:T, O:] == 7.0) and np.all(out[T:] == 7.0)
+    Y, _ = cq.crossquant_w4a4_linear(px, gpu(a), pw, gpu(s), T, I, O)
+    assert np.array_equal(bits16(host(Y)), bits16(Y_ref))
+
+
 @pytest.mark.parametrize("T,I,O", [(5120, 128, 5120),      # 400 tiles: 144 blocks walk two tiles; one K step
                                    (5120, 256, 5120),      # two K steps
                                    (4100, 384, 7688),      # 527 tiles, ragged on both edges; three K steps
