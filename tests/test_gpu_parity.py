@@ -905,6 +905,42 @@ def test_weight_quantize_grouped(cq, I, O, group, bits):
         assert none_dq is None and np.array_equal(host(qw2), qw_ref) and np.array_equal(host(s2), s_ref)
 
 
+# tiles of 128 (256) input channels x 64 output channels: the last tile partial along either axis, groups that end inside a
+# wave's rows, at a wave, at a tile and at two tiles; `off`: buffers that start one element off (element-wise loads, stores)
+@pytest.mark.parametrize("I,O,group", [(160, 136, 32), (192, 72, 64), (640, 64, 128), (768, 80, 256), (512, 77, 256)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_weight_groups_held_in_registers(cq, I, O, group, off):
+    import torch
+    say("grouped weight tiles I=%d O=%d g=%d off=%d" % (I, O, group, off))
+    W = workloads.weight(I, O, seed=I + O + group)
+    W[:group, 1] = 0
+    fold = np.random.default_rng(I).uniform(0.05, 8.0, I).astype(np.float32)
+
+    def at(n, dtype, shape):
+        return torch.full((n + off,), 3, dtype=dtype, device="cuda")[off:].view(shape)
+    Wg = at(I * O, torch.float16, (I, O))
+    Wg.copy_(gpu(W))
+    for bits in (8, 4):
+        qw_ref, s_ref, dq_ref = oracle.weight_quantize_grouped(W, fold, group, bits)
+        qw, s, dq = cq.crossquant_weight_quantize_grouped(Wg, gpu(fold), group, bits, qw=at(O * I, torch.int8, (O, I)),
+                                                          w_dq=at(I * O, torch.float16, (I, O)))
+        assert np.array_equal(bits32(host(s)), bits32(s_ref)) and np.array_equal(host(qw), qw_ref)
+        assert np.array_equal(bits16(host(dq)), bits16(dq_ref))
+
+
+@pytest.mark.parametrize("I,O", [(4096, 520), (4100, 520), (4097, 77),      # steps: a block per 64 channels up to 4096 rows, shared out beyond
+                                 (4100, 4098), (129, 4096)])                # ... and again a block per 64 channels
+def test_weight_steps_by_either_pass(cq, I, O):
+    say("weight steps I=%d O=%d" % (I, O))
+    W = workloads.weight(I, O, seed=I + O)
+    W[:, 3] = 0
+    fold = np.random.default_rng(O).uniform(0.05, 8.0, I).astype(np.float32)
+    for f in (None, fold):
+        qw_ref, s_ref = oracle.weight_quantize(W, f, 8)
+        qw, s = cq.crossquant_weight_quantize(gpu(W), None if f is None else gpu(f), 8)
+        assert np.array_equal(bits32(host(s)), bits32(s_ref)) and np.array_equal(host(qw), qw_ref)
+
+
 def test_weight_quantize_grouped_at_layer_scale(cq):
     """The paper's W4-g128 setting on the low-bit configuration's 4096 x 4096 weight."""
     W = workloads.config_weight("C4")
