@@ -20,5 +20,6 @@ __all__ = list(_EXPORTS)
 def __getattr__(name):
     if name in _EXPORTS:
         from . import binding
-        return getattr(binding, name)
+        value = globals()[name] = getattr(binding, name)       # found directly from now on
+        return value
     raise AttributeError("module %r has no attribute %r" % (__name__, name))
