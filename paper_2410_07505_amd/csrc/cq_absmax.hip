@@ -36,64 +36,9 @@ __global__ void zero_fill_kernel(uint32_t* __restrict__ p0, int n0, uint32_t* __
 }
 
 // Block: 4 waves x (nb batches of 8 rows) x 512 columns.
-template <bool VEC>
-__global__ void __launch_bounds__(kWaves * kLanes)
-absmax_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, uint32_t* __restrict__ t_bits,
-              uint32_t* __restrict__ c_bits, int n_col_chunks, int nb, int blocks_per_matrix, int64_t matrix_stride) {
-    __shared__ uint32_t lds_col[kWaves][4][kLanes];  // [wave][packed reg][lane]
-
-    const int lane = threadIdx.x & (kLanes - 1);
-    const int wave = threadIdx.x / kLanes;
-    const int matrix = blockIdx.x / blocks_per_matrix;
-    const int blk = blockIdx.x - matrix * blocks_per_matrix;
-    X += (int64_t)matrix * matrix_stride;
-    t_bits += (int64_t)matrix * T;
-    c_bits += (int64_t)matrix * I;
-    // flat grid, column chunk fastest: neighbouring blocks read neighbouring 1 KiB pieces of a row
-    const int col_chunk = blk % n_col_chunks;
-    const int row_chunk = blk / n_col_chunks;
-    const int j0 = col_chunk * kColsPerWave + lane * 8;
-    const int rows_per_wave = nb * kBatch;
-    const int row0 = row_chunk * (kWaves * rows_per_wave) + wave * rows_per_wave;
-
-    uint32_t c0 = 0, c1 = 0, c2 = 0, c3 = 0;
-    for (int b = 0; b < nb; ++b) {
-        const int rb = row0 + b * kBatch;
-        if (rb >= T) break;                               // wave-uniform
-        uint4 v[kBatch];
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k)
-            v[k] = (rb + k < T) ? load8<VEC>(X + (int64_t)(rb + k) * ldx, j0, I) : make_uint4(0u, 0u, 0u, 0u);
-        uint32_t rm[kBatch];
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k) rm[k] = absmax8(v[k], c0, c1, c2, c3);
-        const uint32_t m = rows8_reduce(rm, lane);
-        const int r = rb + (lane >> 3);
-        if ((lane & 7) == 0 && r < T && m) atomicMax(&t_bits[r], half_bits_to_float_bits(m));
-    }
-
-    // columns: combine the block's waves through LDS, then one atomic per column.  Thread idx
-    // takes columns 2*idx and 2*idx+1 of the chunk = packed register (idx & 3) of lane (idx >> 2).
-    lds_col[wave][0][lane] = c0;
-    lds_col[wave][1][lane] = c1;
-    lds_col[wave][2][lane] = c2;
-    lds_col[wave][3][lane] = c3;
-    __syncthreads();
-    {
-        const int idx = threadIdx.x;
-        const int reg = idx & 3, ln = idx >> 2;
-        const uint32_t m = pkmax(pkmax(lds_col[0][reg][ln], lds_col[1][reg][ln]),
-                                 pkmax(lds_col[2][reg][ln], lds_col[3][reg][ln]));
-        const int j = col_chunk * kColsPerWave + idx * 2;
-        if (j < I && (m & 0xFFFFu)) atomicMax(&c_bits[j], half_bits_to_float_bits(m & 0xFFFFu));
-        if (j + 1 < I && (m >> 16)) atomicMax(&c_bits[j + 1], half_bits_to_float_bits(m >> 16));
-    }
-}
-
-// The same pass for the layout every real activation has (X 16-byte aligned, ldx % 8 == 0, I % 8 == 0), with three
-// differences:
-//   - rows are read as raw buffers (base and length in scalar registers, range-checked by the hardware: columns
-//     past the end read as 0 with no per-lane branch);
+//   - BUF, the layout every real activation has (X 16-byte aligned, ldx % 8 == 0, I % 8 == 0): rows are read as raw
+//     buffers (base and length in scalar registers, range-checked by the hardware: columns past the end read as 0
+//     with no per-lane branch); any other layout: unaligned 16-byte loads (load8);
 //   - the row maxima wait in LDS until the block has read all its rows, so every atomic of the block is issued at
 //     its very end;
 //   - CLEAR: the launch clears t and c itself.  The first n_clear blocks do nothing but store zeros (at device
@@ -104,7 +49,7 @@ absmax_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, uint32_
 //     launch's clearing blocks are done.  Blocks are dispatched in index order, so the clearing blocks are
 //     running or finished before any other block exists.  This saves the separate clearing kernel and the gap
 //     between the two launches.
-template <bool CLEAR>
+template <bool CLEAR, bool BUF>
 __global__ void __launch_bounds__(kWaves * kLanes)
 absmax_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, uint32_t* __restrict__ t_bits,
                      uint32_t* __restrict__ c_bits, int n_col_chunks, int nb, int blocks_per_matrix,
@@ -142,7 +87,7 @@ absmax_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, 
     const int col_chunk = blk % n_col_chunks;
     const int row_chunk = blk / n_col_chunks;
     const int col0 = col_chunk * kColsPerWave;
-    const int cols_here = min(kColsPerWave, I - col0);           // a multiple of 8
+    const int cols_here = min(kColsPerWave, I - col0);           // a multiple of 8 with BUF
     const int rows_per_wave = nb * kBatch;
     const int rows_per_block = kWaves * rows_per_wave;
     const int block_row0 = row_chunk * rows_per_block;
@@ -154,7 +99,8 @@ absmax_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, 
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
             const int r = min(row0 + b * kBatch + k, T - 1);
-            dst[k] = buffer_load16(row_buffer(X + (int64_t)r * ldx + col0, cols_here * 2), lane * 16);
+            const uint16_t* row = X + (int64_t)r * ldx;
+            dst[k] = BUF ? buffer_load16(row_buffer(row + col0, cols_here * 2), lane * 16) : load8<false>(row, col0 + lane * 8, I);
         }
     };
     uint32_t c0 = 0, c1 = 0, c2 = 0, c3 = 0;
@@ -243,47 +189,40 @@ hipError_t launch_absmax(const uint16_t* X, int B, int T, int I, int64_t ldx, in
     uint32_t* tb = reinterpret_cast<uint32_t*>(t);
     uint32_t* cb = reinterpret_cast<uint32_t*>(c);
     const dim3 block(kWaves * kLanes);
-    if (vec && I % 8 == 0) {
-        // One launch that clears for itself needs a counter of its own (a stream slot) and a target value that
-        // differs from launch to launch, which a captured graph cannot have (its arguments are frozen): captured
-        // calls and streams without a slot clear with a kernel of their own first.
-        const int slot = stream_slot(stream);
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        const bool plain_stream = slot >= 0 && hipStreamIsCapturing(stream, &cap) == hipSuccess &&
-                                  cap == hipStreamCaptureStatusNone;
-        if (plain_stream) {
-            static std::mutex mu;
-            static unsigned int reached[64][kStateSlots];      // what a device's g_cleared[slot] reaches once all launches so far have cleared
-            static unsigned int* counters[64];                 // device address of g_cleared on each device, once known
-            int dev = 0;
-            hipError_t e = hipGetDevice(&dev);
+    const bool buf = vec && I % 8 == 0;
+    // One launch that clears for itself needs a counter of its own (a stream slot) and a target value that
+    // differs from launch to launch, which a captured graph cannot have (its arguments are frozen): captured
+    // calls and streams without a slot clear with a kernel of their own first.
+    const int slot = stream_slot(stream);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool plain_stream = slot >= 0 && hipStreamIsCapturing(stream, &cap) == hipSuccess &&
+                              cap == hipStreamCaptureStatusNone;
+    if (plain_stream) {
+        static std::mutex mu;
+        static unsigned int reached[64][kStateSlots];      // what a device's g_cleared[slot] reaches once all launches so far have cleared
+        static unsigned int* counters[64];                 // device address of g_cleared on each device, once known
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+        std::lock_guard<std::mutex> lock(mu);              // launches and targets stay in the same order
+        if (!counters[dev]) {
+            e = hipGetSymbolAddress(reinterpret_cast<void**>(&counters[dev]), HIP_SYMBOL(g_cleared));
             if (e != hipSuccess) return e;
-            if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-            std::lock_guard<std::mutex> lock(mu);              // launches and targets stay in the same order
-            if (!counters[dev]) {
-                e = hipGetSymbolAddress(reinterpret_cast<void**>(&counters[dev]), HIP_SYMBOL(g_cleared));
-                if (e != hipSuccess) return e;
-            }
-            unsigned int* counter = counters[dev];
-            const unsigned int target = reached[dev][slot] + (unsigned)n_clear;
-            absmax_stream_kernel<true><<<dim3((unsigned)(n_work + n_clear)), block, 0, stream>>>(
-                X, T, I, ldx, tb, cb, ncc, nb, ncc * nrc, matrix_stride, n_clear, B * T, B * I, counter + slot, target,
-                1u << 22);
-            e = hipGetLastError();
-            if (e == hipSuccess) reached[dev][slot] = target;
-            return e;
         }
-        zero_fill_kernel<<<dim3((n_words + 255) / 256), dim3(256), 0, stream>>>(tb, B * T, cb, B * I);
-        absmax_stream_kernel<false><<<dim3((unsigned)n_work), block, 0, stream>>>(X, T, I, ldx, tb, cb, ncc, nb, ncc * nrc,
-                                                                                  matrix_stride, 0, 0, 0, nullptr, 0u, 0u);
-        return hipGetLastError();
+        unsigned int* counter = counters[dev];
+        const unsigned int target = reached[dev][slot] + (unsigned)n_clear;
+        const auto kernel = buf ? &absmax_stream_kernel<true, true> : &absmax_stream_kernel<true, false>;
+        kernel<<<dim3((unsigned)(n_work + n_clear)), block, 0, stream>>>(X, T, I, ldx, tb, cb, ncc, nb, ncc * nrc, matrix_stride,
+                                                                         n_clear, B * T, B * I, counter + slot, target, 1u << 22);
+        e = hipGetLastError();
+        if (e == hipSuccess) reached[dev][slot] = target;
+        return e;
     }
     zero_fill_kernel<<<dim3((n_words + 255) / 256), dim3(256), 0, stream>>>(tb, B * T, cb, B * I);
-    const dim3 grid((unsigned)n_work);
-    if (vec)
-        absmax_kernel<true><<<grid, block, 0, stream>>>(X, T, I, ldx, tb, cb, ncc, nb, ncc * nrc, matrix_stride);
-    else
-        absmax_kernel<false><<<grid, block, 0, stream>>>(X, T, I, ldx, tb, cb, ncc, nb, ncc * nrc, matrix_stride);
+    const auto kernel = buf ? &absmax_stream_kernel<false, true> : &absmax_stream_kernel<false, false>;
+    kernel<<<dim3((unsigned)n_work), block, 0, stream>>>(X, T, I, ldx, tb, cb, ncc, nb, ncc * nrc, matrix_stride, 0, 0, 0,
+                                                         nullptr, 0u, 0u);
     return hipGetLastError();
 }
 

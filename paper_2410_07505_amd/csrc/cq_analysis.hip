@@ -127,9 +127,7 @@ analysis_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, const
                 if (out_vec && nvalid == 8) {
                     __builtin_nontemporal_store(u32x4{out[0], out[1], out[2], out[3]}, reinterpret_cast<u32x4*>(dst));
                 } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (e < nvalid) dst[e] = (uint16_t)((e & 1) ? (out[e >> 1] >> 16) : (out[e >> 1] & 0xFFFFu));
+                    store_piece<16, uint16_t>(u32x4{out[0], out[1], out[2], out[3]}, dst, nvalid * 2);
                 }
             }
         }
@@ -170,7 +168,7 @@ hipError_t launch_kernel_analysis(const uint16_t* X, int T, int I, int64_t ldx, 
     const int nrc = (T + 32 * nb - 1) / (32 * nb);
     if (!grid_fits((int64_t)ncc * nrc, kWaves * kLanes)) return hipErrorInvalidValue;     // before anything is enqueued
     const dim3 grid((unsigned)(ncc * nrc)), block(kWaves * kLanes);
-    const bool vec = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && (ldx % 8 == 0);
+    const bool vec = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && (ldx % 8 == 0) && (I % 8 == 0);
     const bool out_vec = (I % 8 == 0) && (reinterpret_cast<uintptr_t>(xrk) % 16 == 0);
     const double al = (double)alpha;
     if (a && b) {

@@ -23,20 +23,27 @@ __device__ __forceinline__ uint32_t half_bits_to_float_bits(uint32_t h) { return
 
 __device__ __forceinline__ uint32_t shx(uint32_t v, int off) { return (uint32_t)__shfl_xor((int)v, off, kLanes); }
 
-// 8 halfs starting at column j of a row; columns >= I read as zero.
+// 8 halfs starting at column j of a row; columns >= I read as zero, and nothing outside the row is read.
+// VEC: I % 8 == 0 and the row starts on 16 bytes.  Otherwise one 16-byte load without alignment; the lane that holds the
+// row's last columns loads the 8 that end the row and shifts (rows shorter than that: element by element).
 template <bool VEC>
 __device__ __forceinline__ uint4 load8(const uint16_t* __restrict__ row, int j, int I) {
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (VEC && j + 8 <= I) {
-        v = *reinterpret_cast<const uint4*>(row + j);
+    if (VEC) {
+        if (j + 8 <= I) v = *reinterpret_cast<const uint4*>(row + j);
+    } else if (I >= 8) {                                     // uniform
+        const int at = min(j, I - 8), sh = j - at;           // columns to shift out: 0 but for the row's end
+        __builtin_memcpy(&v, row + at, 16);
+        if (sh > 0) {
+            unsigned __int128 w = __builtin_bit_cast(unsigned __int128, v);
+            w = sh >= 8 ? 0 : w >> (16 * (sh & 7));
+            v = __builtin_bit_cast(uint4, w);
+        }
     } else if (j < I) {
         uint32_t h[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) h[e] = (j + e < I) ? row[j + e] : 0u;
-        v.x = h[0] | (h[1] << 16);
-        v.y = h[2] | (h[3] << 16);
-        v.z = h[4] | (h[5] << 16);
-        v.w = h[6] | (h[7] << 16);
+        v = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
     }
     return v;
 }
@@ -204,46 +211,17 @@ __device__ __forceinline__ void quantize8(const uint4& v, float a, float ra, con
     if (quantize8_fast(v, ra, rb, qmax, m, q, tiny)) quantize8_exact(v, a, b, qmax, m, q);   // rare
 }
 
-// Count-only form of quantize8: how many of the wave's 8 x 64 elements of one row have a non-zero code.
+// Count-only form of quantize8: every lane returns how many of its own 8 elements have a non-zero code, and
+// the kernel adds the lanes up once at its end.
 // q = rne(fl32(x / fl32(a b))) is 0 exactly when the quotient is at most 1/2 (a tie rounds to the even
 // 0), so the sign of d = fma(|x|, 1/b, -a/2) decides, unless the two sides are within 2^-20 of each
 // other: |x| / b differs from (x / fl32(a b)) a by at most 2^-22 relative (reciprocal, rounding of
 // a b, the quotient's own rounding; the fma's single rounding never changes its sign).  A wave in
 // which any lane comes that close, or has a factor so small that products leave the normal range,
 // recounts the row piece with the exact division.  ha = a / 2 (exact), tol = ha * 2^-19.
-__device__ __forceinline__ uint32_t count_row8_wave(const uint4& v, float a, float ha, float tol, const float (&b)[8],
-                                                    const float (&rb)[8], float qmax, bool tiny) {
-    float x[8];
-    x[0] = half_lo(v.x); x[1] = half_hi(v.x);
-    x[2] = half_lo(v.y); x[3] = half_hi(v.y);
-    x[4] = half_lo(v.z); x[5] = half_hi(v.z);
-    x[6] = half_lo(v.w); x[7] = half_hi(v.w);
-    uint32_t nz = 0u;
-    unsigned long long close = 0ull;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float d = __builtin_fmaf(__builtin_fabsf(x[e]), rb[e], -ha);
-        nz += (uint32_t)__builtin_popcountll(__ballot(d > 0.0f));
-        close |= __ballot(__builtin_fabsf(d) <= tol);
-    }
-    if (close != 0ull || __any(tiny)) {                 // rare: exact division for this wave's row piece
-        nz = 0u;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float D = a * b[e];
-            float rt = (D == 0.0f) ? 0.0f : x[e] / D;
-            rt = __builtin_amdgcn_fmed3f(rt, -qmax, qmax);
-            nz += (uint32_t)__builtin_popcountll(__ballot(rt + kMagic != kMagic));
-        }
-    }
-    return nz;
-}
-
-// The same decision counted per lane: every lane returns how many of its own 8 elements have a non-zero code, and
-// the kernel adds the lanes up once at its end.  A compare and an add-with-carry per element and one running
-// minimum of |d| for the closeness test, all vector instructions: the form above hands every compare mask to the
-// scalar unit (population count, add, or), which the four SIMDs of a CU share; in the streaming count-only kernel
-// that was 1.6 scalar instructions per vector instruction.
+// A compare and an add-with-carry per element and one running minimum of |d| for the closeness test, all vector
+// instructions: handing every compare mask to the scalar unit (population count, add, or), which the four SIMDs of a
+// CU share, was 1.6 scalar instructions per vector instruction.
 __device__ __forceinline__ uint32_t count_row8_lane(const uint4& v, float a, float ha, float tol, const float (&b)[8],
                                                     const float (&rb)[8], float qmax, bool tiny) {
     float x[8];
@@ -274,16 +252,7 @@ __device__ __forceinline__ uint32_t count_row8_lane(const uint4& v, float a, flo
     return nz;
 }
 
-// number of non-zero codes among the whole wave's m[0..8): one compare per element, the counting is
-// scalar (population count of the compare mask).  Only active lanes are counted.
-__device__ __forceinline__ uint32_t count_nonzero8_wave(const float (&m)[8]) {
-    uint32_t nz = 0u;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) nz += (uint32_t)__builtin_popcountll(__ballot(m[e] != kMagic));
-    return nz;
-}
-
-// The same per lane, for the streaming kernel, which adds the lanes up once at its end: a compare and an add of
+// Number of a lane's non-zero codes among m[0..8); the kernel adds the lanes up once at its end: a compare and an add of
 // its carry per element and nothing for the scalar unit, which the four SIMDs of a CU share.
 __device__ __forceinline__ uint32_t count_nonzero8_lane(const float (&m)[8]) {
     uint32_t nz = 0u;
@@ -340,36 +309,18 @@ __device__ __forceinline__ u32x4 pack_xhat(const float (&q)[8], float a, const f
     return u32x4{pack_half2(y[0], y[1]), pack_half2(y[2], y[3]), pack_half2(y[4], y[5]), pack_half2(y[6], y[7])};
 }
 
-// INT8 codes: 8 bytes at dst
-__device__ __forceinline__ void store_codes_i8(const float (&m)[8], uint8_t* dst, bool vec_ok, int nvalid) {
-    uint32_t u[8];
+// A piece of N bytes at dst, which need not be aligned; of a piece at the end of a row only the first n bytes (whole U's).
+template <int N, typename U, typename V>
+__device__ __forceinline__ void store_piece(V v, void* dst, int n) {
+    static_assert(sizeof(V) == N, "a whole piece");
+    if (n == N) {
+        __builtin_memcpy(dst, &v, N);
+    } else if (n > 0) {
+        U u[N / sizeof(U)];
+        __builtin_memcpy(u, &v, N);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) u[e] = __float_as_uint(m[e]);
-    if (vec_ok && nvalid == 8) {
-        store_through(pack_codes_i8(m), reinterpret_cast<u32x2*>(dst));
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if (e < nvalid) dst[e] = (uint8_t)(u[e] & 0xFFu);
-    }
-}
-
-// INT4 codes: 4 bytes at dst, two's-complement nibbles, even column in the low nibble
-__device__ __forceinline__ void store_codes_i4(const float (&m)[8], uint8_t* dst, bool vec_ok, int nvalid) {
-    uint32_t u[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) u[e] = __float_as_uint(m[e]);
-    uint32_t w0 = pack_bytes(u[0], u[1], u[2], u[3]) & 0x0F0F0F0Fu;
-    uint32_t w1 = pack_bytes(u[4], u[5], u[6], u[7]) & 0x0F0F0F0Fu;
-    w0 |= w0 >> 4;                 // bytes 0 and 2 now hold two nibbles each
-    w1 |= w1 >> 4;
-    const uint32_t w = __builtin_amdgcn_perm(w1, w0, 0x06040200u);
-    if (vec_ok && nvalid == 8) {
-        store_through(w, reinterpret_cast<uint32_t*>(dst));
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (2 * e < nvalid) dst[e] = (uint8_t)((w >> (8 * e)) & 0xFFu);  // the channel count is even
+        for (int e = 0; e < (int)(N / sizeof(U)); ++e)
+            if (e * (int)sizeof(U) < n) static_cast<U*>(dst)[e] = u[e];
     }
 }
 
@@ -377,37 +328,8 @@ __device__ __forceinline__ void store_codes_i4(const float (&m)[8], uint8_t* dst
 // rows x 64 columns = 1536 bytes, fragments ordered [row / 32][column / 64]; fragment lane
 // (row & 31) + 32 * ((column / 32) & 1) holds 32 consecutive columns as a 192-bit little-endian
 // stream of 6-bit fields, its first 16 bytes at fragment + 16 * lane, the last 8 at fragment + 1024
-// + 8 * lane.  The wave's lanes 4g .. 4g+3 hold the 32 columns of group g (8 each): their 48-bit
-// pieces are gathered with three shuffles; lane 4g stores the 16 bytes, lane 4g+2 the 8 bytes.
-// E2M3 of an integer 0..7 is the top of its binary32 pattern: (bits >> 20) - 0x3F0 (0 for 0).
-// `group_ok`: the group's columns exist (I % 64 == 0: all or none).  frags_per_row = I / 64.
-__device__ __forceinline__ void store_codes_fp6(const float (&m)[8], uint8_t* packed, int row, int first_col,
-                                                int lane, int frags_per_row, bool group_ok) {
-    uint32_t e[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const float q = m[k] - kMagic;                                   // the code, exact
-        const int mag = (int)(__float_as_uint(__builtin_fabsf(q)) >> 20) - 0x3F0;
-        e[k] = (uint32_t)max(mag, 0) | (q < 0.0f ? 32u : 0u);
-    }
-    const uint32_t lo = e[0] | (e[1] << 6) | (e[2] << 12) | (e[3] << 18) | (e[4] << 24) | (e[5] << 30);
-    const uint32_t hi = (e[5] >> 2) | (e[6] << 4) | (e[7] << 10);        // 16 bits
-    const uint32_t lo1 = (uint32_t)__shfl_down((int)lo, 1, kLanes), hi1 = (uint32_t)__shfl_down((int)hi, 1, kLanes);
-    const uint32_t lo2 = (uint32_t)__shfl_down((int)lo, 2, kLanes);
-    const int q4 = lane & 3, g = lane >> 2;
-    const int col = first_col + 32 * g;                                  // first column of the group
-    const int64_t frag = (int64_t)(row >> 5) * frags_per_row + (col >> 6);
-    const int flane = (row & 31) + 32 * ((col >> 5) & 1);
-    uint8_t* f = packed + frag * 1536;
-    // plain (cacheable) stores: a 128-byte line of a fragment is completed by 8 (or 16) different rows,
-    // so the pieces have to meet in L2 before they leave for memory
-    if (group_ok && q4 == 0)
-        *reinterpret_cast<u32x4*>(f + flane * 16) = u32x4{lo, hi | (lo1 << 16), (lo1 >> 16) | (hi1 << 16), lo2};
-    if (group_ok && q4 == 2)
-        *reinterpret_cast<u32x2*>(f + 1024 + flane * 8) = u32x2{hi | (lo1 << 16), (lo1 >> 16) | (hi1 << 16)};
-}
-
-// The same fragments written four rows at a time (rows 4 k .. 4 k + 3 of one matrix, as the streaming kernel
+// + 8 * lane.  The wave's lanes 4g .. 4g+3 hold the 32 columns of group g (8 each).
+// They are written four rows at a time (rows 4 k .. 4 k + 3 of one matrix, as the streaming kernel
 // works on them): a lane keeps its 48 bits of each of the four rows, then the quad transposes them (two
 // exchange steps of quad-permute register moves, no LDS) so that lane 4 g + u holds the whole 24-byte record of
 // row u, and each lane stores one 16-byte and one 8-byte piece: a quad writes 64 and 32 contiguous bytes where
@@ -475,22 +397,6 @@ __device__ __forceinline__ void fp6_batch_store(Fp6Batch& out, uint8_t* packed, 
     const int off = ok ? (col >> 6) * 1536 : 0x7FFF0000;
     __builtin_amdgcn_raw_buffer_store_b128(u32x4{out.lo[0], d1, d2, out.lo[2]}, frow, off + flane * 16, 0, kWriteThrough);
     __builtin_amdgcn_raw_buffer_store_b64(u32x2{d4, d5}, frow, off + 1024 + flane * 8, 0, kWriteThrough);
-}
-
-// dequantized values fl16(fl32(q * fl32(a * b))): 16 bytes at dst
-__device__ __forceinline__ void store_xhat(const float (&q)[8], float a, const float (&b)[8], uint16_t* dst,
-                                           bool vec_ok, int nvalid) {
-    float y[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) y[e] = rounded_f32(q[e] * (a * b[e]));
-    if (vec_ok && nvalid == 8) {
-        store_through(u32x4{pack_half2(y[0], y[1]), pack_half2(y[2], y[3]), pack_half2(y[4], y[5]), pack_half2(y[6], y[7])},
-                      reinterpret_cast<u32x4*>(dst));
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if (e < nvalid) dst[e] = (uint16_t)f2h(y[e]);
-    }
 }
 
 }  // namespace cq

@@ -231,9 +231,9 @@ fused_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, float al
             quantize8(xv, a, safe_rcp(a), b, rb, qmax, m, q, false);
             nonzero += count_nonzero8(m);
             if (col_ok) {
-                if (MODE == 1) store_codes_i8(m, cp, true, 8);
-                if (MODE == 2) store_codes_i4(m, cp, true, 8);
-                if (XHAT) store_xhat(q, a, b, hp, true, 8);
+                if (MODE == 1) store_through(pack_codes_i8(m), reinterpret_cast<u32x2*>(cp));
+                if (MODE == 2) store_through(pack_codes_i4(m), reinterpret_cast<uint32_t*>(cp));
+                if (XHAT) store_through(pack_xhat(q, a, b), reinterpret_cast<u32x4*>(hp));
             }
         }
         cp += c_step;

@@ -4,9 +4,6 @@
 // The element-wise step is D_ij = fl32(a_i * b_j) with a_i = t_i^alpha / q_max and
 // b_j = c_j^(1-alpha); the code is q_ij = clamp(rne(fl32(x_ij / D_ij)), +-q_max).
 //
-// Two kernels: quantize_stream_kernel for the layout every real activation has (aligned, I % 8 == 0), and
-// quantize_kernel, its older form with per-lane bounds handling, for everything else.
-//
 // The kernel moves 2 B read + 1 or 0.5 B codes + optionally 2 B dequantized per element, and on this
 // part it is the vector-instruction count per element that decides whether it keeps up with that
 // (packed binary32 arithmetic is not used), so the per-element work is kept small.  A correctly
@@ -53,156 +50,27 @@ __global__ void zero_u64_kernel(unsigned long long* p) { *p = 0ull; }
 // I % 64 == 0).
 // Block: 8 waves sharing 512 columns; each wave streams over nb batches of 4 consecutive rows.
 // The block first forms the scale factors of its own columns and rows from t and c (binary64
-// pow: thread k takes column k, then row k if the block has that many rows; the first batch of X
-// rows is requested before, so the memory system is busy meanwhile) and shares them through LDS;
+// pow: thread k takes column k, then row k if the block has that many rows; the first rows of X
+// are requested before, so the memory system is busy meanwhile) and shares them through LDS;
 // the blocks of column chunk 0 / row chunk 0 also write them to a_out / b_out for the caller.  Every block that needs a factor
 // computes the same bits from the same inputs, so no kernel has to run beforehand.
-// Codes and the dequantized matrix are written through to memory (store_through).
 // A batch of B matrices (each with its own column factors) is one launch: B copies of the
 // one-matrix grid; a block first steps its pointers to its own matrix.
-template <int MODE, bool XHAT, bool VEC>
-__global__ void __launch_bounds__(kWaves * kLanes)
-quantize_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, const float* __restrict__ t_vec,
-                const float* __restrict__ c_vec, double alpha, int qmax_i, float* __restrict__ a_out,
-                float* __restrict__ b_out, uint8_t* __restrict__ codes, uint16_t* __restrict__ xhat,
-                unsigned long long* __restrict__ zero_count, int slot,
-                int n_col_chunks, int nb, bool out_vec, int blocks_per_matrix, int64_t matrix_stride) {
-    __shared__ uint32_t lds_cnt[kWaves];
-    __shared__ float lds_b[kColsPerWave];
-    __shared__ float lds_a[kWaves * kLanes];                // row factors of the block's (at most 512) rows
-    const int lane = threadIdx.x & (kLanes - 1);
-    const int wave = threadIdx.x / kLanes;
-    const int matrix = blockIdx.x / blocks_per_matrix;
-    const int blk = blockIdx.x - matrix * blocks_per_matrix;
-    X += (int64_t)matrix * matrix_stride;
-    t_vec += (int64_t)matrix * T;
-    c_vec += (int64_t)matrix * I;
-    if (a_out) a_out += (int64_t)matrix * T;           // null: the caller does not want the factors (count only)
-    if (b_out) b_out += (int64_t)matrix * I;
-    if (MODE == 1) codes += (int64_t)matrix * T * I;
-    if (MODE == 2) codes += (int64_t)matrix * T * (I / 2);
-    if (XHAT) xhat += (int64_t)matrix * T * I;
-    const int col_chunk = blk % n_col_chunks;
-    const int row_chunk = blk / n_col_chunks;
-    const int j0 = col_chunk * kColsPerWave + lane * 8;
-    const int rows_per_wave = nb * kU;                      // <= 64
-    const int rows_per_block = kWaves * rows_per_wave;      // <= 512 = the block's thread count
-    const int row0 = row_chunk * rows_per_block + wave * rows_per_wave;
-    const float qmax = (float)qmax_i;
-
-    // A wave walks its batches from the last to the first: the absmax kernel, which normally ran just before,
-    // walks them first to last, so the rows it touched last are still in the caches when they are read here
-    // first (measured in a step on 4096 x 8192: this kernel 32.4 -> 30.2 us, the same in five processes).
-    // (The count-only form walks first to last: it normally follows the quantize call, whose last rows are
-    // its first: 20.8 -> 19.3 us on 4096 x 8192.)
-    auto batch_at = [&](int bi) { return MODE == 0 ? bi : nb - 1 - bi; };
-    auto batch_row = [&](int bi) { return row0 + batch_at(bi) * kU; };
-    // first two batches of rows: in flight while the scale factors are formed
-    uint4 v[kU], w[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u)
-        v[u] = (batch_row(0) + u < T) ? load8<VEC>(X + (int64_t)(batch_row(0) + u) * ldx, j0, I)
-                                      : make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-    for (int u = 0; u < kU; ++u)
-        w[u] = (nb > 1 && batch_row(1) + u < T) ? load8<VEC>(X + (int64_t)(batch_row(1) + u) * ldx, j0, I)
-                                                : make_uint4(0u, 0u, 0u, 0u);
-
-    block_scale_factors(t_vec, c_vec, alpha, qmax_i, T, I, col_chunk * kColsPerWave, row_chunk * rows_per_block,
-                        rows_per_block, lds_a, lds_b, col_chunk == 0 ? a_out : nullptr, row_chunk == 0 ? b_out : nullptr);
-    __syncthreads();
-    // the wave's row factors, one per lane, handed out with readlane as the rows come up
-    const float a_lane = lds_a[wave * rows_per_wave + (lane < rows_per_wave ? lane : 0)];
-
-    float b[8], rb[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        b[e] = lds_b[lane * 8 + e];                         // 0 for columns past the end
-        rb[e] = safe_rcp(b[e]);
-    }
-    bool b_tiny = false;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) b_tiny |= tiny_factor(b[e]);
-    int nvalid = I - j0;                                    // columns of this lane that exist
-    nvalid = nvalid < 0 ? 0 : (nvalid > 8 ? 8 : nvalid);
-
-    uint32_t nonzero = 0u;    // codes != 0 seen by this wave (uniform)
-    int rows_done = 0;
-    for (int bi = 0; bi < nb; ++bi) {
-        const int rbase = batch_row(bi);
-        if (bi == 1) {
-#pragma unroll
-            for (int u = 0; u < kU; ++u) v[u] = w[u];
-        } else if (bi > 1) {
-#pragma unroll
-            for (int u = 0; u < kU; ++u)
-                v[u] = (rbase + u < T) ? load8<VEC>(X + (int64_t)(rbase + u) * ldx, j0, I) : make_uint4(0u, 0u, 0u, 0u);
-        }
-        if (rbase >= T) continue;                           // wave-uniform: a batch past the last row
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int r = rbase + u;
-            if (r >= T) break;                              // wave-uniform
-            ++rows_done;
-            const float a = __builtin_bit_cast(
-                float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, a_lane), batch_at(bi) * kU + u));
-            if (MODE == 0) {
-                // a == 0 means D = 0 and every code of the row is 0 by definition: left to the exact path
-                nonzero += count_row8_wave(v[u], a, 0.5f * a, 0.5f * a * kTieTol, b, rb, qmax,
-                                           b_tiny || tiny_factor(a) || a == 0.0f);
-                continue;
-            }
-            float m[8], q[8];
-            quantize8(v[u], a, safe_rcp(a), b, rb, qmax, m, q, b_tiny || tiny_factor(a));
-            nonzero += count_nonzero8_wave(m);
-            if (MODE == 1) store_codes_i8(m, codes + (int64_t)r * I + j0, out_vec, nvalid);
-            if (MODE == 2) store_codes_i4(m, codes + (int64_t)r * (I / 2) + j0 / 2, out_vec, nvalid);
-            if (MODE == 3) store_codes_fp6(m, codes, r, col_chunk * kColsPerWave, lane, I / 64, j0 < I);
-            if (XHAT) store_xhat(q, a, b, xhat + (int64_t)r * I + j0, out_vec, nvalid);
-        }
-    }
-
-    if (zero_count) {
-        // padded columns hold x = 0 and add nothing to `nonzero`
-        int wave_cols = I - col_chunk * kColsPerWave;       // columns of this wave that exist
-        wave_cols = wave_cols > kColsPerWave ? kColsPerWave : wave_cols;
-        const uint32_t zeros = (uint32_t)(rows_done * wave_cols) - nonzero;
-        if (lane == 0) lds_cnt[wave] = zeros;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            uint32_t s = 0;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) s += lds_cnt[w];
-            // one atomic per block: same-address atomics serialise, so the grid is kept small
-            if (slot >= 0) {
-                unsigned long long* zero_state = &g_zero_state[slot];
-                const unsigned long long add = (1ull << kTicketShift) | (unsigned long long)s;
-                const unsigned long long old =
-                    __hip_atomic_fetch_add(zero_state, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if ((unsigned)(old >> kTicketShift) == gridDim.x - 1u) {        // every other block has added
-                    *zero_count = (old + add) & ((1ull << kTicketShift) - 1ull);
-                    __hip_atomic_store(zero_state, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-            } else if (s) {
-                atomicAdd(zero_count, (unsigned long long)s);                    // caller's counter, cleared before
-            }
-        }
-    }
-}
-
-// The same kernel for the layout every real activation has: X 16-byte aligned with ldx % 8 == 0, I % 8 == 0 and
-// aligned outputs, so that a lane's 8 columns exist or not as a whole.  What differs from quantize_kernel:
+// BUF: the layout every real activation has, X 16-byte aligned with ldx % 8 == 0, I % 8 == 0 and aligned outputs, so that
+// a lane's 8 columns exist or not as a whole:
 //   - rows are addressed as raw buffers (base and length in scalar registers, range-checked by the hardware), so
 //     the loop body has no per-lane branches and no 64-bit vector address arithmetic;
 //   - the stores are buffer stores with the write-through policy the compiler knows about, so its vmcnt waits for
-//     the next rows' loads do not also wait for this row's stores to be acknowledged by memory;
-//   - the loop is software-pipelined by hand: two register sets of kU rows alternate, the loads of batch bi + 1
-//     are requested before batch bi is worked on.  (The loop is kept a loop: unrolled completely for a known
-//     number of batches, where the compiler's count of outstanding memory operations becomes exact, it ran 4 us
-//     slower on the 4096 x 8192 layer than with the loop's conservative waits.  Two sets is the optimum also for
-//     the count-only form, which has registers to spare: 4096 x 8192 in a layer step takes 17.7 us with two sets,
-//     18.6 with one, 19.6 with three and 23.3 with four, i.e. with all of X requested at once.)
-template <int MODE, bool XHAT>
+//     the next rows' loads do not also wait for this row's stores to be acknowledged by memory.
+// Any other layout: unaligned 16-byte loads (load8), unaligned stores of whole pieces and element stores of the one lane
+// at the end of a row.
+// The loop is software-pipelined by hand: two register sets of kU rows alternate, the loads of batch bi + 1
+// are requested before batch bi is worked on.  (The loop is kept a loop: unrolled completely for a known
+// number of batches, where the compiler's count of outstanding memory operations becomes exact, it ran 4 us
+// slower on the 4096 x 8192 layer than with the loop's conservative waits.  Two sets is the optimum also for
+// the count-only form, which has registers to spare: 4096 x 8192 in a layer step takes 17.7 us with two sets,
+// 18.6 with one, 19.6 with three and 23.3 with four, i.e. with all of X requested at once.)
+template <int MODE, bool XHAT, bool BUF>
 __global__ void __launch_bounds__(kWaves * kLanes)
 quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, const float* __restrict__ t_vec,
                        const float* __restrict__ c_vec, double alpha, int qmax_i, float* __restrict__ a_out,
@@ -227,13 +95,17 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
     const int col_chunk = blk % n_col_chunks;
     const int row_chunk = blk / n_col_chunks;
     const int col0 = col_chunk * kColsPerWave;
-    const int cols_here = min(kColsPerWave, I - col0);      // columns of this chunk that exist: a multiple of 8
+    const int cols_here = min(kColsPerWave, I - col0);      // columns of this chunk that exist: a multiple of 8 with BUF
     const int rows_per_wave = nb * kU;                      // <= 64
     const int rows_per_block = kWaves * rows_per_wave;      // <= 512 = the block's thread count
     const int row0 = row_chunk * rows_per_block + wave * rows_per_wave;
     const float qmax = (float)qmax_i;
 
-    // walk order as in quantize_kernel: last batch first, except for the count-only form
+    // A wave walks its batches from the last to the first: the absmax kernel, which normally ran just before,
+    // walks them first to last, so the rows it touched last are still in the caches when they are read here
+    // first (measured in a step on 4096 x 8192: this kernel 32.4 -> 30.2 us, the same in five processes).
+    // (The count-only form walks first to last: it normally follows the quantize call, whose last rows are
+    // its first: 20.8 -> 19.3 us on 4096 x 8192.)
     auto batch_at = [&](int bi) { return MODE == 0 ? bi : nb - 1 - bi; };
     // Rows past the last one are read from the last row instead (and never worked on): a register that is
     // written by nothing but loads lets the compiler count outstanding loads instead of waiting for all of them.
@@ -243,7 +115,8 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const int r = min(rbase + u, T - 1);
-            dst[u] = buffer_load16(row_buffer(X + (int64_t)r * ldx + col0, cols_here * 2), lane * 16);
+            const uint16_t* row = X + (int64_t)r * ldx;
+            dst[u] = BUF ? buffer_load16(row_buffer(row + col0, cols_here * 2), lane * 16) : load8<false>(row, col0 + lane * 8, I);
         }
     };
     // The maxima this thread turns into scale factors (column col0 + k, row k of the block) are requested before
@@ -258,7 +131,10 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
     // test of the quantizer would show it (the scale factors would be stale).
     const int k_thread = (int)threadIdx.x;
     float c_in, t_in;
-    {
+    if (!BUF) {                                              // no count of requests to rely on there: ordinary loads
+        c_in = c_vec[min(col0 + k_thread, I - 1)];
+        t_in = t_vec[min(row_chunk * rows_per_block + k_thread, T - 1)];
+    } else {
         const float* cp = c_vec + min(col0 + k_thread, I - 1);
         const float* tp = t_vec + min(row_chunk * rows_per_block + k_thread, T - 1);
         asm volatile("global_load_dword %0, %2, off sc1\n\tglobal_load_dword %1, %3, off sc1"
@@ -271,7 +147,7 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
     if (nb >= 2) load_batch(vb, 1);
     else load_batch(vb, 0);                                 // a wave with one batch requests it twice: always 2 kU requests
     static_assert(kU == 4, "the wait below counts the row requests of two batches");
-    asm volatile("s_waitcnt vmcnt(8)" : "+v"(c_in), "+v"(t_in)::"memory");
+    if (BUF) asm volatile("s_waitcnt vmcnt(8)" : "+v"(c_in), "+v"(t_in)::"memory");
 
     {
         // thread k: factor of column col0 + k (0 past the last column) and, if the block has that many rows, of its
@@ -335,9 +211,19 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
                 continue;
             }
             const int live = row_ok ? cols_here : 0;         // columns of this row that may be stored
+            const int nvalid = max(0, min(8, live - lane * 8));     // ... of this lane's eight
             // count, pack and store one row piece; returns the lane's number of non-zero codes in it
             auto emit = [&](const float (&m)[8], const float (&q)[8]) -> uint32_t {
                 const uint32_t nz = count_nonzero8_lane(m);
+                if (MODE == 3) fp6_batch_row(f6, m, u);
+                if (!BUF) {
+                    if (MODE == 1) store_piece<8, uint8_t>(pack_codes_i8(m), codes + (int64_t)rr * I + col0 + lane * 8, nvalid);
+                    if (MODE == 2)                           // (the channel count is even: whole bytes)
+                        store_piece<4, uint8_t>(pack_codes_i4(m), codes + (int64_t)rr * (I / 2) + (col0 + lane * 8) / 2, nvalid / 2);
+                    if (XHAT)
+                        store_piece<16, uint16_t>(pack_xhat(q, a, b), xhat + (int64_t)rr * I + col0 + lane * 8, nvalid * 2);
+                    return nz;
+                }
                 if (MODE == 1)
                     __builtin_amdgcn_raw_buffer_store_b64(pack_codes_i8(m), row_buffer(codes + (int64_t)rr * I + col0, live),
                                                           lane * 8, 0, kWriteThrough);
@@ -345,7 +231,6 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
                     __builtin_amdgcn_raw_buffer_store_b32(pack_codes_i4(m),
                                                           row_buffer(codes + (int64_t)rr * (I / 2) + col0 / 2, live / 2),
                                                           lane * 4, 0, kWriteThrough);
-                if (MODE == 3) fp6_batch_row(f6, m, u);
                 if (XHAT)
                     __builtin_amdgcn_raw_buffer_store_b128(pack_xhat(q, a, b), row_buffer(xhat + (int64_t)rr * I + col0, live * 2),
                                                            lane * 16, 0, kWriteThrough);
@@ -421,27 +306,16 @@ hipError_t launch_mode(const uint16_t* X, int B, int T, int I, int64_t ldx, int6
     if (!grid_fits((int64_t)B * ncc * nrc, kWaves * kLanes)) return hipErrorInvalidValue;    // hence < 2^23 blocks
     const unsigned n_blocks = (unsigned)(B * ncc * nrc);
     const dim3 grid(n_blocks), block(kWaves * kLanes);
-    const bool vec = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && (ldx % 8 == 0) && (B == 1 || matrix_stride % 8 == 0);
-    // vector stores need every lane's piece aligned: I % 8 == 0 and aligned bases
-    const bool out_vec = (I % 8 == 0) && (reinterpret_cast<uintptr_t>(codes) % 8 == 0) &&
-                         (reinterpret_cast<uintptr_t>(xhat) % 16 == 0);
+    // the layout every real activation has: no partial pieces, no misaligned pointers
+    const bool buf = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && (ldx % 8 == 0) && (B == 1 || matrix_stride % 8 == 0) &&
+                     (I % 8 == 0) && (reinterpret_cast<uintptr_t>(codes) % 8 == 0) &&
+                     (reinterpret_cast<uintptr_t>(xhat) % 16 == 0);
     // no slot: clear the caller's counter and add to it directly
     const int state = zc ? stream_slot(stream) : -1;
     if (zc && state < 0) zero_u64_kernel<<<dim3(1), dim3(1), 0, stream>>>(zc);
-    // the layout every real activation has: the streaming kernel (no partial pieces, no misaligned pointers)
-    const bool stream_ok = vec && (I % 8 == 0) && (reinterpret_cast<uintptr_t>(codes) % 8 == 0) &&
-                           (reinterpret_cast<uintptr_t>(xhat) % 16 == 0);
-    if (stream_ok)
-        quantize_stream_kernel<MODE, XHAT><<<grid, block, 0, stream>>>(X, T, I, ldx, t, c, alpha, qmax, a, b, codes, xhat,
-                                                                      zc, state, ncc, nb, ncc * nrc, matrix_stride);
-    else if (vec)
-        quantize_kernel<MODE, XHAT, true><<<grid, block, 0, stream>>>(X, T, I, ldx, t, c, alpha, qmax, a, b, codes, xhat,
-                                                                     zc, state, ncc, nb, out_vec, ncc * nrc,
-                                                                     matrix_stride);
-    else
-        quantize_kernel<MODE, XHAT, false><<<grid, block, 0, stream>>>(X, T, I, ldx, t, c, alpha, qmax, a, b, codes,
-                                                                      xhat, zc, state, ncc, nb, out_vec, ncc * nrc,
-                                                                      matrix_stride);
+    const auto kernel = buf ? &quantize_stream_kernel<MODE, XHAT, true> : &quantize_stream_kernel<MODE, XHAT, false>;
+    kernel<<<grid, block, 0, stream>>>(X, T, I, ldx, t, c, alpha, qmax, a, b, codes, xhat, zc, state, ncc, nb, ncc * nrc,
+                                       matrix_stride);
     return hipGetLastError();
 }
 

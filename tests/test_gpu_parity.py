@@ -970,6 +970,39 @@ def test_weight_crossquant_through_the_activation_calls(cq):
     assert torch.equal(codes, qw_pc) and torch.equal(u, s_pc)
 
 
+# widths around a lane's 8 columns and a wave's 512 that the range-checked path does not take (odd ones, or rows that start
+# off a 16-byte boundary): whole pieces by unaligned loads and stores, a row's last columns by the lane that shifts
+@pytest.mark.parametrize("I", [2, 7, 8, 9, 16, 23, 505, 512, 513, 518, 1031])
+@pytest.mark.parametrize("T,ldx,first", [(1, 1034, 0), (37, 1037, 1), (70, 1040, 1)])
+def test_quantizer_widths_and_rows_off_the_vector_layout(cq, T, I, ldx, first):
+    import torch
+    say("off the vector layout T=%d I=%d ldx=%d first=%d" % (T, I, ldx, first))
+    X = outliers(T, I, seed=T + I)
+    buf = torch.full((first + T * ldx,), float("nan"), dtype=torch.float16, device="cuda")   # anything read past a row shows
+    Xg = buf[first:].view(T, ldx)[:, :I]
+    Xg.copy_(gpu(X))
+    t_ref, c_ref = oracle.absmax(X)
+    t, c = cq.crossquant_absmax(Xg)
+    assert np.array_equal(host(t), t_ref) and np.array_equal(host(c), c_ref)
+    for bits in (8, 4) if I % 2 == 0 else (8,):
+        ref = oracle.quantize(X, t_ref, c_ref, 0.15, bits)
+        n = I if bits == 8 else I // 2
+        codes = torch.full((T * n + 9,), 99, dtype=torch.int8 if bits == 8 else torch.uint8, device="cuda")
+        xhat = torch.full((T * I + 9,), 7.0, dtype=torch.float16, device="cuda")
+        _, _, a, b, z = cq.crossquant_quantize(Xg, t, c, 0.15, bits, codes=codes[1:1 + T * n].view(T, n),
+                                               xhat=xhat[1:1 + T * I].view(T, I))
+        hc, hx = host(codes), host(xhat)
+        assert np.array_equal(hc[1:1 + T * n].reshape(T, n), ref["codes"]) and int(z.item()) == ref["Z"]
+        assert np.array_equal(bits16(hx[1:1 + T * I].reshape(T, I)), bits16(ref["xhat"]))
+        assert hc[0] == 99 and np.all(hc[1 + T * n:] == 99) and hx[0] == 7.0 and np.all(hx[1 + T * I:] == 7.0)
+        assert np.array_equal(host(a), ref["a"]) and np.array_equal(host(b), ref["b"])
+        assert int(cq.crossquant_kernel_count(Xg, t, c, 0.15, bits).item()) == ref["Z"]
+        xrk, cnt = cq.crossquant_kernel_analysis(Xg, t, c, 0.15, bits)
+        an = oracle.kernel_analysis(X, t_ref, c_ref, 0.15, bits)
+        assert np.array_equal(bits16(host(xrk)), bits16(an["xrk"]))
+        assert [int(v) for v in host(cnt)] == [an["Z"], an["n_col_ge_row"], an["n_bound_smaller"]]
+
+
 # ----------------------------------------------------------------------------- linear
 LINEAR_SHAPES = [(1, 16, 1), (5, 32, 7), (100, 200, 300), (64, 256, 256), (256, 128, 256), (300, 208, 270),
                  (256, 1024, 512), (513, 384, 257), (33, 100, 65),
