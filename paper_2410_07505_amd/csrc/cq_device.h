@@ -81,20 +81,73 @@ __device__ __forceinline__ uint32_t rows8_reduce(const uint32_t* rm, int lane) {
     return m;
 }
 
-// ---- scale factors of the CrossQuant step (binary64 pow, one rounding to binary32).
-// pow(x, 0) = 1 for every x and pow(x, 1) = x are exact in any correct pow; they are written out
-// so that the two special exponents (per-column and per-token steps) never depend on it.
+// ---- scale factors of the CrossQuant step: x^y (divided by q_max for a row) in binary64, rounded once to binary32.
+// The library's pow is good to an ulp of binary64 and takes as long as the rest of a small call (a 64 x 256 quantize call
+// is two of them one after the other); a binary32 result needs far less.  x^y = 2^(y (k + log2 m)), x = 2^k m with m in
+// [sqrt(1/2), sqrt(2)): log2 m is the atanh series in s = (m - 1) / (m + 1), |s| < 0.172, to s^19, and 2^f, |f| <= 1/2, its
+// Taylor series to f^12; their truncation is below 2^-51 and the binary64 roundings (of y log2 x above all, |log2 x| < 128)
+// leave less than 2^-46 relative (2^-46.5 measured over all binary32 x, 2^-48.7 over binary16 ones).  Where the value moved
+// by 2^-42 either way rounds to one binary32 number, every more accurate value does too, pow's included; otherwise (once
+// in 2^17) and for x that is zero, subnormal or not finite pow decides.  The result is pow's, bit for bit.
+// Exponents 0 and 1 (per-column and per-token steps) are written out: exact in any correct pow.
+__device__ __forceinline__ double short_pow(float x, double y) {
+    const uint32_t u = __float_as_uint(x);
+    double m = (double)__uint_as_float((u & 0x7FFFFFu) | 0x3F800000u);
+    int k = (int)(u >> 23) - 127;
+    if (m > 1.4142135623730951) {
+        m *= 0.5;
+        ++k;
+    }
+    const double den = m + 1.0;
+    double r = __builtin_amdgcn_rcp(den);                   // two Newton steps: full precision
+    r = __builtin_fma(__builtin_fma(-den, r, 1.0), r, r);
+    r = __builtin_fma(__builtin_fma(-den, r, 1.0), r, r);
+    const double s = (m - 1.0) * r, z = s * s;
+    // 2 / ((2 n + 1) ln 2)
+    double p = 0.15186263588304877;
+    p = __builtin_fma(p, z, 0.16972882833987804);
+    p = __builtin_fma(p, z, 0.19235933878519512);
+    p = __builtin_fma(p, z, 0.2219530832136867);
+    p = __builtin_fma(p, z, 0.2623081892525388);
+    p = __builtin_fma(p, z, 0.3205988979753252);
+    p = __builtin_fma(p, z, 0.41219858311113244);
+    p = __builtin_fma(p, z, 0.5770780163555853);
+    p = __builtin_fma(p, z, 0.9617966939259757);
+    p = __builtin_fma(p, z, 2.8853900817779268);
+    const double t = y * __builtin_fma(s, p, (double)k);
+    const double n = __builtin_rint(t), f = t - n;
+    // ln2^n / n!
+    double e = 2.5678435993488196e-11;
+    e = __builtin_fma(e, f, 4.44553827187081e-10);
+    e = __builtin_fma(e, f, 7.054911620801121e-09);
+    e = __builtin_fma(e, f, 1.0178086009239696e-07);
+    e = __builtin_fma(e, f, 1.3215486790144305e-06);
+    e = __builtin_fma(e, f, 1.5252733804059838e-05);
+    e = __builtin_fma(e, f, 0.00015403530393381606);
+    e = __builtin_fma(e, f, 0.0013333558146428441);
+    e = __builtin_fma(e, f, 0.009618129107628477);
+    e = __builtin_fma(e, f, 0.055504108664821576);
+    e = __builtin_fma(e, f, 0.2402265069591007);
+    e = __builtin_fma(e, f, 0.6931471805599453);
+    e = __builtin_fma(e, f, 1.0);
+    return __builtin_ldexp(e, (int)n);
+}
+// fl32(x^y / q); inv_q = 1 / q in binary64
+__device__ __forceinline__ float power_over(float x, double y, double q, double inv_q) {
+    if (y == 0.0) return (float)(1.0 / q);
+    if (y == 1.0) return (float)((double)x / q);
+    if (x >= 1.1754943508222875e-38f && x <= 3.4028234663852886e+38f) {
+        const double v = short_pow(x, y) * inv_q;
+        constexpr double kMargin = 2.2737367544323206e-13;   // 2^-42
+        const float lo = (float)__builtin_fma(v, -kMargin, v), hi = (float)__builtin_fma(v, kMargin, v);
+        if (lo == hi) return lo;
+    }
+    return (float)(pow((double)x, y) / q);
+}
 __device__ __forceinline__ float row_factor(float t, double al, int qmax) {
-    const double ti = (double)t;
-    const double p = (al == 0.0) ? 1.0 : (al == 1.0 ? ti : pow(ti, al));
-    return (float)(p / (double)qmax);
+    return power_over(t, al, (double)qmax, qmax == 127 ? 1.0 / 127.0 : 1.0 / 7.0);
 }
-__device__ __forceinline__ float col_factor(float c, double al) {
-    const double cj = (double)c;
-    const double e = 1.0 - al;
-    const double p = (e == 0.0) ? 1.0 : (e == 1.0 ? cj : pow(cj, e));
-    return (float)p;
-}
+__device__ __forceinline__ float col_factor(float c, double al) { return power_over(c, 1.0 - al, 1.0, 1.0); }
 
 // Scale factors of one block of 512 threads, shared through LDS: thread k forms the factor of column col0 + k
 // (lds_b[k]; 0 past the last column) and, if the block has that many rows, of row row0 + k (lds_a[k]; 0 past

@@ -146,6 +146,29 @@ def test_scale_factors_for_every_binary16_maximum(cq, alpha, bits):
     assert bad_a == 0 and bad_b == 0, (bad_a, bad_b)
 
 
+@pytest.mark.parametrize("alpha", [0.003, 0.15, 1.0 / 3.0, 0.5, 0.85, 0.997])
+@pytest.mark.parametrize("bits", [8, 4])
+def test_scale_factors_over_the_binary32_range(cq, alpha, bits):
+    """Calibrated maxima are any non-negative finite binary32 value: 2^17 spread over all exponents, the subnormal, smallest and
+    largest ones and exact powers of four, against the oracle's pow."""
+    import torch
+    say("scale factors over binary32, alpha=%g bits=%d" % (alpha, bits))
+    rng = np.random.default_rng(int(alpha * 1000) + bits)
+    vals = np.concatenate([rng.integers(0, 0x7F800000, 1 << 17, dtype=np.uint32).view(np.float32),
+                           np.array([0, 1, 0x7FFFFF, 0x800000, 0x7F7FFFFF, 0x3F800000, 0x3FB504F3, 0x3FB504F4], np.uint32).view(np.float32),
+                           (4.0 ** np.arange(-60, 61)).astype(np.float32)])
+    n = vals.size
+    a_ref, _ = oracle.scales(vals, vals[:8], alpha, bits)
+    _, b_ref = oracle.scales(vals[:8], vals, alpha, bits)
+    few = gpu(vals[:8].copy())
+    X = torch.zeros((n, 8), dtype=torch.float16, device="cuda")
+    _, _, a, _, _ = cq.crossquant_quantize(X, gpu(vals), few, alpha, bits, want_xhat=False)
+    X2 = torch.zeros((8, n - n % 2), dtype=torch.float16, device="cuda")
+    _, _, _, b, _ = cq.crossquant_quantize(X2, few, gpu(vals[:n - n % 2]), alpha, bits, want_xhat=False)
+    assert np.array_equal(bits32(host(a)), bits32(a_ref))
+    assert np.array_equal(bits32(host(b)), bits32(b_ref[:n - n % 2]))
+
+
 # ----------------------------------------------------------------------------- quantize
 def check_quantize(cq, X, alpha, bits, Xg=None, label=""):
     say("quantize %s shape=%s alpha=%g bits=%d" % (label, X.shape, alpha, bits))
