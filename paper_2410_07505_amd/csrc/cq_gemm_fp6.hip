@@ -501,18 +501,20 @@ gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__
                                             : qw6 + min(n0 / 32 + rb - kRbA, 2 * ((O + 63) / 64) - 1) * row_bytes;
             src[n] = base + frag * kFragBytes + lds_place(pair_offset - frag * kFragBytes) + share[n] * kPair;
         }
-        auto request = [&](int kt, int slot) {
+        // steps are taken from the end of the contraction: step 0 is its last, partly filled stretch, where shares past
+        // the end read zeros
+        auto request = [&](int kt, int slot) {                           // kt > 0
+            const int64_t koff = (int64_t)(nk - 1 - kt) * (WK * kPair);
             const int8_t* dst = lds + slot * kSlot;
-            const int64_t koff = (int64_t)kt * (WK * kPair);
-            if ((kt + 1) * WK <= nk128) {
 #pragma unroll
-                for (int n = 0; n < N; ++n) request_1k(src[n] + koff, dst + min(wave * N + n, kRequests - 1) * 1024);
-            } else {                                                     // shares past the end read zeros
+            for (int n = 0; n < N; ++n) request_1k(src[n] + koff, dst + min(wave * N + n, kRequests - 1) * 1024);
+        };
+        auto request_first = [&]() {
+            const int64_t koff = (int64_t)(nk - 1) * (WK * kPair);
 #pragma unroll
-                for (int n = 0; n < N; ++n)
-                    request_1k(kt * WK + share[n] < nk128 ? static_cast<const void*>(src[n] + koff) : static_cast<const void*>(&g_zero_piece),
-                               dst + min(wave * N + n, kRequests - 1) * 1024);
-            }
+            for (int n = 0; n < N; ++n)
+                request_1k((nk - 1) * WK + share[n] < nk128 ? static_cast<const void*>(src[n] + koff) : static_cast<const void*>(&g_zero_piece),
+                           lds + min(wave * N + n, kRequests - 1) * 1024);
         };
         struct Frags {
             frag6 a[MT], b[NT];
@@ -531,8 +533,9 @@ gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__
 #pragma unroll
             for (int ni = 0; ni < NT; ++ni) acc[mi][ni] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 
+        request_first();
 #pragma unroll
-        for (int s = 0; s < S; ++s)
+        for (int s = 1; s < S; ++s)
             if (s < nk) request(s, s);
         if (nk >= S) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 1) * N, 15));           // step 0 has landed
         else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));

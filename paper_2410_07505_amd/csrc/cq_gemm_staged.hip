@@ -36,8 +36,9 @@ __device__ __forceinline__ v4i load16_tail(const int8_t* row, int kb, int I) {
 // At step kt the fragments of kt are in registers; behind the step's barrier slot kt % S is free (step kt + S is
 // requested into it) and step kt + 1 has landed (its fragments are read while kt is multiplied): one barrier a step.
 // DMA: operands aligned to 16 bytes with I % 16 == 0 go straight to LDS; pieces past a row's end come from a zero
-// block.  Otherwise (I >= 16) they pass through registers, loaded unaligned one step before they are stored: 512 x 2752 x
-// 4096 takes 14.3 us in the first form, and 19.8 to 21.2 us with I = 2760, 2756, 2754, 2753 in the second.
+// block.  Otherwise (I >= 16) they pass through registers, loaded unaligned two steps before they are stored: 512 x 2752 x
+// 4096 takes 13.8 us in the first form, 512 x 2756 x 4096 15.5 us in the second (whether rows start on a word or a byte makes
+// 1 us; with one step in registers, and the row's end dealt with in every step, which spilled, 19.9 us).
 template <int MT, int NT, int WM, int WN, int WK, int S, bool DMA>
 __global__ void __launch_bounds__(64 * kSplitWaves)
 gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ row_scale, const int8_t* __restrict__ qw,
@@ -82,30 +83,23 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
                 src[n] = qw + (int64_t)min(n0 + grp * 16 * NT + NT * (in & 15) + (in >> 4), O - 1) * I + kb[n];
             }
         }
-        v4i reg[DMA ? 1 : N];
-        auto request = [&](int kt, int slot) {                // DMA: straight to LDS; else into registers
-            const int koff = kt * kStepK;
-            const int8_t* dst = lds + slot * kSlot + wave * N * 1024;
-            if (koff + kStepK <= I) {
+        // Steps are taken from the end of the contraction: step 0 is its last, partly filled stretch, so that only the
+        // prologue deals with pieces past a row's end.
+        auto load_step = [&](v4i (&r)[N], int kt) {           // register form: this wave's pieces of a step (kt > 0)
+            const int koff = (nk - 1 - kt) * kStepK;
 #pragma unroll
-                for (int n = 0; n < N; ++n) {
-                    if (DMA) request_1k(src[n] + koff, dst + n * 1024);
-                    else reg[DMA ? 0 : n] = load16(src[n] + koff);
-                }
-            } else {
-#pragma unroll
-                for (int n = 0; n < N; ++n) {
-                    if (DMA) request_1k(koff + kb[n] < I ? static_cast<const void*>(src[n] + koff) : static_cast<const void*>(&g_zero_piece),
-                                        dst + n * 1024);
-                    else reg[DMA ? 0 : n] = load16_tail(src[n] - kb[n], koff + kb[n], I);
-                }
-            }
+            for (int n = 0; n < N; ++n) r[n] = load16(src[n] + koff);
         };
-        auto commit = [&](int slot) {
-            if (DMA) return;
+        auto commit = [&](const v4i (&r)[N], int slot) {
 #pragma unroll
             for (int n = 0; n < N; ++n)
-                *reinterpret_cast<v4i*>(lds + slot * kSlot + (wave * N + n) * 1024 + lane * 16) = reg[DMA ? 0 : n];
+                *reinterpret_cast<v4i*>(lds + slot * kSlot + (wave * N + n) * 1024 + lane * 16) = r[n];
+        };
+        auto request = [&](int kt, int slot) {                // DMA: straight to LDS (kt > 0)
+            const int koff = (nk - 1 - kt) * kStepK;
+            const int8_t* dst = lds + slot * kSlot + wave * N * 1024;
+#pragma unroll
+            for (int n = 0; n < N; ++n) request_1k(src[n] + koff, dst + n * 1024);
         };
 
         struct Frags {
@@ -126,18 +120,33 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
 #pragma unroll
             for (int ni = 0; ni < NT; ++ni) acc[mi][ni] = v4i{0, 0, 0, 0};
 
-        // prologue: steps 0 .. S - 1 requested (register form: steps 0 .. S - 1 stored, step S in the registers)
-#pragma unroll
-        for (int s = 0; s < S; ++s)
-            if (s < nk) {
-                request(s, s);
-                commit(s);
-            }
-        if (!DMA && S < nk) request(S, 0);
+        // prologue: steps 0 .. S - 1 requested (register form: loaded together and stored; steps S and S + 1 on their way
+        // into the two register sets)
+        v4i r0[N], r1[N];
+        const int last = (nk - 1) * kStepK;                   // where step 0 starts
         if (DMA) {
+            const int8_t* dst = lds + wave * N * 1024;
+#pragma unroll
+            for (int n = 0; n < N; ++n)
+                request_1k(last + kb[n] < I ? static_cast<const void*>(src[n] + last) : static_cast<const void*>(&g_zero_piece),
+                           dst + n * 1024);
+#pragma unroll
+            for (int s = 1; s < S; ++s)
+                if (s < nk) request(s, s);
             if (nk >= S) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 1) * N, 15));      // step 0 has landed
             else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
         } else {
+            v4i pre[S][N];
+#pragma unroll
+            for (int n = 0; n < N; ++n) pre[0][n] = load16_tail(src[n] - kb[n], last + kb[n], I);
+#pragma unroll
+            for (int s = 1; s < S; ++s)
+                if (s < nk) load_step(pre[s], s);
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+                if (s < nk) commit(pre[s], s);
+            if (S < nk) load_step(r0, S);
+            if (S + 1 < nk) load_step(r1, S + 1);
             __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
         }
         __builtin_amdgcn_s_barrier();
@@ -146,7 +155,7 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
         read(f0, 0);
 
         int slot = 0;                                         // slot of step kt
-        auto step = [&](int kt, Frags& cur, Frags& nxt) {
+        auto step = [&](int kt, Frags& cur, Frags& nxt, v4i (&r)[N]) {
             // this wave's reads of step kt are done and its share of step kt + 1 has landed (steps kt + 2 .. kt + S - 1
             // may still be in flight; near the end, where there are fewer, all of them)
             if (DMA && kt + S - 1 < nk) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 2) * N, 0));
@@ -159,8 +168,8 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
                     if (DMA) {
                         request(kt + S, slot);
                     } else {
-                        commit(slot);
-                        if (kt + S + 1 < nk) request(kt + S + 1, 0);
+                        commit(r, slot);
+                        if (kt + S + 2 < nk) load_step(r, kt + S + 2);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -178,8 +187,8 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
             slot = next_slot;
         };
         for (int kt = 0; kt < nk; kt += 2) {
-            step(kt, f0, f1);
-            if (kt + 1 < nk) step(kt + 1, f1, f0);
+            step(kt, f0, f1, r0);
+            if (kt + 1 < nk) step(kt + 1, f1, f0, r1);
         }
         __syncthreads();                                      // the ring is free: it holds the partial sums now
         sum_and_store<MT, NT, WM, WN, WK>(acc, reinterpret_cast<v4i*>(lds), wave, lane, row_scale, w_scale, T, O, Y, ldy,
@@ -237,10 +246,9 @@ static bool staged_dma(const int8_t* qx, const int8_t* qw, int I) {
     return reinterpret_cast<uintptr_t>(qx) % 16 == 0 && reinterpret_cast<uintptr_t>(qw) % 16 == 0 && I % 16 == 0;
 }
 
-static int best_kind(bool dma, int T, int O, int n_cu, int64_t* cost) {
+static int best_kind(int T, int O, int n_cu, int64_t* cost) {
     int best = -1;
     for (int k = 0; k < kNumKinds; ++k) {
-        if (k == 2 && !dma) continue;             // through registers this tile loses to its neighbours (512 x 2756 x 4096: 39 against 20 us)
         const int tm = kKinds[k][0], tn = kKinds[k][1];
         const int64_t tiles = (int64_t)((T + tm - 1) / tm) * ((O + tn - 1) / tn);
         const int64_t c = (tiles + n_cu - 1) / n_cu * (tm + tn);
@@ -252,9 +260,9 @@ static int best_kind(bool dma, int T, int O, int n_cu, int64_t* cost) {
     return best;
 }
 
-int64_t w8a8_staged_cost(const int8_t* qx, const int8_t* qw, int T, int I, int O, int n_cu) {
+int64_t w8a8_staged_cost(int T, int O, int n_cu) {
     int64_t cost = 0;
-    best_kind(staged_dma(qx, qw, I), T, O, n_cu, &cost);
+    best_kind(T, O, n_cu, &cost);
     return cost;
 }
 
@@ -267,18 +275,18 @@ hipError_t launch_w8a8_staged(const int8_t* qx, const float* row_scale, const in
     }
     const bool dma = staged_dma(qx, qw, I);
     int64_t cost;
-    // the steps and slots of a kind: as much of the contraction per barrier, and as many slots, as the LDS allows
-    // (through registers shorter steps, which leave registers free, are better: 512 x 2752 x 4096 with 64 x 128 tiles,
-    // WK 2 against 4: 14.3 and 14.3 us straight to LDS, 20.9 and 83 us through registers)
+    // the steps and slots of a kind: as much of the contraction per barrier, and as many slots, as the LDS allows; through
+    // registers shorter steps and fewer slots, which leave the registers for two steps on their way (512 x 2756 x 4096 with
+    // 64 x 128 tiles: 15.5 us with WK 2 and 3 slots, 15.7 with 4, 19.1 with WK 4)
 #define CQ_STAGED(MT, NT, WM, WN, WK, S, DMA) \
     launch_staged<MT, NT, WM, WN, WK, S, DMA>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream)
-    switch (best_kind(dma, T, O, n_cu, &cost)) {
-        case 0: return dma ? CQ_STAGED(1, 1, 1, 1, 8, 4, true) : CQ_STAGED(1, 1, 1, 1, 8, 4, false);
-        case 1: return dma ? CQ_STAGED(2, 2, 1, 1, 8, 4, true) : CQ_STAGED(2, 2, 1, 1, 8, 4, false);
-        case 2: return CQ_STAGED(2, 2, 1, 2, 4, 3, true);
-        case 3: return dma ? CQ_STAGED(2, 4, 2, 1, 4, 4, true) : CQ_STAGED(2, 2, 2, 2, 2, 4, false);
-        case 4: return dma ? CQ_STAGED(4, 4, 1, 2, 4, 3, true) : CQ_STAGED(2, 4, 2, 2, 2, 4, false);
-        default: return dma ? CQ_STAGED(4, 4, 2, 2, 2, 3, true) : CQ_STAGED(4, 4, 2, 2, 2, 3, false);
+    switch (best_kind(T, O, n_cu, &cost)) {
+        case 0: return dma ? CQ_STAGED(1, 1, 1, 1, 8, 4, true) : CQ_STAGED(1, 1, 1, 1, 8, 2, false);
+        case 1: return dma ? CQ_STAGED(2, 2, 1, 1, 8, 4, true) : CQ_STAGED(2, 2, 1, 1, 8, 2, false);
+        case 2: return dma ? CQ_STAGED(2, 2, 1, 2, 4, 3, true) : CQ_STAGED(2, 2, 1, 2, 4, 2, false);
+        case 3: return dma ? CQ_STAGED(2, 4, 2, 1, 4, 4, true) : CQ_STAGED(2, 2, 2, 2, 2, 2, false);
+        case 4: return dma ? CQ_STAGED(4, 4, 1, 2, 4, 3, true) : CQ_STAGED(2, 4, 2, 2, 2, 3, false);
+        default: return dma ? CQ_STAGED(4, 4, 2, 2, 2, 3, true) : CQ_STAGED(4, 4, 2, 2, 2, 2, false);
     }
 #undef CQ_STAGED
 }
