@@ -332,6 +332,7 @@ __device__ __forceinline__ rsrc_t row_buffer(const void* base, int bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);   // raw, 32-bit data
 }
 constexpr int kWriteThrough = 16;     // cache policy sc1: written through to memory at device scope (see store_through)
+constexpr int kStreamThrough = 18;    // sc1 nt: the same as a stream
 __device__ __forceinline__ uint4 buffer_load16(rsrc_t r, int byte_offset) {
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, byte_offset, 0, 0));
 }

@@ -993,6 +993,29 @@ def test_weight_crossquant_through_the_activation_calls(cq):
     assert torch.equal(codes, qw_pc) and torch.equal(u, s_pc)
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+def test_quantize_outputs_beyond_the_memory_side_cache(cq, bits):
+    """8192 x 7424: X and the outputs exceed 256 MiB, so codes and dequantized matrix leave as a stream; the same as the
+    four quarters of the rows on their own (which are written through), and into buffers that held other values."""
+    import torch
+    say("quantize beyond the cache, bits=%d" % bits)
+    T, I = 8192, 7424
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X = (torch.randn(T, I, generator=g, device="cuda") * 3.0).half()
+    t, c = cq.crossquant_absmax(X)
+    codes = torch.full((T, I) if bits == 8 else (T, I // 2), 77, dtype=torch.int8 if bits == 8 else torch.uint8, device="cuda")
+    xhat = torch.full((T, I), 7.0, dtype=torch.float16, device="cuda")
+    _, _, a, b, z = cq.crossquant_quantize(X, t, c, 0.15, bits, codes=codes, xhat=xhat)
+    zeros = 0
+    for r in range(0, T, T // 4):
+        rows = slice(r, r + T // 4)
+        codes_r, xhat_r, a_r, b_r, z_r = cq.crossquant_quantize(X[rows], t[rows].contiguous(), c, 0.15, bits)
+        assert torch.equal(codes[rows], codes_r) and torch.equal(xhat[rows].view(torch.int16), xhat_r.view(torch.int16))
+        assert torch.equal(a[rows], a_r) and torch.equal(b, b_r)
+        zeros += int(z_r.item())
+    assert int(z.item()) == zeros
+
+
 # widths around a lane's 8 columns and a wave's 512 that the range-checked path does not take (odd ones, or rows that start
 # off a 16-byte boundary): whole pieces by unaligned loads and stores, a row's last columns by the lane that shifts
 @pytest.mark.parametrize("I", [2, 7, 8, 9, 16, 23, 505, 512, 513, 518, 1031])
