@@ -57,13 +57,14 @@ typedef enum {
  *   t_i = max_j |X_ij|   (Eq. 1, per-token quantization)
  *   c_j = max_i |X_ij|   (the CrossQuant equation)
  * X: binary16 [T][ldx], ldx >= I (elements), 2-byte aligned (16-byte alignment of X together
- *    with ldx % 8 == 0 selects the vectorised path; any other layout takes a slower one).
+ *    with ldx % 8 == 0 and I % 8 == 0 is the layout the loads are made for; any other takes unaligned
+ *    16-byte loads).
  * t: out, float[T].  c: out, float[I].  Both are exact (a maximum of binary16 values).
- * The maxima are accumulated with atomics, so t and c are cleared first, inside the call.  In the
- * vectorised layout with I % 8 == 0 that is done by the one launch itself: its first blocks store the
+ * The maxima are accumulated with atomics, so t and c are cleared first, inside the call.  That is
+ * done by the one launch itself: its first blocks store the
  * zeros and the others wait for them (a bounded wait on a counter in library-owned device memory, one
  * per stream handle as for crossquant_quantize's zero count) before their atomics.  Calls captured
- * into a graph, calls on a stream without a counter of its own, and other layouts clear with a small
+ * into a graph and calls on a stream without a counter of its own clear with a small
  * kernel of their own before the pass.
  */
 int crossquant_absmax(const void *X, int64_t T, int64_t I, int64_t ldx, float *t, float *c,
@@ -231,9 +232,10 @@ int crossquant_weight_quantize_grouped(const void *W, int64_t I, int64_t O, cons
 /*
  * W8A8 linear layer Y = X . W on integer codes (Background section), INT8 MFMA, int32 accumulate.
  *   acc_ik = sum_j qx_ij * qw_kj  (exact);  Y_ik = fl16(fl32(fl32(float(acc_ik) * row_scale_i) * w_scale_k))
- * qx: int8 [T][I].  qw: int8 [O][I] (contraction axis contiguous).  Fast path: qx, qw, Y and
- *     w_scale 16-byte aligned, I % 128 == 0, O % 8 == 0, ldy % 8 == 0 (any T); other layouts take a
- *     slower, fully bounds-checked kernel with identical results.
+ * qx: int8 [T][I].  qw: int8 [O][I] (contraction axis contiguous).  Layers large enough to fill the chip with
+ *     256 x 256 tiles run fastest with qx, qw, Y and w_scale 16-byte aligned, I % 128 == 0, O % 8 == 0 and
+ *     ldy % 8 == 0 (any T); few tokens, small outputs and other layouts take smaller tiles, operands that are
+ *     16-byte aligned with I % 16 == 0 faster than others.  Identical results.
  * Y: out, binary16 [T][ldy], ldy >= O.  acc_debug: out, nullable, int32 [T][O] raw accumulators.
  * I * 127 * 127 must fit in int32 (I <= 133,000).
  */
