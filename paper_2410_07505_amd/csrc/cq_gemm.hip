@@ -423,7 +423,7 @@ hipError_t launch_w8a8_linear(const int8_t* qx, const float* row_scale, const in
                          al16(acc_debug) && ldy < ((int64_t)1 << 22);
     // The smaller tiles of cq_gemm_staged.hip where they cover the layer in less of their own measure (rounds x rows a
     // CU takes in per step): a round of half tiles counts as 240 there, one of whole tiles as 500.  At the line, us:
-    // 128 x 8192 x 28672 (256 : 240) 57.3 against 61.4 for the ring, 1024 x 4096 x 4096 (256 : 240) 24.5 : 24.3,
+    // 128 x 8192 x 28672 (256 : 240) 57.3 against 61.4 for the ring, 1024 x 4096 x 4096 (256 : 240) 23.1 : 24.2,
     // 512 x 4096 x 4096 (192 : 240) 15.5 : 24.0, 64 x 8192 x 28672 (192 : 240) 52.5 : 60.6, 256 x 4096 x 11008 (256 : 240)
     // 23.4 : 23.5.
     const int64_t ring_cost = (int64_t)((n_main + n_cu - 1) / n_cu) * 500 + (n_main < total ? 240 : 0);

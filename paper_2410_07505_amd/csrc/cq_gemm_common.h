@@ -151,9 +151,12 @@ __device__ const uint4 g_zero_piece = {0u, 0u, 0u, 0u};
 // the builtin the compiler makes every later LDS read wait until all such requests have landed (it cannot tell that the
 // ring's slots differ), which would serialise requests made steps ahead with the reads of the current step.  The kernels
 // order reads and in-flight writes themselves (slot discipline, explicit vmcnt waits, barriers).
+// ONCE: the bytes are read by this block alone and not again (non-temporal).
+template <bool ONCE = false>
 __device__ __forceinline__ void request_1k(const void* src, const int8_t* dst) {
     const uint32_t lds_off = (uint32_t)(uintptr_t)((lptr_t)dst);     // wave-uniform
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc0" : : "v"(src), "s"(lds_off) : "m0");
+    if (ONCE) asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" : : "v"(src), "s"(lds_off) : "m0");
+    else asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc0" : : "v"(src), "s"(lds_off) : "m0");
 }
 
 // The end of a tile: the WK partial sums of every accumulator meet in LDS (parts: [wk][wm][wn][mi][ni][lane]), are

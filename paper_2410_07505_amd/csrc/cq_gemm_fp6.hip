@@ -460,7 +460,7 @@ gemm_f6_ring_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ r
 // meet in LDS.  A step is 128 WK elements; a slot holds [WK][(TM + TN) / 32 row blocks][two fragments along K].  Bound, as
 // there, by the 28 bytes per clock a CU takes in from its L2, and for a decode step by the weights' way from HBM.
 // ---------------------------------------------------------------------------------------------------------------
-template <int MT, int WM, int WN, int WK, int S>
+template <int MT, int WM, int WN, int WK, int S, bool ONCE>
 __global__ void __launch_bounds__(64 * kSplitWaves)
 gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ row_scale,
                       const uint8_t* __restrict__ qw6, const float* __restrict__ w_scale, int T, int I, int O,
@@ -477,7 +477,7 @@ gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__
     const int wm = w / WN, wn = w % WN;
     const int64_t row_bytes = (int64_t)(I / 64) * kFragBytes;             // a row block's fragments
     const int nk128 = I / 128, nk = (nk128 + WK - 1) / WK;
-    const bool early = wave < 4;                                         // see gemm_i8_staged_kernel
+    const bool early = WK > 2 && wave < 4;                               // see gemm_i8_staged_kernel
     const FragLane fl = frag_lane(lane);
 
     const int per_xcd = (total + kXcds - 1) / kXcds;
@@ -507,7 +507,11 @@ gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__
             const int64_t koff = (int64_t)(nk - 1 - kt) * (WK * kPair);
             const int8_t* dst = lds + slot * kSlot;
 #pragma unroll
-            for (int n = 0; n < N; ++n) request_1k(src[n] + koff, dst + min(wave * N + n, kRequests - 1) * 1024);
+            for (int n = 0; n < N; ++n) {
+                const int id = min(wave * N + n, kRequests - 1);
+                if (ONCE && (id / 3) % kRb >= kRbA) request_1k<true>(src[n] + koff, dst + id * 1024);
+                else request_1k(src[n] + koff, dst + id * 1024);
+            }
         };
         auto request_first = [&]() {
             const int64_t koff = (int64_t)(nk - 1) * (WK * kPair);
@@ -574,7 +578,7 @@ gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__
     }
 }
 
-template <int MT, int WM, int WN, int WK, int S>
+template <int MT, int WM, int WN, int WK, int S, bool ONCE = false>
 hipError_t launch_f6_staged(const uint8_t* qx6, const float* row_scale, const uint8_t* qw6, const float* w_scale, int T, int I,
                             int O, uint16_t* Y, int64_t ldy, int32_t* acc_debug, hipStream_t stream) {
     constexpr int TM = 16 * MT * WM, TN = 64 * WN;
@@ -585,10 +589,10 @@ hipError_t launch_f6_staged(const uint8_t* qx6, const float* row_scale, const ui
     const int64_t total = (int64_t)tiles_m * ((O + TN - 1) / TN);
     if (total >= (int64_t)1 << 31) return hipErrorInvalidValue;
     static std::atomic<uint64_t> allowed{0};
-    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_f6_staged_kernel<MT, WM, WN, WK, S>), kLds, allowed);
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_f6_staged_kernel<MT, WM, WN, WK, S, ONCE>), kLds, allowed);
     if (e != hipSuccess) return e;
     const int64_t blocks = std::min<int64_t>((total + kXcds - 1) / kXcds * kXcds, (int64_t)1 << 20);
-    gemm_f6_staged_kernel<MT, WM, WN, WK, S><<<dim3((unsigned)blocks), dim3(64 * kSplitWaves), kLds, stream>>>(
+    gemm_f6_staged_kernel<MT, WM, WN, WK, S, ONCE><<<dim3((unsigned)blocks), dim3(64 * kSplitWaves), kLds, stream>>>(
         qx6, row_scale, qw6, w_scale, T, I, O, Y, ldy, acc_debug, tiles_m, (int)total);
     return hipGetLastError();
 }
@@ -646,9 +650,16 @@ hipError_t launch_w4a4_linear(const void* qx6, const float* row_scale, const voi
             kind = k;
         }
     }
+    // weights that one row of tiles reads once and that no cache keeps: see launch_w8a8_staged (32 x 8192 x 28672 33.9 -> 32.2
+    // us, 64 x 8192 x 28672 35.3 -> 34.1)
+    const bool once = kind >= 0 && T <= kinds[kind][0] && (int64_t)O * I / 4 * 3 > (int64_t)128 << 20;
     switch (kind) {
-        case 0: return launch_f6_staged<4, 2, 2, 2, 3>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
-        case 1: return launch_f6_staged<2, 2, 2, 2, 4>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
+        case 0:
+            return once ? launch_f6_staged<4, 2, 2, 2, 3, true>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream)
+                        : launch_f6_staged<4, 2, 2, 2, 3>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
+        case 1:
+            return once ? launch_f6_staged<2, 2, 2, 2, 4, true>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream)
+                        : launch_f6_staged<2, 2, 2, 2, 4>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
         case 2: return launch_f6_staged<2, 2, 1, 4, 3>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
         case 3: return launch_f6_staged<2, 1, 1, 8, 2>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
         default: break;

@@ -36,10 +36,10 @@ __device__ __forceinline__ v4i load16_tail(const int8_t* row, int kb, int I) {
 // At step kt the fragments of kt are in registers; behind the step's barrier slot kt % S is free (step kt + S is
 // requested into it) and step kt + 1 has landed (its fragments are read while kt is multiplied): one barrier a step.
 // DMA: operands aligned to 16 bytes with I % 16 == 0 go straight to LDS; pieces past a row's end come from a zero
-// block.  Otherwise (I >= 16) they pass through registers, loaded unaligned two steps before they are stored: 512 x 2752 x
+// block.  ONCE: the weights' requests are non-temporal.  Otherwise (I >= 16) they pass through registers, loaded unaligned two steps before they are stored: 512 x 2752 x
 // 4096 takes 13.8 us in the first form, 512 x 2756 x 4096 15.5 us in the second (whether rows start on a word or a byte makes
 // 1 us; with one step in registers, and the row's end dealt with in every step, which spilled, 19.9 us).
-template <int MT, int NT, int WM, int WN, int WK, int S, bool DMA>
+template <int MT, int NT, int WM, int WN, int WK, int S, bool DMA, bool ONCE>
 __global__ void __launch_bounds__(64 * kSplitWaves)
 gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ row_scale, const int8_t* __restrict__ qw,
                       const float* __restrict__ w_scale, int T, int I, int O, uint16_t* __restrict__ Y, int64_t ldy,
@@ -56,9 +56,10 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
     const int wm = w / WN, wn = w % WN;
     const int fr = lane & 15, chunk = lane >> 4;
     const int nk = (I + kStepK - 1) / kStepK;
-    // A request holds its wave for about 100 cycles: waves 0-3 (one per SIMD) request before they multiply and
-    // waves 4-7 after, so that one wave of every SIMD multiplies meanwhile.
-    const bool early = wave < 4;
+    // A request holds its wave for about 100 cycles: with many requests a step waves 0-3 (one per SIMD) make them before
+    // they multiply and waves 4-7 after, so that one wave of every SIMD multiplies meanwhile; with the short steps of WK = 2
+    // all waves make them after (1024 x 4096 x 4096 24.5 -> 23.0 us, 1000 x 2750 x 4090 through registers 26.5 -> 25.1).
+    const bool early = WK > 2 && wave < 4;
 
     const int per_xcd = (total + kXcds - 1) / kXcds;
     for (int i = blockIdx.x / kXcds; i < per_xcd; i += gridDim.x / kXcds) {
@@ -99,7 +100,10 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
             const int koff = (nk - 1 - kt) * kStepK;
             const int8_t* dst = lds + slot * kSlot + wave * N * 1024;
 #pragma unroll
-            for (int n = 0; n < N; ++n) request_1k(src[n] + koff, dst + n * 1024);
+            for (int n = 0; n < N; ++n) {
+                if (ONCE && (8 * (wave * N + n)) % kRows >= TM) request_1k<true>(src[n] + koff, dst + n * 1024);   // (scalar)
+                else request_1k(src[n] + koff, dst + n * 1024);
+            }
         };
 
         struct Frags {
@@ -197,7 +201,7 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
     }
 }
 
-template <int MT, int NT, int WM, int WN, int WK, int S, bool DMA>
+template <int MT, int NT, int WM, int WN, int WK, int S, bool DMA, bool ONCE = false>
 hipError_t launch_staged(const int8_t* qx, const float* row_scale, const int8_t* qw, const float* w_scale, int T, int I,
                          int O, uint16_t* Y, int64_t ldy, int32_t* acc_debug, hipStream_t stream) {
     constexpr int TM = 16 * MT * WM, TN = 16 * NT * WN;
@@ -207,10 +211,10 @@ hipError_t launch_staged(const int8_t* qx, const float* row_scale, const int8_t*
     if (total >= (int64_t)1 << 31) return hipErrorInvalidValue;
     const bool vec_out = O % NT == 0 && ldy % NT == 0 && reinterpret_cast<uintptr_t>(Y) % (2 * NT) == 0;
     static std::atomic<uint64_t> allowed{0};
-    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_i8_staged_kernel<MT, NT, WM, WN, WK, S, DMA>), kLds, allowed);
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_i8_staged_kernel<MT, NT, WM, WN, WK, S, DMA, ONCE>), kLds, allowed);
     if (e != hipSuccess) return e;
     const int64_t blocks = std::min<int64_t>((total + kXcds - 1) / kXcds * kXcds, (int64_t)1 << 20);
-    gemm_i8_staged_kernel<MT, NT, WM, WN, WK, S, DMA><<<dim3((unsigned)blocks), dim3(64 * kSplitWaves), kLds, stream>>>(
+    gemm_i8_staged_kernel<MT, NT, WM, WN, WK, S, DMA, ONCE><<<dim3((unsigned)blocks), dim3(64 * kSplitWaves), kLds, stream>>>(
         qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, tiles_m, (int)total, vec_out);
     return hipGetLastError();
 }
@@ -236,9 +240,11 @@ gemm_i8_short_kernel(const int8_t* __restrict__ qx, const float* __restrict__ ro
 
 // Tile kinds by what a CU has to take in for one 128-byte step of one tile (TM + TN rows).  The cost of a launch is the
 // rounds of tiles over the CUs times that; of equal ones the smaller tile is taken.  Measured at I = 4096 (us, best kind
-// first): 16 x 4096 5.5 (16 x 16), 6.3 (32 x 32), 8.4 (32 x 64); 64 x 4096 7.3 (32 x 32), 8.7 (32 x 64), 10.1 (64 x 64);
-// 64 x 11008 11.3 (64 x 64), 12.8 (32 x 64), 17.1 (32 x 32); 256 x 4096 10.9 (64 x 64), 12.1 (32 x 64), 14.8 (64 x 128);
-// 512 x 4096 16.1 (64 x 128), 19.8 (64 x 64), 23.3 (128 x 128); the rule picks the first of each.
+// first): 16 x 4096 5.5 (16 x 16), 6.3 (32 x 32), 8.0 (32 x 64); 64 x 4096 6.9 (32 x 32), 8.0 (32 x 64), 9.6 (64 x 64);
+// 64 x 11008 11.0 (64 x 64), 12.4 (32 x 64), 16.2 (32 x 32); 256 x 4096 10.1 (64 x 64), 11.8 (32 x 64), 14.1 (64 x 128);
+// 512 x 4096 15.5 (64 x 128), 18.2 (64 x 64), 20.8 (128 x 128); the rule picks the first of each.  Off the 16-byte layout
+// likewise: 128 x 2750 x 4090 9.6 (32 x 64), 11.7 (64 x 64), 15.1 (32 x 32); 509 x 2750 x 4090 17.8 (64 x 128), 18.9
+// (64 x 64), 21.0 (128 x 128); 1000 x 2750 x 4090 24.0 (128 x 128), 33.6 (64 x 128).
 static const int kKinds[][2] = {{16, 16}, {32, 32}, {32, 64}, {64, 64}, {64, 128}, {128, 128}};
 constexpr int kNumKinds = 6;
 
@@ -278,15 +284,20 @@ hipError_t launch_w8a8_staged(const int8_t* qx, const float* row_scale, const in
     // the steps and slots of a kind: as much of the contraction per barrier, and as many slots, as the LDS allows; through
     // registers shorter steps and fewer slots, which leave the registers for two steps on their way (512 x 2756 x 4096 with
     // 64 x 128 tiles: 15.5 us with WK 2 and 3 slots, 15.7 with 4, 19.1 with WK 4)
-#define CQ_STAGED(MT, NT, WM, WN, WK, S, DMA) \
-    launch_staged<MT, NT, WM, WN, WK, S, DMA>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream)
-    switch (best_kind(T, O, n_cu, &cost)) {
+    // Weights that one row of tiles reads once and that no cache keeps are requested non-temporally: 16 x 8192 x 28672 44.2 ->
+    // 37.9 us (6.2 TB/s), 64 x 8192 x 28672 52.6 -> 47.7, 32 x 8192 x 22016 42.2 -> 37.8, but 16 x 4096 x 22016 (86 MiB, part of which
+    // the memory-side cache keeps from one call to the next) 18.5 -> 21.3.
+    const int kind = best_kind(T, O, n_cu, &cost);
+    const bool once = dma && T <= kKinds[kind][0] && (int64_t)O * I > (int64_t)128 << 20;
+#define CQ_STAGED(MT, NT, WM, WN, WK, S, ...) \
+    launch_staged<MT, NT, WM, WN, WK, S, __VA_ARGS__>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream)
+    switch (kind) {
         case 0: return dma ? CQ_STAGED(1, 1, 1, 1, 8, 4, true) : CQ_STAGED(1, 1, 1, 1, 8, 2, false);
         case 1: return dma ? CQ_STAGED(2, 2, 1, 1, 8, 4, true) : CQ_STAGED(2, 2, 1, 1, 8, 2, false);
-        case 2: return dma ? CQ_STAGED(2, 2, 1, 2, 4, 3, true) : CQ_STAGED(2, 2, 1, 2, 4, 2, false);
+        case 2: return once ? CQ_STAGED(2, 2, 1, 2, 4, 3, true, true) : dma ? CQ_STAGED(2, 2, 1, 2, 4, 3, true) : CQ_STAGED(2, 2, 1, 2, 4, 2, false);
         case 3: return dma ? CQ_STAGED(2, 4, 2, 1, 4, 4, true) : CQ_STAGED(2, 2, 2, 2, 2, 2, false);
-        case 4: return dma ? CQ_STAGED(4, 4, 1, 2, 4, 3, true) : CQ_STAGED(2, 4, 2, 2, 2, 3, false);
-        default: return dma ? CQ_STAGED(4, 4, 2, 2, 2, 3, true) : CQ_STAGED(4, 4, 2, 2, 2, 2, false);
+        case 4: return once ? CQ_STAGED(4, 4, 1, 2, 4, 3, true, true) : dma ? CQ_STAGED(4, 4, 1, 2, 4, 3, true) : CQ_STAGED(2, 4, 2, 2, 2, 3, false);
+        default: return once ? CQ_STAGED(4, 4, 2, 2, 2, 3, true, true) : dma ? CQ_STAGED(4, 4, 2, 2, 2, 3, true) : CQ_STAGED(4, 4, 2, 2, 2, 2, false);
     }
 #undef CQ_STAGED
 }
