@@ -174,8 +174,8 @@ int crossquant_kernel_count(const void *X, int64_t T, int64_t I, int64_t ldx, co
  * xrk: out, nullable, binary16 [T][I].  counters: out, three unsigned 64-bit values, 8-byte aligned.
  * row_scale / col_scale: nullable (both or neither): float[T] / float[I] work vectors, overwritten with a and
  *        b (must not overlap t or c: CQ_ERR_ALIAS).  With them the factors are formed once, by a small kernel
- *        of their own; with NULL, NULL every block forms the factors of its own rows and columns, which makes
- *        the call about a tenth slower on a 4096 x 8192 matrix.
+ *        of their own; with NULL, NULL every block forms the factors of its own rows and columns, which takes
+ *        about as long.
  */
 int crossquant_kernel_analysis(const void *X, int64_t T, int64_t I, int64_t ldx, const float *t,
                                const float *c, float alpha, int bits, void *xrk, float *row_scale,

@@ -964,6 +964,22 @@ def test_weight_steps_by_either_pass(cq, I, O):
         assert np.array_equal(bits32(host(s)), bits32(s_ref)) and np.array_equal(host(qw), qw_ref)
 
 
+def test_weight_groups_of_a_weight_beyond_128_mib(cq):
+    """4096 x 16648 (read non-temporally) against its first and last 4096 x 264 columns on their own (which are not)."""
+    import torch
+    I, O, g = 4096, 16648, 128
+    say("grouped weight beyond 128 MiB")
+    W = (torch.randn(I, O, generator=torch.Generator(device="cuda").manual_seed(9), device="cuda") * 0.02).half()
+    qw, s, dq = cq.crossquant_weight_quantize_grouped(W, None, g, 4, want_dq=True)
+    for lo in (0, O - 264):
+        part = W[:, lo:lo + 264].contiguous()
+        qw_p, s_p, dq_p = cq.crossquant_weight_quantize_grouped(part, None, g, 4, want_dq=True)
+        assert torch.equal(qw[lo:lo + 264], qw_p) and torch.equal(s[lo:lo + 264], s_p)
+        assert torch.equal(dq[:, lo:lo + 264].contiguous().view(torch.int16), dq_p.view(torch.int16))
+    qw_ref, s_ref, _ = oracle.weight_quantize_grouped(host(part), None, g, 4)
+    assert np.array_equal(host(qw_p), qw_ref) and np.array_equal(bits32(host(s_p)), bits32(s_ref))
+
+
 def test_weight_quantize_grouped_at_layer_scale(cq):
     """The paper's W4-g128 setting on the low-bit configuration's 4096 x 4096 weight."""
     W = workloads.config_weight("C4")
