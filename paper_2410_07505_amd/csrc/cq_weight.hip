@@ -12,6 +12,8 @@ __global__ void zero_u32_kernel(uint32_t* __restrict__ p, int n) {
     if (i < n) p[i] = 0u;
 }
 
+constexpr int64_t kCachedWeight = (int64_t)128 << 20;        // bytes of W up to which reads leave copies in the caches
+
 // The step of a channel is fl32(max / q_max).  Rounded division by a constant does not change an order, so the largest
 // rounded quotient is the rounded quotient of the largest value: steps can be formed before they are combined, and no
 // pass over them has to follow.
@@ -126,7 +128,7 @@ weight_colmax_kernel(const uint16_t* __restrict__ W, int I, int O, const float* 
 // a wave in which any lane is within the approximation's error of a rounding tie (or has a step so small that its
 // reciprocal leaves the normal range) redoes its eight elements with the division.
 // Bound by the memory: 4096 x 11008 per channel (steps + codes) 65 -> 42 us, 5120 x 20480 in groups of 128 with the
-// dequantized weights 156 -> 109 us = 4.8 TB/s (the group was read twice before).  Outputs leave with non-temporal stores
+// dequantized weights 156 -> 110 us = 4.8 TB/s (the group was read twice before).  Outputs leave with non-temporal stores
 // (118.6 us for the latter with plain ones, 119.5 written through): they do not push the weights out of the caches.
 template <int SWEEPS, bool GROUPED, bool VEC, bool ONCE = false>
 __global__ void __launch_bounds__(256)
@@ -138,7 +140,7 @@ weight_tile_kernel(const uint16_t* __restrict__ W, int I, int O, const float* __
     __shared__ float lmax[GROUPED ? 4 * SWEEPS : 1][64];
     __shared__ float lstep[GROUPED ? 4 * SWEEPS : 1][64];
     // Walk: with given steps, down the rows of one set of channels, the last channels first -- what the pass over the steps
-    // read last is still in the memory-side cache (8192 x 28672: 222 us for the call against 259 along the channels; equal
+    // read last is still in the memory-side cache (8192 x 28672, plain loads: 222 us for the call against 259 along them; equal
     // for weights that fit the cache); else along the channels (4096 x 11008, g = 128: 43.5 us against 51).
     const int n_j_tiles = gridDim.x / n_k_tiles;
     const int kt = GROUPED ? blockIdx.x % n_k_tiles : n_k_tiles - 1 - blockIdx.x / n_j_tiles;
@@ -158,7 +160,7 @@ weight_tile_kernel(const uint16_t* __restrict__ W, int I, int O, const float* __
             const int j = j_base + sw * 128 + jq * 4 + r;
             const uint16_t* row = W + (int64_t)j * O;
             v[sw][r] = make_uint4(0u, 0u, 0u, 0u);
-            if (VEC && ONCE) {                                // W is read once, and no cache keeps it
+            if (VEC && ONCE) {                                // the last read of W, and no cache keeps it for the next call
                 if (j < I && k0 < O) v[sw][r] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(row + k0)));
             } else if (j < I) {
                 v[sw][r] = load8<VEC>(row, k0, O);
@@ -458,7 +460,14 @@ hipError_t launch_weight_quantize(const uint16_t* W, int I, int O, const float* 
         else weight_colmax_kernel<RPW, false><<<grid, dim3(256), 0, stream>>>(W, I, O, fold, qm, bits, ncc);
     }
     const dim3 grid((unsigned)(nkt * ((I + 127) / 128)));       // (tiles of 256 rows measured 0 to 2 us slower)
-    if (vec)
+    // This is the last read of W.  Up to 128 MiB the next call still finds part of it in the memory-side cache if the reads
+    // are plain (4096 x 11008: 42.8 us against 44.6; 8192 x 8192, 128 MiB: 70.2 : 69.9); beyond, non-temporal reads leave
+    // that cache to what the step pass brought in (4096 x 22016: 95.0 -> 87.7, 8192 x 28672 221 -> 213, 28672 x 8192 272 ->
+    // 246).  The same in the step pass, for the channels that the cache will have lost by then, gained 1 % at 8192 x 28672
+    // and lost 3 % at 28672 x 8192.
+    if (vec && (int64_t)I * O * 2 > kCachedWeight)
+        weight_tile_kernel<1, false, true, true><<<grid, dim3(256), 0, stream>>>(W, I, O, fold, 0, qm, qw, w_scale, nullptr, nkt, qw_vec, false);
+    else if (vec)
         weight_tile_kernel<1, false, true><<<grid, dim3(256), 0, stream>>>(W, I, O, fold, 0, qm, qw, w_scale, nullptr, nkt, qw_vec, false);
     else
         weight_tile_kernel<1, false, false><<<grid, dim3(256), 0, stream>>>(W, I, O, fold, 0, qm, qw, w_scale, nullptr, nkt, qw_vec, false);
@@ -482,7 +491,7 @@ hipError_t launch_weight_quantize_grouped(const uint16_t* W, int I, int O, const
             kernel<<<grid, dim3(256), 0, stream>>>(W, I, O, fold, group, qm, qw, w_scale, wdq, nkt, qw_vec, dq_vec);
         };
         // W is read once; one that no cache keeps is read non-temporally (5120 x 20480: 112.3 -> 109.9 us)
-        const bool once = in_vec && (int64_t)I * O * 2 > (int64_t)128 << 20;
+        const bool once = in_vec && (int64_t)I * O * 2 > kCachedWeight;
         if (rows == 256) {
             if (once) run(&weight_tile_kernel<2, true, true, true>);
             else if (in_vec) run(&weight_tile_kernel<2, true, true>);

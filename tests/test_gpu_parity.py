@@ -980,6 +980,23 @@ def test_weight_groups_of_a_weight_beyond_128_mib(cq):
     assert np.array_equal(host(qw_p), qw_ref) and np.array_equal(bits32(host(s_p)), bits32(s_ref))
 
 
+def test_weight_codes_of_a_weight_beyond_128_mib(cq):
+    """4096 x 16648 (its second read is non-temporal) against its first and last 264 columns on their own."""
+    import torch
+    I, O = 4096, 16648
+    say("weight beyond 128 MiB")
+    g = torch.Generator(device="cuda").manual_seed(10)
+    W = (torch.randn(I, O, generator=g, device="cuda") * 0.02).half()
+    fold = torch.rand(I, generator=g, device="cuda") + 0.5
+    qw, s = cq.crossquant_weight_quantize(W, fold, 8)
+    for lo in (0, O - 264):
+        part = W[:, lo:lo + 264].contiguous()
+        qw_p, s_p = cq.crossquant_weight_quantize(part, fold, 8)
+        assert torch.equal(qw[lo:lo + 264], qw_p) and torch.equal(s[lo:lo + 264], s_p)
+    qw_ref, s_ref = oracle.weight_quantize(host(part), host(fold), 8)
+    assert np.array_equal(host(qw_p), qw_ref) and np.array_equal(bits32(host(s_p)), bits32(s_ref))
+
+
 def test_weight_quantize_grouped_at_layer_scale(cq):
     """The paper's W4-g128 setting on the low-bit configuration's 4096 x 4096 weight."""
     W = workloads.config_weight("C4")
