@@ -36,9 +36,10 @@ __device__ __forceinline__ v4i load16_tail(const int8_t* row, int kb, int I) {
 // At step kt the fragments of kt are in registers; behind the step's barrier slot kt % S is free (step kt + S is
 // requested into it) and step kt + 1 has landed (its fragments are read while kt is multiplied): one barrier a step.
 // DMA: operands aligned to 16 bytes with I % 16 == 0 go straight to LDS; pieces past a row's end come from a zero
-// block.  ONCE: the weights' requests are non-temporal.  Otherwise (I >= 16) they pass through registers, loaded unaligned two steps before they are stored: 512 x 2752 x
+// block.  Otherwise (I >= 16) they pass through registers, loaded unaligned two steps before they are stored: 512 x 2752 x
 // 4096 takes 13.8 us in the first form, 512 x 2756 x 4096 15.5 us in the second (whether rows start on a word or a byte makes
 // 1 us; with one step in registers, and the row's end dealt with in every step, which spilled, 19.9 us).
+// ONCE: the weights' requests are non-temporal.
 template <int MT, int NT, int WM, int WN, int WK, int S, bool DMA, bool ONCE>
 __global__ void __launch_bounds__(64 * kSplitWaves)
 gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ row_scale, const int8_t* __restrict__ qw,
