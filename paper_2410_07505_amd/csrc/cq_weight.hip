@@ -128,23 +128,32 @@ weight_colmax_kernel(const uint16_t* __restrict__ W, int I, int O, const float* 
 // a wave in which any lane is within the approximation's error of a rounding tie (or has a step so small that its
 // reciprocal leaves the normal range) redoes its eight elements with the division.
 // Bound by the memory: 4096 x 11008 per channel (steps + codes) 65 -> 42 us, 5120 x 20480 in groups of 128 with the
-// dequantized weights 156 -> 110 us = 4.8 TB/s (the group was read twice before).  Outputs leave with non-temporal stores
+// dequantized weights 156 -> 107 us = 4.9 TB/s (the group was read twice before).  Outputs leave with non-temporal stores
 // (118.6 us for the latter with plain ones, 119.5 written through): they do not push the weights out of the caches.
 template <int SWEEPS, bool GROUPED, bool VEC, bool ONCE = false>
 __global__ void __launch_bounds__(256)
 weight_tile_kernel(const uint16_t* __restrict__ W, int I, int O, const float* __restrict__ fold, int g, float qmax,
                    int8_t* __restrict__ qw, float* __restrict__ s, uint16_t* __restrict__ wdq, int n_k_tiles, bool qw_vec,
-                   bool dq_vec) {
+                   bool dq_vec, int strip) {
     constexpr int kJ = 128 * SWEEPS, kPitch = kJ / 4 + 1;          // words
     __shared__ uint32_t tile[64 * kPitch];
     __shared__ float lmax[GROUPED ? 4 * SWEEPS : 1][64];
     __shared__ float lstep[GROUPED ? 4 * SWEEPS : 1][64];
     // Walk: with given steps, down the rows of one set of channels, the last channels first -- what the pass over the steps
     // read last is still in the memory-side cache (8192 x 28672, plain loads: 222 us for the call against 259 along them; equal
-    // for weights that fit the cache); else along the channels (4096 x 11008, g = 128: 43.5 us against 51).
+    // for weights that fit the cache); else along the channels (4096 x 11008, g = 128: 43.5 us against 51), `strip` row tiles
+    // at a time.
     const int n_j_tiles = gridDim.x / n_k_tiles;
-    const int kt = GROUPED ? blockIdx.x % n_k_tiles : n_k_tiles - 1 - blockIdx.x / n_j_tiles;
-    const int jt = GROUPED ? blockIdx.x / n_k_tiles : blockIdx.x % n_j_tiles;
+    int kt, jt;
+    if (GROUPED) {
+        const int first = (int)blockIdx.x / (n_k_tiles * strip) * strip, height = min(strip, n_j_tiles - first);
+        const int at = (int)blockIdx.x - first * n_k_tiles;
+        kt = at / height;
+        jt = first + at - kt * height;
+    } else {
+        kt = n_k_tiles - 1 - blockIdx.x / n_j_tiles;
+        jt = blockIdx.x % n_j_tiles;
+    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c8 = lane & 7, jq = threadIdx.x >> 3;
     const int k0 = kt * 64 + c8 * 8, j_base = jt * kJ;
@@ -466,11 +475,11 @@ hipError_t launch_weight_quantize(const uint16_t* W, int I, int O, const float* 
     // 246).  The same in the step pass, for the channels that the cache will have lost by then, gained 1 % at 8192 x 28672
     // and lost 3 % at 28672 x 8192.
     if (vec && (int64_t)I * O * 2 > kCachedWeight)
-        weight_tile_kernel<1, false, true, true><<<grid, dim3(256), 0, stream>>>(W, I, O, fold, 0, qm, qw, w_scale, nullptr, nkt, qw_vec, false);
+        weight_tile_kernel<1, false, true, true><<<grid, dim3(256), 0, stream>>>(W, I, O, fold, 0, qm, qw, w_scale, nullptr, nkt, qw_vec, false, 1);
     else if (vec)
-        weight_tile_kernel<1, false, true><<<grid, dim3(256), 0, stream>>>(W, I, O, fold, 0, qm, qw, w_scale, nullptr, nkt, qw_vec, false);
+        weight_tile_kernel<1, false, true><<<grid, dim3(256), 0, stream>>>(W, I, O, fold, 0, qm, qw, w_scale, nullptr, nkt, qw_vec, false, 1);
     else
-        weight_tile_kernel<1, false, false><<<grid, dim3(256), 0, stream>>>(W, I, O, fold, 0, qm, qw, w_scale, nullptr, nkt, qw_vec, false);
+        weight_tile_kernel<1, false, false><<<grid, dim3(256), 0, stream>>>(W, I, O, fold, 0, qm, qw, w_scale, nullptr, nkt, qw_vec, false, 1);
     return hipGetLastError();
 }
 
@@ -487,8 +496,15 @@ hipError_t launch_weight_quantize_grouped(const uint16_t* W, int I, int O, const
         const bool dq_vec = O % 8 == 0 && reinterpret_cast<uintptr_t>(wdq) % 16 == 0;
         const int rows = group == 256 ? 256 : 128;
         const dim3 grid((unsigned)(nkt * ((I + rows - 1) / rows)));
+        // One row tile after another leaves a channel's codes as single 128-byte lines, one row of the weight apart; in strips
+        // of 20 tiles the lines of a channel follow each other.  That pays where the memory takes the codes rather than a
+        // cache: with the dequantized weights 8192 x 28672 266 -> 238 us, 28672 x 8192 253 -> 232, 12288 x 12288 166 -> 153,
+        // 5120 x 20480 111 -> 107, but 8192 x 8256 (129 MiB) 64 -> 66, 4096 x 11008 46 -> 50; codes alone 178 -> 139, 163 -> 150,
+        // 111 -> 94, but 14336 x 8192 74 -> 75, 5120 x 20480 67-70 -> 72.  Strips of 12 and 16 gain less, of 32 lose at 28672 x 8192 (255).
+        const bool strips = rows == 128 && (int64_t)I * O * 2 > (int64_t)144 << 20 && (wdq || I >= 8192);
         auto run = [&](auto kernel) {
-            kernel<<<grid, dim3(256), 0, stream>>>(W, I, O, fold, group, qm, qw, w_scale, wdq, nkt, qw_vec, dq_vec);
+            kernel<<<grid, dim3(256), 0, stream>>>(W, I, O, fold, group, qm, qw, w_scale, wdq, nkt, qw_vec, dq_vec,
+                                                   strips ? 20 : 1);
         };
         // W is read once; one that no cache keeps is read non-temporally (5120 x 20480: 112.3 -> 109.9 us)
         const bool once = in_vec && (int64_t)I * O * 2 > kCachedWeight;

@@ -964,11 +964,13 @@ def test_weight_steps_by_either_pass(cq, I, O):
         assert np.array_equal(bits32(host(s)), bits32(s_ref)) and np.array_equal(host(qw), qw_ref)
 
 
-def test_weight_groups_of_a_weight_beyond_128_mib(cq):
-    """4096 x 16648 (read non-temporally) against its first and last 4096 x 264 columns on their own (which are not)."""
+@pytest.mark.parametrize("O, g", [(16648, 128), (18696, 32), (18696, 128)])
+def test_weight_groups_of_a_weight_beyond_128_mib(cq, O, g):
+    """4096 x 16648 (read non-temporally) and 4096 x 18696 (also in strips of 20 and 12 row tiles) against their first and
+    last 4096 x 264 columns on their own (neither)."""
     import torch
-    I, O, g = 4096, 16648, 128
-    say("grouped weight beyond 128 MiB")
+    I = 4096
+    say(f"grouped weight beyond 128 MiB O={O} g={g}")
     W = (torch.randn(I, O, generator=torch.Generator(device="cuda").manual_seed(9), device="cuda") * 0.02).half()
     qw, s, dq = cq.crossquant_weight_quantize_grouped(W, None, g, 4, want_dq=True)
     for lo in (0, O - 264):
