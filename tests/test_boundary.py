@@ -322,3 +322,20 @@ def test_python_wrappers_check_every_buffer_they_are_given(cq):
         cq.crossquant_w8a8_linear(qx, f32(T), qw, f32(O), acc_debug=torch.zeros((O, T), dtype=torch.int32))
     with pytest.raises(ValueError, match="contraction lengths"):
         cq.crossquant_w8a8_linear(qx, f32(T), torch.zeros((O, I + 1), dtype=torch.int8), f32(O))
+
+
+def test_binding_loads_with_a_torch_that_lacks_the_raw_stream_call(cq, monkeypatch):
+    """torch._C._cuda_getCurrentRawStream is private and absent from a torch without GPU support: the binding has to load
+    all the same (sizes, versions and status strings need no GPU) and to ask for the stream the public way."""
+    import importlib.util
+    import types
+
+    import torch
+    import paper_2410_07505_amd.binding as loaded
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    spec = importlib.util.spec_from_file_location("binding_without_raw_stream", loaded.__file__)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    assert module.crossquant_version() == cq.crossquant_version()
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device: types.SimpleNamespace(cuda_stream=4711))
+    assert module._stream(types.SimpleNamespace(get_device=lambda: 0, device="cuda:0")) == 4711
