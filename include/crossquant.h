@@ -63,7 +63,8 @@ typedef enum {
  * The maxima are accumulated with atomics, so t and c are cleared first, inside the call.  That is
  * done by the one launch itself: its first blocks store the
  * zeros and the others wait for them (a bounded wait on a counter in library-owned device memory, one
- * per stream handle as for crossquant_quantize's zero count) before their atomics.  Calls captured
+ * per stream handle as for crossquant_quantize's zero count; other layouts have 16 counters of their own, so that
+ * their calls take none of those) before their atomics.  Calls captured
  * into a graph and calls on a stream without a counter of its own clear with a small
  * kernel of their own before the pass.
  */

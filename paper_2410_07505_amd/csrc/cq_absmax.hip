@@ -154,8 +154,8 @@ absmax_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, 
     (void)lds_go;
 }
 
-// Clearing blocks that have finished, over all launches of a stream slot (see absmax_stream_kernel).
-__device__ unsigned int g_cleared[kStateSlots];
+// Clearing blocks that have finished, over all launches of a stream slot (see absmax_stream_kernel), for each table of slots.
+__device__ unsigned int g_cleared[kSlotTables * kStateSlots];
 
 }  // namespace
 
@@ -193,13 +193,14 @@ hipError_t launch_absmax(const uint16_t* X, int B, int T, int I, int64_t ldx, in
     // One launch that clears for itself needs a counter of its own (a stream slot) and a target value that
     // differs from launch to launch, which a captured graph cannot have (its arguments are frozen): captured
     // calls and streams without a slot clear with a kernel of their own first.
-    const int slot = stream_slot(stream);
+    const SlotTable table = buf ? kStateTable : kOffLayoutTable;
+    const int slot = stream_slot(stream, table);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     const bool plain_stream = slot >= 0 && hipStreamIsCapturing(stream, &cap) == hipSuccess &&
                               cap == hipStreamCaptureStatusNone;
     if (plain_stream) {
         static std::mutex mu;
-        static unsigned int reached[64][kStateSlots];      // what a device's g_cleared[slot] reaches once all launches so far have cleared
+        static unsigned int reached[64][kSlotTables * kStateSlots];   // what a device's g_cleared words reach once all launches so far have cleared
         static unsigned int* counters[64];                 // device address of g_cleared on each device, once known
         int dev = 0;
         hipError_t e = hipGetDevice(&dev);
@@ -210,13 +211,13 @@ hipError_t launch_absmax(const uint16_t* X, int B, int T, int I, int64_t ldx, in
             e = hipGetSymbolAddress(reinterpret_cast<void**>(&counters[dev]), HIP_SYMBOL(g_cleared));
             if (e != hipSuccess) return e;
         }
-        unsigned int* counter = counters[dev];
-        const unsigned int target = reached[dev][slot] + (unsigned)n_clear;
+        const int word = table * kStateSlots + slot;
+        const unsigned int target = reached[dev][word] + (unsigned)n_clear;
         const auto kernel = buf ? &absmax_stream_kernel<true, true> : &absmax_stream_kernel<true, false>;
         kernel<<<dim3((unsigned)(n_work + n_clear)), block, 0, stream>>>(X, T, I, ldx, tb, cb, ncc, nb, ncc * nrc, matrix_stride,
-                                                                         n_clear, B * T, B * I, counter + slot, target, 1u << 22);
+                                                                         n_clear, B * T, B * I, counters[dev] + word, target, 1u << 22);
         e = hipGetLastError();
-        if (e == hipSuccess) reached[dev][slot] = target;
+        if (e == hipSuccess) reached[dev][word] = target;
         return e;
     }
     zero_fill_kernel<<<dim3((n_words + 255) / 256), dim3(256), 0, stream>>>(tb, B * T, cb, B * I);

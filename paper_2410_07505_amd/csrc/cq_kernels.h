@@ -31,9 +31,6 @@ __device__ __forceinline__ float rounded_f32(float v) {
     return v;
 }
 
-// Library-owned device state comes in kStateSlots pieces; a stream keeps the slot it is given on
-// first use (-1: none left, or a handle that stands for several streams -- the caller then takes
-// the path that clears its accumulators with a kernel of its own first).
 // A launch's total thread count has to stay below 2^32: the runtime forms it in 32 bits, and a larger
 // grid silently runs only as many blocks as the low 32 bits give.  Launchers check this first and
 // return hipErrorInvalidValue with nothing enqueued (reported as a size over the limit).
@@ -57,8 +54,14 @@ inline int quantize_batches_per_wave(int64_t n_chunks, int T) {
     return nb;
 }
 
+// Library-owned device state comes in kStateSlots pieces; a stream keeps the slot it is given on
+// first use (-1: none left, or a handle that stands for several streams -- the caller then takes
+// the path that clears its accumulators with a kernel of its own first).
+// The clearing counters of absmax off the vector layout have a table of their own: crossquant_absmax_quantize_single_read
+// is refused on a stream without a slot, and calls that can do without one must not use up its slots.
 constexpr int kStateSlots = 16;
-int stream_slot(hipStream_t stream);
+enum SlotTable { kStateTable, kOffLayoutTable, kSlotTables };
+int stream_slot(hipStream_t stream, SlotTable table = kStateTable);
 
 // A kernel that needs more dynamic LDS than the default limit has to be told so once per device.
 // `done` is a bit mask of the devices (ordinal < 64) on which that has happened for this kernel; devices with

@@ -11,18 +11,19 @@
 
 namespace cq {
 
-int stream_slot(hipStream_t stream) {
+int stream_slot(hipStream_t stream, SlotTable table) {
     // the per-thread default stream is one handle for many real streams: no slot
     if (stream == hipStreamPerThread) return -1;
     static std::mutex mu;
-    static hipStream_t seen[kStateSlots];
-    static int n_seen = 0;
+    static hipStream_t seen[kSlotTables][kStateSlots];
+    static int n_seen[kSlotTables];
     std::lock_guard<std::mutex> lock(mu);
-    for (int i = 0; i < n_seen; ++i)
-        if (seen[i] == stream) return i;
-    if (n_seen == kStateSlots) return -1;       // callers fall back to the path that clears first
-    seen[n_seen] = stream;
-    return n_seen++;
+    int& n = n_seen[table];
+    for (int i = 0; i < n; ++i)
+        if (seen[table][i] == stream) return i;
+    if (n == kStateSlots) return -1;            // callers fall back to the path that clears first
+    seen[table][n] = stream;
+    return n++;
 }
 
 }  // namespace cq

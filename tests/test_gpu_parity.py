@@ -445,6 +445,38 @@ def test_calls_overlapping_on_many_streams(cq):
         assert int(host(zc)[0]) == oracle.kernel_count(Xs[k], t_ref, c_ref, 1.0, 8), k
 
 
+def test_maxima_off_the_vector_layout_take_no_slot_from_other_calls(cq, tmp_path):
+    """The single-read call needs one of the 16 slots that streams are given.  16 streams that only form the maxima of a
+    matrix of odd width must leave it one (a copy of the library: its slots are all free)."""
+    import ctypes
+    import shutil
+    import torch
+    say("16 streams of absmax at an odd width, then the single-read call on another")
+    lib = ctypes.CDLL(shutil.copy(cq.LIB_PATH, tmp_path / "copy.so"))
+    for name in ("crossquant_absmax", "crossquant_absmax_quantize_single_read"):
+        getattr(lib, name).argtypes = getattr(cq.raw, name).argtypes
+    X, Z = outliers(70, 77, seed=5), outliers(64, 256, seed=6)
+    t_ref, c_ref = oracle.absmax(X)
+    Xg, Zg = gpu(X), gpu(Z)
+    maxima = [(torch.full((70,), 9.0, device="cuda"), torch.full((77,), 9.0, device="cuda")) for _ in range(16)]
+    t, c, a, b = (torch.empty(n, device="cuda") for n in (64, 256, 64, 256))
+    codes = torch.empty((64, 256), dtype=torch.int8, device="cuda")
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(17)]
+    assert len({st.cuda_stream for st in streams}) == 17
+    for _ in range(2):
+        for st, (tt, cc) in zip(streams, maxima):
+            assert lib.crossquant_absmax(Xg.data_ptr(), 70, 77, 77, tt.data_ptr(), cc.data_ptr(), st.cuda_stream) == 0
+    assert lib.crossquant_absmax_quantize_single_read(Zg.data_ptr(), 64, 256, 256, 0.15, 8, t.data_ptr(), c.data_ptr(),
+                                                      codes.data_ptr(), 0, a.data_ptr(), b.data_ptr(), 0,
+                                                      streams[16].cuda_stream) == 0
+    torch.cuda.synchronize()
+    for tt, cc in maxima:
+        assert np.array_equal(host(tt), t_ref) and np.array_equal(host(cc), c_ref)
+    z_t, z_c = oracle.absmax(Z)
+    assert np.array_equal(host(codes), oracle.quantize(Z, z_t, z_c, 0.15, 8)["codes"])
+
+
 def test_more_than_2_to_31_elements(cq):
     """70 000 x 65 544 = 4.59e9 elements (9.2 GB of binary16): every element offset past row 32 767
     needs more than 32 bits.  The oracle computes the maxima of the whole matrix; codes and
