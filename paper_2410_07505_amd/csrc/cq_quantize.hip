@@ -62,8 +62,8 @@ __global__ void zero_u64_kernel(unsigned long long* p) { *p = 0ull; }
 //     the loop body has no per-lane branches and no 64-bit vector address arithmetic;
 //   - the stores are buffer stores with the write-through policy the compiler knows about, so its vmcnt waits for
 //     the next rows' loads do not also wait for this row's stores to be acknowledged by memory.
-//   - STREAM: how they leave.  0: written through at device scope (sc1); 1: the dequantized matrix as a stream besides
-//     (sc1 nt); 2: the codes too (see launch_mode).
+//   - STREAM: they leave as a stream (sc1 nt) instead of written through at device scope (sc1); see launch_mode.  FP6
+//     fragments never do.
 // Any other layout: unaligned 16-byte loads (load8), unaligned stores of whole pieces and element stores of the one lane
 // at the end of a row.
 // The loop is software-pipelined by hand: two register sets of kU rows alternate, the loads of batch bi + 1
@@ -72,7 +72,7 @@ __global__ void zero_u64_kernel(unsigned long long* p) { *p = 0ull; }
 // slower on the 4096 x 8192 layer than with the loop's conservative waits.  Two sets is the optimum also for
 // the count-only form, which has registers to spare: 4096 x 8192 in a layer step takes 17.7 us with two sets,
 // 18.6 with one, 19.6 with three and 23.3 with four, i.e. with all of X requested at once.)
-template <int MODE, bool XHAT, bool BUF, int STREAM>
+template <int MODE, bool XHAT, bool BUF, bool STREAM>
 __global__ void __launch_bounds__(kWaves * kLanes)
 quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, const float* __restrict__ t_vec,
                        const float* __restrict__ c_vec, double alpha, int qmax_i, float* __restrict__ a_out,
@@ -102,7 +102,7 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
     const int rows_per_block = kWaves * rows_per_wave;      // <= 512 = the block's thread count
     const int row0 = row_chunk * rows_per_block + wave * rows_per_wave;
     const float qmax = (float)qmax_i;
-    constexpr int kCodesPolicy = STREAM >= 2 ? kStreamThrough : kWriteThrough, kXhatPolicy = STREAM >= 1 ? kStreamThrough : kWriteThrough;
+    constexpr int kPolicy = STREAM ? kStreamThrough : kWriteThrough;       // MODE 3: of the dequantized matrix
 
     // A wave walks its batches from the last to the first: the absmax kernel, which normally ran just before,
     // walks them first to last, so the rows it touched last are still in the caches when they are read here
@@ -229,14 +229,14 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
                 }
                 if (MODE == 1)
                     __builtin_amdgcn_raw_buffer_store_b64(pack_codes_i8(m), row_buffer(codes + (int64_t)rr * I + col0, live),
-                                                          lane * 8, 0, kCodesPolicy);
+                                                          lane * 8, 0, kPolicy);
                 if (MODE == 2)
                     __builtin_amdgcn_raw_buffer_store_b32(pack_codes_i4(m),
                                                           row_buffer(codes + (int64_t)rr * (I / 2) + col0 / 2, live / 2),
-                                                          lane * 4, 0, kCodesPolicy);
+                                                          lane * 4, 0, kPolicy);
                 if (XHAT)
                     __builtin_amdgcn_raw_buffer_store_b128(pack_xhat(q, a, b), row_buffer(xhat + (int64_t)rr * I + col0, live * 2),
-                                                           lane * 16, 0, kXhatPolicy);
+                                                           lane * 16, 0, kPolicy);
                 return nz;
             };
             // The exact path packs and stores for itself instead of handing m and q back: values that come out of
@@ -316,19 +316,27 @@ hipError_t launch_mode(const uint16_t* X, int B, int T, int I, int64_t ldx, int6
     // no slot: clear the caller's counter and add to it directly
     const int state = zc ? stream_slot(stream) : -1;
     if (zc && state < 0) zero_u64_kernel<<<dim3(1), dim3(1), 0, stream>>>(zc);
-    // The dequantized matrix is written as a stream where X and the outputs together take a good part of the 256 MiB
-    // memory-side cache, the codes too where they exceed it: what is not in the way of the next call's reads then counts for
-    // more than what the next kernel finds there (which reads HBM nearly as fast).  absmax + quantize with INT8 codes and
-    // xhat, three sets of buffers in turn, us, sc1 : xhat sc1 nt : both: 4096 x 4096 (80 MiB) 22.6 : 22.7 : 22.8, 4096 x 5120
-    // (100 MiB) 27.9 : 25.4 : 25.6, 4096 x 8192 (160 MiB) 48.8 : 39.3 : 38.9, 8192 x 8192 (320 MiB) 96.9 : 94.6 : 79.8; followed by
-    // a read of xhat 28.8 : 29.9 : 30.1, 34.4 : 36.0 : 34.5, 58.9 : 57.9 : 53.3, 113.6 : 111.3 : 104.0.  (The codes of a layer
-    // that fits stay written through: the matrix kernel reads them next.)
-    const int64_t moved = (int64_t)B * T * I * 2 * (XHAT ? 2 : 1) + (int64_t)B * T * I / (MODE == 1 ? 1 : 2);
-    const int streamed = !XHAT ? 0 : moved > ((int64_t)256 << 20) ? 2 : moved > ((int64_t)96 << 20) ? 1 : 0;
-    const auto kernel = !buf ? &quantize_stream_kernel<MODE, XHAT, false, 0>
-                        : XHAT && streamed == 2 ? &quantize_stream_kernel<MODE, XHAT, true, XHAT ? 2 : 0>
-                        : XHAT && streamed == 1 ? &quantize_stream_kernel<MODE, XHAT, true, XHAT ? 1 : 0>
-                                                : &quantize_stream_kernel<MODE, XHAT, true, 0>;
+    // With a dequantized matrix the outputs leave as a stream where X and they together take a good part of the 256 MiB
+    // memory-side cache: what they would push out of it counts for more than what the next kernel finds there.  Three sets of
+    // buffers in turn, us, written through : streamed, for absmax + quantize | followed by a read of the codes | of xhat | of both:
+    //   INT8  4096 x 4608  (90 MiB) 24.9 : 24.4 | 29.0 : 28.8 | 32.0 : 32.6        not streamed
+    //         4096 x 5120 (100 MiB) 26.7 : 25.7 | 31.0 : 30.3 | 35.0 : 34.5 | 40.0 : 39.7
+    //         4096 x 8192 (160 MiB) 49.0 : 38.5 | 52.9 : 46.3 | 59.1 : 53.5 | 68.7 : 61.5
+    //         8192 x 8192 (320 MiB) 98.2 : 79.0 |  106 : 92.2 |  116 :  104 |  126 :  117
+    //   INT4  4224 x 5120  (93 MiB) 25.9 : 24.9 | 28.9 : 28.1 | 33.7 : 34.4 | 36.9 : 38.0        not streamed
+    //         2816 x 8192  (99 MiB) 26.7 : 25.8 | 29.7 : 29.0 | 35.5 : 35.4 | 38.9 : 39.4
+    //         4096 x 6144 (108 MiB) 31.3 : 31.0 | 35.2 : 34.2 | 42.3 : 41.4 | 46.6 : 44.8
+    //         4096 x 8192 (144 MiB) 44.8 : 36.1 | 48.3 : 40.2 | 55.5 : 51.2 | 60.5 : 55.6
+    //   FP6   2816 x 8192 (104 MiB) 30.8 : 28.1 | 33.6 : 31.7 | 39.7 : 40.0 | 43.3 : 42.3
+    //         4096 x 8192 (152 MiB) 51.3 : 40.1 | 55.1 : 44.8 | 63.1 : 60.1 | 67.8 : 63.8
+    // The FP6 fragments stay written through: streamed too, 4096 x 8192 takes 45.7 | 50.0 | 60.6 | 66.0.  So do the codes of a
+    // call without xhat: the matrix kernel reads them next.  (xhat streamed and INT8 codes written through lost to a program that
+    // reads xhat: 4096 x 5120 25.4 | 29.5 | 36.8 | 39.3.)
+    const int64_t elems = (int64_t)B * T * I;
+    const bool streamed = XHAT && elems * 4 + elems / (MODE == 1 ? 1 : 2) > (int64_t)96 << 20;
+    const auto kernel = !buf ? &quantize_stream_kernel<MODE, XHAT, false, false>
+                        : streamed ? &quantize_stream_kernel<MODE, XHAT, true, XHAT>
+                                   : &quantize_stream_kernel<MODE, XHAT, true, false>;
     kernel<<<grid, block, 0, stream>>>(X, T, I, ldx, t, c, alpha, qmax, a, b, codes, xhat, zc, state, ncc, nb, ncc * nrc,
                                        matrix_stride);
     return hipGetLastError();

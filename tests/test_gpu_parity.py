@@ -46,6 +46,41 @@ def bits32(a):
     return np.ascontiguousarray(a).view(np.uint32)
 
 
+_capture = {}
+
+
+def launched(cq, call):
+    """Names (mangled, with their template arguments) of the kernels that call() enqueues on the current stream: it is
+    captured into a graph, which is looked at and thrown away without being run.  The runtime's functions are found through
+    the library, which is linked with it."""
+    import ctypes
+    import torch
+
+    class Params(ctypes.Structure):
+        _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                    ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+    hip = ctypes.CDLL(cq.LIB_PATH)
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    stream = _capture.setdefault("stream", torch.cuda.Stream())   # one for all: a stream keeps a slot of the library's state
+    handle, graph, n, names = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p(), ctypes.c_size_t(), []
+    torch.cuda.synchronize()
+    assert hip.hipStreamBeginCapture(handle, 2) == 0              # relaxed: other streams and allocations go on as usual
+    try:
+        with torch.cuda.stream(stream):
+            call()
+    finally:
+        assert hip.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    for node in nodes:
+        params = Params()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(params)) == 0
+        names.append(hip.hipKernelNameRefByPtr(ctypes.c_void_p(params.func), handle).decode())
+    assert hip.hipGraphDestroy(graph) == 0
+    return names
+
+
 def outliers(T, I, seed, n_out=3, scale=60.0, dist="normal"):
     return workloads.activation(T, I, dist=dist, n_outlier=min(n_out, I), scale_lo=scale, scale_hi=scale,
                                 seed=seed)
@@ -1081,6 +1116,53 @@ def test_quantize_outputs_beyond_the_memory_side_cache(cq, bits):
         assert torch.equal(a[rows], a_r) and torch.equal(b, b_r)
         zeros += int(z_r.item())
     assert int(z.item()) == zeros
+
+
+@pytest.mark.parametrize("kind,T,I,streamed", [("int8", 4096, 5120, 1),      # 100 MiB of X and outputs
+                                               ("int8", 2048, 4096, 0),
+                                               ("int4", 4096, 6144, 1),      # 108 MiB
+                                               ("int4", 1024, 4096, 0),
+                                               ("fp6", 4096, 6144, 1),       # only the dequantized matrix leaves as a stream
+                                               ("fp6", 1024, 2048, 0)])
+def test_quantize_outputs_that_leave_as_a_stream(cq, kind, T, I, streamed):
+    """From 96 MiB of X and outputs, a dequantized matrix among them, the codes and it leave with another store policy.
+    Equal to the written-through outputs of the same rows in pieces of a quarter, whose last rows go to the oracle."""
+    import torch
+    say("streamed outputs: %s %dx%d" % (kind, T, I))
+    X = torch.randn((T, I), generator=torch.Generator(device="cuda").manual_seed(12), device="cuda").half()
+    t, c = cq.crossquant_absmax(X)
+    bits = 8 if kind == "int8" else 4
+
+    def quantize(x, t):
+        x = x.contiguous()
+        out = [torch.empty(x.shape, dtype=torch.float16, device="cuda"), torch.empty(x.shape[0], device="cuda"),
+               torch.empty(I, device="cuda"), torch.full((1,), -1, dtype=torch.int64, device="cuda")]
+        kw = dict(zip(("xhat", "row_scale", "col_scale", "zero_count"), out))
+        if kind == "fp6":
+            codes = torch.full(((x.shape[0] + 31) // 32 * (I // 64) * 1536,), 0, dtype=torch.uint8, device="cuda")
+            run = lambda: cq.crossquant_quantize_fp6(x, t, c, 0.15, packed=codes, **kw)
+        else:
+            codes = torch.full((x.shape[0], I * bits // 8), 77, dtype=torch.int8 if bits == 8 else torch.uint8, device="cuda")
+            run = lambda: cq.crossquant_quantize(x, t, c, 0.15, bits, codes=codes, **kw)
+        run()
+        return run, [codes] + out
+
+    run, (codes, xhat, a, b, z) = quantize(X, t)
+    mode = {"int8": 1, "int4": 2, "fp6": 3}[kind]
+    assert [n for n in launched(cq, run) if "quantize_stream_kernelILi%dELb1ELb1ELb%dE" % (mode, streamed) in n]
+    zeros, n = 0, T // 4
+    for r in range(0, T, n):
+        run_r, (codes_r, xhat_r, a_r, b_r, z_r) = quantize(X[r:r + n], t[r:r + n].contiguous())
+        assert [k for k in launched(cq, run_r) if "quantize_stream_kernelILi%dELb1ELb1ELb0E" % mode in k]
+        assert torch.equal(codes.view(4, -1)[r // n], codes_r.view(-1))
+        assert torch.equal(xhat[r:r + n].view(torch.int16), xhat_r.view(torch.int16))
+        assert torch.equal(a[r:r + n], a_r) and torch.equal(b, b_r)
+        zeros += int(z_r.item())
+    assert int(z.item()) == zeros
+    ref = oracle.quantize(host(X[-8:]), host(t[-8:]), host(c), 0.15, bits)
+    assert np.array_equal(bits16(host(xhat[-8:])), bits16(ref["xhat"]))
+    if kind != "fp6":
+        assert np.array_equal(host(codes[-8:]), ref["codes"])
 
 
 # widths around a lane's 8 columns and a wave's 512 that the range-checked path does not take (odd ones, or rows that start
