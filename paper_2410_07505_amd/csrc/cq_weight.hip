@@ -128,7 +128,7 @@ weight_colmax_kernel(const uint16_t* __restrict__ W, int I, int O, const float* 
 // a wave in which any lane is within the approximation's error of a rounding tie (or has a step so small that its
 // reciprocal leaves the normal range) redoes its eight elements with the division.
 // Bound by the memory: 4096 x 11008 per channel (steps + codes) 65 -> 42 us, 5120 x 20480 in groups of 128 with the
-// dequantized weights 156 -> 107 us = 4.9 TB/s (the group was read twice before).  Outputs leave with non-temporal stores
+// dequantized weights 156 -> 106 us = 4.9 TB/s (the group was read twice before).  Outputs leave with non-temporal stores
 // (118.6 us for the latter with plain ones, 119.5 written through): they do not push the weights out of the caches.
 template <int SWEEPS, bool GROUPED, bool VEC, bool ONCE = false>
 __global__ void __launch_bounds__(256)
@@ -496,18 +496,24 @@ hipError_t launch_weight_quantize_grouped(const uint16_t* W, int I, int O, const
         const bool dq_vec = O % 8 == 0 && reinterpret_cast<uintptr_t>(wdq) % 16 == 0;
         const int rows = group == 256 ? 256 : 128;
         const dim3 grid((unsigned)(nkt * ((I + rows - 1) / rows)));
-        // One row tile after another leaves a channel's codes as single 128-byte lines, one row of the weight apart; in strips
-        // of 20 tiles the lines of a channel follow each other.  That pays where the memory takes the codes rather than a
-        // cache: with the dequantized weights 8192 x 28672 266 -> 238 us, 28672 x 8192 253 -> 232, 12288 x 12288 166 -> 153,
-        // 5120 x 20480 111 -> 107, but 8192 x 8256 (129 MiB) 64 -> 66, 4096 x 11008 46 -> 50; codes alone 178 -> 139, 163 -> 150,
-        // 111 -> 94, but 14336 x 8192 74 -> 75, 5120 x 20480 67-70 -> 72.  Strips of 12 and 16 gain less, of 32 lose at 28672 x 8192 (255).
-        const bool strips = rows == 128 && (int64_t)I * O * 2 > (int64_t)144 << 20 && (wdq || I >= 8192);
+        // One row of tiles after another leaves a channel's codes as single 128-byte lines, a row of the codes apart.  Where the
+        // memory takes them rather than a cache, the tiles go in strips of at most 13 rows of tiles, of equal height but for the
+        // last: the lines of a channel follow each other, and neighbouring channels (whose weights share DRAM pages) are still
+        // only a few tiles apart.  By rows : in strips, us: with the dequantized weights 5120 x 20480 111 : 106, 8192 x 28672 267 :
+        // 237, 28672 x 8192 253 : 233, 10240 x 16384 174 : 173, 4096 x 22016 101 : 97; codes alone 68 : 66, 179 : 135, 164 : 151,
+        // 104 : 104, 68 : 60.  Over 23 shapes of 128 to 512 MiB heights of 9 to 14 are within 2 % of each other on average and
+        // this limit is the one that loses nowhere (8192 x 8256, 129 MiB, 63.9 : 64.9 with the dequantized weights, 43.6 : 41.6
+        // without); heights of 8, 16, 20 and 23 cost 6 to 9 % against rows on some shape, whole columns 33 %.  Weights that a
+        // cache keeps lose: 4096 x 11008 46.1 : 46.4 and 29.2 : 31.6.
+        const bool big = (int64_t)I * O * 2 > kCachedWeight;
+        const int row_tiles = (I + rows - 1) / rows, n_strips = (row_tiles + 12) / 13;
+        const int strip = rows == 128 && big ? (row_tiles + n_strips - 1) / n_strips : 1;
         auto run = [&](auto kernel) {
             kernel<<<grid, dim3(256), 0, stream>>>(W, I, O, fold, group, qm, qw, w_scale, wdq, nkt, qw_vec, dq_vec,
-                                                   strips ? 20 : 1);
+                                                   strip);
         };
         // W is read once; one that no cache keeps is read non-temporally (5120 x 20480: 112.3 -> 109.9 us)
-        const bool once = in_vec && (int64_t)I * O * 2 > kCachedWeight;
+        const bool once = in_vec && big;
         if (rows == 256) {
             if (once) run(&weight_tile_kernel<2, true, true, true>);
             else if (in_vec) run(&weight_tile_kernel<2, true, true>);

@@ -1031,13 +1031,16 @@ def test_weight_steps_by_either_pass(cq, I, O):
         assert np.array_equal(bits32(host(s)), bits32(s_ref)) and np.array_equal(host(qw), qw_ref)
 
 
-@pytest.mark.parametrize("O, g", [(16648, 128), (18696, 32), (18696, 128)])
-def test_weight_groups_of_a_weight_beyond_128_mib(cq, O, g):
-    """4096 x 16648 (read non-temporally) and 4096 x 18696 (also in strips of 20 and 12 row tiles) against their first and
-    last 4096 x 264 columns on their own (neither)."""
+@pytest.mark.parametrize("I, O, g", [(4096, 16648, 128), (4096, 18696, 32), (4096, 18696, 128), (4096, 16648, 256),
+                                     (5216, 13064, 32),      # strips of 11, 11, 11 and 8 row tiles, the last a quarter full
+                                     (4096, 16663, 128),     # strips of a weight off the vector layout
+                                     (1664, 40456, 64),      # one strip, 13 row tiles high
+                                     (1792, 37576, 64)])     # two of 7
+def test_weight_groups_of_a_weight_beyond_128_mib(cq, I, O, g):
+    """Weights read non-temporally and (groups up to 128) worked on in strips of row tiles, against their first and last 264
+    columns on their own (neither)."""
     import torch
-    I = 4096
-    say(f"grouped weight beyond 128 MiB O={O} g={g}")
+    say(f"grouped weight beyond 128 MiB I={I} O={O} g={g}")
     W = (torch.randn(I, O, generator=torch.Generator(device="cuda").manual_seed(9), device="cuda") * 0.02).half()
     qw, s, dq = cq.crossquant_weight_quantize_grouped(W, None, g, 4, want_dq=True)
     for lo in (0, O - 264):
