@@ -454,10 +454,13 @@ hipError_t launch_weight_quantize(const uint16_t* W, int I, int O, const float* 
     const bool vec = (reinterpret_cast<uintptr_t>(W) % 16 == 0) && (O % 8 == 0);
     const bool qw_vec = (reinterpret_cast<uintptr_t>(qw) % 16 == 0) && (I % 16 == 0);
     const float qm = (float)qmax;
-    // One block per 64 channels wherever that is not far behind the shared-out form, whose clearing kernel and gap cost
-    // about 6 us: a block reads a row piece at 62 GB/s, 8.4 us for 4096 rows (8192 x 1024: 27.5 us for the call against 25.5;
-    // 1024 x 512: 8.9 against 12.9; 8192 x 4096: 38.9 against 39.3; 4096 x 11008: 42 against 55).
-    if (I <= 4096 || O >= 4096) {
+    // One block per 64 channels wherever that is not behind the shared-out form, whose clearing kernel and gap cost about 5 us.
+    // A block reads a row piece at 62 GB/s, so the time of few blocks grows with their rows; beyond 8192 rows the shared-out
+    // form is ahead until the weight is wide.  Block per 64 channels : shared out, us for the call: 1024 x 512 8.6 : 12.2, 4096 x
+    // 512 15.3 : 16.2, 6144 x 2048 24.8 : 24.0, 8192 x 2048 30.8 : 29.0, 28672 x 2048 140 : 85; 4096 x 4096 22.9 : 25.5, 8192 x 4096
+    // 39.0 : 42.5, 9216 x 4096 42.9 : 42.6, 28672 x 4096 172 : 114, 9216 x 5120 60.3 : 48.9, 28672 x 8192 247 : 224; 4096 x 11008
+    // 41.9 : 46.5, 12288 x 11008 121 : 122, 28672 x 16384 434 : 442.
+    if (I <= 4096 || (O >= 4096 && (I <= 8192 || O >= 10240))) {
         if (vec) weight_step_kernel<true><<<dim3((unsigned)nkt), dim3(1024), 0, stream>>>(W, I, O, fold, qm, w_scale);
         else weight_step_kernel<false><<<dim3((unsigned)nkt), dim3(1024), 0, stream>>>(W, I, O, fold, qm, w_scale);
     } else {
@@ -471,9 +474,9 @@ hipError_t launch_weight_quantize(const uint16_t* W, int I, int O, const float* 
     const dim3 grid((unsigned)(nkt * ((I + 127) / 128)));       // (tiles of 256 rows measured 0 to 2 us slower)
     // This is the last read of W.  Up to 128 MiB the next call still finds part of it in the memory-side cache if the reads
     // are plain (4096 x 11008: 42.8 us against 44.6; 8192 x 8192, 128 MiB: 70.2 : 69.9); beyond, non-temporal reads leave
-    // that cache to what the step pass brought in (4096 x 22016: 95.0 -> 87.7, 8192 x 28672 221 -> 213, 28672 x 8192 272 ->
-    // 246).  The same in the step pass, for the channels that the cache will have lost by then, gained 1 % at 8192 x 28672
-    // and lost 3 % at 28672 x 8192.
+    // that cache to what the step pass brought in (4096 x 22016: 95.0 -> 87.7, 8192 x 28672 221 -> 213).
+    // The same in the step pass, for the channels that the cache will have lost by then, gained 1 % at 8192 x 28672 and lost
+    // 3 % at 28672 x 8192.
     if (vec && (int64_t)I * O * 2 > kCachedWeight)
         weight_tile_kernel<1, false, true, true><<<grid, dim3(256), 0, stream>>>(W, I, O, fold, 0, qm, qw, w_scale, nullptr, nkt, qw_vec, false, 1);
     else if (vec)

@@ -1018,17 +1018,22 @@ def test_weight_groups_held_in_registers(cq, I, O, group, off):
         assert np.array_equal(bits16(host(dq)), bits16(dq_ref))
 
 
-@pytest.mark.parametrize("I,O", [(4096, 520), (4100, 520), (4097, 77),      # steps: a block per 64 channels up to 4096 rows, shared out beyond
-                                 (4100, 4098), (129, 4096)])                # ... and again a block per 64 channels
-def test_weight_steps_by_either_pass(cq, I, O):
+@pytest.mark.parametrize("I,O,shared", [(4096, 520, 0), (4100, 520, 1), (4097, 77, 1),      # steps: a block per 64 channels up to 4096 rows, shared out beyond
+                                        (4100, 4098, 0), (129, 4096, 0),                    # ... and again a block per 64 channels
+                                        (8192, 4096, 0), (8200, 4104, 1), (8193, 4099, 1),  # shared out again beyond 8192 rows
+                                        (8200, 10240, 0)])                                  # ... but for wide ones
+def test_weight_steps_by_either_pass(cq, I, O, shared):
     say("weight steps I=%d O=%d" % (I, O))
     W = workloads.weight(I, O, seed=I + O)
     W[:, 3] = 0
     fold = np.random.default_rng(O).uniform(0.05, 8.0, I).astype(np.float32)
     for f in (None, fold):
         qw_ref, s_ref = oracle.weight_quantize(W, f, 8)
-        qw, s = cq.crossquant_weight_quantize(gpu(W), None if f is None else gpu(f), 8)
+        Wg, fg = gpu(W), None if f is None else gpu(f)
+        qw, s = cq.crossquant_weight_quantize(Wg, fg, 8)
         assert np.array_equal(bits32(host(s)), bits32(s_ref)) and np.array_equal(host(qw), qw_ref)
+    names = launched(cq, lambda: cq.crossquant_weight_quantize(Wg, fg, 8, qw=qw, w_scale=s))
+    assert any("weight_colmax_kernel" in n for n in names) == bool(shared)
 
 
 @pytest.mark.parametrize("I, O, g", [(4096, 16648, 128), (4096, 18696, 32), (4096, 18696, 128), (4096, 16648, 256),
