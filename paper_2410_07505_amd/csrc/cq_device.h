@@ -39,10 +39,13 @@ __device__ __forceinline__ uint4 load8(const uint16_t* __restrict__ row, int j, 
             w = sh >= 8 ? 0 : w >> (16 * (sh & 7));
             v = __builtin_bit_cast(uint4, w);
         }
-    } else if (j < I) {
+    } else {                                                 // unconditional, so that the loads of several rows overlap
         uint32_t h[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) h[e] = (j + e < I) ? row[j + e] : 0u;
+        for (int e = 0; e < 8; ++e) h[e] = row[min(j + e, I - 1)];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (j + e >= I) h[e] = 0u;
         v = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
     }
     return v;

@@ -148,7 +148,7 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
     uint4 va[kU], vb[kU];
     load_batch(va, 0);
     if (nb >= 2) load_batch(vb, 1);
-    else load_batch(vb, 0);                                 // a wave with one batch requests it twice: always 2 kU requests
+    else if (BUF) load_batch(vb, 0);                        // a wave with one batch requests it twice: always 2 kU requests
     static_assert(kU == 4, "the wait below counts the row requests of two batches");
     if (BUF) asm volatile("s_waitcnt vmcnt(8)" : "+v"(c_in), "+v"(t_in)::"memory");
 
@@ -187,9 +187,10 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
 
     uint32_t nonzero_lane = 0u;   // codes != 0 seen by this lane
     int rows_done = 0;
-    // No branch depends on whether a row exists: rows past the last one are worked on like the others (their data
+    // With BUF no branch depends on whether a row exists: rows past the last one are worked on like the others (their data
     // is the last row's, their factor is 0), but their stores go to an empty buffer, which drops them, and their
-    // counts are not added.  The only branch left is the rare exact-division path inside quantize8.
+    // counts are not added.  The only branch left is the rare exact-division path inside quantize8.  (Off that layout they are
+    // left out: with a factor of 0 the count-only form takes the division for every one of them.)
     auto work = [&](const uint4 (&v)[kU], int bi) {
         const int rbase = row0 + batch_at(bi) * kU;
         Fp6Batch f6;                                        // MODE 3: the batch's four rows leave together
@@ -201,6 +202,7 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
         for (int u = 0; u < kU; ++u) {
             const int r = rbase + u;
             const bool row_ok = r < T;                      // scalar
+            if (!BUF && !row_ok) break;
             const int rr = row_ok ? r : 0;
             rows_done += row_ok ? 1 : 0;
             const int ri = batch_at(bi) * kU + u;
