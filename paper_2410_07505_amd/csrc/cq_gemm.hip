@@ -421,13 +421,17 @@ hipError_t launch_w8a8_linear(const int8_t* qx, const float* row_scale, const in
     // (the epilogue addresses a wave's 128 output rows with 32-bit byte offsets)
     const bool ring_ok = al16(qx) && al16(qw) && (I % BK == 0) && (O % 8 == 0) && al16(Y) && (ldy % 8 == 0) && al16(w_scale) &&
                          al16(acc_debug) && ldy < ((int64_t)1 << 22);
-    // The smaller tiles of cq_gemm_staged.hip where they cover the layer in less of their own measure (rounds x rows a
-    // CU takes in per step): a round of half tiles counts as 240 there, one of whole tiles as 500.  At the line, us:
-    // 128 x 8192 x 28672 (256 : 240) 57.3 against 61.4 for the ring, 1024 x 4096 x 4096 (256 : 240) 23.1 : 24.2,
-    // 512 x 4096 x 4096 (192 : 240) 15.5 : 24.0, 64 x 8192 x 28672 (192 : 240) 52.5 : 60.6, 256 x 4096 x 11008 (256 : 240)
-    // 23.4 : 23.5.
-    const int64_t ring_cost = (int64_t)((n_main + n_cu - 1) / n_cu) * 500 + (n_main < total ? 240 : 0);
-    if (!ring_ok || w8a8_staged_cost(T, O, n_cu) < ring_cost)
+    // The smaller tiles of cq_gemm_staged.hip where they take less time by what both were measured to take: in the unit of
+    // w8a8_staged_time a round of half tiles here 336 I + 164000, one of whole tiles 500 I + 300000 (the latter is compared only
+    // with small tiles for few tokens and more than 32768 channels).  At the line, us, small tiles : ring:
+    //   64 x 128 tiles   512 x 512 x 4096 7.4 : 6.3, 512 x 1024 x 4096 8.4 : 8.4, 512 x 2048 x 4096 10.6 : 13.0, 512 x 4096 x 4096 15.6 : 22.4
+    //   128 x 128 tiles  1024 x 512 x 4096 9.2 : 7.0, 1024 x 2048 x 4096 14.7 : 13.6, 1024 x 4096 x 4096 23.0 : 24.0, 512 x 8192 x
+    //                    5120 33.6 : 40.3, 128 x 8192 x 28672 54.2 : 64.1, 256 x 4096 x 11008 21.1 : 22.8, 1024 x 11008 x 4096 50.4 : 57.6
+    //   whole tiles      60 x 1024 x 49152 17.3 : 15.6, 60 x 2048 x 49152 26.9 : 25.6, 60 x 8192 x 49152 88 : 102, 16 x 512 x 98304
+    //                    13.8 : 17.0
+    // (a constant line, 240 against the rounds times (TM + TN) of the small tiles, lost up to 40 % on either side of it)
+    const int64_t ring_time = (int64_t)((n_main + n_cu - 1) / n_cu) * ((int64_t)500 * I + 300000) + (n_main < total ? (int64_t)336 * I + 164000 : 0);
+    if (!ring_ok || w8a8_staged_time(T, I, O, n_cu) < ring_time)
         return launch_w8a8_staged(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, n_cu, stream);
     // four instances: with or without the raw accumulators, Y streamed to memory or left in the caches
     using kernel_t = void (*)(const int8_t*, const float*, const int8_t*, const float*, int, int, int, uint16_t*,

@@ -239,7 +239,7 @@ gemm_i8_short_kernel(const int8_t* __restrict__ qx, const float* __restrict__ ro
 
 }  // namespace
 
-// Tile kinds by what a CU has to take in for one 128-byte step of one tile (TM + TN rows).  The cost of a launch is the
+// Tile kinds by what a CU has to take in for one byte of the contraction of one tile (TM + TN rows).  The cost of a launch is the
 // rounds of tiles over the CUs times that; of equal ones the smaller tile is taken.  Measured at I = 4096 (us, best kind
 // first): 16 x 4096 5.5 (16 x 16), 6.3 (32 x 32), 8.0 (32 x 64); 64 x 4096 6.9 (32 x 32), 8.0 (32 x 64), 9.6 (64 x 64);
 // 64 x 11008 11.0 (64 x 64), 12.4 (32 x 64), 16.2 (32 x 32); 256 x 4096 10.1 (64 x 64), 11.8 (32 x 64), 14.1 (64 x 128);
@@ -267,10 +267,17 @@ static int best_kind(int T, int O, int n_cu, int64_t* cost) {
     return best;
 }
 
-int64_t w8a8_staged_cost(int T, int O, int n_cu) {
+// The time of the launch in the unit of the kinds' cost (one operand row and one byte of the contraction; 75000 of them are
+// about 1 us), with what a round of tiles takes besides: first requests, partial sums, stores.  Fitted to launches of 1 to 6
+// rounds with I from 128 to 8192, e.g. one round of 64 x 64 tiles 4.2 us + 1.45 us per 1024 bytes of I, of 64 x 128 6.0 + 2.4, of
+// 128 x 128 6.6 + 3.5.  More than 2048 tokens under 128 x 128 tiles are left to the ring: every XCD walks one column of
+// tiles there and fetches all the activations (4096 x 4096 x 1024 26.7 us against 24.3; 2048 x 4096 x 2048 23.7 : 24.3).
+int64_t w8a8_staged_time(int T, int I, int O, int n_cu) {
+    static const int kRound[kNumKinds] = {82000, 142000, 90000, 187000, 329000, 351000};
     int64_t cost = 0;
-    best_kind(T, O, n_cu, &cost);
-    return cost;
+    const int kind = best_kind(T, O, n_cu, &cost);
+    if (kind == kNumKinds - 1 && T > 2048) return INT64_MAX;
+    return cost * I + cost / (kKinds[kind][0] + kKinds[kind][1]) * kRound[kind];
 }
 
 hipError_t launch_w8a8_staged(const int8_t* qx, const float* row_scale, const int8_t* qw, const float* w_scale, int T, int I,

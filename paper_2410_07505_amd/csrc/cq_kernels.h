@@ -135,8 +135,8 @@ hipError_t launch_w8a8_linear(const int8_t* qx, const float* row_scale, const in
                               const float* w_scale, int T, int I, int O, uint16_t* Y, int64_t ldy,
                               int32_t* acc_debug, hipStream_t stream);
 
-// The small-tile form of it, any layout; its cost in the measure launch_w8a8_linear compares (see there).
-int64_t w8a8_staged_cost(int T, int O, int n_cu);
+// The small-tile form of it, any layout; its time in the measure launch_w8a8_linear compares (see there).
+int64_t w8a8_staged_time(int T, int I, int O, int n_cu);
 hipError_t launch_w8a8_staged(const int8_t* qx, const float* row_scale, const int8_t* qw, const float* w_scale, int T, int I,
                               int O, uint16_t* Y, int64_t ldy, int32_t* acc_debug, int n_cu, hipStream_t stream);
 

@@ -1359,6 +1359,31 @@ def test_linear_ring_kernel_on_ragged_half_tiles(cq, T, I, O):
     assert np.all(out[:T, O:] == 7.0) and np.all(out[T:] == 7.0)
 
 
+@pytest.mark.parametrize("T,I,O,kernel", [(505, 640, 4088, "ring_kernelILb0"),         # a round of 64 x 128 tiles or of half tiles
+                                          (505, 1280, 4088, "staged_kernelILi4ELi4ELi1ELi2E"),
+                                          (1000, 2048, 4088, "ring_kernelILb0"),       # a round of 128 x 128 tiles
+                                          (1000, 3072, 4088, "staged_kernelILi4ELi4ELi2ELi2E"),
+                                          (2040, 3072, 2040, "staged_kernelILi4ELi4ELi2ELi2E"),
+                                          (4000, 3072, 1000, "ring_kernelILb0"),       # too many tokens for those
+                                          (60, 1024, 33024, "ring_kernelILb0"),        # 129 whole tiles or three rounds of 64 x 64
+                                          (60, 4096, 33024, "staged_kernelILi2ELi4ELi2ELi1E")])
+def test_linear_on_either_side_of_the_line_between_its_kernels(cq, T, I, O, kernel):
+    """Which of the two kernels is faster depends on the length of the contraction too."""
+    import torch
+    say("linear, line between the kernels: T=%d I=%d O=%d" % (T, I, O))
+    qx, qw = workloads.int8_codes(T, I, seed=T), workloads.int8_codes(O, I, seed=O)
+    rng = np.random.default_rng(T + O)
+    a = rng.uniform(1e-3, 1e-1, T).astype(np.float32)
+    s = rng.uniform(1e-5, 1e-3, O).astype(np.float32)
+    Y_ref, _ = oracle.w8a8_linear(qx, a, qw, s)
+    gx, ga, gw, gs = gpu(qx), gpu(a), gpu(qw), gpu(s)
+    Y = torch.full((T + 1, O), 7.0, dtype=torch.float16, device="cuda")
+    cq.crossquant_w8a8_linear(gx, ga, gw, gs, Y=Y[:T])
+    assert np.array_equal(bits16(host(Y[:T])), bits16(Y_ref)) and bool((Y[T:] == 7.0).all())
+    names = launched(cq, lambda: cq.crossquant_w8a8_linear(gx, ga, gw, gs, Y=Y[:T]))
+    assert len(names) == 1 and "gemm_i8_" + kernel in names[0]
+
+
 def test_linear_extreme_accumulators(cq):
     say("linear extremes")
     T, I, O = 256, 8192, 256
