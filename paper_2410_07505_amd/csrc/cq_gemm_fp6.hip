@@ -633,14 +633,12 @@ hipError_t launch_w4a4_linear(const void* qx6, const float* row_scale, const voi
         n_cu = 256;
     const uint8_t* qx = static_cast<const uint8_t*>(qx6);
     const uint8_t* qw = static_cast<const uint8_t*>(qw6);
-    // Small tiles where they cover the layer in less of their own measure: rounds of tiles over the CUs times the rows
-    // (TM + TN) a CU takes in per step; a round of the ring kernel's 256 x 256 tiles counts as 400 there.  Of equal ones
-    // the larger tile.  Measured at I = 4096 (us; ring first, then 32 x 64, 64 x 64, 64 x 128, 128 x 128): 32 x 4096 27.7 :
-    // 8.8 8.5 12.2 15.9; 256 x 4096 27.3 : 15.6 9.0 12.6 17.1; 512 x 4096 27.5 : 29.2 16.2 13.4 17.6; 1024 x 4096 28.9 :
-    // 56.6 31.1 25.4 19.9; 2048 x 4096 (two rounds of the last) 31.3 : 122 77 53 39; and 32 x 5120 x 20480 34.7 : 21.8 20.6
-    // 15.8 19.0.
+    // Small tiles: the kind with the fewest rounds of tiles over the CUs times rows (TM + TN) a CU takes in per step, of equal
+    // ones the larger tile.  Measured at I = 4096 (us; ring first, then 32 x 64, 64 x 64, 64 x 128, 128 x 128): 32 x 4096 27 : 8.5
+    // 8.7 12.1 16; 256 x 4096 27 : 15.5 9.3 12.9 17.2; 512 x 4096 27 : 28.8 17.0 13.4 17.5; 1024 x 4096 28 : 57 32.0 25.5 19.2;
+    // 2048 x 4096 (two rounds of the last) 31 : 122 77 53 39; and 32 x 5120 x 20480 34.7 : 21.8 20.6 15.8 19.0.
     static const int kinds[4][2] = {{128, 128}, {64, 128}, {64, 64}, {32, 64}};
-    int64_t cost = (int64_t)((total + n_cu - 1) / n_cu) * 400;
+    int64_t cost = INT64_MAX;
     int kind = -1;
     for (int k = 0; k < 4; ++k) {
         const int tm = kinds[k][0], tn = kinds[k][1];
@@ -650,6 +648,14 @@ hipError_t launch_w4a4_linear(const void* qx6, const float* row_scale, const voi
             kind = k;
         }
     }
+    // Taken where they are faster than the ring's rounds of 256 x 256 tiles, in that unit times the contraction (100000 are about
+    // 1 us): up to 192 always, beyond with the fixed part of larger tiles or more rounds.  At the line, us, small tiles : ring: 512 x
+    // 128 x 4096 6.3 : 6.8 (192); 1024 x I x 4096 (256) 9.3 : 7.4 at I = 128, 9.9 : 9.2 at 512, 10.9 : 11.8 at 1024, 19.2 : 28.1 at 4096;
+    // 60 x I x 33024 (384) 12.5 : 9.4 at 512, 20.0 : 18.0 at 2048, 59.7 : 55.2 at 8192; 16 x I x 98304 (576, two rounds of the
+    // ring) 17.0 : 17.8 at 512, 58 : 68 at 4096; 128 x I x 81920 (768) 27.8 : 19.1 at 512, 73 : 81 at 4096.
+    const int64_t rounds = (total + n_cu - 1) / n_cu;
+    const int64_t ring_time = rounds * ((int64_t)500 * I + 110000) - (int64_t)100 * I;
+    if (cost > 192 && cost * (I + 930) >= ring_time) kind = -1;
     // weights that one row of tiles reads once and that no cache keeps: see launch_w8a8_staged (32 x 8192 x 28672 33.9 -> 32.2
     // us, 64 x 8192 x 28672 35.3 -> 34.1)
     const bool once = kind >= 0 && T <= kinds[kind][0] && (int64_t)O * I / 4 * 3 > (int64_t)128 << 20;

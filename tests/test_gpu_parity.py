@@ -1819,6 +1819,29 @@ def test_w4a4_linear_tiles_that_split_the_contraction(cq, T, O, I):
     assert np.array_equal(bits16(host(Y)), bits16(Y_ref))
 
 
+@pytest.mark.parametrize("T,I,O,kernel", [(1000, 640, 4088, "ring_kernelILb0"),        # a round of 128 x 128 tiles or of 256 x 256
+                                          (1000, 1024, 4088, "staged_kernelILi4E"),
+                                          (505, 128, 4088, "staged_kernelILi2ELi2ELi2E"),
+                                          (60, 2048, 33024, "ring_kernelILb0"),        # two rounds of 64 x 128, or 129 tiles
+                                          (16, 1024, 65600, "staged_kernelILi2ELi1ELi1E"),     # five rounds of 32 x 64, or 257 tiles
+                                          (2100, 256, 4104, "ring_kernelILb0")])
+def test_w4a4_linear_on_either_side_of_the_line_between_its_kernels(cq, T, I, O, kernel):
+    """Which of the two kernels is faster depends on the length of the contraction too."""
+    import torch
+    say("w4a4, line between the kernels: T=%d I=%d O=%d" % (T, I, O))
+    qx, qw = workloads.int8_codes(T, I, seed=T, lo=-7, hi=7), workloads.int8_codes(O, I, seed=O, lo=-7, hi=7)
+    rng = np.random.default_rng(T + O)
+    a = rng.uniform(1e-3, 1e-1, T).astype(np.float32)
+    s = rng.uniform(1e-5, 1e-3, O).astype(np.float32)
+    Y_ref, _ = oracle.w8a8_linear(qx, a, qw, s)
+    px, pw, ga, gs = cq.crossquant_pack_fp6(gpu(qx)), cq.crossquant_pack_fp6_weights(gpu(qw)), gpu(a), gpu(s)
+    Y = torch.full((T + 1, O), 7.0, dtype=torch.float16, device="cuda")
+    cq.crossquant_w4a4_linear(px, ga, pw, gs, T, I, O, Y=Y[:T])
+    assert np.array_equal(bits16(host(Y[:T])), bits16(Y_ref)) and bool((Y[T:] == 7.0).all())
+    names = launched(cq, lambda: cq.crossquant_w4a4_linear(px, ga, pw, gs, T, I, O, Y=Y[:T]))
+    assert len(names) == 1 and "gemm_f6_" + kernel in names[0]
+
+
 @pytest.mark.parametrize("T,I,O", [(5120, 128, 5120),      # 400 tiles: 144 blocks walk two tiles; one K step
                                    (5120, 256, 5120),      # two K steps
                                    (4100, 384, 7688),      # 527 tiles, ragged on both edges; three K steps
