@@ -1209,7 +1209,7 @@ def test_quantizer_widths_and_rows_off_the_vector_layout(cq, T, I, ldx, first):
 # ----------------------------------------------------------------------------- linear
 LINEAR_SHAPES = [(1, 16, 1), (5, 32, 7), (100, 200, 300), (64, 256, 256), (256, 128, 256), (300, 208, 270),
                  (256, 1024, 512), (513, 384, 257), (33, 100, 65),
-                 # ragged token / channel counts on the MFMA fast path (I % 128 == 0, O % 8 == 0)
+                 # ragged token / channel counts in the aligned layout (I % 128 == 0, O % 8 == 0); all of these take small tiles
                  (1, 128, 8), (300, 256, 520), (257, 384, 264), (513, 1024, 1000), (700, 512, 776), (255, 128, 248)]
 
 
@@ -1232,11 +1232,12 @@ def test_linear_small_and_ragged(cq, T, I, O):
 @pytest.mark.parametrize("T,I,O", [(2304, 256, 10240),     # 9 x 40 = 360 tiles = 1.41 rounds of 256: 104 tiles run as halves
                                    (2250, 256, 10248),     # 9 x 41 = 369 tiles, ragged: the last tile column is 8 wide
                                    (1280, 384, 5120),      # 100 tiles, less than half a round: every tile runs as two halves
-                                   (300, 128, 392),        # 4 tiles; the last one's second half is empty
-                                   (256, 128, 128)])       # one tile that is a single half
+                                   (1100, 128, 4104),      # 85 tiles; the second halves of the last tile column are empty
+                                   (300, 128, 392),        # 4 tiles, and one: small tiles instead
+                                   (256, 128, 128)])
 def test_linear_with_a_partly_filled_last_round_of_tiles(cq, T, I, O):
-    """One block fills a CU, so output tiles run in rounds of 256; a last round that is at most half full is run as
-    256 x 128 half tiles.  Every accumulator and output against the oracle."""
+    """One block of the ring kernel fills a CU, so output tiles run in rounds of 256; a last round that is at most half full
+    is run as 256 x 128 half tiles.  Every accumulator and output against the oracle."""
     say("linear, half-tile round: T=%d I=%d O=%d" % (T, I, O))
     qx = workloads.int8_codes(T, I, seed=T + 1)
     qw = workloads.int8_codes(O, I, seed=O + 11)
@@ -1244,9 +1245,12 @@ def test_linear_with_a_partly_filled_last_round_of_tiles(cq, T, I, O):
     a = rng.uniform(1e-3, 1e-1, T).astype(np.float32)
     s = rng.uniform(1e-5, 1e-3, O).astype(np.float32)
     Y_ref, acc_ref = oracle.w8a8_linear(qx, a, qw, s)
-    Y, acc = cq.crossquant_w8a8_linear(gpu(qx), gpu(a), gpu(qw), gpu(s), want_acc=True)
+    gx, ga, gw, gs = gpu(qx), gpu(a), gpu(qw), gpu(s)
+    Y, acc = cq.crossquant_w8a8_linear(gx, ga, gw, gs, want_acc=True)
     assert np.array_equal(host(acc), acc_ref)
     assert np.array_equal(bits16(host(Y)), bits16(Y_ref))
+    names = launched(cq, lambda: cq.crossquant_w8a8_linear(gx, ga, gw, gs, Y=Y, acc_debug=acc))
+    assert ("gemm_i8_ring_kernel" if T > 300 else "gemm_i8_staged_kernel") in names[0]
     # without the raw accumulators a block requests its next (half) tile's first operands before its epilogue
     for _ in range(2):
         Y2, none_acc = cq.crossquant_w8a8_linear(gpu(qx), gpu(a), gpu(qw), gpu(s))
@@ -1276,6 +1280,7 @@ def test_linear_blocks_walk_several_tiles(cq, T, I, O):
     assert np.array_equal(bits16(host(Y)), bits16(Y_ref))
     Y2, acc = cq.crossquant_w8a8_linear(gx, ga, gw, gs, want_acc=True)
     assert np.array_equal(host(acc), acc_ref) and np.array_equal(bits16(host(Y2)), bits16(Y_ref))
+    assert "gemm_i8_ring_kernel" in launched(cq, lambda: cq.crossquant_w8a8_linear(gx, ga, gw, gs, Y=Y))[0]
 
 
 # (T, O) for which the launcher takes, on 256 CUs, tiles of 16 x 16, 32 x 32, 32 x 64 (32 x 32 through registers), 64 x 64,
@@ -1384,9 +1389,10 @@ def test_linear_on_either_side_of_the_line_between_its_kernels(cq, T, I, O, kern
     assert len(names) == 1 and "gemm_i8_" + kernel in names[0]
 
 
-def test_linear_extreme_accumulators(cq):
-    say("linear extremes")
-    T, I, O = 256, 8192, 256
+@pytest.mark.parametrize("T,O,kernel", [(256, 256, "staged"), (1100, 4104, "ring")])
+def test_linear_extreme_accumulators(cq, T, O, kernel):
+    say("linear extremes, %s kernel" % kernel)
+    I = 8192
     qx = np.full((T, I), 127, np.int8)
     qx[1::2] = -127
     qw = np.full((O, I), 127, np.int8)
@@ -1394,12 +1400,37 @@ def test_linear_extreme_accumulators(cq):
     a = np.full(T, 2.0 ** -20, np.float32)
     s = np.full(O, 2.0 ** -6, np.float32)
     Y_ref, acc_ref = oracle.w8a8_linear(qx[:4], a[:4], qw, s)
-    Y, acc = cq.crossquant_w8a8_linear(gpu(qx), gpu(a), gpu(qw), gpu(s), want_acc=True)
-    acc = host(acc)
+    gx, ga, gw, gs = gpu(qx), gpu(a), gpu(qw), gpu(s)
+    Y, acc_g = cq.crossquant_w8a8_linear(gx, ga, gw, gs, want_acc=True)
+    acc = host(acc_g)
     assert np.array_equal(acc[:4], acc_ref) and abs(int(acc[0, 1])) == 127 * 127 * I
     assert np.array_equal(acc[0::2], np.broadcast_to(acc[0], (T // 2, O)))
     assert np.array_equal(acc[1::2], np.broadcast_to(acc[1], (T // 2, O)))
     assert np.array_equal(bits16(host(Y))[:4], bits16(Y_ref))
+    names = launched(cq, lambda: cq.crossquant_w8a8_linear(gx, ga, gw, gs, Y=Y, acc_debug=acc_g))
+    assert "gemm_i8_%s_kernel" % kernel in names[0]
+
+
+@pytest.mark.parametrize("T,O,I,kernel", [(1100, 4104, 132992, "ring"), (40, 72, 132992, "staged"), (40, 70, 133000, "staged")])
+def test_linear_longest_contraction(cq, T, O, I, kernel):
+    """I up to 133 000, the documented limit: |acc| reaches 127 * 127 * 133 000 = 2 145 157 000 < 2^31, still exact."""
+    import torch
+    say("linear, longest contraction %dx%dx%d" % (T, I, O))
+    row = torch.ones(T, dtype=torch.int8, device="cuda")
+    row[1::2] = -1
+    col = torch.ones(O, dtype=torch.int8, device="cuda")
+    col[::3] = -1
+    qx, qw = (row * 127)[:, None].repeat(1, I), (col * 127)[:, None].repeat(1, I)
+    qx[2, ::2] = 3
+    ga, gs = torch.full((T,), 2.0 ** -20, device="cuda"), torch.full((O,), 2.0 ** -10, device="cuda")
+    Y, acc = cq.crossquant_w8a8_linear(qx, ga, qw, gs, want_acc=True)
+    expect = row.to(torch.int64)[:, None] * col.to(torch.int64)[None, :] * (127 * 127 * I)
+    expect[2] = col.to(torch.int64) * 127 * (3 * (I // 2) + 127 * (I // 2))
+    assert int(expect.abs().max()) == 127 * 127 * I and torch.equal(acc.to(torch.int64), expect)
+    y = ((expect.to(torch.float32) * ga[:, None]) * gs[None, :]).half()
+    assert torch.equal(Y.view(torch.int16), y.view(torch.int16))
+    names = launched(cq, lambda: cq.crossquant_w8a8_linear(qx, ga, qw, gs, Y=Y, acc_debug=acc))
+    assert "gemm_i8_%s_kernel" % kernel in names[0]
 
 
 def test_linear_strided_output(cq):
@@ -1416,21 +1447,25 @@ def test_linear_strided_output(cq):
     assert np.array_equal(bits16(out[:, :O]), bits16(Y_ref)) and np.all(out[:, O:] == 7.0)
 
 
-def test_linear_ragged_fast_path_writes_nothing_outside_its_output(cq):
-    """Ragged T and O on the MFMA fast path (edge tiles read clamped rows and drop the surplus
+@pytest.mark.parametrize("T,O,kernel", [(300, 520, "staged"), (1100, 4104, "ring")])
+def test_linear_ragged_fast_path_writes_nothing_outside_its_output(cq, T, O, kernel):
+    """Ragged T and O in the aligned layout (edge tiles read clamped rows and drop the surplus
     outputs): rows past T and columns past O of the surrounding buffer must stay untouched."""
     import torch
-    say("linear ragged fast path, guarded buffer")
-    T, I, O = 300, 256, 520
+    say("linear ragged fast path, guarded buffer, %s kernel" % kernel)
+    I = 256
     qx, qw = workloads.int8_codes(T, I, seed=3), workloads.int8_codes(O, I, seed=4)
     rng = np.random.default_rng(6)
     a = rng.uniform(1e-3, 1e-1, T).astype(np.float32)
     s = rng.uniform(1e-5, 1e-3, O).astype(np.float32)
     Y_ref, acc_ref = oracle.w8a8_linear(qx, a, qw, s)
-    buf = torch.full((T + 20, 640), 7.0, dtype=torch.float16, device="cuda")
+    buf = torch.full((T + 20, O + 120), 7.0, dtype=torch.float16, device="cuda")
     accbuf = torch.full((T + 20, O), -5, dtype=torch.int32, device="cuda")
-    cq.crossquant_w8a8_linear(gpu(qx), gpu(a), gpu(qw), gpu(s), Y=buf[:T, :O], acc_debug=accbuf[:T])
+    gx, ga, gw, gs = gpu(qx), gpu(a), gpu(qw), gpu(s)
+    cq.crossquant_w8a8_linear(gx, ga, gw, gs, Y=buf[:T, :O], acc_debug=accbuf[:T])
     out, acc = host(buf), host(accbuf)
+    names = launched(cq, lambda: cq.crossquant_w8a8_linear(gx, ga, gw, gs, Y=buf[:T, :O], acc_debug=accbuf[:T]))
+    assert "gemm_i8_%s_kernel" % kernel in names[0]
     assert np.array_equal(bits16(out[:T, :O]), bits16(Y_ref)) and np.array_equal(acc[:T], acc_ref)
     assert np.all(out[:T, O:] == 7.0) and np.all(out[T:] == 7.0) and np.all(acc[T:] == -5)
 
@@ -1867,25 +1902,30 @@ def test_w4a4_linear_fp6_blocks_walk_several_tiles(cq, T, I, O):
     assert np.array_equal(host(acc), acc_ref) and np.array_equal(bits16(host(Y2)), bits16(Y_ref))
 
 
-def test_w4a4_linear_fp6_extreme_accumulators_and_guarded_output(cq):
+@pytest.mark.parametrize("T,O,kernel", [(70, 72, "staged"), (2100, 4104, "ring")])
+def test_w4a4_linear_fp6_extreme_accumulators_and_guarded_output(cq, T, O, kernel):
     """All codes at +-7 over 4096 channels (|acc| = 49 * 4096, exact in binary32), written into a
     window of a larger buffer whose surroundings must stay untouched."""
     import torch
-    T, I, O = 70, 4096, 72
+    I = 4096
     qx = np.full((T, I), 7, np.int8)
     qx[::2] = -7
     qw = np.full((O, I), -7, np.int8)
     qw[::3] = 7
     a = np.full(T, 0.01, np.float32)
     s = np.full(O, 0.001, np.float32)
-    Y_ref, acc_ref = oracle.w8a8_linear(qx, a, qw, s)
+    Y_ref, acc_ref = oracle.w8a8_linear(qx[:4], a[:4], qw, s)
     assert np.abs(acc_ref).max() == 49 * I
-    buf = torch.full((T + 5, 96), 7.0, dtype=torch.float16, device="cuda")
+    Y_ref, acc_ref = (np.tile(m[:2], (T // 2, 1)) for m in (Y_ref, acc_ref))         # two kinds of rows
+    buf = torch.full((T + 5, O + 24), 7.0, dtype=torch.float16, device="cuda")
     px, pw = cq.crossquant_pack_fp6(gpu(qx)), cq.crossquant_pack_fp6_weights(gpu(qw))
-    _, acc = cq.crossquant_w4a4_linear(px, gpu(a), pw, gpu(s), T, I, O, Y=buf[:T, :O], want_acc=True)
+    ga, gs = gpu(a), gpu(s)
+    _, acc = cq.crossquant_w4a4_linear(px, ga, pw, gs, T, I, O, Y=buf[:T, :O], want_acc=True)
     out = host(buf)
     assert np.array_equal(host(acc), acc_ref) and np.array_equal(bits16(out[:T, :O]), bits16(Y_ref))
     assert np.all(out[:T, O:] == 7.0) and np.all(out[T:] == 7.0)
+    names = launched(cq, lambda: cq.crossquant_w4a4_linear(px, ga, pw, gs, T, I, O, Y=buf[:T, :O], acc_debug=acc))
+    assert "gemm_f6_%s_kernel" % kernel in names[0]
 
 
 def test_w4a4_linear_fp6_longest_contraction(cq):
@@ -1904,6 +1944,29 @@ def test_w4a4_linear_fp6_longest_contraction(cq):
     px, pw = cq.crossquant_pack_fp6(gpu(qx)), cq.crossquant_pack_fp6_weights(gpu(qw))
     Y, acc = cq.crossquant_w4a4_linear(px, gpu(a), pw, gpu(s), T, I, O, want_acc=True)
     assert np.array_equal(host(acc), acc_ref) and np.array_equal(bits16(host(Y)), bits16(Y_ref))
+
+
+def test_w4a4_linear_fp6_longest_contraction_in_the_ring_kernel(cq):
+    """The same limit with enough outputs for the kernel of the large layers (1040 x 4104)."""
+    import torch
+    say("w4a4, longest contraction, ring kernel")
+    T, I, O = 1040, 1 << 18, 4104
+    row = torch.ones(T, dtype=torch.int8, device="cuda")
+    row[1::2] = -1
+    col = torch.ones(O, dtype=torch.int8, device="cuda")
+    col[::3] = -1
+    qx, qw = (row * 7)[:, None].repeat(1, I), (col * 7)[:, None].repeat(1, I)
+    qx[2, ::2] = 3
+    px, pw = cq.crossquant_pack_fp6(qx), cq.crossquant_pack_fp6_weights(qw)
+    ga, gs = torch.full((T,), 2.0 ** -20, device="cuda"), torch.full((O,), 2.0 ** -3, device="cuda")
+    Y, acc = cq.crossquant_w4a4_linear(px, ga, pw, gs, T, I, O, want_acc=True)
+    expect = row.to(torch.int64)[:, None] * col.to(torch.int64)[None, :] * (49 * I)
+    expect[2] = col.to(torch.int64) * 7 * 5 * I
+    assert torch.equal(acc.to(torch.int64), expect)
+    y = ((expect.to(torch.float32) * ga[:, None]) * gs[None, :]).half()
+    assert torch.equal(Y.view(torch.int16), y.view(torch.int16))
+    names = launched(cq, lambda: cq.crossquant_w4a4_linear(px, ga, pw, gs, T, I, O, Y=Y, acc_debug=acc))
+    assert "gemm_f6_ring_kernel" in names[0]
 
 
 @pytest.mark.parametrize("T,I", [(1, 128), (32, 128), (45, 256), (300, 640), (257, 1024), (64, 2048)])
