@@ -159,6 +159,15 @@ __device__ __forceinline__ void request_1k(const void* src, const int8_t* dst) {
     else asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc0" : : "v"(src), "s"(lds_off) : "m0");
 }
 
+// The step barrier of those kernels: bare, since __syncthreads would wait for all requests in flight.  The barrier
+// builtin orders no memory for the compiler, which sees neither the requests' writes to LDS nor a reason to keep a
+// step's LDS reads behind the barrier: the empty asm says that memory may have changed (it adds no instruction).
+__device__ __forceinline__ void step_barrier() {
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // The end of a tile: the WK partial sums of every accumulator meet in LDS (parts: [wk][wm][wn][mi][ni][lane]), are
 // scaled and stored.  Weight tile ni of a wave holds the channels NT fr + ni (fr = lane & 15) of the wave's 16 NT.
 // vec_out: every lane's NT channels exist or not together and their 2 NT bytes of Y are aligned.

@@ -543,8 +543,7 @@ gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__
             if (s < nk) request(s, s);
         if (nk >= S) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 1) * N, 15));           // step 0 has landed
         else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
+        step_barrier();
         Frags f0, f1;
         read(f0, 0);
 
@@ -552,8 +551,7 @@ gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__
         auto step = [&](int kt, Frags& cur, Frags& nxt) {
             if (kt + S - 1 < nk) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 2) * N, 0));
             else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_sched_barrier(0);
+            step_barrier();
             const int next_slot = slot + 1 == S ? 0 : slot + 1;
             if (early && kt + S < nk) request(kt + S, slot);
             __builtin_amdgcn_sched_barrier(0);

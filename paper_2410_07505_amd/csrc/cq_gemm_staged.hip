@@ -154,8 +154,7 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
             if (S + 1 < nk) load_step(r1, S + 1);
             __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
         }
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
+        step_barrier();
         Frags f0, f1;
         read(f0, 0);
 
@@ -166,8 +165,7 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
             if (DMA && kt + S - 1 < nk) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 2) * N, 0));
             else if (DMA) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
             else __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_sched_barrier(0);
+            step_barrier();
             auto fetch = [&]() {
                 if (kt + S < nk) {
                     if (DMA) {
