@@ -350,3 +350,8 @@ def test_package_names_follow_the_binding(cq, monkeypatch):
     assert cq.crossquant_absmax is replacement
     monkeypatch.undo()
     assert cq.crossquant_absmax is binding.crossquant_absmax
+    monkeypatch.setattr(cq, "crossquant_absmax", replacement)            # ... and the package's own names can be replaced too
+    assert cq.crossquant_absmax is replacement and binding.crossquant_absmax is not replacement
+    monkeypatch.undo()
+    assert cq.crossquant_absmax is binding.crossquant_absmax
+    assert not hasattr(cq, "no_such_name")
