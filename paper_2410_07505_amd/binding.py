@@ -94,15 +94,14 @@ def _check(status: int) -> None:
 # fails goes through them again to say which.  64 x 256 x 256 as three calls: 32.5 -> 22.1 us on the host (three launches
 # from C: 13.4 us).
 _Tensor = torch.Tensor
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # private: a torch without GPU support lacks it
+# (private: a torch without GPU support lacks it)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda index: torch.cuda.current_stream(index).cuda_stream)
 
 
 def _stream(t: torch.Tensor) -> int:
     """Handle of the current stream on t's device (without building a torch Stream object around it)."""
     index = t.get_device()
-    if index >= 0 and _raw_stream is not None:
-        return _raw_stream(index)
-    return torch.cuda.current_stream(t.device).cuda_stream
+    return _raw_stream(index) if index >= 0 else torch.cuda.current_stream(t.device).cuda_stream
 
 
 def _ptr(t) -> int:
