@@ -43,8 +43,8 @@ __device__ __forceinline__ bool tile_of_block(int block, int tiles_m, int tiles_
     return true;
 }
 
-// Store policy of Y: up to 64 MiB it is written with plain stores, beyond that written through as a stream (see
-// epilogue_rows_store).  Measured in a layer step: 2048 x 11008 outputs (43 MiB) 84.1 -> 82.5 us for the matrix
+// Store policy of Y in the ring kernels: up to 64 MiB it is written with plain stores, beyond that written through as a
+// stream (see epilogue16_store).  Measured in a layer step: 2048 x 11008 outputs (43 MiB) 84.1 -> 82.5 us for the matrix
 // kernel with plain stores and no change after it; 4096 x 20480 (160 MiB) and 4096 x 28672 (224 MiB) make the
 // absmax call that follows 1.5 and 6 us slower with plain stores.
 inline bool y_stays_cached(int T, int O) { return (int64_t)T * O * 2 <= (int64_t)64 << 20; }
@@ -172,6 +172,9 @@ __device__ __forceinline__ void step_barrier() {
 // scaled and stored.  Weight tile ni of a wave holds the channels NT fr + ni (fr = lane & 15) of the wave's 16 NT.
 // vec_out: every lane's NT channels exist or not together and their 2 NT bytes of Y are aligned.
 // V: four int32 or four binary32 values (sums of the FP6 products are integers below 2^24, exact in any order).
+// Y leaves with plain stores whatever its size.  Outputs beyond 64 MiB come here only off the ring's layout: 4096 x 4112 x 20480
+// (160 MiB) takes 582 us, and 686 with the absmax of a cold 4096 x 8192 matrix behind each (14.5 on its own), where the ring
+// takes 254 and 264 for 4096 x 4096 x 20480.
 template <int MT, int NT, int WM, int WN, int WK, typename V>
 __device__ __forceinline__ void sum_and_store(const V (&acc)[MT][NT], V* parts, int wave, int lane,
                                               const float* __restrict__ row_scale, const float* __restrict__ w_scale, int T,

@@ -292,7 +292,10 @@ hipError_t launch_w8a8_staged(const int8_t* qx, const float* row_scale, const in
     // 64 x 128 tiles: 15.5 us with WK 2 and 3 slots, 15.7 with 4, 19.1 with WK 4)
     // Weights that one row of tiles reads once and that no cache keeps are requested non-temporally: 16 x 8192 x 28672 44.2 ->
     // 37.9 us (6.2 TB/s), 64 x 8192 x 28672 52.6 -> 47.7, 32 x 8192 x 22016 42.2 -> 37.8, but 16 x 4096 x 22016 (86 MiB, part of which
-    // the memory-side cache keeps from one call to the next) 18.5 -> 21.3.
+    // the memory-side cache keeps from one call to the next) 18.5 -> 21.3.  The kinds without such an instance request plainly: they
+    // are not the fastest ones for these up-projections.  (Down-projections take some of them, 16 x 28672 x 8192 the 16 x 16
+    // tiles; on 16 x 8192 x 28672 non-temporal requests took them from 45.2 to 42.7 us, 32 x 32 from 51.3 to 45.8, 64 x 64 from 48.3
+    // to 43.9.)
     const int kind = best_kind(T, O, n_cu, &cost);
     const bool once = dma && T <= kKinds[kind][0] && (int64_t)O * I > (int64_t)128 << 20;
 #define CQ_STAGED(MT, NT, WM, WN, WK, S, ...) \
