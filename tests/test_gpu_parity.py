@@ -1308,15 +1308,18 @@ def test_linear_tiles_that_split_the_contraction(cq, T, O, I):
         assert np.all(out[:T, O:] == 7.0) and np.all(out[T:] == 7.0)
 
 
-@pytest.mark.parametrize("T,I,O", [(5, 4736, 28672), (60, 4688, 28672), (100, 4688, 28672)])     # tiles of 32 x 64, 64 x 128, 128 x 128
+@pytest.mark.parametrize("T,I,O", [(5, 4736, 28672), (60, 4688, 28672), (100, 4688, 28672), (100, 4736, 28672)])     # tiles of 32 x 64, 64 x 128, 128 x 128
 def test_linear_weights_requested_once(cq, T, I, O):
     """More than 128 MiB of weights under one row of tiles: requested non-temporally.  (4688: a partial last step.)"""
     say("linear, large weights: T=%d I=%d O=%d" % (T, I, O))
     qx, qw = workloads.int8_codes(T, I, seed=T), workloads.int8_codes(O, I, seed=O)
     a, s = np.full(T, 0.01, np.float32), np.full(O, 0.0001, np.float32)
     Y_ref, acc_ref = oracle.w8a8_linear(qx, a, qw, s)
-    Y, acc = cq.crossquant_w8a8_linear(gpu(qx), gpu(a), gpu(qw), gpu(s), want_acc=True)
+    gx, ga, gw, gs = gpu(qx), gpu(a), gpu(qw), gpu(s)
+    Y, acc = cq.crossquant_w8a8_linear(gx, ga, gw, gs, want_acc=True)
     assert np.array_equal(host(acc), acc_ref) and np.array_equal(bits16(host(Y)), bits16(Y_ref))
+    (name,) = launched(cq, lambda: cq.crossquant_w8a8_linear(gx, ga, gw, gs, Y=Y, acc_debug=acc))
+    assert "gemm_i8_staged_kernel" in name and "ELb1ELb1EE" in name                  # straight to LDS, once
 
 
 @pytest.mark.parametrize("T", [30, 100])                                                          # 64 x 128, 128 x 128
