@@ -66,13 +66,16 @@ __global__ void zero_u64_kernel(unsigned long long* p) { *p = 0ull; }
 //     fragments never do.
 // Any other layout: unaligned 16-byte loads (load8), unaligned stores of whole pieces and element stores of the one lane
 // at the end of a row.
+// COUNT: the zero codes are counted.  Codes alone are bound by vector instructions, of which the count is two per element in
+// some fourteen: without it 4096 x 4096 takes 9.4 us (10.7 with it), 2048 x 4096 6.5 (7.2), 16 x 8192 3.9 (4.2), as FP6 fragments
+// 4096 x 8192 18.5 (20.8).  With a dequantized matrix the memory is the bound and the instances that count are the only ones.
 // The loop is software-pipelined by hand: two register sets of kU rows alternate, the loads of batch bi + 1
 // are requested before batch bi is worked on.  (The loop is kept a loop: unrolled completely for a known
 // number of batches, where the compiler's count of outstanding memory operations becomes exact, it ran 4 us
 // slower on the 4096 x 8192 layer than with the loop's conservative waits.  Two sets is the optimum also for
 // the count-only form, which has registers to spare: 4096 x 8192 in a layer step takes 17.7 us with two sets,
 // 18.6 with one, 19.6 with three and 23.3 with four, i.e. with all of X requested at once.)
-template <int MODE, bool XHAT, bool BUF, bool STREAM>
+template <int MODE, bool XHAT, bool BUF, bool STREAM, bool COUNT>
 __global__ void __launch_bounds__(kWaves * kLanes)
 quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, const float* __restrict__ t_vec,
                        const float* __restrict__ c_vec, double alpha, int qmax_i, float* __restrict__ a_out,
@@ -219,7 +222,7 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
             const int nvalid = max(0, min(8, live - lane * 8));     // ... of this lane's eight
             // count, pack and store one row piece; returns the lane's number of non-zero codes in it
             auto emit = [&](const float (&m)[8], const float (&q)[8]) -> uint32_t {
-                const uint32_t nz = count_nonzero8_lane(m);
+                const uint32_t nz = COUNT ? count_nonzero8_lane(m) : 0u;
                 if (MODE == 3) fp6_batch_row(f6, m, u);
                 if (!BUF) {
                     if (MODE == 1) store_piece<8, uint8_t>(pack_codes_i8(m), codes + (int64_t)rr * I + col0 + lane * 8, nvalid);
@@ -253,7 +256,7 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
             } else {
                 nz = emit(m, q);
             }
-            nonzero_lane += row_ok ? nz : 0u;
+            if (COUNT) nonzero_lane += row_ok ? nz : 0u;
             __builtin_amdgcn_sched_barrier(0);               // rows one after the other: keeps scalar register pressure down
         }
         if (MODE == 3) {
@@ -272,7 +275,7 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
         }
     }
 
-    if (zero_count) {
+    if (COUNT && zero_count) {
         uint32_t nonzero = nonzero_lane;                    // ... and by the wave
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) nonzero += shx(nonzero, off);
@@ -336,9 +339,12 @@ hipError_t launch_mode(const uint16_t* X, int B, int T, int I, int64_t ldx, int6
     // reads xhat: 4096 x 5120 25.4 | 29.5 | 36.8 | 39.3.)
     const int64_t elems = (int64_t)B * T * I;
     const bool streamed = XHAT && elems * 4 + elems / (MODE == 1 ? 1 : 2) > (int64_t)96 << 20;
-    const auto kernel = !buf ? &quantize_stream_kernel<MODE, XHAT, false, false>
-                        : streamed ? &quantize_stream_kernel<MODE, XHAT, true, XHAT>
-                                   : &quantize_stream_kernel<MODE, XHAT, true, false>;
+    constexpr bool kCounts = MODE == 0 || XHAT;             // instances without the count: codes alone
+    const auto kernel = zc || kCounts ? (!buf ? &quantize_stream_kernel<MODE, XHAT, false, false, true>
+                                         : streamed ? &quantize_stream_kernel<MODE, XHAT, true, XHAT, true>
+                                                    : &quantize_stream_kernel<MODE, XHAT, true, false, true>)
+                                      : (!buf ? &quantize_stream_kernel<MODE, XHAT, false, false, kCounts>
+                                              : &quantize_stream_kernel<MODE, XHAT, true, false, kCounts>);
     kernel<<<grid, block, 0, stream>>>(X, T, I, ldx, t, c, alpha, qmax, a, b, codes, xhat, zc, state, ncc, nb, ncc * nrc,
                                        matrix_stride);
     return hipGetLastError();

@@ -1991,6 +1991,26 @@ def test_quantize_straight_to_fp6(cq, T, I):
         assert np.array_equal(host(cq.crossquant_pack_fp6(nib)), want)
 
 
+@pytest.mark.parametrize("kind,T,I", [("int8", 1, 8), ("int8", 70, 520), ("int8", 37, 1031), ("int4", 33, 512), ("int4", 70, 518),
+                                      ("fp6", 1, 128), ("fp6", 45, 640)])
+def test_codes_without_the_zero_count(cq, kind, T, I):
+    """Codes alone come from kernels of their own that do not count: on and off the vector layout, against the oracle."""
+    import torch
+    say("codes without the count: %s %dx%d" % (kind, T, I))
+    bits = 8 if kind == "int8" else 4
+    X = outliers(T, I, seed=T + I)
+    t, c = cq.crossquant_absmax(gpu(X))
+    for scale in (1.0, 0.25):                               # calibrated maxima below the data's: clamped codes
+        ref = oracle.quantize(X, host(t), host(c) * np.float32(scale), 0.15, bits)
+        kw = dict(want_xhat=False, want_count=False)
+        run = ((lambda: cq.crossquant_quantize_fp6(gpu(X), t, c * scale, 0.15, **kw)) if kind == "fp6" else
+               (lambda: cq.crossquant_quantize(gpu(X), t, c * scale, 0.15, bits, **kw)))
+        codes, xhat, a, b, z = run()
+        assert xhat is None and z is None
+        assert np.array_equal(host(codes), fp6_fragments(oracle.unpack_int4(ref["codes"])) if kind == "fp6" else ref["codes"])
+        assert np.array_equal(bits32(host(a)), bits32(ref["a"])) and np.array_equal(bits32(host(b)), bits32(ref["b"]))
+
+
 def test_end_to_end_a4w4_fp6_config(cq):
     """The low-bit configuration end to end with the FP6 linear layer: CrossQuant INT4 activation
     codes (packed nibbles) and INT4 per-channel weights, compared with the oracle on sampled rows
