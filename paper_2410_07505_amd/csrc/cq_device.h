@@ -387,64 +387,90 @@ __device__ __forceinline__ void store_piece(V v, void* dst, int n) {
 // stream of 6-bit fields, its first 16 bytes at fragment + 16 * lane, the last 8 at fragment + 1024
 // + 8 * lane.  The wave's lanes 4g .. 4g+3 hold the 32 columns of group g (8 each).
 // They are written four rows at a time (rows 4 k .. 4 k + 3 of one matrix, as the streaming kernel
-// works on them): a lane keeps its 48 bits of each of the four rows, then the quad transposes them (two
-// exchange steps of quad-permute register moves, no LDS) so that lane 4 g + u holds the whole 24-byte record of
-// row u, and each lane stores one 16-byte and one 8-byte piece: a quad writes 64 and 32 contiguous bytes where
-// the row-by-row form writes four scattered 16-byte and 8-byte pieces.
+// works on them): a lane keeps its eight codes of each of the four rows as binary16 (exact), then the quad transposes them
+// (quad-permuting selects, no LDS) so that lane 4 g + u holds the 32 codes of row u, which one instruction turns
+// into the 24-byte record (E2M3 holds every code exactly), and each lane stores one 16-byte and one 8-byte piece: a quad
+// writes 64 and 32 contiguous bytes.  The kernel is bound by vector instructions, 8.8 per element with this (12.5 with E2M3
+// fields from table lookups and shifts and a transposition of 48-bit pieces): 4096 x 4096 9.9 -> 8.7 us, 4096 x 8192 18.3 -> 16.7.
 struct Fp6Batch {
-    uint32_t lo[4], hi[4];      // this lane's fields of rows 0 .. 3: 32 + 16 bits each
+    uint32_t h[4][4];           // [pair of columns][row]: this lane's codes, two binary16 values each
 };
-template <int CTRL>
-__device__ __forceinline__ uint32_t quad_permute(uint32_t x) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xF, 0xF, true);
+// row u (0..3) of the batch: the lane's 8 codes
+__device__ __forceinline__ void fp6_batch_row(Fp6Batch& out, const float (&q)[8], int u) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) out.h[p][u] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(q[2 * p], q[2 * p + 1]));
 }
-// r[k] = this lane's value of row k  ->  r[k] = the value lane k of the quad had for row (lane & 3)
-__device__ __forceinline__ void quad_transpose(uint32_t (&r)[4], int lane) {
-    const bool odd = lane & 1, up = lane & 2;
-    // neighbours exchange: an even lane ends up with rows 0 and 2 of both lanes, an odd lane with rows 1 and 3
-    const uint32_t g01 = quad_permute<0xB1>(odd ? r[0] : r[1]);         // lanes 1 0 3 2
-    const uint32_t g23 = quad_permute<0xB1>(odd ? r[2] : r[3]);
-    const uint32_t a01 = odd ? g01 : r[0], b01 = odd ? r[1] : g01;
-    const uint32_t a23 = odd ? g23 : r[2], b23 = odd ? r[3] : g23;
+// One exchange step of the 4 x 4 transposition over a quad, for eight pairs of registers: the lanes of `mask` (32 bits,
+// repeated) keep their own register, the others take one of their partner's:
+//   o[i] = lane in mask ? keep[i] : (partner lane's) take[i]
+// v_cndmask takes its second source where vcc is set and its first, here read from the partner lane, elsewhere.  (The
+// compiler makes a move and a select of each.)  The two wait states are those between a vector instruction
+// that writes a register and one that reads it from another lane.
+#define CQ_QUAD_STEP(NAME, PERM)                                                                                             \
+    template <uint32_t MASK>                                                                                                 \
+    __device__ __forceinline__ void NAME(uint32_t (&o)[8], const uint32_t (&take)[8], const uint32_t (&keep)[8]) {           \
+        asm("s_mov_b32 vcc_lo, %24\n\ts_mov_b32 vcc_hi, %24\n\ts_nop 1\n\t"                                                 \
+            "v_cndmask_b32_dpp %0, %8, %16, vcc quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                           \
+            "v_cndmask_b32_dpp %1, %9, %17, vcc quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                           \
+            "v_cndmask_b32_dpp %2, %10, %18, vcc quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                          \
+            "v_cndmask_b32_dpp %3, %11, %19, vcc quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                          \
+            "v_cndmask_b32_dpp %4, %12, %20, vcc quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                          \
+            "v_cndmask_b32_dpp %5, %13, %21, vcc quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                          \
+            "v_cndmask_b32_dpp %6, %14, %22, vcc quad_perm:" PERM " row_mask:0xf bank_mask:0xf\n\t"                          \
+            "v_cndmask_b32_dpp %7, %15, %23, vcc quad_perm:" PERM " row_mask:0xf bank_mask:0xf"                               \
+            : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]), "=&v"(o[7])          \
+            : "v"(take[0]), "v"(take[1]), "v"(take[2]), "v"(take[3]), "v"(take[4]), "v"(take[5]), "v"(take[6]), "v"(take[7]), \
+              "v"(keep[0]), "v"(keep[1]), "v"(keep[2]), "v"(keep[3]), "v"(keep[4]), "v"(keep[5]), "v"(keep[6]), "v"(keep[7]), \
+              "i"(MASK)                                                                                                       \
+            : "vcc");                                                                                                         \
+    }
+CQ_QUAD_STEP(quad_neighbours, "[1,0,3,2]")
+CQ_QUAD_STEP(quad_pairs, "[2,3,0,1]")
+#undef CQ_QUAD_STEP
+// h[p][k] = this lane's value of row k  ->  r[4 k + p] = the value lane k of the quad had for row (lane & 3)
+__device__ __forceinline__ void quad_transpose(const uint32_t (&h)[4][4], uint32_t (&r)[16]) {
+    // neighbours exchange: an even lane ends up with rows 0 and 2 of both lanes (even[..]: the even lane's, odd[..]: the odd
+    // one's), an odd lane with rows 1 and 3
+    uint32_t row_e[8], row_o[8];                            // [2 p + 0]: rows 0 / 1, [2 p + 1]: rows 2 / 3
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        row_e[2 * p] = h[p][0];
+        row_e[2 * p + 1] = h[p][2];
+        row_o[2 * p] = h[p][1];
+        row_o[2 * p + 1] = h[p][3];
+    }
+    uint32_t even[8], odd[8];
+    quad_neighbours<0x55555555u>(even, row_o, row_e);
+    quad_neighbours<0xAAAAAAAAu>(odd, row_e, row_o);
     // pairs exchange: lanes 0, 1 give away their rows 2, 3 and lanes 2, 3 their rows 0, 1
-    const uint32_t ga = quad_permute<0x4E>(up ? a01 : a23);             // lanes 2 3 0 1
-    const uint32_t gb = quad_permute<0x4E>(up ? b01 : b23);
-    r[0] = up ? ga : a01;
-    r[1] = up ? gb : b01;
-    r[2] = up ? a23 : ga;
-    r[3] = up ? b23 : gb;
-}
-// Four INT4 codes (two's-complement bytes, -7 .. 7) -> their four E2M3 patterns packed into 24 bits.  Byte-wise:
-// |q| = (q ^ mask) + sign bit with mask = 0xFF in negative bytes (no carry can cross a byte: |q| <= 7); the E2M3
-// pattern of 0 .. 7 is one lookup in an 8-byte table (v_perm_b32 takes its selector bytes 0 .. 7 from the codes
-// themselves); bit 5 is the sign.  Then the four 6-bit fields are squeezed together in two steps.
-__device__ __forceinline__ uint32_t fp6_fields4(uint32_t w) {
-    const uint32_t s = w & 0x80808080u;
-    const uint32_t ones = s >> 7;
-    const uint32_t mask = s | (s - ones);                               // 0xFF where negative
-    const uint32_t mag = (w ^ mask) + ones;
-    uint32_t e = __builtin_amdgcn_perm(0x1E1C1A18u, 0x14100800u, mag);  // 0 8 16 20 | 24 26 28 30
-    e |= ones << 5;
-    const uint32_t y = (e & 0x003F003Fu) | ((e & 0x3F003F00u) >> 2);    // two 12-bit fields in the half words
-    return (y & 0xFFFu) | ((y >> 4) & 0xFFF000u);
-}
-// row u (0..3) of the batch: the lane's 8 codes as rounding-step values m
-__device__ __forceinline__ void fp6_batch_row(Fp6Batch& out, const float (&m)[8], int u) {
-    const u32x2 w = pack_codes_i8(m);
-    const uint32_t f0 = fp6_fields4(w.x), f1 = fp6_fields4(w.y);        // 24 bits each
-    out.lo[u] = f0 | (f1 << 24);
-    out.hi[u] = f1 >> 8;                                                // 16 bits
+    uint32_t low[8], high[8], first[8], second[8];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        low[p] = even[2 * p];
+        low[4 + p] = odd[2 * p];
+        high[p] = even[2 * p + 1];
+        high[4 + p] = odd[2 * p + 1];
+    }
+    quad_pairs<0x33333333u>(first, high, low);
+    quad_pairs<0xCCCCCCCCu>(second, low, high);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        r[i] = first[i];                                    // lanes 0 and 1 of the quad
+        r[8 + i] = second[i];
+    }
 }
 // rows row4 .. row4 + 3 (row4 % 4 == 0); rows_ok: bit u set if row row4 + u exists; group_ok: the lane's columns exist.
 // The four rows lie in one row of fragments, which is addressed as a raw buffer (frags_per_row * 1536 bytes).
 // Must be called by the whole wave (the transposition exchanges registers between lanes).
-__device__ __forceinline__ void fp6_batch_store(Fp6Batch& out, uint8_t* packed, int row4, int first_col, int lane,
+__device__ __forceinline__ void fp6_batch_store(const Fp6Batch& out, uint8_t* packed, int row4, int first_col, int lane,
                                                 int frags_per_row, uint32_t rows_ok, bool group_ok) {
-    quad_transpose(out.lo, lane);
-    quad_transpose(out.hi, lane);
-    // the group's 192-bit record of this lane's row: four lanes' 32 + 16 bits one after the other
-    const uint32_t d1 = out.hi[0] | (out.lo[1] << 16), d2 = (out.lo[1] >> 16) | (out.hi[1] << 16);
-    const uint32_t d4 = out.hi[2] | (out.lo[3] << 16), d5 = (out.lo[3] >> 16) | (out.hi[3] << 16);
+    typedef _Float16 f16x32 __attribute__((ext_vector_type(32)));
+    typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
+    struct Regs {
+        uint32_t r[16];
+    } codes;
+    quad_transpose(out.h, codes.r);
+    const u32x6 rec = __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(__builtin_bit_cast(f16x32, codes), 1.0f);
     const int u = lane & 3, g = lane >> 2;
     const int col = first_col + 32 * g;
     const int flane = ((row4 + u) & 31) + 32 * ((col >> 5) & 1);
@@ -452,8 +478,8 @@ __device__ __forceinline__ void fp6_batch_store(Fp6Batch& out, uint8_t* packed, 
     const rsrc_t frow = row_buffer(packed + (int64_t)(row4 >> 5) * frags_per_row * 1536, frags_per_row * 1536);
     // a lane that must not store points past the buffer's end: the hardware's range check drops its stores
     const int off = ok ? (col >> 6) * 1536 : 0x7FFF0000;
-    __builtin_amdgcn_raw_buffer_store_b128(u32x4{out.lo[0], d1, d2, out.lo[2]}, frow, off + flane * 16, 0, kWriteThrough);
-    __builtin_amdgcn_raw_buffer_store_b64(u32x2{d4, d5}, frow, off + 1024 + flane * 8, 0, kWriteThrough);
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4{rec[0], rec[1], rec[2], rec[3]}, frow, off + flane * 16, 0, kWriteThrough);
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2{rec[4], rec[5]}, frow, off + 1024 + flane * 8, 0, kWriteThrough);
 }
 
 }  // namespace cq

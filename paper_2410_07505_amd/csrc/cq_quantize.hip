@@ -199,7 +199,7 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
         Fp6Batch f6;                                        // MODE 3: the batch's four rows leave together
         if (MODE == 3) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) f6.lo[k] = f6.hi[k] = 0u;
+            for (int k = 0; k < 16; ++k) f6.h[k >> 2][k & 3] = 0u;
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
@@ -223,7 +223,7 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
             // count, pack and store one row piece; returns the lane's number of non-zero codes in it
             auto emit = [&](const float (&m)[8], const float (&q)[8]) -> uint32_t {
                 const uint32_t nz = COUNT ? count_nonzero8_lane(m) : 0u;
-                if (MODE == 3) fp6_batch_row(f6, m, u);
+                if (MODE == 3) fp6_batch_row(f6, q, u);
                 if (!BUF) {
                     if (MODE == 1) store_piece<8, uint8_t>(pack_codes_i8(m), codes + (int64_t)rr * I + col0 + lane * 8, nvalid);
                     if (MODE == 2)                           // (the channel count is even: whole bytes)
