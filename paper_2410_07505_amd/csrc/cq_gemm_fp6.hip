@@ -548,26 +548,37 @@ gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__
         read(f0, 0);
 
         int slot = 0;                                                    // slot of step kt
-        auto step = [&](int kt, Frags& cur, Frags& nxt) {
-            if (kt + S - 1 < nk) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 2) * N, 0));
-            else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+        auto step = [&](auto full_c, int kt, Frags& cur, Frags& nxt) {   // (see gemm_i8_staged_kernel)
+            constexpr bool FULL = decltype(full_c)::value;
+            __builtin_amdgcn_s_waitcnt(waitcnt_imm(FULL ? (S - 2) * N : 63, 0));
+            if (!FULL) {
+                if (kt + S - 1 < nk) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 2) * N, 15));
+                else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
+            }
             step_barrier();
             const int next_slot = slot + 1 == S ? 0 : slot + 1;
-            if (early && kt + S < nk) request(kt + S, slot);
+            if (early && (FULL || kt + S < nk)) request(kt + S, slot);
             __builtin_amdgcn_sched_barrier(0);
-            if (kt + 1 < nk) read(nxt, next_slot);
+            if (FULL || kt + 1 < nk) read(nxt, next_slot);
 #pragma unroll
             for (int mi = 0; mi < MT; ++mi)
 #pragma unroll
                 for (int ni = 0; ni < NT; ++ni) acc[mi][ni] = mfma6(cur.a[mi], cur.b[ni], acc[mi][ni]);
             __builtin_amdgcn_sched_barrier(0);
-            if (!early && kt + S < nk) request(kt + S, slot);
+            if (!early && (FULL || kt + S < nk)) request(kt + S, slot);
             __builtin_amdgcn_sched_barrier(0);
             slot = next_slot;
         };
-        for (int kt = 0; kt < nk; kt += 2) {
-            step(kt, f0, f1);
-            if (kt + 1 < nk) step(kt + 1, f1, f0);
+        using yes = std::integral_constant<bool, true>;
+        using no = std::integral_constant<bool, false>;
+        int kt = 0;
+        for (; kt + 1 + S < nk; kt += 2) {
+            step(yes{}, kt, f0, f1);
+            step(yes{}, kt + 1, f1, f0);
+        }
+        for (; kt < nk; kt += 2) {
+            step(no{}, kt, f0, f1);
+            if (kt + 1 < nk) step(no{}, kt + 1, f1, f0);
         }
         __syncthreads();                                                 // the ring is free: it holds the partial sums now
         sum_and_store<MT, NT, WM, WN, WK>(acc, reinterpret_cast<v4f*>(lds), wave, lane, row_scale, w_scale, T, O, Y, ldy,

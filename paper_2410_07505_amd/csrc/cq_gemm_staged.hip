@@ -9,6 +9,7 @@
 // 3-slot and a 4-slot ring run alike; 64 and 256 active CUs run alike), so a step costs (TM + TN) x 128 bytes of that;
 // a decode step of a large layer is bound by the weights' way from HBM.
 #include <algorithm>
+#include <type_traits>
 
 #include "cq_gemm_common.h"
 
@@ -158,28 +159,34 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
         Frags f0, f1;
         read(f0, 0);
 
+        // FULL: a step whose requests and reads all exist; the others, at the contraction's end, ask.  The wait for this wave's
+        // LDS reads has to stand on every path by itself: as part of the one or the other wait the compiler sees a way
+        // around it, and puts a wait for *all* reads, the next step's too, in front of this step's matrix instructions.
         int slot = 0;                                         // slot of step kt
-        auto step = [&](int kt, Frags& cur, Frags& nxt, v4i (&r)[N]) {
+        auto step = [&](auto full_c, int kt, Frags& cur, Frags& nxt, v4i (&r)[N]) {
+            constexpr bool FULL = decltype(full_c)::value;
             // this wave's reads of step kt are done and its share of step kt + 1 has landed (steps kt + 2 .. kt + S - 1
             // may still be in flight; near the end, where there are fewer, all of them)
-            if (DMA && kt + S - 1 < nk) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 2) * N, 0));
-            else if (DMA) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
-            else __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
+            __builtin_amdgcn_s_waitcnt(waitcnt_imm(DMA && FULL ? (S - 2) * N : 63, 0));
+            if (DMA && !FULL) {
+                if (kt + S - 1 < nk) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 2) * N, 15));
+                else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
+            }
             step_barrier();
             auto fetch = [&]() {
-                if (kt + S < nk) {
+                if (FULL || kt + S < nk) {
                     if (DMA) {
                         request(kt + S, slot);
                     } else {
                         commit(r, slot);
-                        if (kt + S + 2 < nk) load_step(r, kt + S + 2);
+                        if (FULL || kt + S + 2 < nk) load_step(r, kt + S + 2);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             };
             const int next_slot = slot + 1 == S ? 0 : slot + 1;
             if (early) fetch();
-            if (kt + 1 < nk) read(nxt, next_slot);
+            if (FULL || kt + 1 < nk) read(nxt, next_slot);
 #pragma unroll
             for (int mi = 0; mi < MT; ++mi)
 #pragma unroll
@@ -189,9 +196,17 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
             if (!early) fetch();
             slot = next_slot;
         };
-        for (int kt = 0; kt < nk; kt += 2) {
-            step(kt, f0, f1, r0);
-            if (kt + 1 < nk) step(kt + 1, f1, f0, r1);
+        using yes = std::integral_constant<bool, true>;
+        using no = std::integral_constant<bool, false>;
+        constexpr int kAhead = DMA ? S : S + 2;               // a step asks for the one this many on
+        int kt = 0;
+        for (; kt + 1 + kAhead < nk; kt += 2) {
+            step(yes{}, kt, f0, f1, r0);
+            step(yes{}, kt + 1, f1, f0, r1);
+        }
+        for (; kt < nk; kt += 2) {
+            step(no{}, kt, f0, f1, r0);
+            if (kt + 1 < nk) step(no{}, kt + 1, f1, f0, r1);
         }
         __syncthreads();                                      // the ring is free: it holds the partial sums now
         sum_and_store<MT, NT, WM, WN, WK>(acc, reinterpret_cast<v4i*>(lds), wave, lane, row_scale, w_scale, T, O, Y, ldy,
