@@ -168,57 +168,95 @@ __device__ __forceinline__ void step_barrier() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// The end of a tile: the WK partial sums of every accumulator meet in LDS (parts: [wk][wm][wn][mi][ni][lane]), are
-// scaled and stored.  Weight tile ni of a wave holds the channels NT fr + ni (fr = lane & 15) of the wave's 16 NT.
+// The end of a tile.  The rows of a wave tile are dealt to the WK waves that share it: unit (mi, h) is the two tokens of
+// accumulator registers 2 h, 2 h + 1 of the tiles (mi, 0 .. NT - 1), and wave wk ends up with the units [wk U, wk U + U)
+// (with more waves than units the first ones have one each).  A wave keeps its own units' partial sums in registers and hands
+// those of the others over in LDS.  Weight tile ni of a wave holds the channels NT fr + ni (fr = lane & 15) of the wave's 16 NT;
+// lane l holds channel l & 15 of a weight tile and, in register r, token 4 (l >> 4) + r.
+// What it costs beside the LDS traffic is latency, so the scales are requested at the tile's start (tile_scales).  Against all
+// partial sums through LDS and the scales after that: 512 x 4096 x 4096 15.3 -> 14.3 us, 1024 x 4096 x 4096 22.0 -> 20.0, FP6 512
+// x 4096 x 4096 14.0 -> 13.2, 1024 x 4096 x 4096 19.8 -> 17.0, 32 x 5120 x 20480 16.2 -> 15.5; a 16 x 512 x 1024 FP6 launch 6.0 -> 6.1.
+template <int MT, int WK>
+constexpr int kUnitsPerWave = 2 * MT >= WK ? 2 * MT / WK : 1;
+
+// The scales a lane needs for its wave's units.
+template <int MT, int NT, int WK>
+struct TileScales {
+    float s[NT];                            // steps of its NT channels
+    float a[kUnitsPerWave<MT, WK>][2];      // factors of its tokens
+};
+template <int MT, int NT, int WN, int WK>
+__device__ __forceinline__ void tile_scales(TileScales<MT, NT, WK>& sc, const float* __restrict__ row_scale,
+                                            const float* __restrict__ w_scale, int T, int O, int m0, int n0, int w, int wk, int lane) {
+    constexpr int U = kUnitsPerWave<MT, WK>;
+    const int col = n0 + ((w % WN) * 16 + (lane & 15)) * NT, row = m0 + (w / WN) * 16 * MT + 4 * (lane >> 4);
+#pragma unroll
+    for (int ni = 0; ni < NT; ++ni) sc.s[ni] = w_scale[min(col + ni, O - 1)];
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+        const int u = min(wk * U + i, 2 * MT - 1);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) sc.a[i][r] = row_scale[min(row + 16 * (u >> 1) + 2 * (u & 1) + r, T - 1)];
+    }
+}
+
+// LDS bytes of the partial sums that change hands
+template <int MT, int NT, int WM, int WN, int WK>
+constexpr int kPartsBytes = WM * WN * 2 * MT * (WK - 1) * NT * 64 * 8;
+
 // vec_out: every lane's NT channels exist or not together and their 2 NT bytes of Y are aligned.
 // V: four int32 or four binary32 values (sums of the FP6 products are integers below 2^24, exact in any order).
 // Y leaves with plain stores whatever its size.  Outputs beyond 64 MiB come here only off the ring's layout: 4096 x 4112 x 20480
 // (160 MiB) takes 582 us, and 686 with the absmax of a cold 4096 x 8192 matrix behind each (14.5 on its own), where the ring
 // takes 254 and 264 for 4096 x 4096 x 20480.
 template <int MT, int NT, int WM, int WN, int WK, typename V>
-__device__ __forceinline__ void sum_and_store(const V (&acc)[MT][NT], V* parts, int wave, int lane,
-                                              const float* __restrict__ row_scale, const float* __restrict__ w_scale, int T,
-                                              int O, uint16_t* __restrict__ Y, int64_t ldy, int32_t* __restrict__ acc_debug,
-                                              int m0, int n0, bool vec_out) {
+__device__ __forceinline__ void sum_and_store(const V (&acc)[MT][NT], int8_t* lds, const TileScales<MT, NT, WK>& sc, int w, int wk,
+                                              int lane, int T, int O, uint16_t* __restrict__ Y, int64_t ldy,
+                                              int32_t* __restrict__ acc_debug, int m0, int n0, bool vec_out) {
+    constexpr int U = kUnitsPerWave<MT, WK>, kUnits = 2 * MT;
+    typedef decltype(acc[0][0][0] + acc[0][0][0]) elem;
+    typedef elem pair __attribute__((ext_vector_type(2)));
+    // [w][unit][share of one of the other WK - 1 waves][ni][lane]
+    pair* parts = reinterpret_cast<pair*>(lds) + w * (kUnits * (WK - 1) * NT * 64) + lane;
+    pair own[U][NT];
 #pragma unroll
-    for (int mi = 0; mi < MT; ++mi)
+    for (int k = 0; k < WK; ++k) {                           // (wave-uniform: registers cannot be indexed by wk)
+        if (wk != k) continue;
 #pragma unroll
-        for (int ni = 0; ni < NT; ++ni) parts[((wave * MT + mi) * NT + ni) * 64 + lane] = acc[mi][ni];
-    __syncthreads();
-    // A unit is two tokens x NT channels: accumulator registers 2 h, 2 h + 1 of lane l of the tiles (mi, 0 .. NT - 1) of
-    // wave position w.  Lane l holds channel l & 15 of a weight tile and, in register r, token 4 (l >> 4) + r.
-    constexpr int kUnits = WM * WN * MT * 64 * 2;
-    for (int u = threadIdx.x; u < kUnits; u += 64 * kSplitWaves) {
-        const int l = u & 63, h = (u >> 6) & 1, mi = (u >> 7) % MT, w = (u >> 7) / MT;
-        typedef decltype(acc[0][0][0] + acc[0][0][0]) elem;
-        elem sum[NT][2];
-#pragma unroll
-        for (int ni = 0; ni < NT; ++ni) sum[ni][0] = sum[ni][1] = 0;
-#pragma unroll
-        for (int p = 0; p < WK; ++p)
+        for (int u = 0; u < kUnits; ++u) {
+            const int owner = u / U;
 #pragma unroll
             for (int ni = 0; ni < NT; ++ni) {
-                typedef elem pair __attribute__((ext_vector_type(2)));
-                const pair v = *reinterpret_cast<const pair*>(
-                    reinterpret_cast<const int8_t*>(parts + (((p * WM * WN + w) * MT + mi) * NT + ni) * 64 + l) + 8 * h);
-                sum[ni][0] += v.x;
-                sum[ni][1] += v.y;
+                const V& v = acc[u >> 1][ni];
+                const pair p = {v[2 * (u & 1)], v[2 * (u & 1) + 1]};
+                if (owner == k) own[u % U][ni] = p;
+                else parts[((u * (WK - 1) + (k < owner ? k : k - 1)) * NT + ni) * 64] = p;
             }
-        const int col = n0 + ((w % WN) * 16 + (l & 15)) * NT;
-        const int row = m0 + (w / WN) * 16 * MT + 16 * mi + 4 * (l >> 4) + 2 * h;
-        if (col >= O) continue;
-        float s[NT];
+        }
+    }
+    __syncthreads();
+    if (wk * U >= kUnits) return;                            // more waves than units (scalar)
+    const int col = n0 + ((w % WN) * 16 + (lane & 15)) * NT;
 #pragma unroll
-        for (int ni = 0; ni < NT; ++ni) s[ni] = w_scale[min(col + ni, O - 1)];
+    for (int i = 0; i < U; ++i) {
+        const int u = wk * U + i;
+        const int row = m0 + (w / WN) * 16 * MT + 16 * (u >> 1) + 4 * (lane >> 4) + 2 * (u & 1);
+        pair sum[NT];
+#pragma unroll
+        for (int ni = 0; ni < NT; ++ni) sum[ni] = own[i][ni];
+#pragma unroll
+        for (int p = 0; p < WK - 1; ++p)
+#pragma unroll
+            for (int ni = 0; ni < NT; ++ni) sum[ni] += parts[((u * (WK - 1) + p) * NT + ni) * 64];
+        if (col >= O) continue;
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
             if (row + r >= T) break;
-            const float a = row_scale[row + r];
             float y[NT];
 #pragma unroll
             for (int ni = 0; ni < NT; ++ni) {
-                y[ni] = (float)sum[ni][r] * a;
-                y[ni] = rounded_f32(y[ni] * s[ni]);
+                y[ni] = (float)sum[ni][r] * sc.a[i][r];
+                y[ni] = rounded_f32(y[ni] * sc.s[ni]);
             }
             uint16_t* dst = Y + (int64_t)(row + r) * ldy + col;
             if (NT == 4 && vec_out) {

@@ -5,9 +5,10 @@
 // 256 x 4096 output gives it 32 half tiles for 256 CUs.  Here a block's 8 waves are WM x WN wave tiles of 16 MT tokens x
 // 16 NT channels times WK shares of the contraction; the WK partial sums (int32, so their order cannot matter) meet in
 // LDS at the end.  The tile is chosen so that one round of blocks covers the chip (launch_w8a8_staged).
-// What bounds it: a CU takes in about 28 bytes per clock from its L2, whatever is in flight (128 x 128 tiles with a
-// 3-slot and a 4-slot ring run alike; 64 and 256 active CUs run alike), so a step costs (TM + TN) x 128 bytes of that;
-// a decode step of a large layer is bound by the weights' way from HBM.
+// What bounds it: what a CU takes in.  Its L2 delivers 64 bytes per clock where it hits; with the requests of a layer, whose
+// tiles share rows across the CUs, loads alone reach 41 to 44 (25 TB/s over the chip), so a step costs (TM + TN) x 128 bytes of
+// that; a decode step of a large layer is bound by the weights' way from HBM.  Every tile pays some 3.5 us besides (launch and
+// first requests), partial sums and stores another 1 to 3.
 #include <algorithm>
 #include <type_traits>
 
@@ -126,6 +127,11 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
 #pragma unroll
             for (int ni = 0; ni < NT; ++ni) acc[mi][ni] = v4i{0, 0, 0, 0};
 
+        // The scales first, held until the end.  (Behind the first requests, or a few steps before the end, the waits for
+        // requests become waits for more of them: FP6 32 x 5120 x 20480 15.5 us, 15.8 and 17.3.  The fence keeps the loads here.)
+        TileScales<MT, NT, WK> scales;
+        tile_scales<MT, NT, WN, WK>(scales, row_scale, w_scale, T, O, m0, n0, w, wk, lane);
+        asm volatile("" ::: "memory");
         // prologue: steps 0 .. S - 1 requested (register form: loaded together and stored; steps S and S + 1 on their way
         // into the two register sets)
         v4i r0[N], r1[N];
@@ -139,8 +145,6 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
 #pragma unroll
             for (int s = 1; s < S; ++s)
                 if (s < nk) request(s, s);
-            if (nk >= S) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 1) * N, 15));      // step 0 has landed
-            else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
         } else {
             v4i pre[S][N];
 #pragma unroll
@@ -153,8 +157,10 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
                 if (s < nk) commit(pre[s], s);
             if (S < nk) load_step(r0, S);
             if (S + 1 < nk) load_step(r1, S + 1);
-            __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
         }
+        if (!DMA) __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
+        else if (nk >= S) __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 1) * N, 15));     // step 0 has landed
+        else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
         step_barrier();
         Frags f0, f1;
         read(f0, 0);
@@ -198,9 +204,11 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
         };
         using yes = std::integral_constant<bool, true>;
         using no = std::integral_constant<bool, false>;
+        // (full steps only where there are many: for smaller tiles their code costs more, fetched once, than they save)
+        constexpr bool kFullSteps = TM * TN >= 8192;
         constexpr int kAhead = DMA ? S : S + 2;               // a step asks for the one this many on
         int kt = 0;
-        for (; kt + 1 + kAhead < nk; kt += 2) {
+        for (; kFullSteps && kt + 1 + kAhead < nk; kt += 2) {
             step(yes{}, kt, f0, f1, r0);
             step(yes{}, kt + 1, f1, f0, r1);
         }
@@ -209,8 +217,7 @@ gemm_i8_staged_kernel(const int8_t* __restrict__ qx, const float* __restrict__ r
             if (kt + 1 < nk) step(no{}, kt + 1, f1, f0, r1);
         }
         __syncthreads();                                      // the ring is free: it holds the partial sums now
-        sum_and_store<MT, NT, WM, WN, WK>(acc, reinterpret_cast<v4i*>(lds), wave, lane, row_scale, w_scale, T, O, Y, ldy,
-                                          acc_debug, m0, n0, vec_out);
+        sum_and_store<MT, NT, WM, WN, WK>(acc, lds, scales, w, wk, lane, T, O, Y, ldy, acc_debug, m0, n0, vec_out);
         __syncthreads();
     }
 }
@@ -219,7 +226,7 @@ template <int MT, int NT, int WM, int WN, int WK, int S, bool DMA, bool ONCE = f
 hipError_t launch_staged(const int8_t* qx, const float* row_scale, const int8_t* qw, const float* w_scale, int T, int I,
                          int O, uint16_t* Y, int64_t ldy, int32_t* acc_debug, hipStream_t stream) {
     constexpr int TM = 16 * MT * WM, TN = 16 * NT * WN;
-    constexpr int kRing = S * (TM + TN) * 64 * WK, kParts = kSplitWaves * MT * NT * 64 * 16, kLds = kRing > kParts ? kRing : kParts;
+    constexpr int kRing = S * (TM + TN) * 64 * WK, kParts = kPartsBytes<MT, NT, WM, WN, WK>, kLds = kRing > kParts ? kRing : kParts;
     const int tiles_m = (T + TM - 1) / TM;
     const int64_t total = (int64_t)tiles_m * ((O + TN - 1) / TN);
     if (total >= (int64_t)1 << 31) return hipErrorInvalidValue;

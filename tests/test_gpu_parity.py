@@ -1833,6 +1833,32 @@ def test_w4a4_linear_fp6(cq, T, I, O):
     assert np.array_equal(bits16(host(Y8)), bits16(host(Y)))
 
 
+# Contractions around the point where a tile has its first steps that ask for nothing (five to eight steps), with a partly
+# filled step and without, for the tiles that have such steps: 64 x 128 and 128 x 128.
+@pytest.mark.parametrize("T", [500, 1000])
+@pytest.mark.parametrize("kind,I", [("int8", 1040), ("int8", 1296), ("int8", 1552), ("int8", 1792), ("int8", 2064),     # straight to LDS
+                                    ("int8", 515), ("int8", 643), ("int8", 771), ("int8", 897), ("int8", 1027),        # through registers
+                                    ("fp6", 896), ("fp6", 1024), ("fp6", 1280), ("fp6", 1408), ("fp6", 1664), ("fp6", 2048)])
+def test_small_tile_linears_around_their_first_full_steps(cq, kind, T, I):
+    import torch
+    say("first full steps: %s %dx%d" % (kind, T, I))
+    O, top = 4000, 127 if kind == "int8" else 7
+    g = torch.Generator(device="cuda").manual_seed(T + I)
+    qx = torch.randint(-top, top + 1, (T, I), generator=g, device="cuda", dtype=torch.int8)
+    qw = torch.randint(-top, top + 1, (O, I), generator=g, device="cuda", dtype=torch.int8)
+    a, s = torch.rand(T, generator=g, device="cuda") * 1e-2, torch.rand(O, generator=g, device="cuda") * 1e-3
+    if kind == "int8":
+        run = lambda: cq.crossquant_w8a8_linear(qx, a, qw, s, want_acc=True)
+    else:
+        px, pw = cq.crossquant_pack_fp6(qx), cq.crossquant_pack_fp6_weights(qw)
+        run = lambda: cq.crossquant_w4a4_linear(px, a, pw, s, T, I, O, want_acc=True)
+    Y, acc = run()
+    want = (qx.double() @ qw.double().t().contiguous()).int()           # exact: below 2^53
+    assert torch.equal(acc, want)
+    assert torch.equal(Y.view(torch.int16), ((want.float() * a[:, None]) * s[None, :]).half().view(torch.int16))
+    assert "staged_kernel" in launched(cq, run)[0]
+
+
 # (T, O) for which the launcher takes, on 256 CUs, tiles of 32 x 64, 64 x 64, 64 x 128, 128 x 128 and 256 x 256, ragged on
 # both edges; I: one step shared by all, several with shares past the end, and more steps than LDS slots
 @pytest.mark.parametrize("I", [128, 384, 2688])
