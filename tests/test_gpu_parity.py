@@ -1836,7 +1836,7 @@ def test_w4a4_linear_fp6(cq, T, I, O):
 # Contractions around the point where a tile has its first steps that ask for nothing (five to eight steps), with a partly
 # filled step and without, for the tiles that have such steps: 64 x 128 and 128 x 128.
 @pytest.mark.parametrize("T", [500, 1000])
-@pytest.mark.parametrize("kind,I", [("int8", 1040), ("int8", 1296), ("int8", 1552), ("int8", 1792), ("int8", 2064),     # straight to LDS
+@pytest.mark.parametrize("kind,I", [("int8", 1040), ("int8", 1296), ("int8", 1552), ("int8", 1808), ("int8", 2064),     # straight to LDS
                                     ("int8", 515), ("int8", 643), ("int8", 771), ("int8", 897), ("int8", 1027),        # through registers
                                     ("fp6", 896), ("fp6", 1024), ("fp6", 1280), ("fp6", 1408), ("fp6", 1664), ("fp6", 2048)])
 def test_small_tile_linears_around_their_first_full_steps(cq, kind, T, I):
