@@ -4,7 +4,7 @@
 // Both operands are stored with the contraction axis contiguous (qx [T][I], qw [O][I]), which is
 // the layout the INT8 matrix instructions want: every lane supplies 16 consecutive bytes of one row.
 //
-// Two kernels, same results (integer accumulation is exact, so tiling and order cannot matter):
+// Three kernels, same results (integer accumulation is exact, so tiling and order cannot matter):
 //   - gemm_i8_ring_kernel, here, for layers that fill the chip with large tiles: 16-byte aligned operands, K a
 //     multiple of 128, any T (edge tiles read clamped rows and drop the surplus outputs).  512 threads = 8 waves in a
 //     2 x 4 arrangement, each wave owning 128 x 64 = 8 x 4 MFMA tiles of 16 x 16 (128 accumulator registers); operands go
@@ -12,6 +12,8 @@
 //     several tiles, requesting the next tile's first operands before it scales and stores the current one, and
 //     the results leave straight from the accumulator registers (8 bytes per lane, whole 128-byte lines per
 //     16 lanes); a last round of tiles that is at most half full runs as 256 x 128 half tiles;
+//   - gemm_i8_wide_kernel (cq_gemm_wide.hip): tiles of 256 x 160 to 352 for outputs that these cover in one round of the CUs and
+//     256 x 256 tiles do not, same operands;
 //   - gemm_i8_staged_kernel (cq_gemm_staged.hip): smaller tiles with the contraction split inside a block, for few
 //     tokens or small outputs, and any shape and alignment.
 // The ring kernel:
@@ -430,9 +432,19 @@ hipError_t launch_w8a8_linear(const int8_t* qx, const float* row_scale, const in
     //   whole tiles      60 x 1024 x 49152 17.3 : 15.6, 60 x 2048 x 49152 26.9 : 25.6, 60 x 8192 x 49152 88 : 102, 16 x 512 x 98304
     //                    13.8 : 17.0
     // (a constant line, 240 against the rounds times (TM + TN) of the small tiles, lost up to 40 % on either side of it)
-    const int64_t ring_time = (int64_t)((n_main + n_cu - 1) / n_cu) * ((int64_t)500 * I + 300000) + (n_main < total ? (int64_t)336 * I + 164000 : 0);
+    int64_t ring_time = (int64_t)((n_main + n_cu - 1) / n_cu) * ((int64_t)500 * I + 300000) + (n_main < total ? (int64_t)336 * I + 164000 : 0);
+    // Tiles of another width where one round of them takes less than the rounds here: a round of whole tiles is 100, one of half
+    // tiles 42 behind whole ones and 60 by itself (2048 x 4096 x O: O = 8448, 264 tiles, 68.5 us, of 288 columns 54.0; O = 11776, 368
+    // tiles, 73.5 against 114 for two rounds of 352).  One round is at most 46 MiB of Y, which stays in the caches as there.  Not for
+    // few tokens, which were not measured, nor with the raw accumulators, which that kernel does not store.
+    int wide_units = 0;
+    const int ring_units = 100 * ((n_main + n_cu - 1) / n_cu) + (n_main < total ? (n_main ? 42 : 60) : 0);
+    int wide = ring_ok && T >= BM && !acc_debug && (int64_t)352 * I < (int64_t)1 << 31 ? w8a8_wide_tile(T, O, n_cu, &wide_units) : 0;
+    if (wide && wide_units < ring_units) ring_time = ring_time * wide_units / ring_units;
+    else wide = 0;
     if (!ring_ok || w8a8_staged_time(T, I, O, n_cu) < ring_time)
         return launch_w8a8_staged(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, n_cu, stream);
+    if (wide) return launch_w8a8_wide(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, wide, n_cu, stream);
     // four instances: with or without the raw accumulators, Y streamed to memory or left in the caches
     using kernel_t = void (*)(const int8_t*, const float*, const int8_t*, const float*, int, int, int, uint16_t*,
                               int64_t, int32_t*, int, int, int);

@@ -140,6 +140,12 @@ int64_t w8a8_staged_time(int T, int I, int O, int n_cu);
 hipError_t launch_w8a8_staged(const int8_t* qx, const float* row_scale, const int8_t* qw, const float* w_scale, int T, int I,
                               int O, uint16_t* Y, int64_t ldy, int32_t* acc_debug, int n_cu, hipStream_t stream);
 
+// The form with tiles of 256 x 32 nt, for outputs that these cover in one round of the CUs (16-byte aligned operands, I % 128 ==
+// 0, 352 I < 2^31, O and ldy multiples of 8, ldy < 2^22), and which nt that is.
+int w8a8_wide_tile(int T, int O, int n_cu, int* units);
+hipError_t launch_w8a8_wide(const int8_t* qx, const float* row_scale, const int8_t* qw, const float* w_scale, int T, int I, int O,
+                            uint16_t* Y, int64_t ldy, int nt, int n_cu, hipStream_t stream);
+
 // CrossQuant step inside the GEMM's activation load (X binary16 -> Y, no codes in memory); a, b receive the factors.
 hipError_t launch_quantize_linear(const uint16_t* X, int T, int I, int64_t ldx, const float* t, const float* c,
                                   float alpha, int bits, float* a, float* b, const int8_t* qw, const float* w_scale,

@@ -1392,6 +1392,31 @@ def test_linear_on_either_side_of_the_line_between_its_kernels(cq, T, I, O, kern
     assert len(names) == 1 and "gemm_i8_" + kernel in names[0]
 
 
+# Outputs that tiles of 256 x 32 nt cover in one round of 256 CUs, for each nt, ragged on both edges and not; I: one to five steps
+@pytest.mark.parametrize("I", [128, 256, 384, 512, 640])
+@pytest.mark.parametrize("T,O,nt", [(1000, 8600, 5), (1024, 11008, 6), (2048, 8456, 9), (1900, 10000, 10), (4096, 5120, 10), (2040, 11256, 11)])
+def test_linear_in_one_round_of_tiles_of_another_width(cq, T, O, nt, I):
+    import torch
+    say("linear, tiles of 256 x %d: %dx%dx%d" % (32 * nt, T, I, O))
+    g = torch.Generator(device="cuda").manual_seed(T + I)
+    qx = torch.randint(-127, 128, (T, I), generator=g, device="cuda", dtype=torch.int8)
+    qw = torch.randint(-127, 128, (O, I), generator=g, device="cuda", dtype=torch.int8)
+    qx[1], qw[1] = 127, -127                                 # the largest sums
+    a, s = torch.rand(T, generator=g, device="cuda") * 1e-2, torch.rand(O, generator=g, device="cuda") * 1e-3
+    buf = torch.full((T + 2, O + 8), 7.0, device="cuda", dtype=torch.float16)
+    Y = buf[1:T + 1, :O]
+    run = lambda: cq.crossquant_w8a8_linear(qx, a, qw, s, Y=Y)
+    run()
+    acc = (qx.double() @ qw.double().t().contiguous()).float()          # exact: integers below 2^24
+    want = ((acc * a[:, None]) * s[None, :]).half()
+    assert torch.equal(Y.contiguous().view(torch.int16), want.view(torch.int16))
+    assert bool((buf[0] == 7.0).all() and (buf[-1] == 7.0).all() and (buf[:, O:] == 7.0).all())
+    Y_acc, acc_out = cq.crossquant_w8a8_linear(qx, a, qw, s, want_acc=True)      # another kernel
+    assert torch.equal(acc_out.float(), acc) and torch.equal(Y_acc.view(torch.int16), want.view(torch.int16))
+    names = launched(cq, run)
+    assert len(names) == 1 and "gemm_i8_wide_kernelILi%dE" % nt in names[0]
+
+
 @pytest.mark.parametrize("T,O,kernel", [(256, 256, "staged"), (1100, 4104, "ring")])
 def test_linear_extreme_accumulators(cq, T, O, kernel):
     say("linear extremes, %s kernel" % kernel)
