@@ -8,6 +8,8 @@ such as the benchmark allocates nothing inside its timed region.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -89,10 +91,39 @@ def _check(status: int) -> None:
         raise CrossQuantError(status)
 
 
-# The checks below run on every call: about half of what a small layer costs, the kernels being short.  Each first asks
-# all its questions in the cheapest form (0.3 us; integer device index, shapes compared as tuples) and only when one
-# fails goes through them again to say which.  64 x 256 x 256 as three calls: 32.5 -> 22.1 us on the host (three launches
-# from C: 13.4 us).
+# The calls a layer is made of go through cq_fastcall.cpp where every output is given and every argument is of the plain kind:
+# it asks what the functions below ask and calls the C entry, and answers _NOT_PLAIN, having done nothing, for all else.
+_FASTCALL_PATH = os.path.join(_HERE, "_fastcall" + importlib.machinery.EXTENSION_SUFFIXES[0])
+_FAST_ENTRIES = ("crossquant_absmax", "crossquant_quantize", "crossquant_absmax_quantize", "crossquant_quantize_fp6",
+                 "crossquant_absmax_batched", "crossquant_quantize_batched", "crossquant_kernel_count", "crossquant_kernel_analysis", "crossquant_w8a8_linear", "crossquant_w4a4_linear",
+                 "crossquant_fp6_packed_bytes", "crossquant_fp6_packed_weight_bytes")
+_NOT_PLAIN = 1
+
+
+class _NoFastcall:
+    """Stands in where the native part was built for another Python or torch: nothing is plain."""
+    absmax = quantize = absmax_quantize = quantize_fp6 = absmax_batched = quantize_batched = staticmethod(lambda *args: _NOT_PLAIN)
+    kernel_count = kernel_analysis = w8a8_linear = w4a4_linear = absmax
+
+
+def _load_fastcall():
+    if not os.path.exists(_FASTCALL_PATH):
+        raise ImportError("%s is not built. Run `python -m paper_2410_07505_amd.build`." % _FASTCALL_PATH)
+    try:
+        spec = importlib.util.spec_from_file_location("_fastcall", _FASTCALL_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+    except ImportError:                       # (an undefined symbol, or a library that is not there)
+        return _NoFastcall
+    assert module.NOT_PLAIN == _NOT_PLAIN
+    module.set_entries(*(ctypes.cast(getattr(lib, n), _vp).value for n in _FAST_ENTRIES))
+    return module
+
+
+_fast = _load_fastcall()
+
+# The checks below run on every other call.  Each first asks all its questions in the cheapest form (0.3 us; integer device
+# index, shapes compared as tuples) and only when one fails goes through them again to say which.
 _Tensor = torch.Tensor
 # (private: a torch without GPU support lacks it)
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda index: torch.cuda.current_stream(index).cuda_stream)
@@ -170,6 +201,11 @@ def _code_shape(T: int, I: int, bits: int):
 
 def crossquant_absmax(X: torch.Tensor, *, t: torch.Tensor = None, c: torch.Tensor = None):
     """Row maxima t (float32 [T]) and column maxima c (float32 [I]) of |X| in one pass."""
+    if t is not None and c is not None:
+        status = _fast.absmax(X, t, c)
+        if status != _NOT_PLAIN:
+            _check(status)
+            return t, c
     _matrix(X, torch.float16, "X")
     T, I = X.shape
     if t is None:
@@ -204,6 +240,12 @@ def crossquant_quantize(X: torch.Tensor, t: torch.Tensor, c: torch.Tensor, alpha
 
     Returns (codes, xhat_or_None, row_scale, col_scale, zero_count_or_None); zero_count is a
     one-element int64 tensor (the library's unsigned 64-bit counter)."""
+    if (codes is not None and row_scale is not None and col_scale is not None and (xhat is not None or not want_xhat)
+            and (zero_count is not None or not want_count)):
+        status = _fast.quantize(X, t, c, alpha, bits, codes, xhat, row_scale, col_scale, zero_count)
+        if status != _NOT_PLAIN:
+            _check(status)
+            return codes, xhat, row_scale, col_scale, zero_count
     _matrix(X, torch.float16, "X")
     T, I = X.shape
     dev = X.device
@@ -236,6 +278,12 @@ def crossquant_absmax_quantize(X: torch.Tensor, alpha: float, bits: int, *, sing
     single_read=True calls crossquant_absmax_quantize_single_read instead (one kernel that keeps X on
     chip): same results; raises CrossQuantError with status -6 when the matrix does not fit on chip or
     is not in the vector layout."""
+    if (not single_read and t is not None and c is not None and codes is not None and row_scale is not None
+            and col_scale is not None and (xhat is not None or not want_xhat) and (zero_count is not None or not want_count)):
+        status = _fast.absmax_quantize(X, alpha, bits, t, c, codes, xhat, row_scale, col_scale, zero_count)
+        if status != _NOT_PLAIN:
+            _check(status)
+            return t, c, codes, xhat, row_scale, col_scale, zero_count
     _matrix(X, torch.float16, "X")
     T, I = X.shape
     dev = X.device
@@ -275,6 +323,11 @@ def _req3(X: torch.Tensor):
 
 def crossquant_absmax_batched(X: torch.Tensor, *, t: torch.Tensor = None, c: torch.Tensor = None):
     """Per-token maxima t (float32 [B][S]) and per-sequence column maxima c (float32 [B][I])."""
+    if t is not None and c is not None:
+        status = _fast.absmax_batched(X, t, c)
+        if status != _NOT_PLAIN:
+            _check(status)
+            return t, c
     _req3(X)
     B, S, I = X.shape
     if t is None:
@@ -294,6 +347,11 @@ def crossquant_quantize_batched(X: torch.Tensor, t: torch.Tensor, c: torch.Tenso
 
     Returns (codes [B][S][I or I/2] or None, xhat or None, row_scale [B][S], col_scale [B][I],
     zero_count or None)."""
+    out = _fast.quantize_batched(X, t, c, alpha, bits, want_codes, want_xhat, want_count)
+    if out.__class__ is tuple:
+        return out
+    if out != _NOT_PLAIN:
+        _check(out)
     _req3(X)
     B, S, I = X.shape
     dev = X.device
@@ -352,6 +410,12 @@ def crossquant_quantize_fp6(X: torch.Tensor, t: torch.Tensor, c: torch.Tensor, a
     """INT4 CrossQuant codes written directly as FP6 fragments for crossquant_w4a4_linear.
 
     Returns (packed, xhat_or_None, row_scale, col_scale, zero_count_or_None)."""
+    if (packed is not None and row_scale is not None and col_scale is not None and (xhat is not None or not want_xhat)
+            and (zero_count is not None or not want_count)):
+        status = _fast.quantize_fp6(X, t, c, alpha, packed, xhat, row_scale, col_scale, zero_count)
+        if status != _NOT_PLAIN:
+            _check(status)
+            return packed, xhat, row_scale, col_scale, zero_count
     _matrix(X, torch.float16, "X")
     T, I = X.shape
     dev = X.device
@@ -403,6 +467,11 @@ def crossquant_w4a4_linear(qx_fp6: torch.Tensor, row_scale: torch.Tensor, qw_fp6
                            T: int, I: int, O: int, *, Y: torch.Tensor = None, acc_debug: torch.Tensor = None,
                            want_acc: bool = False):
     """A4W4 linear layer on FP6-packed INT4 codes (exact).  Returns (Y, acc_or_None)."""
+    if Y is not None and acc_debug is None and not want_acc:
+        status = _fast.w4a4_linear(qx_fp6, row_scale, qw_fp6, w_scale, T, I, O, Y)
+        if status != _NOT_PLAIN:
+            _check(status)
+            return Y, None
     for ten, name in ((qx_fp6, "qx_fp6"), (qw_fp6, "qw_fp6")):
         if not ten.is_cuda or ten.dtype != torch.uint8 or not ten.is_contiguous():
             raise ValueError("%s must be a contiguous uint8 GPU tensor from crossquant_pack_fp6 / _weights" % name)
@@ -454,6 +523,11 @@ def crossquant_kernel_count(X: torch.Tensor, t: torch.Tensor, c: torch.Tensor, a
                             zero_count: torch.Tensor = None) -> torch.Tensor:
     """Number of elements whose code is zero (one-element int64 tensor on the GPU).  row_scale / col_scale:
     optional buffers that receive the scale factors; without them the library uses none."""
+    if zero_count is not None:
+        status = _fast.kernel_count(X, t, c, alpha, bits, row_scale, col_scale, zero_count)
+        if status != _NOT_PLAIN:
+            _check(status)
+            return zero_count
     _matrix(X, torch.float16, "X")
     T, I = X.shape
     dev = X.device
@@ -481,6 +555,12 @@ def crossquant_kernel_analysis(X: torch.Tensor, t: torch.Tensor, c: torch.Tensor
     """"Remove Kernel" matrix (float16 [T][I] or None) and a three-element int64 tensor
     {kernel size, #{c_j >= t_i}, #{B~_ij < B_ij}}.  row_scale / col_scale are the call's work vectors
     (allocated here when not given); work_vectors=False passes NULL for both instead."""
+    if (counters is not None and (xrk is not None or not want_xrk)
+            and (row_scale is not None or col_scale is not None or not work_vectors)):
+        status = _fast.kernel_analysis(X, t, c, alpha, bits, xrk, row_scale, col_scale, counters)
+        if status != _NOT_PLAIN:
+            _check(status)
+            return xrk, counters
     _matrix(X, torch.float16, "X")
     T, I = X.shape
     dev = X.device
@@ -589,6 +669,11 @@ def crossquant_weight_quantize_grouped(W: torch.Tensor, fold, group: int, bits: 
 def crossquant_w8a8_linear(qx: torch.Tensor, row_scale: torch.Tensor, qw: torch.Tensor, w_scale: torch.Tensor, *,
                            Y: torch.Tensor = None, acc_debug: torch.Tensor = None, want_acc: bool = False):
     """Y = fl16(acc * row_scale_i * w_scale_k) with acc = qx . qw^T in int32.  Returns (Y, acc_or_None)."""
+    if Y is not None and acc_debug is None and not want_acc:
+        status = _fast.w8a8_linear(qx, row_scale, qw, w_scale, Y)
+        if status != _NOT_PLAIN:
+            _check(status)
+            return Y, None
     _matrix(qx, torch.int8, "qx")
     _matrix(qw, torch.int8, "qw")
     if not qx.is_contiguous() or not qw.is_contiguous():

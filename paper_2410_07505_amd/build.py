@@ -1,15 +1,18 @@
-"""Build libcrossquant.so (hand-written HIP for gfx950) in-tree with hipcc.
+"""Build libcrossquant.so (hand-written HIP for gfx950) in-tree with hipcc, and the binding's native part with g++.
 
     python -m paper_2410_07505_amd.build
 
-Cross-compiles without a GPU.  The shared library is placed next to this file so that it
-travels with the source tree.
+Cross-compiles without a GPU.  The shared libraries are placed next to this file so that they
+travel with the source tree.
 """
 from __future__ import annotations
 
+import importlib.machinery
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -17,6 +20,9 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libcrossquant.so")
 SOURCES = ["cq_api.hip", "cq_slots.hip", "cq_absmax.hip", "cq_quantize.hip", "cq_analysis.hip", "cq_static.hip", "cq_fused.hip", "cq_weight.hip", "cq_gemm.hip", "cq_gemm_staged.hip", "cq_gemm_wide.hip", "cq_gemm_fusedq.hip", "cq_gemm_fp6.hip", "cq_ceilings.hip"]
+
+# The binding's own native part (no device code): built against the Python and torch that run this.
+FASTCALL = os.path.join(HERE, "_fastcall" + importlib.machinery.EXTENSION_SUFFIXES[0])
 
 # -ffp-contract=off: every binary32 operation rounds on its own (results are specified bit for
 # bit).  -packed-fp32-ops off: packed FP32 VALU forms are not used on the test machines.
@@ -44,10 +50,27 @@ def _compile(src: str, extra) -> str:
     return obj
 
 
+def _build_fastcall() -> None:
+    torch = importlib.util.find_spec("torch").submodule_search_locations[0]
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    tmp = FASTCALL + ".tmp%d" % os.getpid()
+    includes = [os.path.join(torch, "include"), os.path.join(torch, "include", "torch", "csrc", "api", "include"),
+                os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           *("-I" + i for i in includes), os.path.join(CSRC, "cq_fastcall.cpp"), "-o", tmp,
+           "-L" + os.path.join(torch, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed for cq_fastcall.cpp:\n" + res.stdout)
+    os.replace(tmp, FASTCALL)
+
+
 def build(extra_flags=(), verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+        fastcall = ex.submit(_build_fastcall)
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), SOURCES))
+        fastcall.result()
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
@@ -56,6 +79,7 @@ def build(extra_flags=(), verbose: bool = False) -> str:
     os.replace(tmp, LIB)
     if verbose:
         print("built", LIB)
+        print("built", FASTCALL)
     return LIB
 
 

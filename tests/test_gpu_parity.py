@@ -2105,3 +2105,89 @@ def test_random_shapes_w4a4_fp6(cq):
         Y, acc = cq.crossquant_w4a4_linear(px, gpu(a), pw, gpu(s), T, I, O, want_acc=True)
         assert np.array_equal(host(acc), acc_ref)
         assert np.array_equal(bits16(host(Y)), bits16(Y_ref))
+
+
+def fast_and_checked_calls(cq, T=40, I=256, O=72):
+    """name -> (call, its keyword arguments that may be spoilt) for the calls that have a native form."""
+    import torch
+    f32, i8, u8, f16, i64 = torch.float32, torch.int8, torch.uint8, torch.float16, torch.int64
+    new = lambda dt, *shape: torch.empty(shape, dtype=dt, device="cuda")
+    X = gpu(outliers(T, I, seed=5))
+    t, c = cq.crossquant_absmax(X)
+    qx, qw = gpu(workloads.int8_codes(T, I, seed=1, lo=-7, hi=7)), gpu(workloads.int8_codes(O, I, seed=2, lo=-7, hi=7))
+    a, s = torch.rand(T, device="cuda"), torch.rand(O, device="cuda")
+    px, pw = cq.crossquant_pack_fp6(qx), cq.crossquant_pack_fp6_weights(qw)
+    outs = lambda: dict(row_scale=new(f32, T), col_scale=new(f32, I))
+    return {
+        "absmax": (cq.crossquant_absmax, dict(X=X, t=new(f32, T), c=new(f32, I))),
+        "quantize": (cq.crossquant_quantize, dict(X=X, t=t, c=c, alpha=0.15, bits=8, codes=new(i8, T, I), xhat=new(f16, T, I),
+                                                  zero_count=new(i64, 1), **outs())),
+        "quantize4": (cq.crossquant_quantize, dict(X=X, t=t, c=c, alpha=0.15, bits=4, want_xhat=False, want_count=False,
+                                                   codes=new(u8, T, I // 2), **outs())),
+        "absmax_quantize": (cq.crossquant_absmax_quantize, dict(X=X, alpha=0.15, bits=8, t=new(f32, T), c=new(f32, I), codes=new(i8, T, I),
+                                                                xhat=new(f16, T, I), zero_count=new(i64, 1), **outs())),
+        "quantize_fp6": (cq.crossquant_quantize_fp6, dict(X=X, t=t, c=c, alpha=0.15, want_count=False, packed=torch.zeros_like(px), **outs())),
+        "absmax_batched": (cq.crossquant_absmax_batched, dict(X=X.view(4, T // 4, I), t=new(f32, 4, T // 4), c=new(f32, 4, I))),
+        "quantize_batched": (cq.crossquant_quantize_batched, dict(X=X.view(4, T // 4, I), t=t.view(4, T // 4), c=torch.rand(4, I, device="cuda"),
+                                                                  alpha=0.15, bits=4, want_xhat=True, want_count=True)),
+        "count_batched": (cq.crossquant_quantize_batched, dict(X=X.view(4, T // 4, I), t=t.view(4, T // 4), c=torch.rand(4, I, device="cuda"),
+                                                               alpha=0.15, bits=8, want_codes=False)),
+        "kernel_count": (cq.crossquant_kernel_count, dict(X=X, t=t, c=c, alpha=1.0, bits=8, zero_count=new(i64, 1))),
+        "kernel_analysis": (cq.crossquant_kernel_analysis, dict(X=X, t=t, c=c, alpha=0.15, bits=8, xrk=new(f16, T, I), counters=new(i64, 3),
+                                                                **outs())),
+        "w8a8_linear": (cq.crossquant_w8a8_linear, dict(qx=qx, row_scale=a, qw=qw, w_scale=s, Y=new(f16, T, O))),
+        "w4a4_linear": (cq.crossquant_w4a4_linear, dict(qx_fp6=px, row_scale=a, qw_fp6=pw, w_scale=s, T=T, I=I, O=O, Y=new(f16, T, O))),
+    }
+
+
+@pytest.mark.parametrize("name", ["absmax", "quantize", "quantize4", "absmax_quantize", "quantize_fp6", "absmax_batched", "quantize_batched",
+                                  "count_batched", "kernel_count", "kernel_analysis", "w8a8_linear", "w4a4_linear"])
+def test_native_and_checked_forms_of_a_call_agree(cq, monkeypatch, name):
+    """The native form takes the plain call, fills the same buffers with the same bits as the checked form and hands them back;
+    with any one argument spoilt, both forms of the binding do the same: the same result or the same error."""
+    import torch
+    from paper_2410_07505_amd import binding
+    say("native form of " + name)
+    native = binding._fast
+    assert native is not binding._NoFastcall
+    run, kw = fast_and_checked_calls(cq)[name]
+
+    def outcome(kw):
+        try:
+            out = run(**kw)
+        except Exception as e:
+            return type(e), str(e)
+        torch.cuda.synchronize()
+        flat = [o for o in (out if isinstance(out, tuple) else (out,)) if o is not None]
+        return [(o.dtype, tuple(o.shape), o.cpu().numpy().tobytes()) for o in flat]
+
+    taken = []
+    class Watched:
+        def __getattr__(self, entry):
+            return lambda *args: (taken.append(getattr(native, entry)(*args)), taken[-1])[1]
+
+    def both(kw):
+        monkeypatch.setattr(binding, "_fast", Watched())
+        got = outcome(kw)
+        monkeypatch.setattr(binding, "_fast", binding._NoFastcall)
+        return got, outcome(kw)
+
+    got, want = both(kw)
+    assert len(taken) == 1 and taken[0] != binding._NOT_PLAIN and got == want and isinstance(got, list)
+    monkeypatch.setattr(binding, "_fast", native)
+    out = run(**kw)
+    outputs = [v for v in kw.values() if isinstance(v, torch.Tensor)]
+    if not run.__name__.endswith("quantize_batched"):       # (which allocates its outputs)
+        assert all(any(o is v for v in outputs) for o in (out if isinstance(out, tuple) else (out,)) if o is not None)
+    spoilt = {"a list": lambda v: [v], "another type": lambda v: v.to(torch.float64), "on the host": lambda v: v.cpu(),
+              "a row less": lambda v: v[:-1], "strided": lambda v: torch.stack([v, v], -1)[..., 0], "another rank": lambda v: v[None],
+              "a subclass": lambda v: torch.nn.Parameter(v, requires_grad=False)}
+    for key, value in kw.items():
+        changes = spoilt if isinstance(value, torch.Tensor) else {"a float": float, "3": lambda v: 3, "a text": str}
+        for how, change in changes.items():
+            got, want = both({**kw, key: change(value)})
+            assert got == want, (key, how, got if isinstance(got, tuple) else "results", want if isinstance(want, tuple) else "results")
+    for alpha in (-0.5, 2.0, float("nan"), 1):
+        if "alpha" in kw:
+            got, want = both({**kw, "alpha": alpha})
+            assert got == want, alpha
