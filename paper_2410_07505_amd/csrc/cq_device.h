@@ -326,6 +326,33 @@ __device__ __forceinline__ float count_nonzero8(const float (&m)[8]) {
     return nz;
 }
 
+// ---- A count summed over the blocks of a launch without anything cleared in front of it.  A word of library-owned memory, zero
+// between launches, holds the running sum in bits 0..40 (at most 2^40 elements) and the number of adds in bits 41..63 (a launch
+// of 512-thread blocks has fewer than 2^23 of them).  The add that brings the second field to `adds` knows the total and
+// clears the word again.
+constexpr int kTicketShift = 41;
+__device__ __forceinline__ bool ticketed_add(unsigned long long* word, unsigned long long& sum, unsigned adds) {
+    const unsigned long long add = (1ull << kTicketShift) | sum;
+    const unsigned long long old = __hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((unsigned)(old >> kTicketShift) != adds - 1u) return false;
+    sum = (old + add) & ((1ull << kTicketShift) - 1ull);
+    __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+// Adds to one word queue up (8.4 ns each: 512 blocks that end together wait 4.3 us), so the blocks of a larger launch add in
+// kCountGroups groups first, each on a 128-byte line of its own, and the groups' last blocks to the launch's word.  Count-only
+// call 4096 x 4096 11.0 -> 7.7 us, 1024 x 8192 7.8 -> 6.2, 512 x 4096 5.5 -> 5.3, INT4 with the dequantized matrix 32 x 128 x 4096 14.7
+// -> 13.4; where the blocks end one by one the second round trip shows (3000 x 3000 9.3 -> 9.8).
+constexpr int kCountGroups = 16, kCountLine = 16;            // words a line has
+constexpr int kCountWords = (1 + kCountGroups) * kCountLine; // of a stream slot
+__device__ __forceinline__ bool launch_sum(unsigned long long* state, unsigned long long& sum) {
+    const bool groups = gridDim.x > 4 * kCountGroups;        // uniform
+    const unsigned g = blockIdx.x % kCountGroups;
+    if (!ticketed_add(groups ? state + (1 + g) * kCountLine : state, sum,
+                      groups ? (gridDim.x - g + kCountGroups - 1) / kCountGroups : gridDim.x)) return false;
+    return !groups || ticketed_add(state, sum, kCountGroups);
+}
+
 // ---- buffer access for the streaming kernels.  A row piece is addressed as a raw buffer: its base and its
 // length in bytes sit in scalar registers, every lane adds its own byte offset, and the hardware's range check
 // does the masking: a load at or past the end returns 0, a store there is dropped.  Only used where a lane's

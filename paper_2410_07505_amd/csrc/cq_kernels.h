@@ -40,16 +40,17 @@ inline bool grid_fits(int64_t blocks, int threads) {
 
 // Rows per block of the quantize / count / analysis kernels = 32 * nb (8 waves x nb batches of 4 rows, nb <= 16).
 // Two of these blocks fit a CU, and a launch is fastest when all its blocks are resident at once, with as little
-// work each as that allows: the smallest nb >= 2 that gives at most 512 blocks (measured over a dozen shapes, for
-// the count-only form too, whose blocks all end with an atomic on one word: within 2 % of the best nb everywhere;
-// "at least 512 blocks, nb a power of two" lost up to 20 % on shapes whose chunk count is not a power of two).
+// work each as that allows: the smallest nb >= 2 that gives at most 512 blocks (measured over a dozen shapes: within 2 % of the
+// best nb everywhere; "at least 512 blocks, nb a power of two" lost up to 20 % on shapes whose chunk count is not a power
+// of two).  The count-only form has registers for three blocks a CU and takes up to 1024: 4096 x 5120 12.4 us with 430 blocks,
+// 10.4 with 640; 4096 x 8192 16.0 with 512, 14.0 with 1024; 4096 x 6144 12.8 : 10.4.
 // One-batch blocks spend most of their time forming scale factors and are left to problems that would otherwise
 // fill less than the chip.  n_chunks = column chunks of 512, times matrices in a batch.
-inline int quantize_batches_per_wave(int64_t n_chunks, int T) {
+inline int quantize_batches_per_wave(int64_t n_chunks, int T, int max_blocks = 512) {
     auto n_blocks_for = [&](int n) { return n_chunks * ((T + 32 * n - 1) / (32 * n)); };
     const int nb_max = T >= 512 ? 16 : (T + 31) / 32;
     int nb = nb_max < 2 ? nb_max : 2;
-    while (nb < nb_max && n_blocks_for(nb) > 512) ++nb;
+    while (nb < nb_max && n_blocks_for(nb) > max_blocks) ++nb;
     if (nb == 2 && n_blocks_for(2) < 200) nb = 1;
     return nb;
 }

@@ -2107,6 +2107,24 @@ def test_random_shapes_w4a4_fp6(cq):
         assert np.array_equal(bits16(host(Y)), bits16(Y_ref))
 
 
+# one column chunk, 32 rows a block: 64 blocks, which add to the launch's word, and 65, 80 and 107, which add in 16 groups of equal
+# and of different sizes first; 3 chunks in one launch of a batch
+@pytest.mark.parametrize("T,I", [(2048, 512), (2049, 512), (2560, 509), (3400, 512), (1100, 1300)])
+def test_counts_of_launches_on_either_side_of_the_grouped_adds(cq, T, I):
+    say("grouped adds: %dx%d" % (T, I))
+    X = outliers(T, I, seed=T + I)
+    Xg = gpu(X)
+    t, c = cq.crossquant_absmax(Xg)
+    for alpha, bits in ((1.0, 8), (0.15, 4 if I % 2 == 0 else 8), (0.15, 8)):       # the accumulators are clear for each next call
+        ref = oracle.quantize(X, host(t), host(c), alpha, bits)
+        assert int(cq.crossquant_kernel_count(Xg, t, c, alpha, bits)) == ref["Z"]
+        assert int(cq.crossquant_quantize(Xg, t, c, alpha, bits, want_xhat=False)[4]) == ref["Z"]
+        assert int(cq.crossquant_quantize(Xg, t, c, alpha, bits)[4]) == ref["Z"]
+        counters = cq.crossquant_kernel_analysis(Xg, t, c, alpha, bits)[1]
+        assert int(counters[0]) == ref["Z"]
+        assert int(counters[1]) == int((host(c)[None, :] >= host(t)[:, None]).sum())
+
+
 def fast_and_checked_calls(cq, T=40, I=256, O=72):
     """name -> (call, its keyword arguments that may be spoilt) for the calls that have a native form."""
     import torch
