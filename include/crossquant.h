@@ -173,25 +173,19 @@ int crossquant_kernel_count(const void *X, int64_t T, int64_t I, int64_t ldx, co
  *   counters[1] = #{(i,j): c_j >= t_i}     case II
  *   counters[2] = #{(i,j): B~_ij < B_ij}   B~ = 0.5 fl32(a_i b_j), B = 0.5 fl32(t_i / q_max) (Eq. 1's step)
  * xrk: out, nullable, binary16 [T][I].  counters: out, three unsigned 64-bit values, 8-byte aligned.
- * row_scale / col_scale: nullable (both or neither): float[T] / float[I] work vectors, overwritten with a and
- *        b (must not overlap t or c: CQ_ERR_ALIAS).  With them the factors are formed once, by a small kernel
- *        of their own; with NULL, NULL every block forms the factors of its own rows and columns, which takes
- *        about as long.
+ * row_scale / col_scale: nullable (both or neither): float[T] / float[I], receive a and b (must not overlap t
+ *        or c: CQ_ERR_ALIAS).
  */
 int crossquant_kernel_analysis(const void *X, int64_t T, int64_t I, int64_t ldx, const float *t,
                                const float *c, float alpha, int bits, void *xrk, float *row_scale,
                                float *col_scale, unsigned long long *counters, void *stream);
 
 /*
- * crossquant_kernel_analysis for callers that cannot allocate device memory and therefore cannot
- * supply the two work vectors: code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc.  Same arguments, outputs and arithmetic, but the scale factors are kept in a
- * static device array of the library (2 x CQ_ANALYSIS_STATIC_MAX floats = 4 MiB, one copy on every
- * device the library runs on, there until the process ends).  The call allocates nothing.
+ * crossquant_kernel_analysis for callers that have no vectors for the scale factors: code under HIP
+ * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, outputs and
+ * arithmetic as that call with row_scale and col_scale NULL: the factors stay on chip.
  * Limits: T <= CQ_ANALYSIS_STATIC_MAX and I <= CQ_ANALYSIS_STATIC_MAX, else CQ_ERR_SHAPE with
- * nothing enqueued.  All calls on one device share that device's array: calls that overlap on one
- * device (different streams, or replays of graphs that contain it) race and must be ordered by the
- * caller; calls on one stream are ordered anyway.
+ * nothing enqueued.
  */
 #define CQ_ANALYSIS_STATIC_MAX (1 << 19)
 int crossquant_kernel_analysis_static(const void *X, int64_t T, int64_t I, int64_t ldx, const float *t,

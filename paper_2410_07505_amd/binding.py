@@ -553,7 +553,7 @@ def crossquant_kernel_analysis(X: torch.Tensor, t: torch.Tensor, c: torch.Tensor
                                col_scale: torch.Tensor = None, counters: torch.Tensor = None,
                                work_vectors: bool = True):
     """"Remove Kernel" matrix (float16 [T][I] or None) and a three-element int64 tensor
-    {kernel size, #{c_j >= t_i}, #{B~_ij < B_ij}}.  row_scale / col_scale are the call's work vectors
+    {kernel size, #{c_j >= t_i}, #{B~_ij < B_ij}}.  row_scale / col_scale receive the scale factors
     (allocated here when not given); work_vectors=False passes NULL for both instead."""
     if (counters is not None and (xrk is not None or not want_xrk)
             and (row_scale is not None or col_scale is not None or not work_vectors)):
@@ -590,7 +590,7 @@ def crossquant_kernel_analysis(X: torch.Tensor, t: torch.Tensor, c: torch.Tensor
 
 def crossquant_kernel_analysis_static(X: torch.Tensor, t: torch.Tensor, c: torch.Tensor, alpha: float, bits: int, *,
                                       xrk: torch.Tensor = None, counters: torch.Tensor):
-    """crossquant_kernel_analysis with the work vectors in the library's static device array: nothing is
+    """crossquant_kernel_analysis without vectors for the scale factors: nothing is
     allocated here or in the library, so every buffer (xrk optional, counters required) comes from the caller."""
     _matrix(X, torch.float16, "X")
     T, I = X.shape

@@ -19,7 +19,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libcrossquant.so")
-SOURCES = ["cq_api.hip", "cq_slots.hip", "cq_absmax.hip", "cq_quantize.hip", "cq_analysis.hip", "cq_static.hip", "cq_fused.hip", "cq_weight.hip", "cq_gemm.hip", "cq_gemm_staged.hip", "cq_gemm_wide.hip", "cq_gemm_fusedq.hip", "cq_gemm_fp6.hip", "cq_ceilings.hip"]
+SOURCES = ["cq_api.hip", "cq_slots.hip", "cq_absmax.hip", "cq_quantize.hip", "cq_analysis.hip", "cq_fused.hip", "cq_weight.hip", "cq_gemm.hip", "cq_gemm_staged.hip", "cq_gemm_wide.hip", "cq_gemm_fusedq.hip", "cq_gemm_fp6.hip", "cq_ceilings.hip"]
 
 # The binding's own native part (no device code): built against the Python and torch that run this.
 FASTCALL = os.path.join(HERE, "_fastcall" + importlib.machinery.EXTENSION_SUFFIXES[0])

@@ -7,7 +7,7 @@
 // the two sides within 2^-20 of each other (the approximation is within 2^-22) takes the correctly
 // rounded division for its row piece instead.  The three counts are kept per lane (one compare and
 // one add of its carry each) and summed once per wave at the end.
-// Bound by the memory now (4096 x 5120: 84 MB in 15.7 us = 5.35 TB/s): with the counts left to the compiler, which
+// Bound by the memory (4096 x 5120: 84 MB in 15.9 us = 5.3 TB/s, factors and counters included): with the counts left to the compiler, which
 // counted the bits of compare masks, one register set and plain bounds handling the kernel took 26 us there, and
 // 32.4 against 21.8 us on 4096 x 8192.
 #include "cq_device.h"
@@ -22,20 +22,25 @@ __global__ void zero_counters_kernel(unsigned long long* __restrict__ counters) 
     if (threadIdx.x < 3) counters[threadIdx.x] = 0ull;
 }
 
+// The three counts' accumulators for each stream slot, zero between launches (launch_sum): nothing has to be cleared before.
+__device__ unsigned long long g_analysis_state[kStateSlots][3][kCountWords];
+
 // Block: 8 waves share 512 columns; each wave takes nb batches of 4 consecutive rows, last batch first, two register sets
 // alternating as in the quantize kernel (rows as raw buffers with BUF, the layout every real activation has; unaligned
 // loads and stores otherwise; rows past the last one are read as copies of it and not worked on).
-// OWN_FACTORS: a_vec / b_vec are not given; the block forms the factors of its rows and columns itself
-// (as the quantize kernel does) and keeps them in LDS.
-template <bool BUF, bool OWN_FACTORS>
+// The block forms the factors of its rows and columns itself, while its first rows are on their way; the blocks of column
+// chunk 0 / row chunk 0 write them to a_out / b_out if given.  (A kernel in front of this one
+// formed them and cleared the counters, 2.5 us of a call: 4096 x 4096 16.2 -> 12.4 us, 4096 x 5120 18.4 -> 16.0, 512 x 4096 8.6 -> 6.9,
+// 64 x 1024 7.2 -> 5.9.  Part of it is the counts, which were 1536 adds to one line of the caller.)
+template <bool BUF>
 __global__ void __launch_bounds__(kWaves * kLanes)
 analysis_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, const float* __restrict__ t_vec,
-                const float* __restrict__ c_vec, const float* __restrict__ a_vec, const float* __restrict__ b_vec,
-                double alpha, int qmax_i, uint16_t* __restrict__ xrk, unsigned long long* __restrict__ counters,
+                const float* __restrict__ c_vec, double alpha, int qmax_i, float* __restrict__ a_out,
+                float* __restrict__ b_out, uint16_t* __restrict__ xrk, unsigned long long* __restrict__ counters, int slot,
                 int n_col_chunks, int nb) {
     __shared__ uint32_t lds_cnt[kWaves][3];
-    __shared__ float lds_a[OWN_FACTORS ? kWaves * kLanes : 1];
-    __shared__ float lds_b[OWN_FACTORS ? kColsPerWave : 1];
+    __shared__ float lds_a[kWaves * kLanes], lds_t[kWaves * kLanes];
+    __shared__ float lds_b[kColsPerWave], lds_c[kColsPerWave];
     const float qmax = (float)qmax_i;
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
@@ -43,8 +48,8 @@ analysis_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, const
     const int row_chunk = blockIdx.x / n_col_chunks;
     const int col0 = col_chunk * kColsPerWave, j0 = col0 + lane * 8;
     const int cols_here = min(kColsPerWave, I - col0);      // a multiple of 8 with BUF
-    const int rows_per_wave = nb * kU;
-    const int row0 = row_chunk * (kWaves * rows_per_wave) + wave * rows_per_wave;
+    const int rows_per_wave = nb * kU, rows_per_block = kWaves * rows_per_wave;
+    const int block_row0 = row_chunk * rows_per_block, row0 = block_row0 + wave * rows_per_wave;
 
     auto load_batch = [&](uint4 (&dst)[kU], int bi) {
         if (bi >= nb) return;                                // scalar condition
@@ -55,46 +60,59 @@ analysis_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, const
             dst[u] = BUF ? buffer_load16(row_buffer(row + col0, cols_here * 2), lane * 16) : load8<false>(row, j0, I);
         }
     };
+    // the maxima that become factors before the rows, as in the quantize kernel: 2 kU requests follow the two
+    const int k = (int)threadIdx.x;
+    float c_in, t_in;
+    if (!BUF) {
+        c_in = c_vec[min(col0 + k, I - 1)];
+        t_in = t_vec[min(block_row0 + k, T - 1)];
+    } else {
+        const float* cp = c_vec + min(col0 + k, I - 1);
+        const float* tp = t_vec + min(block_row0 + k, T - 1);
+        asm volatile("global_load_dword %0, %2, off\n\tglobal_load_dword %1, %3, off"
+                     : "=&v"(c_in), "=&v"(t_in)
+                     : "v"(cp), "v"(tp)
+                     : "memory");
+    }
     uint4 va[kU], vb[kU];
     load_batch(va, 0);
-    load_batch(vb, 1);
-
-    if (OWN_FACTORS) {
-        block_scale_factors(t_vec, c_vec, alpha, qmax_i, T, I, col0, row_chunk * (kWaves * rows_per_wave),
-                            kWaves * rows_per_wave, lds_a, lds_b, nullptr, nullptr);
-        __syncthreads();
-    }
+    if (nb >= 2) load_batch(vb, 1);
+    else if (BUF) load_batch(vb, 0);                        // a wave with one batch requests it twice: always 2 kU requests
+    static_assert(kU == 4, "the wait below counts the row requests of two batches");
+    if (BUF) asm volatile("s_waitcnt vmcnt(8)" : "+v"(c_in), "+v"(t_in)::"memory");
 
     // Columns past the end: x reads as 0 there and their step is infinite, so the code is 0 (not counted as non-zero) and
     // the step (NaN for a_i = 0) is never below the per-token step; c = -1 is never >= t_i.
+    {
+        const int j = col0 + k, r = block_row0 + k;
+        float bj = __builtin_inff();
+        if (j < I) {
+            bj = col_factor(c_in, alpha);
+            if (row_chunk == 0 && b_out) b_out[j] = bj;
+        }
+        lds_b[k] = bj;
+        lds_c[k] = j < I ? c_in : -1.0f;
+        float ar = 0.0f;
+        if (k < rows_per_block && r < T) {
+            ar = row_factor(t_in, alpha, qmax_i);
+            if (col_chunk == 0 && a_out) a_out[r] = ar;
+        }
+        lds_a[k] = ar;
+        lds_t[k] = r < T ? t_in : 0.0f;
+    }
+    __syncthreads();
     float b[8], rb[8], c[8];
     bool odd = false;
-    if (BUF) {                                              // all eight exist or none: two loads each, none past the end
-        const int j = min(j0, I - 8);
-        __builtin_memcpy(c, c_vec + j, 32);
-        if (OWN_FACTORS) __builtin_memcpy(b, lds_b + lane * 8, 32);
-        else __builtin_memcpy(b, b_vec + j, 32);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int j = min(j0 + e, I - 1);
-            c[e] = c_vec[j];
-            b[e] = OWN_FACTORS ? lds_b[lane * 8 + e] : b_vec[j];
-        }
-    }
+    __builtin_memcpy(c, lds_c + lane * 8, 32);
+    __builtin_memcpy(b, lds_b + lane * 8, 32);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        if (j0 + e >= I) {
-            b[e] = __builtin_inff();
-            c[e] = -1.0f;
-        }
         rb[e] = safe_rcp(b[e]);
         odd |= tiny_factor(b[e]);
     }
     // per row: a_i, t_i and the per-token step fl32(t_i / q_max), one row per lane
-    const bool has_row = lane < rows_per_wave && row0 + lane < T;
-    const float a_lane = has_row ? (OWN_FACTORS ? lds_a[wave * rows_per_wave + lane] : a_vec[row0 + lane]) : 0.0f;
-    const float t_lane = has_row ? t_vec[row0 + lane] : 0.0f;
+    const int row_of_lane = wave * rows_per_wave + (lane < rows_per_wave ? lane : 0);
+    const float a_lane = lds_a[row_of_lane], t_lane = lds_t[row_of_lane];
     const float pt_lane = (float)((double)t_lane / (double)qmax);
 
     uint32_t nz_lane = 0, ge_lane = 0, sm_lane = 0;         // this lane's counts: codes != 0, c_j >= t_i, B~ < B
@@ -187,18 +205,21 @@ analysis_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, const
         lds_cnt[wave][2] = sm_lane;
     }
     __syncthreads();
-    if (threadIdx.x < 3) {
-        uint32_t s = 0;
+    if (threadIdx.x < 3) {                                  // a thread per count
+        unsigned long long s = 0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) s += lds_cnt[w][threadIdx.x];
-        if (s) atomicAdd(&counters[threadIdx.x], (unsigned long long)s);
+        if (slot < 0) {                                     // no state: the caller's counters, cleared before
+            if (s) atomicAdd(&counters[threadIdx.x], s);
+        } else if (launch_sum(g_analysis_state[slot][threadIdx.x], s)) {
+            counters[threadIdx.x] = s;                      // every other block has added
+        }
     }
 }
 
 }  // namespace
 
-// a, b null: the kernel forms the factors itself (counters cleared by a kernel of their own first);
-// otherwise a, b are work vectors that a scale-finalize kernel fills first (it also clears the counters).
+// a, b (both or neither): receive the scale factors.
 hipError_t launch_kernel_analysis(const uint16_t* X, int T, int I, int64_t ldx, const float* t, const float* c,
                                   float* a, float* b, float alpha, int qmax, uint16_t* xrk,
                                   unsigned long long* counters, hipStream_t stream) {
@@ -210,16 +231,10 @@ hipError_t launch_kernel_analysis(const uint16_t* X, int T, int I, int64_t ldx, 
     const bool buf = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && (ldx % 8 == 0) && (I % 8 == 0) &&
                      (reinterpret_cast<uintptr_t>(xrk) % 16 == 0);
     const double al = (double)alpha;
-    if (a && b) {
-        const hipError_t e = launch_scale_finalize(t, c, T, I, alpha, qmax, a, b, counters, 3, stream);
-        if (e != hipSuccess) return e;
-        const auto kernel = buf ? &analysis_kernel<true, false> : &analysis_kernel<false, false>;
-        kernel<<<grid, block, 0, stream>>>(X, T, I, ldx, t, c, a, b, al, qmax, xrk, counters, ncc, nb);
-    } else {
-        zero_counters_kernel<<<dim3(1), dim3(64), 0, stream>>>(counters);
-        const auto kernel = buf ? &analysis_kernel<true, true> : &analysis_kernel<false, true>;
-        kernel<<<grid, block, 0, stream>>>(X, T, I, ldx, t, c, nullptr, nullptr, al, qmax, xrk, counters, ncc, nb);
-    }
+    const int slot = stream_slot(stream);
+    if (slot < 0) zero_counters_kernel<<<dim3(1), dim3(64), 0, stream>>>(counters);
+    const auto kernel = buf ? &analysis_kernel<true> : &analysis_kernel<false>;
+    kernel<<<grid, block, 0, stream>>>(X, T, I, ldx, t, c, al, qmax, a, b, xrk, counters, slot, ncc, nb);
     return hipGetLastError();
 }
 

@@ -1,11 +1,10 @@
 // C-ABI entry points: argument validation on the host, then kernel launches on the caller's
 // stream.  No allocation and no host synchronisation.  The library does hold a little process-wide
 // state, all of it behind these calls: the table that gives every stream handle a slot of device-side
-// accumulators (cq_slots.hip: the quantize kernel's zero-count words, the counters of the absmax launch
-// that clears for itself, with the values they reach kept on the host, the barrier words of the
-// single-read kernel and its poll limit), the device addresses of those and of the static work array of
-// crossquant_kernel_analysis_static, and one flag per kernel and device saying that the kernel has been
-// allowed its dynamic LDS size.
+// accumulators (cq_slots.hip: the quantize and analysis kernels' count words, the counters of the absmax
+// launch that clears for itself, with the values they reach kept on the host, the barrier words of the
+// single-read kernel and its poll limit), the device addresses of those, and one flag per kernel and device
+// saying that the kernel has been allowed its dynamic LDS size.
 #include "../../include/crossquant.h"
 #include "../../include/crossquant_bench.h"
 
@@ -168,7 +167,7 @@ int crossquant_kernel_analysis(const void* X, int64_t T, int64_t I, int64_t ldx,
     if (!aligned(t, 4) || !aligned(c, 4) || !aligned(row_scale, 4) || !aligned(col_scale, 4) ||
         !aligned(xrk, 2) || !aligned(counters, 8))
         return CQ_ERR_ALIGN;
-    // the factors are written by one kernel while the next one still reads t and c
+    // some blocks write the factors while others still read t and c
     if (row_scale && (overlap(t, T, row_scale, T) || overlap(c, I, col_scale, I))) return CQ_ERR_ALIAS;
     const int qmax = (1 << (bits - 1)) - 1;
     return from_hip(cq::launch_kernel_analysis(static_cast<const uint16_t*>(X), (int)T, (int)I, ldx, t, c,
@@ -185,9 +184,9 @@ int crossquant_kernel_analysis_static(const void* X, int64_t T, int64_t I, int64
     if (!(alpha >= 0.0f && alpha <= 1.0f)) return CQ_ERR_ALPHA;
     if (!aligned(t, 4) || !aligned(c, 4) || !aligned(xrk, 2) || !aligned(counters, 8)) return CQ_ERR_ALIGN;
     const int qmax = (1 << (bits - 1)) - 1;
-    return from_hip(cq::launch_kernel_analysis_static(static_cast<const uint16_t*>(X), (int)T, (int)I, ldx, t, c, alpha,
-                                                      qmax, static_cast<uint16_t*>(xrk), counters,
-                                                      static_cast<hipStream_t>(stream)));
+    return from_hip(cq::launch_kernel_analysis(static_cast<const uint16_t*>(X), (int)T, (int)I, ldx, t, c, nullptr, nullptr,
+                                               alpha, qmax, static_cast<uint16_t*>(xrk), counters,
+                                               static_cast<hipStream_t>(stream)));
 }
 
 int crossquant_unpack_int4(const void* packed, int64_t T, int64_t I, int8_t* codes, void* stream) {

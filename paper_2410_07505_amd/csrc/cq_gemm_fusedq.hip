@@ -180,7 +180,7 @@ hipError_t launch_quantize_linear(const uint16_t* X, int T, int I, int64_t ldx, 
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_xq_kernel), kLdsBytes, lds_allowed);
     if (e != hipSuccess) return e;
     const int qmax = (1 << (bits - 1)) - 1;
-    e = launch_scale_finalize(t, c, T, I, alpha, qmax, a, b, nullptr, 0, stream);
+    e = launch_scale_finalize(t, c, T, I, alpha, qmax, a, b, stream);
     if (e != hipSuccess) return e;
     gemm_xq_kernel<<<dim3((unsigned)(per_xcd * kXcds)), dim3(kThreads), kLdsBytes, stream>>>(
         X, ldx, a, b, (float)qmax, qw, w_scale, T, I, O, Y, ldy, acc_debug, tiles_m, tiles_n);

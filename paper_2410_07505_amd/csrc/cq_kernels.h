@@ -83,24 +83,15 @@ inline hipError_t allow_dynamic_lds(const void* kernel, int bytes, std::atomic<u
 hipError_t launch_absmax(const uint16_t* X, int B, int T, int I, int64_t ldx, int64_t matrix_stride, float* t,
                          float* c, hipStream_t stream);
 
-// a_i = t_i^alpha / qmax, b_j = c_j^(1-alpha) (binary64 pow, one rounding); counters[0..n) <- 0.
+// a_i = t_i^alpha / qmax, b_j = c_j^(1-alpha) (binary64 pow, one rounding).
 hipError_t launch_scale_finalize(const float* t, const float* c, int T, int I, float alpha, int qmax,
-                                 float* a, float* b, unsigned long long* counters, int n_counters,
-                                 hipStream_t stream);
+                                 float* a, float* b, hipStream_t stream);
 
 // "Remove Kernel" matrix and the Table 1 indicators; counters = {Z, #{c_j >= t_i}, #{B~ < B}}.
-// a, b: work vectors that receive the scale factors, or both null (the kernel then forms the factors itself).
-// Clears the counters on the stream first.
+// a, b: receive the scale factors, or both null.
 hipError_t launch_kernel_analysis(const uint16_t* X, int T, int I, int64_t ldx, const float* t,
                                   const float* c, float* a, float* b, float alpha, int qmax,
                                   uint16_t* xrk, unsigned long long* counters, hipStream_t stream);
-
-
-// The same with the work vectors in the library's static device array (T, I <= CQ_ANALYSIS_STATIC_MAX, else
-// hipErrorInvalidValue with nothing enqueued).  Calls that overlap on one device race on that array.
-hipError_t launch_kernel_analysis_static(const uint16_t* X, int T, int I, int64_t ldx, const float* t, const float* c,
-                                         float alpha, int qmax, uint16_t* xrk, unsigned long long* counters,
-                                         hipStream_t stream);
 
 // Scale factors (as launch_scale_finalize: a, b are outputs), then fused quantize / dequantize / zero
 // count, in one kernel.  codes or xhat may be null (count only = both null).

@@ -22,12 +22,9 @@ namespace cq {
 namespace {
 
 __global__ void scale_finalize_kernel(const float* __restrict__ t, const float* __restrict__ c, int T,
-                                      int I, float alpha, int qmax, float* __restrict__ a,
-                                      float* __restrict__ b, unsigned long long* __restrict__ counters,
-                                      int n_counters) {
+                                      int I, float alpha, int qmax, float* __restrict__ a, float* __restrict__ b) {
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     const double al = (double)alpha;
-    if (idx < n_counters && counters) counters[idx] = 0ull;
     if (idx < T) a[idx] = row_factor(t[idx], al, qmax);
     else if (idx - T < I) b[idx - T] = col_factor(c[idx - T], al);
 }
@@ -395,11 +392,9 @@ hipError_t launch_unpack_int4(const uint8_t* packed, int64_t n_bytes, int8_t* co
 }
 
 hipError_t launch_scale_finalize(const float* t, const float* c, int T, int I, float alpha, int qmax,
-                                 float* a, float* b, unsigned long long* counters, int n_counters,
-                                 hipStream_t stream) {
+                                 float* a, float* b, hipStream_t stream) {
     const int n = T + I;
-    scale_finalize_kernel<<<dim3((n + 255) / 256), dim3(256), 0, stream>>>(t, c, T, I, alpha, qmax, a, b,
-                                                                           counters, n_counters);
+    scale_finalize_kernel<<<dim3((n + 255) / 256), dim3(256), 0, stream>>>(t, c, T, I, alpha, qmax, a, b);
     return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 // Slots of library-owned device state, one per stream.
 //
-// The quantize kernel combines its per-block zero counts in a word of static device memory that
-// is zero between launches and is cleared again by the last block to finish, so that no clearing
+// The quantize and analysis kernels combine their per-block counts in words of static device memory that
+// are zero between launches and are cleared again by the last block to finish, so that no clearing
 // kernel has to run before it.  Calls on one stream are ordered and can
 // share a piece; calls on different streams may run at the same time and must not.  Each stream
 // handle seen is therefore given a slot of its own, for the life of the process.
