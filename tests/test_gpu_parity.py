@@ -2125,6 +2125,28 @@ def test_counts_of_launches_on_either_side_of_the_grouped_adds(cq, T, I):
         assert int(counters[1]) == int((host(c)[None, :] >= host(t)[:, None]).sum())
 
 
+@pytest.mark.parametrize("T", [1, 3, 4, 5, 8, 9, 31, 33, 64, 65])
+@pytest.mark.parametrize("I,ldx", [(8, 8), (504, 512), (520, 520), (4096, 4104), (4104, 4104), (8192, 8192), (8200, 8200)])
+def test_absmax_of_few_tokens(cq, T, I, ldx):
+    """Up to 64 rows of at most 8192 columns have a kernel that stores every maximum from one place (and needs no state);
+    on either side of both limits, padded rows of large values, stale outputs, and which kernel it is."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(T * 10000 + I)
+    buf = torch.full((T, ldx), 60000.0, dtype=torch.float16, device="cuda")
+    X = buf[:, :I]
+    X.copy_(torch.randn((T, I), generator=g, device="cuda").half() * 3)
+    X[T // 2, I - 1], X[T - 1, I // 2] = -65504.0, -0.0
+    t, c = torch.full((T,), 7e4, device="cuda"), torch.full((I,), 7e4, device="cuda")
+    run = lambda: cq.crossquant_absmax(X, t=t, c=c)
+    run()
+    assert torch.equal(t, X.abs().amax(1).float()) and torch.equal(c, X.abs().amax(0).float())
+    X.zero_()
+    run()
+    assert not t.any() and not c.any()
+    names = launched(cq, run)
+    assert (len(names) == 1 and "absmax_direct" in names[0]) == (T <= 64 and I <= 8192)
+
+
 def fast_and_checked_calls(cq, T=40, I=256, O=72):
     """name -> (call, its keyword arguments that may be spoilt) for the calls that have a native form."""
     import torch
