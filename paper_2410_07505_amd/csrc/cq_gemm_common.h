@@ -159,6 +159,12 @@ __device__ __forceinline__ void request_1k(const void* src, const int8_t* dst) {
     else asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc0" : : "v"(src), "s"(lds_off) : "m0");
 }
 
+// 4 bytes per lane from src to LDS at dst + 4 lane
+__device__ __forceinline__ void request_words(const float* src, const int8_t* dst) {
+    const uint32_t lds_off = (uint32_t)(uintptr_t)((lptr_t)dst);
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(src), "s"(lds_off) : "m0");
+}
+
 // The step barrier of those kernels: bare, since __syncthreads would wait for all requests in flight.  The barrier
 // builtin orders no memory for the compiler, which sees neither the requests' writes to LDS nor a reason to keep a
 // step's LDS reads behind the barrier: the empty asm says that memory may have changed (it adds no instruction).

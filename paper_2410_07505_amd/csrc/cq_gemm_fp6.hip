@@ -36,6 +36,7 @@
 // so this kernel is bound by operand movement rather than by the matrix pipe.
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "cq_gemm_common.h"
 
@@ -620,6 +621,298 @@ hipError_t launch_f6_staged(const uint8_t* qx6, const float* row_scale, const ui
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------------------------------------------
+// Tiles of 256 tokens x 32 NT channels (320 or 384), for outputs that 256 x 256 tiles do not divide over the CUs (the rule
+// and what both take stand at w4a4_wide_tile): the structure of gemm_i8_wide_kernel (cq_gemm_wide.hip) on FP6 fragments.
+//   8 waves in 4 x 2, wave tiles of 64 x 16 NT; a step is 128 elements, 4 + NT fragments for 4 NT matrix instructions (LDS reads
+//   and writes of a step keep the LDS busy for 1780 / 2020 cycles, the matrix instructions the matrix cores for 1280 / 1540).
+//   NT is even: a block's 32 NT channels are NT / 2 whole groups of 64.  Wave wn has NT / 4 of them to itself; of the one in the
+//   middle that NT = 10 leaves it takes the weight tiles 2 wn and 2 wn + 1.
+//   LDS: two buffers of activations, three slots of weights (141 / 160 KB).  The barrier near the end of step kt stands behind the last reads
+//   of tile kt; what tile kt occupied is then requested for the activations of kt + 2 and the weights of kt + 3, by the waves
+//   0 to 3 at once, by 4 to 7 at the end of the step.  The weights are what no cache holds: with two slots of them 4096 x
+//   4096 x 5120 takes 52.6 us instead of 49.2 where nothing is left in the caches, 4096 x 8192 x 5120 90.7 instead of 85.2.
+// STREAM: Y passes the caches (see y_stays_cached).
+// ---------------------------------------------------------------------------------------------------------------
+typedef int v6i __attribute__((ext_vector_type(6)));
+
+// acc += a x b with the result in the same registers (see cq_gemm_wide.hip)
+__device__ __forceinline__ void mfma6_in_place(v4f& acc, const v6i& a, const v6i& b) {
+    asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0 cbsz:2 blgp:2" : "+v"(acc) : "v"(a), "v"(b));
+}
+
+// 16 bytes per lane from base + offset (base: scalar) to LDS at dst + 16 lane
+__device__ __forceinline__ void request_at(const uint8_t* base, uint32_t offset, const int8_t* dst) {
+    const uint32_t lds_off = (uint32_t)(uintptr_t)((lptr_t)dst);
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 sc0" : : "v"(offset), "s"(base), "s"(lds_off) : "m0");
+}
+
+template <int NT, bool STREAM>
+__global__ void __launch_bounds__(512)
+gemm_f6_wide_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ row_scale, const uint8_t* __restrict__ qw6,
+                    const float* __restrict__ w_scale, int T, int I, int O, uint16_t* __restrict__ Y, int64_t ldy, int tiles_m,
+                    int tiles_n) {
+    static_assert(NT % 2 == 0, "whole groups of 64 channels per block");
+    constexpr int F = NT / 4, P = NT % 4 / 2;                // groups of 64 channels a wave has to itself, and shares
+    constexpr int WTN = 16 * NT, BNW = 2 * WTN, kPair = 2 * kFragBytes;
+    constexpr int kSets = NT < 12 ? 4 : 3;                   // weight tiles in registers: read kSets - 1 ahead (12: no room for more)
+        constexpr int kTileA = 8 * kPair, kTileB = NT * kPair, kReq = (8 + NT) * 3;  // LDS bytes; 1 KiB requests
+    constexpr int N = (kReq + 7) / 8;                        // ... of a wave at most: ids wave, wave + 8, ...
+    extern __shared__ __align__(16) int8_t lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int nk = I / 128;
+    const bool early = wave < 4;
+    const bool all = wave < kReq - 8 * (N - 1);              // this wave has N requests, the others N - 1 (scalar)
+    const int64_t row_bytes = (int64_t)(I / 64) * kFragBytes;
+
+    const int total = tiles_m * tiles_n, per_xcd = (total + kXcds - 1) / kXcds;
+    for (int i = blockIdx.x / kXcds; i < per_xcd; i += gridDim.x / kXcds) {
+        const int L = (blockIdx.x % kXcds) * per_xcd + i;
+        if (L >= total) break;                               // block-uniform
+        int tile_m, tile_n;
+        tile_of_index(L, tiles_m, tiles_n, tile_m, tile_n);
+        const int m0 = tile_m * BM, n0 = tile_n * BNW;
+        int tl = lane;                                       // (worked out for every tile, not kept and spilled)
+        asm volatile("" : "+v"(tl));
+
+        // request id: KiB id % 3 of the pair of fragments of row block id / 3; row blocks past an operand's end are replaced by its last
+        const int a_last = (T + 31) / 32 - 1, b_last = 2 * ((O + 63) / 64) - 1;
+        const uint8_t* src[N];                               // (scalar)
+        uint32_t off[3];                                     // lane's bytes of ids wave, wave + 8, wave + 16, and every 24
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            const int id = wave + 8 * n, rb = id / 3;
+            src[n] = rb < 8 ? qx6 + min(m0 / 32 + rb, a_last) * row_bytes : qw6 + min(n0 / 32 + rb - 8, b_last) * row_bytes;
+            if (n < 3) {
+                const int pair_offset = (id - 3 * rb) * 1024 + tl * 16, frag = pair_offset >= kFragBytes ? 1 : 0;
+                off[n] = frag * kFragBytes + lds_place(pair_offset - frag * kFragBytes);
+            }
+        }
+        auto request_a = [&](int kt, int buf) {              // ids 0 to 23
+            const int8_t* dst = lds + buf * kTileA + wave * 1024;
+#pragma unroll
+            for (int n = 0; n < 3; ++n) request_at(src[n] + (int64_t)kt * kPair, off[n], dst + n * 8192);
+        };
+        auto request_b = [&](int kt, int slot) {             // slot: its byte offset from the first one
+            const int8_t* dst = lds + kTileA + slot + wave * 1024;         // (n = 3: 2 kTileA)
+#pragma unroll
+            for (int n = 3; n < N; ++n)
+                if (n < N - 1 || all) request_at(src[n] + (int64_t)kt * kPair, off[n % 3], dst + n * 8192);
+        };
+
+        v4f acc[4][NT];
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NT; ++ni) {
+                acc[mi][ni] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+                asm volatile("" : "+v"(acc[mi][ni]));        // here, far ahead of the first matrix instruction
+            }
+
+        // the epilogue's scales: 256 row factors and, behind them, the steps of 64 ceil(NT / 2) channels
+        int8_t* const scales = lds + 2 * kTileA + 3 * kTileB;
+        if (wave < 4) request_words(row_scale + min(m0 + wave * 64 + tl, T - 1), scales + wave * 256);
+        if (wave < NT / 2) request_words(w_scale + min(n0 + wave * 64 + tl, O - 1), scales + (4 + wave) * 256);
+        request_a(0, 0);
+        request_b(0, 0);
+        if (nk > 1) {
+            request_b(1, kTileB);
+            request_a(1, 1);
+        }
+        if (nk > 2) {
+            request_b(2, 2 * kTileB);
+            if (all) __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * N - 3, 15));          // tile 0 has landed
+            else __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * N - 5, 15));
+        } else {
+            __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
+        }
+        step_barrier();
+
+        // LDS addresses of a lane's fragment pieces: 16 bytes and 8 bytes, the latter for the two halves p of a row block
+        // (frag_lane; the first half's 16 bytes are 256 further on in the second).  Through an empty asm, as in the INT8 kernel.
+        struct At {
+            uint32_t lo, hi[2];
+        };
+        At a_at, f_at, p_at;                                 // activations, a wave's own groups, the shared group
+        {
+            const int r = tl & 15, c = tl >> 4, slot = r + 32 * (c & 1);
+            const uint32_t base = (uint32_t)(uintptr_t)((lptr_t)lds) + (c >> 1) * kFragBytes;
+            auto at = [&](At& x, uint32_t o) {
+                x = At{base + o + slot * 16, {base + o + lds_place(kFragLo + slot * 8), base + o + lds_place(kFragLo + (16 + slot) * 8)}};
+                asm volatile("" : "+v"(x.lo), "+v"(x.hi[0]), "+v"(x.hi[1]));
+            };
+            at(a_at, wm * 2 * kPair);
+            at(f_at, 2 * kTileA + 2 * wn * (F + P) * kPair);
+            at(p_at, 2 * kTileA + (2 * F + wn) * kPair);
+        }
+        typedef int v2i __attribute__((ext_vector_type(2)));
+        typedef __attribute__((address_space(3))) const v4i* lo_ptr;
+        typedef __attribute__((address_space(3))) const v2i* hi_ptr;
+        auto read = [&](v6i& f, const At& at, int tile, int buf_bytes) {      // 16 rows: half tile & 1 of row block tile >> 1
+            const v4i lo = ((lo_ptr)at.lo)[(buf_bytes + (tile >> 1) * kPair + (tile & 1) * 256) / 16];
+            const v2i hi = ((hi_ptr)at.hi[tile & 1])[(buf_bytes + (tile >> 1) * kPair) / 8];
+            f = v6i{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y};
+        };
+        v6i af[4], bf[kSets];
+        auto read_a = [&](int buf, int mi) { read(af[mi], a_at, mi, buf * kTileA); };
+        auto read_b = [&](int set, int s) {                  // of the slot that f_at and p_at stand at
+            if (s < 4 * F) read(bf[set], f_at, s, 0);
+            else read(bf[set], p_at, s - 4 * F, 0);
+        };
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi) read_a(0, mi);
+#pragma unroll
+        for (int s = 0; s < kSets - 1; ++s) read_b(s, s);
+
+        int slot = 0;                                        // of the weights of step kt
+        // Step kt, its activations in buffer PAR.  FULL: tiles up to kt + 3 exist.  The last two weight tiles are multiplied activation tile by
+        // activation tile, so that the next step's activations replace this one's as they are done with.
+        auto k_step = [&](int kt, auto par_c, auto full_c) {
+            constexpr int PAR = decltype(par_c)::value;
+            constexpr bool FULL = decltype(full_c)::value;
+            constexpr int kFirst = PAR * NT;                 // the sets rotate on through the two steps
+            const bool land = FULL || kt + 1 < nk, more_a = FULL || kt + 2 < nk, more_b = FULL || kt + 3 < nk;
+            const int freed = slot, on = slot == 2 * kTileB ? -2 * kTileB : kTileB;
+            auto ask = [&]() {                               // into what step kt leaves
+                if (more_a) request_a(kt + 2, PAR);
+                if (more_b) request_b(kt + 3, freed);
+            };
+            auto turn = [&]() {
+                // this wave's reads of tile kt are done and its requests for kt + 1 have landed: only weights of kt + 2 may be under way
+                if (!more_a) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+                else if (all) __builtin_amdgcn_s_waitcnt(waitcnt_imm(N - 3, 0));
+                else __builtin_amdgcn_s_waitcnt(waitcnt_imm(N - 4, 0));
+                step_barrier();
+                if (early) ask();
+                slot += on;
+                f_at.lo += on, f_at.hi[0] += on, f_at.hi[1] += on;
+                if (P) p_at.lo += on, p_at.hi[0] += on, p_at.hi[1] += on;
+                __builtin_amdgcn_sched_barrier(0);
+            };
+#pragma unroll
+            for (int s = 0; s < NT - 2; ++s) {
+                if (s == NT + 1 - kSets) turn();             // (three sets: behind this loop)
+                if (s + kSets - 1 < NT) read_b((kFirst + s + kSets - 1) % kSets, s + kSets - 1);
+                else if (land) read_b((kFirst + s + kSets - 1) % kSets, s + kSets - 1 - NT);
+#pragma unroll
+                for (int mi = 0; mi < 4; ++mi) mfma6_in_place(acc[mi][s], af[mi], bf[(kFirst + s) % kSets]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (kSets == 3) turn();
+            if (land) read_b((kFirst + NT + kSets - 3) % kSets, kSets - 3);
+#pragma unroll
+            for (int mi = 0; mi < 4; ++mi) {
+                mfma6_in_place(acc[mi][NT - 2], af[mi], bf[(kFirst + NT - 2) % kSets]);
+                mfma6_in_place(acc[mi][NT - 1], af[mi], bf[(kFirst + NT - 1) % kSets]);
+                if (land) read_a(PAR ^ 1, mi);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (land) read_b((kFirst + NT + kSets - 2) % kSets, kSets - 2);
+            if (!early) ask();
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        using even = std::integral_constant<int, 0>;
+        using odd = std::integral_constant<int, 1>;
+        using yes = std::integral_constant<bool, true>;
+        using no = std::integral_constant<bool, false>;
+        int kt = 0;
+        for (; kt + 4 < nk; kt += 2) {
+            k_step(kt, even{}, yes{});
+            k_step(kt + 1, odd{}, yes{});
+        }
+        for (; kt < nk; kt += 2) {
+            k_step(kt, even{}, no{});
+            if (kt + 1 < nk) k_step(kt + 1, odd{}, no{});
+        }
+        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");    // the last matrix instructions' results ...
+#pragma unroll
+        for (int ni = 0; ni < NT; ++ni)                      // ... are read behind this
+            asm volatile("" : "+v"(acc[0][ni]), "+v"(acc[1][ni]), "+v"(acc[2][ni]), "+v"(acc[3][ni]));
+
+        // Scale and store: 64 rows of the block's 32 NT channels as a raw buffer that ends at the last valid element
+        int el = lane;
+        asm volatile("" : "+v"(el));
+        const int fr = el & 15, grp = el >> 4;
+        const int row0 = m0 + wm * 64;
+        const int first_four = 64 * wn * (F + P) + 4 * fr, first_pair = 64 * F + 4 * fr + 2 * wn;     // channels of the block
+        const float* const row_f = reinterpret_cast<const float*>(scales) + wm * 64 + 4 * grp;
+        const float* const step_f = reinterpret_cast<const float*>(scales) + BM;
+        float s_own[NT];
+#pragma unroll
+        for (int ni = 0; ni < NT; ++ni) s_own[ni] = step_f[ni < 4 * F ? first_four + 64 * (ni >> 2) + (ni & 3) : first_pair + ni - 4 * F];
+        const int n_rows = min(64, T - row0), n_cols = min(BNW, O - n0), pitch = (int)ldy * 2;
+        const int bytes = n_rows > 0 && n_cols > 0 ? (n_rows - 1) * pitch + n_cols * 2 : 0;
+        const __amdgpu_buffer_rsrc_t yb = __builtin_amdgcn_make_buffer_rsrc(Y + (int64_t)row0 * ldy + n0, 0, bytes, 0x00020000);
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi) {
+            const float4 a4 = *reinterpret_cast<const float4*>(row_f + 16 * mi);
+            const float a_own[4] = {a4.x, a4.y, a4.z, a4.w};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float y[NT];
+#pragma unroll
+                for (int ni = 0; ni < NT; ++ni) {
+                    y[ni] = acc[mi][ni][r] * a_own[r];
+                    y[ni] = rounded_f32(y[ni] * s_own[ni]);
+                }
+                const uint32_t row_off = (uint32_t)((16 * mi + 4 * grp + r) * pitch);
+                // O % 8 == 0: the channels of a group exist or not together
+                auto offset_of = [&](int c) { return (int)(c < n_cols ? row_off + 2 * c : 0x80000000u); };
+                typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
+#pragma unroll
+                for (int g = 0; g < F; ++g)
+                    __builtin_amdgcn_raw_buffer_store_b64(u32x2v{pack_half2(y[4 * g], y[4 * g + 1]), pack_half2(y[4 * g + 2], y[4 * g + 3])}, yb,
+                                                          offset_of(first_four + 64 * g), 0, STREAM ? 2 : 0);
+                if (P) __builtin_amdgcn_raw_buffer_store_b32(pack_half2(y[NT - 2], y[NT - 1]), yb, offset_of(first_pair), 0, STREAM ? 2 : 0);
+            }
+        }
+        step_barrier();                                      // (every wave is past its last read of the tile's LDS)
+    }
+}
+
+template <int NT, bool STREAM>
+hipError_t launch_f6_wide(const uint8_t* qx6, const float* row_scale, const uint8_t* qw6, const float* w_scale, int T, int I, int O,
+                          uint16_t* Y, int64_t ldy, int cu_blocks, hipStream_t stream) {
+    constexpr int kLds = (2 * 8 + 3 * NT) * 2 * kFragBytes + (4 + NT / 2) * 256;
+    static_assert(kLds <= 160 * 1024, "LDS of a gfx950 CU");
+    static std::atomic<uint64_t> allowed{0};
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_f6_wide_kernel<NT, STREAM>), kLds, allowed);
+    if (e != hipSuccess) return e;
+    const int tiles_m = (T + BM - 1) / BM, tiles_n = (O + 32 * NT - 1) / (32 * NT), total = tiles_m * tiles_n;
+    const int blocks = std::min(cu_blocks, (total + kXcds - 1) / kXcds * kXcds);
+    gemm_f6_wide_kernel<NT, STREAM><<<dim3((unsigned)blocks), dim3(512), kLds, stream>>>(qx6, row_scale, qw6, w_scale, T, I, O, Y, ldy, tiles_m, tiles_n);
+    return hipGetLastError();
+}
+
+// Which tile of the kernel above: 16-column weight tiles per wave (NT), or 0 for the ring's 256 x 256 tiles.  Where those need more
+// than one round over the CUs, in hundredths of a round of them: a round of 256 x 320 takes 126, of 256 x 384 139.  Measured with
+// operands and results that nothing has left in the caches (us, ring : here), I = 512, 1024, 2048, 4096, 8192:
+//   4096 x I x 5120 (320 ring tiles, one round of 256 x 320)    21.8 : 17.0   28.8 : 21.8   42.5 : 31.2   67.3 : 49.1   120 : 85
+//   2048 x I x 11008 (344, one round of 256 x 384)              22.8 : 18.0   30.1 : 22.9   43.0 : 32.7   68.1 : 51.9   120 : 92
+//   4096 x I x 10240 (640, two rounds of 256 x 320)             28.6 : 31.2   39.4 : 39.8   59.3 : 55.8   99 : 87       187 : 158
+//   4096 x I x 11008 (688, two of 256 x 384)                    32.5 : 33.6   43.2 : 43.3   62.2 : 61.0   102 : 95      191 : 174
+//   4096 x I x 13824 (864, three of 256 x 320)                  38.0 : 41.4   51.8 : 53.4   78.5 : 76.4   131 : 121     246 : 222
+//   4096 x I x 28672 (1792, five of 256 x 384)                  62.7 : 69.3   89.6 : 92.8   140 : 138     242 : 228
+// so more than one round only from I = 2048 on (the ring requests a block's next tile under the stores of the last, here they
+// follow each other).  With as many rounds as the ring the wider tiles lose: 4096 x 4096 x 4096 38.7 : 47.0, 256 x 256
+// tiles in this kernel 42.1.
+int w4a4_wide_tile(int T, int I, int O, int n_cu) {
+    if (T < 256) return 0;
+    auto rounds = [&](int bn) { return ((int64_t)((T + BM - 1) / BM) * ((O + bn - 1) / bn) + n_cu - 1) / n_cu; };
+    if (rounds(BN) < 2) return 0;
+    int64_t cost = 100 * rounds(BN);
+    int nt = 0;
+    for (const auto& [tiles, unit] : {std::pair<int, int>{10, 126}, {12, 139}}) {
+        const int64_t r = rounds(32 * tiles);
+        if ((r == 1 || I >= 2048) && r * unit < cost) {
+            cost = r * unit;
+            nt = tiles;
+        }
+    }
+    return nt;
+}
+
 }  // namespace
 
 int64_t fp6_packed_bytes(int64_t R, int64_t K) { return ((R + 31) / 32) * (K / 64) * (int64_t)kFragBytes; }
@@ -693,17 +986,27 @@ hipError_t launch_w4a4_linear(const void* qx6, const float* row_scale, const voi
         case 3: return launch_f6_staged<2, 1, 1, 8, 2>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
         default: break;
     }
+    // one block per CU (a multiple of the XCD count), fewer when there are fewer tiles than that
+    const int cu_blocks = n_cu >= kXcds ? n_cu / kXcds * kXcds : kXcds;
+    const bool stream_y = !y_stays_cached(T, O);
+    switch (acc_debug ? 0 : w4a4_wide_tile(T, I, O, cu_blocks)) {
+        case 10:
+            return stream_y ? launch_f6_wide<10, true>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, cu_blocks, stream)
+                            : launch_f6_wide<10, false>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, cu_blocks, stream);
+        case 12:
+            return stream_y ? launch_f6_wide<12, true>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, cu_blocks, stream)
+                            : launch_f6_wide<12, false>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, cu_blocks, stream);
+        default: break;
+    }
     // four instances: with or without the raw accumulators, Y streamed to memory or left in the caches
     using kernel_t = void (*)(const uint8_t*, const float*, const uint8_t*, const float*, int, int, int, uint16_t*, int64_t,
                               int32_t*, int, int);
     static const kernel_t kernels[4] = {&gemm_f6_ring_kernel<false, false>, &gemm_f6_ring_kernel<false, true>,
                                         &gemm_f6_ring_kernel<true, false>, &gemm_f6_ring_kernel<true, true>};
     static std::atomic<uint64_t> lds_allowed[4];
-    const int which = (acc_debug ? 2 : 0) + (y_stays_cached(T, O) ? 0 : 1);
+    const int which = (acc_debug ? 2 : 0) + (stream_y ? 1 : 0);
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernels[which]), kF6Lds, lds_allowed[which]);
     if (e != hipSuccess) return e;
-    // one block per CU (a multiple of the XCD count), fewer when there are fewer tiles than that
-    const int cu_blocks = n_cu >= kXcds ? n_cu / kXcds * kXcds : kXcds;
     const int blocks = std::min(cu_blocks, per_xcd * kXcds);
     kernels[which]<<<dim3((unsigned)blocks), dim3(512), kF6Lds, stream>>>(
         qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, tiles_m, tiles_n);

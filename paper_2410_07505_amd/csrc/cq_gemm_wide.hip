@@ -50,12 +50,6 @@ __device__ __forceinline__ void mfma_in_place(v4i& acc, const v4i& a, const v4i&
     asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 }
 
-// 4 bytes per lane from src to LDS at dst + 4 lane
-__device__ __forceinline__ void request_words(const float* src, const int8_t* dst) {
-    const uint32_t lds_off = (uint32_t)(uintptr_t)((lptr_t)dst);
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(src), "s"(lds_off) : "m0");
-}
-
 template <int NT>
 __global__ void __launch_bounds__(512)
 gemm_i8_wide_kernel(const int8_t* __restrict__ qx, const float* __restrict__ row_scale, const int8_t* __restrict__ qw,

@@ -1417,6 +1417,33 @@ def test_linear_in_one_round_of_tiles_of_another_width(cq, T, O, nt, I):
     assert len(names) == 1 and "gemm_i8_wide_kernelILi%dE" % nt in names[0]
 
 
+# FP6 outputs of more than one round of 256 x 256 tiles: one round of 256 x 32 nt, one to seven steps, and several rounds
+@pytest.mark.parametrize("T,I,O,nt", [(T, I, O, nt) for T, O, nt in [(300, 34000, 10), (1900, 10000, 10), (4096, 5120, 10), (1000, 20488, 12), (2040, 11256, 12)]
+                                      for I in (128, 256, 384, 512, 640, 896)]
+                         + [(4000, 2048, 10184, 10), (4096, 2176, 11008, 12)])
+def test_w4a4_linear_in_rounds_of_wider_tiles(cq, T, I, O, nt):
+    import torch
+    say("w4a4 linear, tiles of 256 x %d: %dx%dx%d" % (32 * nt, T, I, O))
+    g = torch.Generator(device="cuda").manual_seed(T + I)
+    qx = torch.randint(-7, 8, (T, I), generator=g, device="cuda", dtype=torch.int8)
+    qw = torch.randint(-7, 8, (O, I), generator=g, device="cuda", dtype=torch.int8)
+    qx[1], qw[1] = 7, -7                                     # the largest sums
+    a, s = torch.rand(T, generator=g, device="cuda") * 1e-2, torch.rand(O, generator=g, device="cuda") * 1e-1
+    px, pw = cq.crossquant_pack_fp6(qx), cq.crossquant_pack_fp6_weights(qw)
+    buf = torch.full((T + 2, O + 8), 7.0, device="cuda", dtype=torch.float16)
+    Y = buf[1:T + 1, :O]
+    run = lambda: cq.crossquant_w4a4_linear(px, a, pw, s, T, I, O, Y=Y)
+    run()
+    acc = (qx.double() @ qw.double().t().contiguous()).float()          # exact: integers below 2^24
+    want = ((acc * a[:, None]) * s[None, :]).half()
+    assert torch.equal(Y.contiguous().view(torch.int16), want.view(torch.int16))
+    assert bool((buf[0] == 7.0).all() and (buf[-1] == 7.0).all() and (buf[:, O:] == 7.0).all())
+    Y_acc, acc_out = cq.crossquant_w4a4_linear(px, a, pw, s, T, I, O, want_acc=True)         # another kernel
+    assert torch.equal(acc_out.float(), acc) and torch.equal(Y_acc.view(torch.int16), want.view(torch.int16))
+    names = launched(cq, run)
+    assert len(names) == 1 and "gemm_f6_wide_kernelILi%dE" % nt in names[0]
+
+
 @pytest.mark.parametrize("T,O,kernel", [(256, 256, "staged"), (1100, 4104, "ring")])
 def test_linear_extreme_accumulators(cq, T, O, kernel):
     say("linear extremes, %s kernel" % kernel)
