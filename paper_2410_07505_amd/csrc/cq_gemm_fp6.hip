@@ -632,7 +632,8 @@ hipError_t launch_f6_staged(const uint8_t* qx6, const float* row_scale, const ui
 //   of tile kt; what tile kt occupied is then requested for the activations of kt + 2 and the weights of kt + 3, by the waves
 //   0 to 3 at once, by 4 to 7 at the end of the step.  The weights are what no cache holds: with two slots of them 4096 x
 //   4096 x 5120 takes 52.6 us instead of 49.2 where nothing is left in the caches, 4096 x 8192 x 5120 90.7 instead of 85.2.
-// STREAM: Y passes the caches (see y_stays_cached).
+// STREAM: Y is stored as a stream (see y_stays_cached), here nt alone: a wave writes a line in pieces, which have to meet in the L2.
+//   With the ring's sc1 nt whole layers of 4096 x 5120 x 13824 and 2048 x 8192 x 28672 take 171 us and 231 instead of 158 and 220.
 // ---------------------------------------------------------------------------------------------------------------
 typedef int v6i __attribute__((ext_vector_type(6)));
 
