@@ -887,13 +887,16 @@ hipError_t launch_f6_wide(const uint8_t* qx6, const float* row_scale, const uint
 }
 
 // Which tile of the kernel above: 16-column weight tiles per wave (NT), or 0 for the ring's 256 x 256 tiles.  Where those need more
-// than one round over the CUs, in hundredths of a round of them: a round of 256 x 320 takes 126, of 256 x 384 139.  Measured with
+// than one round over the CUs, in hundredths of a round of them: a round of 256 x 320 takes 126, of 256 x 384 139, from I = 4096 on
+// (where first tiles and stores weigh less) 124 and 133.  Measured with
 // operands and results that nothing has left in the caches (us, ring : here), I = 512, 1024, 2048, 4096, 8192:
 //   4096 x I x 5120 (320 ring tiles, one round of 256 x 320)    21.8 : 17.0   28.8 : 21.8   42.5 : 31.2   67.3 : 49.1   120 : 85
 //   2048 x I x 11008 (344, one round of 256 x 384)              22.8 : 18.0   30.1 : 22.9   43.0 : 32.7   68.1 : 51.9   120 : 92
 //   4096 x I x 10240 (640, two rounds of 256 x 320)             28.6 : 31.2   39.4 : 39.8   59.3 : 55.8   99 : 87       187 : 158
 //   4096 x I x 11008 (688, two of 256 x 384)                    32.5 : 33.6   43.2 : 43.3   62.2 : 61.0   102 : 95      191 : 174
 //   4096 x I x 13824 (864, three of 256 x 320)                  38.0 : 41.4   51.8 : 53.4   78.5 : 76.4   131 : 121     246 : 222
+//   4096 x I x 16384 (1024, three of 256 x 384)                                              85.3 : 85.4   145 : 142     270 : 260
+//   4096 x I x 20480 (1280, four of 256 x 320)                                              103 : 105     176 : 169     333 : 312
 //   4096 x I x 28672 (1792, five of 256 x 384)                  62.7 : 69.3   89.6 : 92.8   140 : 138     242 : 228
 // so more than one round only from I = 2048 on (the ring requests a block's next tile under the stores of the last, here they
 // follow each other).  With as many rounds as the ring the wider tiles lose: 4096 x 4096 x 4096 38.7 : 47.0, 256 x 256
@@ -904,7 +907,7 @@ int w4a4_wide_tile(int T, int I, int O, int n_cu) {
     if (rounds(BN) < 2) return 0;
     int64_t cost = 100 * rounds(BN);
     int nt = 0;
-    for (const auto& [tiles, unit] : {std::pair<int, int>{10, 126}, {12, 139}}) {
+    for (const auto& [tiles, unit] : {std::pair<int, int>{10, I < 4096 ? 126 : 124}, {12, I < 4096 ? 139 : 133}}) {
         const int64_t r = rounds(32 * tiles);
         if ((r == 1 || I >= 2048) && r * unit < cost) {
             cost = r * unit;
