@@ -5,7 +5,7 @@
 // function here takes the tensors of one public call, all of its outputs among them, asks what binding.py asks of them, and
 // calls the C entry: 64 x 256 x 256 as
 // three calls 20.3 -> 11.1 us, which is what their kernels take.  Whatever is not the plain case (a subclass, a wrong type or
-// shape, another device, an output that has to be allocated) is not judged here: kNotPlain sends the caller through the checks
+// shape, another device, an output that has to be allocated) is not decided here: kNotPlain sends the caller through the checks
 // in binding.py, which say what is wrong or make the call.  Nothing is kept from one call for the next.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
