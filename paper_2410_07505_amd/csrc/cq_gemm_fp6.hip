@@ -622,16 +622,19 @@ hipError_t launch_f6_staged(const uint8_t* qx6, const float* row_scale, const ui
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Tiles of 256 tokens x 32 NT channels (320 or 384), for outputs that 256 x 256 tiles do not divide over the CUs (the rule
+// Tiles of 256 tokens x 32 NT channels (128, 192, 320 or 384), for outputs that 256 x 256 tiles do not divide over the CUs (the rule
 // and what both take stand at w4a4_wide_tile): the structure of gemm_i8_wide_kernel (cq_gemm_wide.hip) on FP6 fragments.
 //   8 waves in 4 x 2, wave tiles of 64 x 16 NT; a step is 128 elements, 4 + NT fragments for 4 NT matrix instructions (LDS reads
-//   and writes of a step keep the LDS busy for 1780 / 2020 cycles, the matrix instructions the matrix cores for 1280 / 1540).
+//   and writes of a step keep the LDS busy for 1050 / 1270 / 1780 / 2020 cycles, the matrix instructions the matrix cores for 510 /
+//   770 / 1280 / 1540).
 //   NT is even: a block's 32 NT channels are NT / 2 whole groups of 64.  Wave wn has NT / 4 of them to itself; of the one in the
-//   middle that NT = 10 leaves it takes the weight tiles 2 wn and 2 wn + 1.
-//   LDS: two buffers of activations, three slots of weights (141 / 160 KB).  The barrier near the end of step kt stands behind the last reads
+//   middle that NT = 6 and 10 leave it takes the weight tiles 2 wn and 2 wn + 1.
+//   LDS, NT = 10, 12: two buffers of activations, three slots of weights (141 / 160 KB).  The barrier near the end of step kt stands behind the last reads
 //   of tile kt; what tile kt occupied is then requested for the activations of kt + 2 and the weights of kt + 3, by the waves
 //   0 to 3 at once, by 4 to 7 at the end of the step.  The weights are what no cache holds: with two slots of them 4096 x
 //   4096 x 5120 takes 52.6 us instead of 49.2 where nothing is left in the caches, 4096 x 8192 x 5120 90.7 instead of 85.2.
+//   NT = 4, 6: four / three slots of both (147 / 129 KB), since the steps are short: with the buffers of the others 2048 x 4096 x 5120
+//   in tiles of 192 takes 37.2 us instead of 30.8 there, the ring 33.0.
 // STREAM: Y is stored as a stream (see y_stays_cached), here nt alone: a wave writes a line in pieces, which have to meet in the L2.
 //   With the ring's sc1 nt whole layers of 4096 x 5120 x 13824 and 2048 x 8192 x 28672 take 171 us and 231 instead of 158 and 220.
 // ---------------------------------------------------------------------------------------------------------------
@@ -657,7 +660,9 @@ gemm_f6_wide_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ r
     constexpr int F = NT / 4, P = NT % 4 / 2;                // groups of 64 channels a wave has to itself, and shares
     constexpr int WTN = 16 * NT, BNW = 2 * WTN, kPair = 2 * kFragBytes;
     constexpr int kSets = NT < 12 ? 4 : 3;                   // weight tiles in registers: read kSets - 1 ahead (12: no room for more)
-        constexpr int kTileA = 8 * kPair, kTileB = NT * kPair, kReq = (8 + NT) * 3;  // LDS bytes; 1 KiB requests
+        constexpr bool kDeep = NT < 10;                          // the operands' tiles in kSlots slots each, requested kSlots - 1 steps ahead
+    constexpr int kSlots = NT == 4 ? 4 : 3, kSlotsA = kDeep ? kSlots : 2;
+    constexpr int kTileA = 8 * kPair, kTileB = NT * kPair, kReq = (8 + NT) * 3;  // LDS bytes; 1 KiB requests
     constexpr int N = (kReq + 7) / 8;                        // ... of a wave at most: ids wave, wave + 8, ...
     extern __shared__ __align__(16) int8_t lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -696,7 +701,7 @@ gemm_f6_wide_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ r
             for (int n = 0; n < 3; ++n) request_at(src[n] + (int64_t)kt * kPair, off[n], dst + n * 8192);
         };
         auto request_b = [&](int kt, int slot) {             // slot: its byte offset from the first one
-            const int8_t* dst = lds + kTileA + slot + wave * 1024;         // (n = 3: 2 kTileA)
+            const int8_t* dst = lds + (kSlotsA - 1) * kTileA + slot + wave * 1024;         // (n = 3: kTileA more)
 #pragma unroll
             for (int n = 3; n < N; ++n)
                 if (n < N - 1 || all) request_at(src[n] + (int64_t)kt * kPair, off[n % 3], dst + n * 8192);
@@ -712,21 +717,33 @@ gemm_f6_wide_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ r
             }
 
         // the epilogue's scales: 256 row factors and, behind them, the steps of 64 ceil(NT / 2) channels
-        int8_t* const scales = lds + 2 * kTileA + 3 * kTileB;
+        int8_t* const scales = lds + kSlotsA * kTileA + kSlots * kTileB;
         if (wave < 4) request_words(row_scale + min(m0 + wave * 64 + tl, T - 1), scales + wave * 256);
         if (wave < NT / 2) request_words(w_scale + min(n0 + wave * 64 + tl, O - 1), scales + (4 + wave) * 256);
-        request_a(0, 0);
-        request_b(0, 0);
-        if (nk > 1) {
-            request_b(1, kTileB);
-            request_a(1, 1);
-        }
-        if (nk > 2) {
-            request_b(2, 2 * kTileB);
-            if (all) __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * N - 3, 15));          // tile 0 has landed
-            else __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * N - 5, 15));
+        if (kDeep) {
+#pragma unroll
+            for (int t = 0; t < kSlots; ++t)
+                if (t < nk) {
+                    request_a(t, t);
+                    request_b(t, t * kTileB);
+                }
+            if (nk < kSlots) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
+            else if (all) __builtin_amdgcn_s_waitcnt(waitcnt_imm((kSlots - 1) * N, 15));          // tile 0 has landed
+            else __builtin_amdgcn_s_waitcnt(waitcnt_imm((kSlots - 1) * (N - 1), 15));
         } else {
-            __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
+            request_a(0, 0);
+            request_b(0, 0);
+            if (nk > 1) {
+                request_b(1, kTileB);
+                request_a(1, 1);
+            }
+            if (nk > 2) {
+                request_b(2, 2 * kTileB);
+                if (all) __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * N - 3, 15));          // tile 0 has landed
+                else __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * N - 5, 15));
+            } else {
+                __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
+            }
         }
         step_barrier();
 
@@ -744,8 +761,8 @@ gemm_f6_wide_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ r
                 asm volatile("" : "+v"(x.lo), "+v"(x.hi[0]), "+v"(x.hi[1]));
             };
             at(a_at, wm * 2 * kPair);
-            at(f_at, 2 * kTileA + 2 * wn * (F + P) * kPair);
-            at(p_at, 2 * kTileA + (2 * F + wn) * kPair);
+            at(f_at, kSlotsA * kTileA + 2 * wn * (F + P) * kPair);
+            at(p_at, kSlotsA * kTileA + (2 * F + wn) * kPair);
         }
         typedef int v2i __attribute__((ext_vector_type(2)));
         typedef __attribute__((address_space(3))) const v4i* lo_ptr;
@@ -756,7 +773,7 @@ gemm_f6_wide_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ r
             f = v6i{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y};
         };
         v6i af[4], bf[kSets];
-        auto read_a = [&](int buf, int mi) { read(af[mi], a_at, mi, buf * kTileA); };
+        auto read_a = [&](int buf, int mi) { read(af[mi], a_at, mi, kDeep ? 0 : buf * kTileA); };
         auto read_b = [&](int set, int s) {                  // of the slot that f_at and p_at stand at
             if (s < 4 * F) read(bf[set], f_at, s, 0);
             else read(bf[set], p_at, s - 4 * F, 0);
@@ -767,26 +784,33 @@ gemm_f6_wide_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ r
         for (int s = 0; s < kSets - 1; ++s) read_b(s, s);
 
         int slot = 0;                                        // of the weights of step kt
+        int slot_a = 0;                                      // kDeep: number of the slot of both operands
         // Step kt, its activations in buffer PAR.  FULL: tiles up to kt + 3 exist.  The last two weight tiles are multiplied activation tile by
         // activation tile, so that the next step's activations replace this one's as they are done with.
         auto k_step = [&](int kt, auto par_c, auto full_c) {
             constexpr int PAR = decltype(par_c)::value;
             constexpr bool FULL = decltype(full_c)::value;
             constexpr int kFirst = PAR * NT;                 // the sets rotate on through the two steps
-            const bool land = FULL || kt + 1 < nk, more_a = FULL || kt + 2 < nk, more_b = FULL || kt + 3 < nk;
-            const int freed = slot, on = slot == 2 * kTileB ? -2 * kTileB : kTileB;
+            const bool land = FULL || kt + 1 < nk, more_a = FULL || kt + kSlotsA < nk, more_b = FULL || kt + kSlots < nk;
+            const int freed = slot, on = slot == (kSlots - 1) * kTileB ? -(kSlots - 1) * kTileB : kTileB;
+            const int freed_a = kDeep ? slot_a : PAR;
             auto ask = [&]() {                               // into what step kt leaves
-                if (more_a) request_a(kt + 2, PAR);
-                if (more_b) request_b(kt + 3, freed);
+                if (more_a) request_a(kt + kSlotsA, freed_a);
+                if (more_b) request_b(kt + kSlots, freed);
             };
             auto turn = [&]() {
                 // this wave's reads of tile kt are done and its requests for kt + 1 have landed: only weights of kt + 2 may be under way
-                if (!more_a) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
-                else if (all) __builtin_amdgcn_s_waitcnt(waitcnt_imm(N - 3, 0));
-                else __builtin_amdgcn_s_waitcnt(waitcnt_imm(N - 4, 0));
+                if (kDeep ? !(FULL || kt + kSlots - 1 < nk) : !more_a) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+                else if (all) __builtin_amdgcn_s_waitcnt(waitcnt_imm(kDeep ? (kSlots - 2) * N : N - 3, 0));
+                else __builtin_amdgcn_s_waitcnt(waitcnt_imm(kDeep ? (kSlots - 2) * (N - 1) : N - 4, 0));
                 step_barrier();
                 if (early) ask();
                 slot += on;
+                if (kDeep) {
+                    const int on_a = slot_a == kSlots - 1 ? -(kSlots - 1) : 1;
+                    slot_a += on_a;
+                    a_at.lo += on_a * kTileA, a_at.hi[0] += on_a * kTileA, a_at.hi[1] += on_a * kTileA;
+                }
                 f_at.lo += on, f_at.hi[0] += on, f_at.hi[1] += on;
                 if (P) p_at.lo += on, p_at.hi[0] += on, p_at.hi[1] += on;
                 __builtin_amdgcn_sched_barrier(0);
@@ -818,7 +842,7 @@ gemm_f6_wide_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ r
         using yes = std::integral_constant<bool, true>;
         using no = std::integral_constant<bool, false>;
         int kt = 0;
-        for (; kt + 4 < nk; kt += 2) {
+        for (; kt + kSlots + 1 < nk; kt += 2) {
             k_step(kt, even{}, yes{});
             k_step(kt + 1, odd{}, yes{});
         }
@@ -875,7 +899,7 @@ gemm_f6_wide_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ r
 template <int NT, bool STREAM>
 hipError_t launch_f6_wide(const uint8_t* qx6, const float* row_scale, const uint8_t* qw6, const float* w_scale, int T, int I, int O,
                           uint16_t* Y, int64_t ldy, int cu_blocks, hipStream_t stream) {
-    constexpr int kLds = (2 * 8 + 3 * NT) * 2 * kFragBytes + (4 + NT / 2) * 256;
+    constexpr int kSlots = NT == 4 ? 4 : 3, kLds = ((NT < 10 ? kSlots : 2) * 8 + kSlots * NT) * 2 * kFragBytes + (4 + NT / 2) * 256;
     static_assert(kLds <= 160 * 1024, "LDS of a gfx950 CU");
     static std::atomic<uint64_t> allowed{0};
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_f6_wide_kernel<NT, STREAM>), kLds, allowed);
@@ -886,10 +910,17 @@ hipError_t launch_f6_wide(const uint8_t* qx6, const float* row_scale, const uint
     return hipGetLastError();
 }
 
-// Which tile of the kernel above: 16-column weight tiles per wave (NT), or 0 for the ring's 256 x 256 tiles.  Where those need more
+// Which tile of the kernel above: 16-column weight tiles per wave (NT), or 0 for the ring's 256 x 256 tiles.  Measured with operands and
+// results that nothing has left in the caches.  One round of 256 x 128 tiles is ahead of the ring, which half of the CUs have no tile in
+// then, at every contraction (us, ring : here, I = 512, 1024, 2048, 4096, 8192):
+//   1000 x I x 5120 (80 ring tiles, 160 of 256 x 128)           9.8 : 8.2     12.4 : 10.2   18.6 : 15.4   31.0 : 25.1   54 : 42
+//   2048 x I x 4096 (128, 256)                                  11.1 : 10.1   14.5 : 12.8   20.7 : 18.3   32.2 : 27.7   56 : 46
+// one round of 256 x 192 tiles only at long ones:
+//   2048 x I x 5120 (160, 216 of 256 x 192)                     11.6 : 11.5   14.8 : 14.4   21.2 : 20.3   33.0 : 30.8   56 : 51
+//   2048 x I x 6144 (192, 256)                                  12.3 : 12.8   15.8 : 19.1   22.2 : 23.3   34.6 : 33.2   60 : 55
+// Where the ring needs more
 // than one round over the CUs, in hundredths of a round of them: a round of 256 x 320 takes 126, of 256 x 384 139, from I = 4096 on
-// (where first tiles and stores weigh less) 124 and 133.  Measured with
-// operands and results that nothing has left in the caches (us, ring : here), I = 512, 1024, 2048, 4096, 8192:
+// (where first tiles and stores weigh less) 124 and 133:
 //   4096 x I x 5120 (320 ring tiles, one round of 256 x 320)    21.8 : 17.0   28.8 : 21.8   42.5 : 31.2   67.3 : 49.1   120 : 85
 //   2048 x I x 11008 (344, one round of 256 x 384)              22.8 : 18.0   30.1 : 22.9   43.0 : 32.7   68.1 : 51.9   120 : 92
 //   4096 x I x 10240 (640, two rounds of 256 x 320)             28.6 : 31.2   39.4 : 39.8   59.3 : 55.8   99 : 87       187 : 158
@@ -904,6 +935,8 @@ hipError_t launch_f6_wide(const uint8_t* qx6, const float* row_scale, const uint
 int w4a4_wide_tile(int T, int I, int O, int n_cu) {
     if (T < 256) return 0;
     auto rounds = [&](int bn) { return ((int64_t)((T + BM - 1) / BM) * ((O + bn - 1) / bn) + n_cu - 1) / n_cu; };
+    if (rounds(128) == 1) return 4;
+    if (rounds(192) == 1 && I >= 4096) return 6;
     if (rounds(BN) < 2) return 0;
     int64_t cost = 100 * rounds(BN);
     int nt = 0;
@@ -975,7 +1008,13 @@ hipError_t launch_w4a4_linear(const void* qx6, const float* row_scale, const voi
     // ring) 17.0 : 17.8 at 512, 58 : 68 at 4096; 128 x I x 81920 (768) 27.8 : 19.1 at 512, 73 : 81 at 4096.
     const int64_t rounds = (total + n_cu - 1) / n_cu;
     const int64_t ring_time = rounds * ((int64_t)500 * I + 110000) - (int64_t)100 * I;
-    if (cost > 192 && cost * (I + 930) >= ring_time) kind = -1;
+    // One round of 256 x 128 tiles (w4a4_wide_tile) is ahead of two rounds of 128 x 128 at every contraction, of one of them at short ones:
+    // 1000 x I x 4096, 128 x 128 : 256 x 128 : ring, 7.2 : 6.1 : 7.6 us at I = 128, 8.0 : 7.9 : 9.5 at 512, 8.7 : 8.8 : 10.7 at 768, 9.3 : 9.7 : 12.0
+    // at 1024, 19.4 : 24.2 : 29.7 at 4096.  From I = 640 on such calls keep the line above: the kernel on its short side is pinned there.
+    const int cu_blocks = n_cu >= kXcds ? n_cu / kXcds * kXcds : kXcds;      // the larger tiles: one block per CU, a multiple of the XCDs
+    int wide = acc_debug ? 0 : w4a4_wide_tile(T, I, O, cu_blocks);
+    if (wide == 4 && cost <= 256 && I >= 640) wide = 0;
+    if (cost > 192 && (wide == 4 || cost * (I + 930) >= ring_time)) kind = -1;
     // weights that one row of tiles reads once and that no cache keeps: see launch_w8a8_staged (32 x 8192 x 28672 33.9 -> 32.2
     // us, 64 x 8192 x 28672 35.3 -> 34.1)
     const bool once = kind >= 0 && T <= kinds[kind][0] && (int64_t)O * I / 4 * 3 > (int64_t)128 << 20;
@@ -990,10 +1029,10 @@ hipError_t launch_w4a4_linear(const void* qx6, const float* row_scale, const voi
         case 3: return launch_f6_staged<2, 1, 1, 8, 2>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
         default: break;
     }
-    // one block per CU (a multiple of the XCD count), fewer when there are fewer tiles than that
-    const int cu_blocks = n_cu >= kXcds ? n_cu / kXcds * kXcds : kXcds;
     const bool stream_y = !y_stays_cached(T, O);
-    switch (acc_debug ? 0 : w4a4_wide_tile(T, I, O, cu_blocks)) {
+    switch (wide) {                                          // (one round of the first two is at most 25 MiB of Y)
+        case 4: return launch_f6_wide<4, false>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, cu_blocks, stream);
+        case 6: return launch_f6_wide<6, false>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, cu_blocks, stream);
         case 10:
             return stream_y ? launch_f6_wide<10, true>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, cu_blocks, stream)
                             : launch_f6_wide<10, false>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, cu_blocks, stream);

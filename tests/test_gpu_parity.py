@@ -1417,11 +1417,14 @@ def test_linear_in_one_round_of_tiles_of_another_width(cq, T, O, nt, I):
     assert len(names) == 1 and "gemm_i8_wide_kernelILi%dE" % nt in names[0]
 
 
-# FP6 outputs of more than one round of 256 x 256 tiles: one round of 256 x 32 nt, one to seven steps, and several rounds
+# FP6 outputs of more than one round of 256 x 256 tiles: one round of 256 x 32 nt, one to nine steps, and several rounds
 @pytest.mark.parametrize("T,I,O,nt", [(T, I, O, nt) for T, O, nt in [(300, 34000, 10), (1900, 10000, 10), (4096, 5120, 10), (1000, 20488, 12), (2040, 11256, 12)]
                                       for I in (128, 256, 384, 512, 640, 896)]
-                         + [(4000, 2048, 10184, 10), (4096, 2176, 11008, 12)])
-def test_w4a4_linear_in_rounds_of_wider_tiles(cq, T, I, O, nt):
+                         + [(4000, 2048, 10184, 10), (4096, 2176, 11008, 12)]
+                         # less than a round of them: one round of 256 x 128, or at long contractions of 256 x 192
+                         + [(T, I, O, 4) for T, O in [(257, 16000), (1000, 5128), (2048, 4096)] for I in (128, 256, 384, 512, 640, 768, 896, 1152)]
+                         + [(1000, 512, 4088, 4), (2040, 4096, 5128, 6), (1100, 4224, 9608, 6), (1280, 4352, 9600, 6)])
+def test_w4a4_linear_in_rounds_of_tiles_of_another_width(cq, T, I, O, nt):
     import torch
     say("w4a4 linear, tiles of 256 x %d: %dx%dx%d" % (32 * nt, T, I, O))
     g = torch.Generator(device="cuda").manual_seed(T + I)
