@@ -629,9 +629,9 @@ hipError_t launch_f6_staged(const uint8_t* qx6, const float* row_scale, const ui
 //   770 / 1280 / 1540).
 //   NT is even: a block's 32 NT channels are NT / 2 whole groups of 64.  Wave wn has NT / 4 of them to itself; of the one in the
 //   middle that NT = 6 and 10 leave it takes the weight tiles 2 wn and 2 wn + 1.
-//   LDS, NT = 10, 12: two buffers of activations, three slots of weights (141 / 160 KB).  The barrier near the end of step kt stands behind the last reads
-//   of tile kt; what tile kt occupied is then requested for the activations of kt + 2 and the weights of kt + 3, by the waves
-//   0 to 3 at once, by 4 to 7 at the end of the step.  The weights are what no cache holds: with two slots of them 4096 x
+//   LDS, NT = 10, 12: two buffers of activations, three slots of weights (141 / 160 KB).  The barrier near the end of step kt stands
+//   behind the last reads of tile kt; what tile kt occupied is then requested for the activations of kt + 2 and the weights of
+//   kt + 3, by the waves 0 to 3 at once, by 4 to 7 at the end of the step.  The weights are what no cache holds: with two slots of them 4096 x
 //   4096 x 5120 takes 52.6 us instead of 49.2 where nothing is left in the caches, 4096 x 8192 x 5120 90.7 instead of 85.2.
 //   NT = 4, 6: four / three slots of both (147 / 129 KB), since the steps are short: with the buffers of the others 2048 x 4096 x 5120
 //   in tiles of 192 takes 37.2 us instead of 30.8 there, the ring 33.0.
@@ -799,7 +799,8 @@ gemm_f6_wide_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ r
                 if (more_b) request_b(kt + kSlots, freed);
             };
             auto turn = [&]() {
-                // this wave's reads of tile kt are done and its requests for kt + 1 have landed: only weights of kt + 2 may be under way
+                // this wave's reads of tile kt are done and its requests for kt + 1 have landed: only the weights of kt + 2 may be under
+                // way (kDeep: both operands of kt + 2 to kt + kSlots - 1)
                 if (kDeep ? !(FULL || kt + kSlots - 1 < nk) : !more_a) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
                 else if (all) __builtin_amdgcn_s_waitcnt(waitcnt_imm(kDeep ? (kSlots - 2) * N : N - 3, 0));
                 else __builtin_amdgcn_s_waitcnt(waitcnt_imm(kDeep ? (kSlots - 2) * (N - 1) : N - 4, 0));
