@@ -175,6 +175,10 @@ int crossquant_kernel_count(const void *X, int64_t T, int64_t I, int64_t ldx, co
  * xrk: out, nullable, binary16 [T][I].  counters: out, three unsigned 64-bit values, 8-byte aligned.
  * row_scale / col_scale: nullable (both or neither): float[T] / float[I], receive a and b (must not overlap t
  *        or c: CQ_ERR_ALIAS).
+ * The counts are summed in library-owned device memory, a piece per stream handle (16 per process, apart from those of
+ * the calls above), and stored by the last block.  Calls captured into a graph, and calls on a stream without a piece,
+ * clear `counters` with a small kernel and add to it directly: graphs with outputs of their own may be replayed on any
+ * stream, at the same time as each other and as other calls.
  */
 int crossquant_kernel_analysis(const void *X, int64_t T, int64_t I, int64_t ldx, const float *t,
                                const float *c, float alpha, int bits, void *xrk, float *row_scale,
@@ -182,10 +186,10 @@ int crossquant_kernel_analysis(const void *X, int64_t T, int64_t I, int64_t ldx,
 
 /*
  * crossquant_kernel_analysis for callers that have no vectors for the scale factors: code under HIP
- * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, outputs and
- * arithmetic as that call with row_scale and col_scale NULL: the factors stay on chip.
- * Limits: T <= CQ_ANALYSIS_STATIC_MAX and I <= CQ_ANALYSIS_STATIC_MAX, else CQ_ERR_SHAPE with
- * nothing enqueued.
+ * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, outputs,
+ * arithmetic and rules for streams and graphs as that call with row_scale and col_scale NULL: the
+ * factors stay on chip.  Its contract limits T and I to CQ_ANALYSIS_STATIC_MAX, else CQ_ERR_SHAPE
+ * with nothing enqueued; the plain call takes larger ones.
  */
 #define CQ_ANALYSIS_STATIC_MAX (1 << 19)
 int crossquant_kernel_analysis_static(const void *X, int64_t T, int64_t I, int64_t ldx, const float *t,

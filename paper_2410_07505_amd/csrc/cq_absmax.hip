@@ -252,11 +252,8 @@ hipError_t launch_absmax(const uint16_t* X, int B, int T, int I, int64_t ldx, in
     // differs from launch to launch, which a captured graph cannot have (its arguments are frozen): captured
     // calls and streams without a slot clear with a kernel of their own first.
     const SlotTable table = buf ? kStateTable : kOffLayoutTable;
-    const int slot = stream_slot(stream, table);
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    const bool plain_stream = slot >= 0 && hipStreamIsCapturing(stream, &cap) == hipSuccess &&
-                              cap == hipStreamCaptureStatusNone;
-    if (plain_stream) {
+    const int slot = uncaptured_stream_slot(stream, table);
+    if (slot >= 0) {
         static std::mutex mu;
         static unsigned int reached[64][kSlotTables * kStateSlots];   // what a device's g_cleared words reach once all launches so far have cleared
         static unsigned int* counters[64];                 // device address of g_cleared on each device, once known

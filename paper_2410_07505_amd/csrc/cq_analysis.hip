@@ -231,7 +231,8 @@ hipError_t launch_kernel_analysis(const uint16_t* X, int T, int I, int64_t ldx, 
     const bool buf = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && (ldx % 8 == 0) && (I % 8 == 0) &&
                      (reinterpret_cast<uintptr_t>(xrk) % 16 == 0);
     const double al = (double)alpha;
-    const int slot = stream_slot(stream);
+    // (a captured call clears the caller's counters and adds to them: graphs with counters of their own are independent)
+    const int slot = uncaptured_stream_slot(stream, kAnalysisTable);
     if (slot < 0) zero_counters_kernel<<<dim3(1), dim3(64), 0, stream>>>(counters);
     const auto kernel = buf ? &analysis_kernel<true> : &analysis_kernel<false>;
     kernel<<<grid, block, 0, stream>>>(X, T, I, ldx, t, c, al, qmax, a, b, xrk, counters, slot, ncc, nb);

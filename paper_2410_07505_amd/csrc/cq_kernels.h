@@ -58,11 +58,15 @@ inline int quantize_batches_per_wave(int64_t n_chunks, int T, int max_blocks = 5
 // Library-owned device state comes in kStateSlots pieces; a stream keeps the slot it is given on
 // first use (-1: none left, or a handle that stands for several streams -- the caller then takes
 // the path that clears its accumulators with a kernel of its own first).
-// The clearing counters of absmax off the vector layout have a table of their own: crossquant_absmax_quantize_single_read
-// is refused on a stream without a slot, and calls that can do without one must not use up its slots.
+// The clearing counters of absmax off the vector layout and the analysis kernel's sums have tables of their own:
+// crossquant_absmax_quantize_single_read is refused on a stream without a slot, and calls that can do without one must not
+// use up its slots.
 constexpr int kStateSlots = 16;
-enum SlotTable { kStateTable, kOffLayoutTable, kSlotTables };
+enum SlotTable { kStateTable, kOffLayoutTable, kAnalysisTable, kSlotTables };
 int stream_slot(hipStream_t stream, SlotTable table = kStateTable);
+// The same, -1 while the stream is being captured: a graph may be replayed on any stream, beside other graphs and beside the
+// capture stream's own calls, and must not share their state.
+int uncaptured_stream_slot(hipStream_t stream, SlotTable table);
 
 // A kernel that needs more dynamic LDS than the default limit has to be told so once per device.
 // `done` is a bit mask of the devices (ordinal < 64) on which that has happened for this kernel; devices with

@@ -26,4 +26,10 @@ int stream_slot(hipStream_t stream, SlotTable table) {
     return n++;
 }
 
+int uncaptured_stream_slot(hipStream_t stream, SlotTable table) {
+    const int slot = stream_slot(stream, table);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    return slot >= 0 && hipStreamIsCapturing(stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone ? slot : -1;
+}
+
 }  // namespace cq

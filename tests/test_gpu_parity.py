@@ -512,6 +512,86 @@ def test_maxima_off_the_vector_layout_take_no_slot_from_other_calls(cq, tmp_path
     assert np.array_equal(host(codes), oracle.quantize(Z, z_t, z_c, 0.15, 8)["codes"])
 
 
+def analysis_case(T, I, seed):
+    """(X on the GPU, t, c, outputs of crossquant_kernel_analysis to fill, what the oracle says they have to hold)"""
+    import torch
+    X = outliers(T, I, seed=seed)
+    t_ref, c_ref = oracle.absmax(X)
+    out = dict(xrk=torch.full((T, I), 7.0, dtype=torch.float16, device="cuda"), counters=torch.full((3,), -1, dtype=torch.int64, device="cuda"),
+               row_scale=torch.full((T,), 7.0, device="cuda"), col_scale=torch.full((I,), 7.0, device="cuda"))
+    return gpu(X), gpu(t_ref), gpu(c_ref), out, oracle.kernel_analysis(X, t_ref, c_ref, 0.15, 8)
+
+
+def check_analysis_case(case, label):
+    out, ref = case[3:]
+    assert [int(v) for v in host(out["counters"])] == [ref["Z"], ref["n_col_ge_row"], ref["n_bound_smaller"]], label
+    assert np.array_equal(bits16(host(out["xrk"])), bits16(ref["xrk"])), label
+    assert np.array_equal(bits32(host(out["row_scale"])), bits32(ref["a"])), label
+    assert np.array_equal(bits32(host(out["col_scale"])), bits32(ref["b"])), label
+
+
+def test_analysis_calls_on_many_streams_and_the_slots_they_leave(cq, tmp_path):
+    """20 streams with analyses that may overlap (more streams than the library has pieces of memory for their sums), on a copy
+    of the library, whose slots are all free; then the single-read call, which is refused without one of the other calls'
+    slots, on a 21st stream: the analysis takes none of them."""
+    import ctypes
+    import shutil
+    import torch
+    say("20 streams of analyses, then the single-read call on another")
+    lib = ctypes.CDLL(shutil.copy(cq.LIB_PATH, tmp_path / "copy.so"))
+    for name in ("crossquant_kernel_analysis", "crossquant_absmax_quantize_single_read"):
+        getattr(lib, name).argtypes = getattr(cq.raw, name).argtypes
+    cases = [analysis_case(60 + 150 * k, 200 + 90 * k, 900 + k) for k in range(20)]
+    streams = [torch.cuda.Stream() for _ in range(21)]
+    assert len({st.cuda_stream for st in streams}) == 21
+    Z = outliers(64, 256, seed=6)
+    Zg, t, c, a, b = (gpu(Z), *(torch.empty(n, device="cuda") for n in (64, 256, 64, 256)))
+    codes = torch.empty((64, 256), dtype=torch.int8, device="cuda")
+    torch.cuda.synchronize()
+    for _ in range(2):
+        for (Xg, tg, cg, out, _), st in zip(cases, streams):
+            assert lib.crossquant_kernel_analysis(Xg.data_ptr(), *Xg.shape, Xg.stride(0), tg.data_ptr(), cg.data_ptr(), 0.15, 8,
+                                                  out["xrk"].data_ptr(), out["row_scale"].data_ptr(), out["col_scale"].data_ptr(),
+                                                  out["counters"].data_ptr(), st.cuda_stream) == 0
+    assert lib.crossquant_absmax_quantize_single_read(Zg.data_ptr(), 64, 256, 256, 0.15, 8, t.data_ptr(), c.data_ptr(), codes.data_ptr(), 0,
+                                                      a.data_ptr(), b.data_ptr(), 0, streams[20].cuda_stream) == 0
+    torch.cuda.synchronize()
+    for k, case in enumerate(cases):
+        check_analysis_case(case, k)
+    assert np.array_equal(host(codes), oracle.quantize(Z, *oracle.absmax(Z), 0.15, 8)["codes"])
+
+
+def test_captured_analyses_share_no_state(cq):
+    """Two graphs captured on one stream, replayed at the same time on two others while the capture stream itself runs analyses:
+    every call counts by itself.  A captured call therefore clears the caller's counters and adds to them."""
+    import torch
+    say("two graphs of analyses beside each other and beside eager ones")
+    cases = [analysis_case(T, I, seed) for T, I, seed in ((1500, 2048, 1), (2300, 1031, 2), (700, 4096, 3))]
+    call = lambda case: cq.crossquant_kernel_analysis(case[0], case[1], case[2], 0.15, 8, **case[3])
+    capture, others = torch.cuda.Stream(), [torch.cuda.Stream(), torch.cuda.Stream()]
+    graphs = []
+    for case in cases[:2]:
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1], stream=capture):
+            call(case)
+    for rep in range(3):
+        for case in cases:                                   # stale contents
+            for buf in case[3].values():
+                buf.fill_(3)
+        torch.cuda.synchronize()
+        for _ in range(6):
+            for graph, st in zip(graphs, others):
+                with torch.cuda.stream(st):
+                    graph.replay()
+            with torch.cuda.stream(capture):
+                call(cases[2])
+        torch.cuda.synchronize()
+        for k, case in enumerate(cases):
+            check_analysis_case(case, (rep, k))
+    names = launched(cq, lambda: call(cases[0]))
+    assert len(names) == 2 and "zero_counters" in names[0] and "analysis_kernel" in names[1], names
+
+
 def test_more_than_2_to_31_elements(cq):
     """70 000 x 65 544 = 4.59e9 elements (9.2 GB of binary16): every element offset past row 32 767
     needs more than 32 bits.  The oracle computes the maxima of the whole matrix; codes and
