@@ -3,10 +3,10 @@
 // A small layer is three calls of a few microseconds each on the GPU, and checking their tensors in Python and handing the
 // arguments through ctypes took 2 to 2.6 us a call beside the 3.4 to 4.8 of the library's own entry (a launch is 2.4).  Each
 // function here takes the tensors of one public call, all of its outputs among them, asks what binding.py asks of them, and
-// calls the C entry: 64 x 256 x 256 as
-// three calls 20.3 -> 11.1 us, which is what their kernels take.  Whatever is not the plain case (a subclass, a wrong type or
-// shape, another device, an output that has to be allocated) is not decided here: kNotPlain sends the caller through the checks
-// in binding.py, which say what is wrong or make the call.  Nothing is kept from one call for the next.
+// calls the C entry: 64 x 256 x 256 as three calls 20.3 -> 11.1 us, which is what their kernels take.  Whatever is not the
+// plain case (a subclass, a wrong type or shape, another device, an output that has to be allocated) is not decided here:
+// kNotPlain, after 0.1 us, sends the caller through the checks in binding.py, which say what is wrong or make the call.
+// Nothing is kept from one call for the next.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -20,8 +20,6 @@
 namespace {
 
 constexpr int kNotPlain = 1;             // no status of the library is positive
-
-struct NotPlain {};
 
 // The C entries, by the addresses that binding.py hands over: the library that it has loaded is the one that is called.
 decltype(&crossquant_absmax) p_absmax;
@@ -37,57 +35,86 @@ decltype(&crossquant_w4a4_linear) p_w4a4_linear;
 decltype(&crossquant_fp6_packed_bytes) p_fp6_packed_bytes;
 decltype(&crossquant_fp6_packed_weight_bytes) p_fp6_packed_weight_bytes;
 
-const at::Tensor& tensor(PyObject* o) {
-    if (Py_TYPE(o) != reinterpret_cast<PyTypeObject*>(THPVariableClass)) throw NotPlain{};      // subclasses have their own ideas
-    return THPVariable_Unpack(o);
+// The questions below answer false for what is not plain and leave their results unset.  (No exceptions: one costs as much as the
+// whole Python check, 4.6 us against 0.1 for a refused w8a8_linear.)
+
+// a tensor or a parameter; other subclasses have their own ideas
+bool tensor(PyObject* o, const at::Tensor*& t) {
+    if (!THPVariable_CheckExact(o)) return false;
+    t = &THPVariable_Unpack(o);
+    return true;
+}
+
+bool is(const at::Tensor& t, at::ScalarType type, c10::DeviceIndex device) {
+    return t.scalar_type() == type && t.is_cuda() && t.get_device() == device;
 }
 
 // the leading operand: a 2-D GPU tensor with unit stride along rows that do not overlap
 struct Matrix {
-    const at::Tensor& t;
+    const at::Tensor* t;
     int64_t rows, cols, ld;
     c10::DeviceIndex device;
     void* data;
-    Matrix(PyObject* o, at::ScalarType type) : t(tensor(o)) {
-        if (t.scalar_type() != type || t.dim() != 2 || !t.is_cuda()) throw NotPlain{};
-        rows = t.size(0);
-        cols = t.size(1);
-        ld = t.stride(0);
-        if (t.stride(1) != 1 || ld < cols) throw NotPlain{};
-        device = t.get_device();
-        data = t.data_ptr();
-    }
     void* stream() const { return c10::hip::getCurrentHIPStream(device).stream(); }
 };
+bool matrix(PyObject* o, at::ScalarType type, Matrix& X) {
+    if (!tensor(o, X.t) || X.t->scalar_type() != type || X.t->dim() != 2 || !X.t->is_cuda()) return false;
+    X.rows = X.t->size(0);
+    X.cols = X.t->size(1);
+    X.ld = X.t->stride(0);
+    if (X.t->stride(1) != 1 || X.ld < X.cols) return false;
+    X.device = X.t->get_device();
+    X.data = X.t->data_ptr();
+    return true;
+}
 
-void* buffer(PyObject* o, at::ScalarType type, c10::DeviceIndex device, int64_t n0, int64_t n1 = -1) {
-    const at::Tensor& t = tensor(o);
-    if (t.scalar_type() != type || !t.is_cuda() || t.get_device() != device || !t.is_contiguous()) throw NotPlain{};
-    if (n1 < 0 ? (t.dim() != 1 || t.size(0) != n0) : (t.dim() != 2 || t.size(0) != n0 || t.size(1) != n1)) throw NotPlain{};
-    return t.data_ptr();
+template <typename P>
+bool buffer(PyObject* o, P*& p, at::ScalarType type, c10::DeviceIndex device, int64_t n0, int64_t n1 = -1) {
+    const at::Tensor* t;
+    if (!tensor(o, t) || !is(*t, type, device) || !t->is_contiguous()) return false;
+    if (n1 < 0 ? (t->dim() != 1 || t->size(0) != n0) : (t->dim() != 2 || t->size(0) != n0 || t->size(1) != n1)) return false;
+    p = static_cast<P*>(t->data_ptr());
+    return true;
 }
-void* optional_buffer(PyObject* o, at::ScalarType type, c10::DeviceIndex device, int64_t n0, int64_t n1 = -1) {
-    return o == Py_None ? nullptr : buffer(o, type, device, n0, n1);
+template <typename P>
+bool optional_buffer(PyObject* o, P*& p, at::ScalarType type, c10::DeviceIndex device, int64_t n0, int64_t n1 = -1) {
+    p = nullptr;
+    return o == Py_None || buffer(o, p, type, device, n0, n1);
 }
-float* floats(PyObject* o, c10::DeviceIndex device, int64_t n) { return static_cast<float*>(buffer(o, at::kFloat, device, n)); }
+template <typename P>                    // (float or const float)
+bool floats(PyObject* o, P*& p, c10::DeviceIndex device, int64_t n) { return buffer(o, p, at::kFloat, device, n); }
 
-int64_t integer(PyObject* o) {
-    if (!PyLong_CheckExact(o)) throw NotPlain{};
-    const long long v = PyLong_AsLongLong(o);
-    if (v == -1 && PyErr_Occurred()) throw NotPlain{};
-    return v;
+bool integer(PyObject* o, int64_t& v) {
+    if (!PyLong_CheckExact(o)) return false;
+    int overflow;
+    v = PyLong_AsLongLongAndOverflow(o, &overflow);
+    return !overflow;
 }
-float real(PyObject* o) {
-    if (!PyFloat_CheckExact(o)) throw NotPlain{};
-    return (float)PyFloat_AS_DOUBLE(o);
+// alpha, also as an integer
+bool real(PyObject* o, float& v) {
+    int64_t whole;
+    if (PyFloat_CheckExact(o)) v = (float)PyFloat_AS_DOUBLE(o);
+    else if (integer(o, whole)) v = (float)(double)whole;
+    else return false;
+    return true;
 }
-int bits_of(PyObject* o, int64_t cols) {
-    const int64_t bits = integer(o);
-    if (bits != 8 && (bits != 4 || cols % 2)) throw NotPlain{};
-    return (int)bits;
+bool bits_of(PyObject* o, int64_t cols, int& bits) {
+    int64_t v;
+    if (!integer(o, v) || (v != 8 && (v != 4 || cols % 2))) return false;
+    bits = (int)v;
+    return true;
 }
-void* codes_of(PyObject* o, const Matrix& X, int bits) {
-    return bits == 8 ? buffer(o, at::kChar, X.device, X.rows, X.cols) : buffer(o, at::kByte, X.device, X.rows, X.cols / 2);
+bool codes_of(PyObject* o, const Matrix& X, int bits, void*& p) {
+    return bits == 8 ? buffer(o, p, at::kChar, X.device, X.rows, X.cols) : buffer(o, p, at::kByte, X.device, X.rows, X.cols / 2);
+}
+// an output of T rows of O values that may be padded
+bool output(PyObject* o, c10::DeviceIndex device, int64_t T, int64_t O, void*& p, int64_t& ldy) {
+    const at::Tensor* t;
+    if (!tensor(o, t) || !is(*t, at::kHalf, device) || t->dim() != 2 || t->size(0) != T || t->size(1) != O) return false;
+    ldy = t->stride(0);
+    if (t->stride(1) != 1 || ldy < O) return false;
+    p = t->data_ptr();
+    return true;
 }
 
 // the C entry without the interpreter's lock, as ctypes calls it
@@ -100,8 +127,8 @@ int unlocked(F&& f) {
     return status;
 }
 
-// N arguments, a status back; whatever is thrown on the way -- NotPlain, or torch's own errors, for instance for a tensor without
-// storage -- is for the Python checks to say
+// N arguments, a status back; what torch throws on the way, for instance for a tensor without storage, is for the Python checks
+// to say
 template <int N, typename F>
 PyObject* call(Py_ssize_t n, F&& f) {
     if (n != N) {
@@ -119,8 +146,9 @@ PyObject* call(Py_ssize_t n, F&& f) {
 
 PyObject* absmax(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return call<3>(n, [&] {
-        const Matrix X(a[0], at::kHalf);
-        float *t = floats(a[1], X.device, X.rows), *c = floats(a[2], X.device, X.cols);
+        Matrix X;
+        float *t, *c;
+        if (!matrix(a[0], at::kHalf, X) || !floats(a[1], t, X.device, X.rows) || !floats(a[2], c, X.device, X.cols)) return kNotPlain;
         void* s = X.stream();
         return unlocked([&] { return p_absmax(X.data, X.rows, X.cols, X.ld, t, c, s); });
     });
@@ -129,12 +157,16 @@ PyObject* absmax(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // X, t, c, alpha, bits, codes, xhat or None, row_scale, col_scale, zero_count or None
 PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return call<10>(n, [&] {
-        const Matrix X(a[0], at::kHalf);
-        const float *t = floats(a[1], X.device, X.rows), *c = floats(a[2], X.device, X.cols), alpha = real(a[3]);
-        const int bits = bits_of(a[4], X.cols);
-        void *codes = codes_of(a[5], X, bits), *xhat = optional_buffer(a[6], at::kHalf, X.device, X.rows, X.cols);
-        float *rs = floats(a[7], X.device, X.rows), *cs = floats(a[8], X.device, X.cols);
-        auto* z = static_cast<unsigned long long*>(optional_buffer(a[9], at::kLong, X.device, 1));
+        Matrix X;
+        const float *t, *c;
+        float alpha, *rs, *cs;
+        int bits;
+        void *codes, *xhat;
+        unsigned long long* z;
+        if (!matrix(a[0], at::kHalf, X) || !floats(a[1], t, X.device, X.rows) || !floats(a[2], c, X.device, X.cols) || !real(a[3], alpha) ||
+            !bits_of(a[4], X.cols, bits) || !codes_of(a[5], X, bits, codes) || !optional_buffer(a[6], xhat, at::kHalf, X.device, X.rows, X.cols) ||
+            !floats(a[7], rs, X.device, X.rows) || !floats(a[8], cs, X.device, X.cols) || !optional_buffer(a[9], z, at::kLong, X.device, 1))
+            return kNotPlain;
         void* s = X.stream();
         return unlocked([&] { return p_quantize(X.data, X.rows, X.cols, X.ld, t, c, alpha, bits, codes, xhat, rs, cs, z, s); });
     });
@@ -143,13 +175,15 @@ PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // X, alpha, bits, t, c, codes, xhat or None, row_scale, col_scale, zero_count or None
 PyObject* absmax_quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return call<10>(n, [&] {
-        const Matrix X(a[0], at::kHalf);
-        const float alpha = real(a[1]);
-        const int bits = bits_of(a[2], X.cols);
-        float *t = floats(a[3], X.device, X.rows), *c = floats(a[4], X.device, X.cols);
-        void *codes = codes_of(a[5], X, bits), *xhat = optional_buffer(a[6], at::kHalf, X.device, X.rows, X.cols);
-        float *rs = floats(a[7], X.device, X.rows), *cs = floats(a[8], X.device, X.cols);
-        auto* z = static_cast<unsigned long long*>(optional_buffer(a[9], at::kLong, X.device, 1));
+        Matrix X;
+        float alpha, *t, *c, *rs, *cs;
+        int bits;
+        void *codes, *xhat;
+        unsigned long long* z;
+        if (!matrix(a[0], at::kHalf, X) || !real(a[1], alpha) || !bits_of(a[2], X.cols, bits) || !floats(a[3], t, X.device, X.rows) ||
+            !floats(a[4], c, X.device, X.cols) || !codes_of(a[5], X, bits, codes) || !optional_buffer(a[6], xhat, at::kHalf, X.device, X.rows, X.cols) ||
+            !floats(a[7], rs, X.device, X.rows) || !floats(a[8], cs, X.device, X.cols) || !optional_buffer(a[9], z, at::kLong, X.device, 1))
+            return kNotPlain;
         void* s = X.stream();
         return unlocked([&] { return p_absmax_quantize(X.data, X.rows, X.cols, X.ld, alpha, bits, t, c, codes, xhat, rs, cs, z, s); });
     });
@@ -158,13 +192,17 @@ PyObject* absmax_quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // X, t, c, alpha, packed, xhat or None, row_scale, col_scale, zero_count or None
 PyObject* quantize_fp6(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return call<9>(n, [&] {
-        const Matrix X(a[0], at::kHalf);
+        Matrix X;
+        const float *t, *c;
+        float alpha, *rs, *cs;
+        void *packed, *xhat;
+        unsigned long long* z;
+        if (!matrix(a[0], at::kHalf, X)) return kNotPlain;
         const int64_t bytes = p_fp6_packed_bytes(X.rows, X.cols);
-        if (bytes < 0) throw NotPlain{};
-        const float *t = floats(a[1], X.device, X.rows), *c = floats(a[2], X.device, X.cols), alpha = real(a[3]);
-        void *packed = buffer(a[4], at::kByte, X.device, bytes), *xhat = optional_buffer(a[5], at::kHalf, X.device, X.rows, X.cols);
-        float *rs = floats(a[6], X.device, X.rows), *cs = floats(a[7], X.device, X.cols);
-        auto* z = static_cast<unsigned long long*>(optional_buffer(a[8], at::kLong, X.device, 1));
+        if (bytes < 0 || !floats(a[1], t, X.device, X.rows) || !floats(a[2], c, X.device, X.cols) || !real(a[3], alpha) ||
+            !buffer(a[4], packed, at::kByte, X.device, bytes) || !optional_buffer(a[5], xhat, at::kHalf, X.device, X.rows, X.cols) ||
+            !floats(a[6], rs, X.device, X.rows) || !floats(a[7], cs, X.device, X.cols) || !optional_buffer(a[8], z, at::kLong, X.device, 1))
+            return kNotPlain;
         void* s = X.stream();
         return unlocked([&] { return p_quantize_fp6(X.data, X.rows, X.cols, X.ld, t, c, alpha, packed, xhat, rs, cs, z, s); });
     });
@@ -172,27 +210,32 @@ PyObject* quantize_fp6(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 // a [B][S][I] GPU tensor with contiguous rows
 struct Batch {
-    const at::Tensor& t;
-    int64_t B, S, I;
+    const at::Tensor* t;
+    int64_t B, S, I, ld, step;
     c10::DeviceIndex device;
-    explicit Batch(PyObject* o) : t(tensor(o)) {
-        if (t.scalar_type() != at::kHalf || t.dim() != 3 || !t.is_cuda()) throw NotPlain{};
-        B = t.size(0);
-        S = t.size(1);
-        I = t.size(2);
-        if (t.stride(2) != 1 && I != 1) throw NotPlain{};
-        device = t.get_device();
-    }
+    void* data;
+    void* stream() const { return c10::hip::getCurrentHIPStream(device).stream(); }
 };
+bool batch(PyObject* o, Batch& X) {
+    if (!tensor(o, X.t) || X.t->scalar_type() != at::kHalf || X.t->dim() != 3 || !X.t->is_cuda()) return false;
+    X.B = X.t->size(0);
+    X.S = X.t->size(1);
+    X.I = X.t->size(2);
+    if (X.t->stride(2) != 1 && X.I != 1) return false;
+    X.ld = X.t->stride(1);
+    X.step = X.t->stride(0);
+    X.device = X.t->get_device();
+    X.data = X.t->data_ptr();
+    return true;
+}
 
 PyObject* absmax_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return call<3>(n, [&] {
-        const Batch X(a[0]);
-        auto *t = static_cast<float*>(buffer(a[1], at::kFloat, X.device, X.B, X.S)), *c = static_cast<float*>(buffer(a[2], at::kFloat, X.device, X.B, X.I));
-        const void* x = X.t.data_ptr();
-        const int64_t ld = X.t.stride(1), step = X.t.stride(0);
-        void* s = c10::hip::getCurrentHIPStream(X.device).stream();
-        return unlocked([&] { return p_absmax_batched(x, X.B, X.S, X.I, ld, step, t, c, s); });
+        Batch X;
+        float *t, *c;
+        if (!batch(a[0], X) || !buffer(a[1], t, at::kFloat, X.device, X.B, X.S) || !buffer(a[2], c, at::kFloat, X.device, X.B, X.I)) return kNotPlain;
+        void* s = X.stream();
+        return unlocked([&] { return p_absmax_batched(X.data, X.B, X.S, X.I, X.ld, X.step, t, c, s); });
     });
 }
 
@@ -200,31 +243,30 @@ PyObject* absmax_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* quantize_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
     at::Tensor codes, xhat, rs, cs, z;
     PyObject* status = call<8>(n, [&] {
-        const Batch X(a[0]);
-        const at::Tensor &t = tensor(a[1]), &c = tensor(a[2]);
-        const float alpha = real(a[3]);
-        const int64_t bits = integer(a[4]);
-        const bool want_codes = a[5] == Py_True, want_xhat = a[6] == Py_True && want_codes, want_count = a[7] == Py_True || !want_codes;
+        Batch X;
+        float alpha;
+        int bits;
+        if (!batch(a[0], X) || !real(a[3], alpha) || !bits_of(a[4], X.I, bits)) return kNotPlain;
         for (int i = 5; i < 8; ++i)
-            if (a[i] != Py_True && a[i] != Py_False) throw NotPlain{};
-        if (bits != 8 && (bits != 4 || X.I % 2)) throw NotPlain{};
-        for (const at::Tensor* v : {&t, &c})
-            if (v->scalar_type() != at::kFloat || !v->is_cuda() || v->get_device() != X.device || !v->is_contiguous() ||
-                v->numel() != X.B * (v == &t ? X.S : X.I)) throw NotPlain{};
-        auto empty = [&](at::IntArrayRef shape, at::ScalarType type) { return at::empty(shape, at::TensorOptions().dtype(type).device(X.t.device())); };
+            if (a[i] != Py_True && a[i] != Py_False) return kNotPlain;
+        const bool want_codes = a[5] == Py_True, want_xhat = a[6] == Py_True && want_codes, want_count = a[7] == Py_True || !want_codes;
+        const float* in[2];                                  // any shape that holds as many values
+        for (int i = 0; i < 2; ++i) {
+            const at::Tensor* v;
+            if (!tensor(a[1 + i], v) || !is(*v, at::kFloat, X.device) || !v->is_contiguous() || v->numel() != X.B * (i ? X.I : X.S)) return kNotPlain;
+            in[i] = static_cast<const float*>(v->data_ptr());
+        }
+        auto empty = [&](at::IntArrayRef shape, at::ScalarType type) { return at::empty(shape, at::TensorOptions().dtype(type).device(X.t->device())); };
         if (want_codes) codes = bits == 8 ? empty({X.B, X.S, X.I}, at::kChar) : empty({X.B, X.S, X.I / 2}, at::kByte);
         if (want_xhat) xhat = empty({X.B, X.S, X.I}, at::kHalf);
         rs = empty({X.B, X.S}, at::kFloat);
         cs = empty({X.B, X.I}, at::kFloat);
         if (want_count) z = empty({1}, at::kLong);
-        const void* x = X.t.data_ptr();
-        const int64_t ld = X.t.stride(1), step = X.t.stride(0);
-        const auto *tp = static_cast<const float*>(t.data_ptr()), *cp = static_cast<const float*>(c.data_ptr());
         void *codes_p = want_codes ? codes.data_ptr() : nullptr, *xhat_p = want_xhat ? xhat.data_ptr() : nullptr;
         auto *rs_p = static_cast<float*>(rs.data_ptr()), *cs_p = static_cast<float*>(cs.data_ptr());
         auto* z_p = want_count ? static_cast<unsigned long long*>(z.data_ptr()) : nullptr;
-        void* s = c10::hip::getCurrentHIPStream(X.device).stream();
-        return unlocked([&] { return p_quantize_batched(x, X.B, X.S, X.I, ld, step, tp, cp, alpha, (int)bits, codes_p, xhat_p, rs_p, cs_p, z_p, s); });
+        void* s = X.stream();
+        return unlocked([&] { return p_quantize_batched(X.data, X.B, X.S, X.I, X.ld, X.step, in[0], in[1], alpha, bits, codes_p, xhat_p, rs_p, cs_p, z_p, s); });
     });
     if (!status || PyLong_AsLong(status) != 0) return status;
     Py_DECREF(status);
@@ -242,47 +284,56 @@ PyObject* quantize_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return out;
 }
 
+// 4 or 8 for the calls that write no codes, whatever the number of channels
+bool count_bits(PyObject* o, int& bits) { return bits_of(o, 0, bits); }
+
 // X, t, c, alpha, bits, row_scale and col_scale or None, zero_count
 PyObject* kernel_count(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return call<8>(n, [&] {
-        const Matrix X(a[0], at::kHalf);
-        const float *t = floats(a[1], X.device, X.rows), *c = floats(a[2], X.device, X.cols), alpha = real(a[3]);
-        const int64_t bits = integer(a[4]);
-        if (bits != 4 && bits != 8) throw NotPlain{};
-        if ((a[5] == Py_None) != (a[6] == Py_None)) throw NotPlain{};
-        auto* rs = static_cast<float*>(optional_buffer(a[5], at::kFloat, X.device, X.rows));
-        auto* cs = static_cast<float*>(optional_buffer(a[6], at::kFloat, X.device, X.cols));
-        auto* z = static_cast<unsigned long long*>(buffer(a[7], at::kLong, X.device, 1));
+        Matrix X;
+        const float *t, *c;
+        float alpha, *rs, *cs;
+        int bits;
+        unsigned long long* z;
+        if (!matrix(a[0], at::kHalf, X) || !floats(a[1], t, X.device, X.rows) || !floats(a[2], c, X.device, X.cols) || !real(a[3], alpha) ||
+            !count_bits(a[4], bits) || (a[5] == Py_None) != (a[6] == Py_None) || !optional_buffer(a[5], rs, at::kFloat, X.device, X.rows) ||
+            !optional_buffer(a[6], cs, at::kFloat, X.device, X.cols) || !buffer(a[7], z, at::kLong, X.device, 1))
+            return kNotPlain;
         void* s = X.stream();
-        return unlocked([&] { return p_kernel_count(X.data, X.rows, X.cols, X.ld, t, c, alpha, (int)bits, rs, cs, z, s); });
+        return unlocked([&] { return p_kernel_count(X.data, X.rows, X.cols, X.ld, t, c, alpha, bits, rs, cs, z, s); });
     });
 }
 
 // X, t, c, alpha, bits, xrk or None, row_scale and col_scale or None, counters
 PyObject* kernel_analysis(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return call<9>(n, [&] {
-        const Matrix X(a[0], at::kHalf);
-        const float *t = floats(a[1], X.device, X.rows), *c = floats(a[2], X.device, X.cols), alpha = real(a[3]);
-        const int64_t bits = integer(a[4]);
-        if (bits != 4 && bits != 8) throw NotPlain{};
-        void* xrk = optional_buffer(a[5], at::kHalf, X.device, X.rows, X.cols);
-        if ((a[6] == Py_None) != (a[7] == Py_None)) throw NotPlain{};
-        auto* rs = static_cast<float*>(optional_buffer(a[6], at::kFloat, X.device, X.rows));
-        auto* cs = static_cast<float*>(optional_buffer(a[7], at::kFloat, X.device, X.cols));
-        auto* counters = static_cast<unsigned long long*>(buffer(a[8], at::kLong, X.device, 3));
+        Matrix X;
+        const float *t, *c;
+        float alpha, *rs, *cs;
+        int bits;
+        void* xrk;
+        unsigned long long* counters;
+        if (!matrix(a[0], at::kHalf, X) || !floats(a[1], t, X.device, X.rows) || !floats(a[2], c, X.device, X.cols) || !real(a[3], alpha) ||
+            !count_bits(a[4], bits) || !optional_buffer(a[5], xrk, at::kHalf, X.device, X.rows, X.cols) || (a[6] == Py_None) != (a[7] == Py_None) ||
+            !optional_buffer(a[6], rs, at::kFloat, X.device, X.rows) || !optional_buffer(a[7], cs, at::kFloat, X.device, X.cols) ||
+            !buffer(a[8], counters, at::kLong, X.device, 3))
+            return kNotPlain;
         void* s = X.stream();
-        return unlocked([&] { return p_kernel_analysis(X.data, X.rows, X.cols, X.ld, t, c, alpha, (int)bits, xrk, rs, cs, counters, s); });
+        return unlocked([&] { return p_kernel_analysis(X.data, X.rows, X.cols, X.ld, t, c, alpha, bits, xrk, rs, cs, counters, s); });
     });
 }
 
-// qx, row_scale, qw, w_scale, Y (contiguous)
+// qx, row_scale, qw, w_scale, Y
 PyObject* w8a8_linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return call<5>(n, [&] {
-        const Matrix qx(a[0], at::kChar), qw(a[2], at::kChar);
-        if (!qx.t.is_contiguous() || !qw.t.is_contiguous() || qx.cols != qw.cols || qw.device != qx.device) throw NotPlain{};
-        const float *rs = floats(a[1], qx.device, qx.rows), *ws = floats(a[3], qx.device, qw.rows);
-        void* Y = buffer(a[4], at::kHalf, qx.device, qx.rows, qw.rows);
-        const int64_t ldy = THPVariable_Unpack(a[4]).stride(0);
+        Matrix qx, qw;
+        const float *rs, *ws;
+        void* Y;
+        int64_t ldy;
+        if (!matrix(a[0], at::kChar, qx) || !matrix(a[2], at::kChar, qw) || !qx.t->is_contiguous() || !qw.t->is_contiguous() ||
+            qx.cols != qw.cols || qw.device != qx.device || !floats(a[1], rs, qx.device, qx.rows) || !floats(a[3], ws, qx.device, qw.rows) ||
+            !output(a[4], qx.device, qx.rows, qw.rows, Y, ldy))
+            return kNotPlain;
         void* s = qx.stream();
         return unlocked([&] {
             return p_w8a8_linear(static_cast<const int8_t*>(qx.data), rs, static_cast<const int8_t*>(qw.data), ws, qx.rows, qx.cols, qw.rows, Y, ldy, nullptr, s);
@@ -290,20 +341,21 @@ PyObject* w8a8_linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-// qx_fp6, row_scale, qw_fp6, w_scale, T, I, O, Y (contiguous)
+// qx_fp6, row_scale, qw_fp6, w_scale, T, I, O, Y
 PyObject* w4a4_linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return call<8>(n, [&] {
-        const int64_t T = integer(a[4]), I = integer(a[5]), O = integer(a[6]);
-        const at::Tensor &qx = tensor(a[0]), &qw = tensor(a[2]);
-        if (!qx.is_cuda()) throw NotPlain{};
-        const c10::DeviceIndex device = qx.get_device();
-        for (const at::Tensor* q : {&qx, &qw})
-            if (q->scalar_type() != at::kByte || !q->is_cuda() || q->get_device() != device || !q->is_contiguous()) throw NotPlain{};
-        if (qx.numel() != p_fp6_packed_bytes(T, I) || qw.numel() != p_fp6_packed_weight_bytes(O, I)) throw NotPlain{};
-        const float *rs = floats(a[1], device, T), *ws = floats(a[3], device, O);
-        void* Y = buffer(a[7], at::kHalf, device, T, O);
-        const int64_t ldy = THPVariable_Unpack(a[7]).stride(0);
-        const void *x = qx.data_ptr(), *w = qw.data_ptr();
+        const at::Tensor* q[2];
+        int64_t T, I, O, ldy;
+        const float *rs, *ws;
+        void* Y;
+        if (!tensor(a[0], q[0]) || !tensor(a[2], q[1]) || !q[0]->is_cuda() || !integer(a[4], T) || !integer(a[5], I) || !integer(a[6], O))
+            return kNotPlain;
+        const c10::DeviceIndex device = q[0]->get_device();
+        for (int i = 0; i < 2; ++i)
+            if (!is(*q[i], at::kByte, device) || !q[i]->is_contiguous() ||
+                q[i]->numel() != (i ? p_fp6_packed_weight_bytes(O, I) : p_fp6_packed_bytes(T, I))) return kNotPlain;
+        if (!floats(a[1], rs, device, T) || !floats(a[3], ws, device, O) || !output(a[7], device, T, O, Y, ldy)) return kNotPlain;
+        const void *x = q[0]->data_ptr(), *w = q[1]->data_ptr();
         void* s = c10::hip::getCurrentHIPStream(device).stream();
         return unlocked([&] { return p_w4a4_linear(x, rs, w, ws, T, I, O, Y, ldy, nullptr, s); });
     });

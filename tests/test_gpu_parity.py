@@ -2341,3 +2341,45 @@ def test_native_and_checked_forms_of_a_call_agree(cq, monkeypatch, name):
         if "alpha" in kw:
             got, want = both({**kw, "alpha": alpha})
             assert got == want, alpha
+
+
+def test_usual_calls_are_made_natively(cq, monkeypatch):
+    """Outputs with padded rows, weights and scales held as parameters and a whole alpha take the native form, with the results of the
+    checked form and nothing written between the rows."""
+    import torch
+    from paper_2410_07505_amd import binding
+    say("padded outputs, parameters, alpha = 1 in the native form")
+    calls = fast_and_checked_calls(cq)
+    held = lambda v: torch.nn.Parameter(v, requires_grad=False)
+    native = binding._fast
+
+    def run(name, **changes):
+        fn, kw = calls[name]
+        kw = {**kw, **changes}
+        statuses, outs = [], []
+
+        class Watched:
+            def __getattr__(self, entry):
+                return lambda *args: (statuses.append(getattr(native, entry)(*args)), statuses[-1])[1]
+        for form in (Watched(), binding._NoFastcall):
+            monkeypatch.setattr(binding, "_fast", form)
+            for v in kw.values():
+                if isinstance(v, torch.Tensor) and v is changes.get("Y"):
+                    v.fill_(5)
+            out = fn(**kw)
+            torch.cuda.synchronize()
+            outs.append([o.cpu().numpy().tobytes() for o in (out if isinstance(out, tuple) else (out,)) if o is not None])
+        assert [type(v) for v in statuses] in ([int], [tuple]) and statuses[0] != binding._NOT_PLAIN, (name, statuses)
+        assert outs[0] == outs[1], name
+
+    for name, pad in (("w8a8_linear", 5), ("w8a8_linear", 8), ("w4a4_linear", 8)):
+        T, O = calls[name][1]["Y"].shape
+        buf = torch.full((T, O + pad), 7.0, dtype=torch.float16, device="cuda")
+        run(name, Y=buf[:, :O])
+        assert bool((buf[:, O:] == 7.0).all())
+    run("w8a8_linear", qw=held(calls["w8a8_linear"][1]["qw"]), w_scale=held(calls["w8a8_linear"][1]["w_scale"]))
+    run("w4a4_linear", qw_fp6=held(calls["w4a4_linear"][1]["qw_fp6"]), w_scale=held(calls["w4a4_linear"][1]["w_scale"]))
+    run("quantize", c=held(calls["quantize"][1]["c"]))
+    for name in ("quantize", "quantize4", "absmax_quantize", "quantize_fp6", "quantize_batched", "count_batched", "kernel_count", "kernel_analysis"):
+        for alpha in (0, 1):
+            run(name, alpha=alpha)
