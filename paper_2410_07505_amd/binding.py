@@ -101,19 +101,22 @@ _NOT_PLAIN = 1
 
 
 class _NoFastcall:
-    """Stands in where the native part was built for another Python or torch: nothing is plain."""
+    """Stands in where there is no native part for this Python and torch: nothing is plain."""
     absmax = quantize = absmax_quantize = quantize_fp6 = absmax_batched = quantize_batched = staticmethod(lambda *args: _NOT_PLAIN)
     kernel_count = kernel_analysis = w8a8_linear = w4a4_linear = absmax
 
 
 def _load_fastcall():
+    # (it reads torch's tensors through its headers: only with the very torch that it was built for)
     if not os.path.exists(_FASTCALL_PATH):
-        raise ImportError("%s is not built. Run `python -m paper_2410_07505_amd.build`." % _FASTCALL_PATH)
+        return _NoFastcall
     try:
         spec = importlib.util.spec_from_file_location("_fastcall", _FASTCALL_PATH)
         module = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(module)
     except ImportError:                       # (an undefined symbol, or a library that is not there)
+        return _NoFastcall
+    if getattr(module, "TORCH_VERSION", None) != str(torch.__version__):
         return _NoFastcall
     assert module.NOT_PLAIN == _NOT_PLAIN
     module.set_entries(*(ctypes.cast(getattr(lib, n), _vp).value for n in _FAST_ENTRIES))

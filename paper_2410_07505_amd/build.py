@@ -50,13 +50,26 @@ def _compile(src: str, extra) -> str:
     return obj
 
 
+def _torch_version(torch_dir: str) -> str:
+    spec = importlib.util.spec_from_file_location("torch_version", os.path.join(torch_dir, "version.py"))
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module.__version__
+
+
 def _build_fastcall() -> None:
-    torch = importlib.util.find_spec("torch").submodule_search_locations[0]
+    if os.path.exists(FASTCALL):
+        os.remove(FASTCALL)                   # none rather than one of another library's age
+    found = importlib.util.find_spec("torch")
+    if found is None:
+        raise RuntimeError("no torch to build the binding's native part for")
+    torch = found.submodule_search_locations[0]
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     tmp = FASTCALL + ".tmp%d" % os.getpid()
     includes = [os.path.join(torch, "include"), os.path.join(torch, "include", "torch", "csrc", "api", "include"),
                 os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           '-DCQ_TORCH_VERSION="%s"' % _torch_version(torch),
            *("-I" + i for i in includes), os.path.join(CSRC, "cq_fastcall.cpp"), "-o", tmp,
            "-L" + os.path.join(torch, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
@@ -66,20 +79,25 @@ def _build_fastcall() -> None:
 
 
 def build(extra_flags=(), verbose: bool = False) -> str:
+    """The library; and the binding's native part, without which every call goes through the Python checks, where there is a
+    torch with headers and a g++ to build it: where that fails, the library is built all the same and a line says so."""
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         fastcall = ex.submit(_build_fastcall)
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), SOURCES))
-        fastcall.result()
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if res.returncode != 0:
         raise RuntimeError("link failed:\n" + res.stdout)
     os.replace(tmp, LIB)
+    failure = fastcall.exception()
+    if failure is not None:
+        sys.stderr.write("the binding's native part is not built: %s\n" % failure)
     if verbose:
         print("built", LIB)
-        print("built", FASTCALL)
+        if failure is None:
+            print("built", FASTCALL)
     return LIB
 
 

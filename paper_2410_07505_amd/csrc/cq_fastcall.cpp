@@ -395,7 +395,7 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, 
 
 PyMODINIT_FUNC PyInit__fastcall() {
     PyObject* m = PyModule_Create(&module);
-    if (m && PyModule_AddIntConstant(m, "NOT_PLAIN", kNotPlain) < 0) {
+    if (m && (PyModule_AddIntConstant(m, "NOT_PLAIN", kNotPlain) < 0 || PyModule_AddStringConstant(m, "TORCH_VERSION", CQ_TORCH_VERSION) < 0)) {
         Py_DECREF(m);
         return nullptr;
     }

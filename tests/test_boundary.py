@@ -380,3 +380,54 @@ def test_refusals_by_the_native_form_cost_next_to_nothing(cq):
                 call()
             best = min(best, (time.perf_counter() - start) / 100)
         assert best < 1.5e-6, best
+
+
+def test_package_loads_without_a_native_part_for_this_python_and_torch(cq, monkeypatch, tmp_path):
+    """No native part (another Python looks for another file name), or one that was built for another torch, whose tensors it would
+    misread: the Python checks and ctypes serve every call."""
+    import importlib.util
+
+    import torch
+    from paper_2410_07505_amd import binding
+    assert binding._load_fastcall().TORCH_VERSION == str(torch.__version__)
+    with monkeypatch.context() as m:
+        m.setattr(torch, "__version__", "0.0.1")
+        assert binding._load_fastcall() is binding._NoFastcall
+    monkeypatch.setattr(binding, "_FASTCALL_PATH", str(tmp_path / "_fastcall.none.so"))
+    assert binding._load_fastcall() is binding._NoFastcall
+    (tmp_path / "libcrossquant.so").symlink_to(cq.LIB_PATH)              # the whole module, beside a library only
+    (tmp_path / "binding.py").write_text(open(binding.__file__).read())
+    spec = importlib.util.spec_from_file_location("binding_without_native_part", tmp_path / "binding.py")
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    assert module._fast is module._NoFastcall and module.crossquant_version() == cq.crossquant_version()
+    with pytest.raises(ValueError, match="GPU"):
+        z = torch.zeros
+        module.crossquant_absmax(z((2, 8), dtype=torch.float16), t=z(2), c=z(8))
+
+
+@pytest.mark.parametrize("missing", ["torch", "g++"])
+def test_library_builds_without_the_native_part(monkeypatch, tmp_path, capsys, missing):
+    """The library needs neither torch nor g++.  (A stand-in for hipcc: what is asked is whether build() gets that far.)  A native part
+    that was there before goes: it may not fit the new library."""
+    import importlib.util
+
+    from paper_2410_07505_amd import build
+    hipcc = tmp_path / "hipcc"
+    hipcc.write_text('#!/bin/sh\nwhile [ $# -gt 1 ]; do [ "$1" = -o ] && echo built > "$2"; shift; done\n')
+    hipcc.chmod(0o755)
+    monkeypatch.setenv("HIPCC", str(hipcc))
+    for name in ("LIB", "FASTCALL", "OBJ"):
+        monkeypatch.setattr(build, name, str(tmp_path / name))
+    (tmp_path / "FASTCALL").write_text("old")
+    if missing == "torch":
+        find = importlib.util.find_spec
+        monkeypatch.setattr(importlib.util, "find_spec", lambda name, *a: None if name == "torch" else find(name, *a))
+    else:
+        (tmp_path / "bin").mkdir()
+        (tmp_path / "bin" / "g++").write_text("#!/bin/sh\nexit 1\n")
+        (tmp_path / "bin" / "g++").chmod(0o755)
+        monkeypatch.setenv("PATH", "%s:%s" % (tmp_path / "bin", os.environ["PATH"]))
+    assert build.build() == str(tmp_path / "LIB") and (tmp_path / "LIB").read_text() == "built\n"
+    assert not (tmp_path / "FASTCALL").exists()
+    assert "native part is not built" in capsys.readouterr().err
