@@ -200,8 +200,17 @@ constexpr float kTinyFactor = 8.673617379884035e-19f;   // 2^-60: both products 
 
 __device__ __forceinline__ bool tiny_factor(float f) { return f != 0.0f && f < kTinyFactor; }
 
+// max(|a|, |b|, |c|), NaN where one of them is (written out: the compiler makes two-operand steps of some of a chain of these)
+__device__ __forceinline__ float ordered_max3(float a, float b, float c) {
+    float r;
+    asm("v_maximum3_f32 %0, |%1|, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
 // The fast part: m, q from the reciprocals; returns whether this wave's row piece has to be redone exactly
-// (wave-uniform).
+// (wave-uniform).  An element that is no number (outside the contract) does not ask for that, its code is the low bits of m, 0;
+// ORDERED: it does too.
+template <bool ORDERED = false>
 __device__ __forceinline__ bool quantize8_fast(const uint4& v, float ra, const float (&rb)[8], float qmax,
                                                float (&m)[8], float (&q)[8], bool tiny) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -217,9 +226,9 @@ __device__ __forceinline__ bool quantize8_fast(const uint4& v, float ra, const f
         q[e] = m[e] - kMagic;
         const float f = __builtin_fmaf((float)h[e], k, -q[e]);
         score = __builtin_fmaxf(score, __builtin_fmaf(__builtin_fabsf(q[e]), kTieTol, __builtin_fabsf(f)));
-        big = __builtin_fmaxf(big, __builtin_fabsf(q[e]));
+        if (!ORDERED) big = __builtin_fmaxf(big, __builtin_fabsf(q[e]));
+        else if (e & 1) big = ordered_max3(e == 1 ? q[1] : big, q[e - 1], q[e]);
     }
-    // !(big <= qmax) also catches a NaN from an overflowed product
     return __any(score >= 0.5f - kTieTol || !(big <= qmax) || tiny);
 }
 // The exact part: the correctly rounded division and the clamp, for all 8 elements.

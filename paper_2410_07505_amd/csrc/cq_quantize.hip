@@ -213,9 +213,9 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
             const int live = row_ok ? cols_here : 0;         // columns of this row that may be stored
             const int nvalid = max(0, min(8, live - lane * 8));     // ... of this lane's eight
             // count, pack and store one row piece; returns the lane's number of non-zero codes in it
-            auto emit = [&](const float (&m)[8], const float (&q)[8]) -> uint32_t {
+            auto emit = [&](const float (&m)[8], const float (&q)[8], const float (&ordered_q)[8]) -> uint32_t {
                 const uint32_t nz = COUNT ? count_nonzero8_lane(m) : 0u;
-                if (MODE == 3) fp6_batch_row(f6, q, u);
+                if (MODE == 3) fp6_batch_row(f6, ordered_q, u);
                 if (!BUF) {
                     if (MODE == 1) store_piece<8, uint8_t>(pack_codes_i8(m), codes + (int64_t)rr * I + col0 + lane * 8, nvalid);
                     if (MODE == 2)                           // (the channel count is even: whole bytes)
@@ -241,12 +241,20 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
             // (3 per element) on the common path.
             float m[8], q[8];
             uint32_t nz;
-            if (__builtin_expect(quantize8_fast(v[u], ra, rb, qmax, m, q, b_tiny || tiny_factor(a)), 0)) {
+            // (The conversion to FP6 makes the largest code of what is no number: such an element goes through here too.  The maximum that
+            // sees it is the same instruction's other form, and costs nothing.)
+            if (__builtin_expect(quantize8_fast<MODE == 3>(v[u], ra, rb, qmax, m, q, b_tiny || tiny_factor(a)), 0)) {
                 float mx[8], qx[8];
-                quantize8_exact(v[u], a, b, qmax, mx, qx);
-                nz = emit(mx, qx);
+                if (MODE == 3 && !quantize8_fast(v[u], ra, rb, qmax, m, q, b_tiny || tiny_factor(a))) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) qx[e] = q[e] == q[e] ? q[e] : 0.0f;
+                    nz = emit(m, q, qx);
+                } else {
+                    quantize8_exact(v[u], a, b, qmax, mx, qx);
+                    nz = emit(mx, qx, qx);
+                }
             } else {
-                nz = emit(m, q);
+                nz = emit(m, q, q);
             }
             if (COUNT) nonzero_lane += row_ok ? nz : 0u;
             __builtin_amdgcn_sched_barrier(0);               // rows one after the other: keeps scalar register pressure down

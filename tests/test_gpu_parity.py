@@ -2152,6 +2152,30 @@ def test_quantize_straight_to_fp6(cq, T, I):
         assert np.array_equal(host(cq.crossquant_pack_fp6(nib)), want)
 
 
+@pytest.mark.parametrize("T,I", [(1, 128), (39, 1536), (70, 640)])
+def test_fp6_codes_of_elements_that_are_no_numbers(cq, T, I):
+    """Outside the contract, but the same in every form of the codes: what the INT4 call makes of infinities and NaN, with maxima
+    formed from them, without them, and with maxima of zero, the FP6 call makes of them too."""
+    import torch
+    say("fp6 codes of inf and NaN: %dx%d" % (T, I))
+    g = torch.Generator(device="cuda").manual_seed(T + I)
+    X = torch.randn((T, I), generator=g, device="cuda").half()
+    at = torch.randint(0, T * I, (max(4, T * I // 400),), generator=g, device="cuda")
+    for bad in (float("nan"), float("inf"), -float("inf")):
+        Xb = X.clone()
+        Xb.view(-1)[at] = bad
+        t, c = cq.crossquant_absmax(Xb)
+        t0, c0 = cq.crossquant_absmax(X)
+        tz, cz = t0.clone(), c0.clone()
+        tz[::3], cz[::5] = 0.0, 0.0
+        for tt, cc in ((t, c), (t0, c0), (tz, cz), (t0, c)):
+            for want_xhat in (False, True):
+                nib, xhat, a, b, z = cq.crossquant_quantize(Xb, tt, cc, 0.15, 4, want_xhat=want_xhat)
+                packed, xhat6, a6, b6, z6 = cq.crossquant_quantize_fp6(Xb, tt, cc, 0.15, want_xhat=want_xhat)
+                assert torch.equal(packed, cq.crossquant_pack_fp6(nib)), bad
+                assert torch.equal(z, z6) and (xhat is None or torch.equal(xhat.view(torch.int16), xhat6.view(torch.int16))), bad
+
+
 @pytest.mark.parametrize("kind,T,I", [("int8", 1, 8), ("int8", 70, 520), ("int8", 37, 1031), ("int4", 33, 512), ("int4", 70, 518),
                                       ("fp6", 1, 128), ("fp6", 45, 640)])
 def test_codes_without_the_zero_count(cq, kind, T, I):
