@@ -211,7 +211,7 @@ analysis_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, const
         for (int w = 0; w < kWaves; ++w) s += lds_cnt[w][threadIdx.x];
         if (slot < 0) {                                     // no state: the caller's counters, cleared before
             if (s) atomicAdd(&counters[threadIdx.x], s);
-        } else if (launch_sum(g_analysis_state[slot][threadIdx.x], s)) {
+        } else if (launch_sum(g_analysis_state[slot][threadIdx.x], s, gridDim.x > 4 * kCountGroups)) {
             counters[threadIdx.x] = s;                      // every other block has added
         }
     }

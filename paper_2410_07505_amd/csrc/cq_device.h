@@ -324,13 +324,10 @@ __device__ __forceinline__ bool ticketed_add(unsigned long long* word, unsigned 
     return true;
 }
 // Adds to one word queue up (8.4 ns each: 512 blocks that end together wait 4.3 us), so the blocks of a larger launch add in
-// kCountGroups groups first, each on a 128-byte line of its own, and the groups' last blocks to the launch's word.  Count-only
-// call 4096 x 4096 11.0 -> 7.7 us, 1024 x 8192 7.8 -> 6.2, 512 x 4096 5.5 -> 5.3, INT4 with the dequantized matrix 32 x 128 x 4096 14.7
-// -> 13.4; where the blocks end one by one the second round trip shows (3000 x 3000 9.3 -> 9.8).
+// kCountGroups groups first, each on a 128-byte line of its own, and the groups' last blocks to the launch's word.
 constexpr int kCountGroups = 16, kCountLine = 16;            // words a line has
 constexpr int kCountWords = (1 + kCountGroups) * kCountLine; // of a stream slot
-__device__ __forceinline__ bool launch_sum(unsigned long long* state, unsigned long long& sum) {
-    const bool groups = gridDim.x > 4 * kCountGroups;        // uniform
+__device__ __forceinline__ bool launch_sum(unsigned long long* state, unsigned long long& sum, bool groups) {
     const unsigned g = blockIdx.x % kCountGroups;
     if (!ticketed_add(groups ? state + (1 + g) * kCountLine : state, sum,
                       groups ? (gridDim.x - g + kCountGroups - 1) / kCountGroups : gridDim.x)) return false;

@@ -72,7 +72,7 @@ __global__ void __launch_bounds__(kWaves * kLanes)
 quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx, const float* __restrict__ t_vec,
                        const float* __restrict__ c_vec, double alpha, int qmax_i, float* __restrict__ a_out,
                        float* __restrict__ b_out, uint8_t* __restrict__ codes, uint16_t* __restrict__ xhat,
-                       unsigned long long* __restrict__ zero_count, int slot, int n_col_chunks, int nb,
+                       unsigned long long* __restrict__ zero_count, int slot, bool groups, int n_col_chunks, int nb,
                        int blocks_per_matrix, int64_t matrix_stride) {
     __shared__ uint32_t lds_cnt[kWaves];
     __shared__ float lds_b[kColsPerWave];
@@ -289,9 +289,7 @@ quantize_stream_kernel(const uint16_t* __restrict__ X, int T, int I, int64_t ldx
             for (int w = 0; w < kWaves; ++w) s += lds_cnt[w];
             if (slot >= 0) {
                 unsigned long long sum = s;
-                // (launches whose outputs stream end one block after the other: 4096 x 8192 25.8 us, 26.1 with groups)
-                if (STREAM ? ticketed_add(g_zero_state[slot], sum, gridDim.x) : launch_sum(g_zero_state[slot], sum))
-                    *zero_count = sum;                                           // every other block has added
+                if (launch_sum(g_zero_state[slot], sum, groups)) *zero_count = sum;      // every other block has added
             } else if (s) {
                 atomicAdd(zero_count, (unsigned long long)s);                    // caller's counter, cleared before
             }
@@ -340,7 +338,19 @@ hipError_t launch_mode(const uint16_t* X, int B, int T, int I, int64_t ldx, int6
                                                     : &quantize_stream_kernel<MODE, XHAT, true, false, true>)
                                       : (!buf ? &quantize_stream_kernel<MODE, XHAT, false, false, kCounts>
                                               : &quantize_stream_kernel<MODE, XHAT, true, false, kCounts>);
-    kernel<<<grid, block, 0, stream>>>(X, T, I, ldx, t, c, alpha, qmax, a, b, codes, xhat, zc, state, ncc, nb, ncc * nrc,
+    // Groups (launch_sum) where enough blocks end together that their adds queue up, single : grouped us:
+    //   vector layout  INT8, count only  INT8 codes 282 x 4096 (72 blocks) 6.3 : 6.5, 1617 x 640 (102) 6.4 : 6.5, 3687 x 128 (116) 6.6 : 6.3, 1024 x 8192 (256)
+    //                                    9.9 : 8.2; count 1024 x 8192 8.0 : 5.9, 4096 x 4096 (512) 11.0 : 7.2
+    //                  INT4, FP6         FP6 783 x 1280 (75) 6.3 : 6.5, 313 x 3968 (80) 6.5 : 6.5, 3242 x 384 (102) 6.7 : 6.6, 1107 x 3456 (245) 8.5 : 6.7;
+    //                                    INT4 and xhat 3279 x 384 (103) 6.9 : 6.6, 923 x 3968 (232) 8.4 : 6.7
+    //   off it         INT8 codes 303 x 4967 (100) 7.0 : 7.3, 2257 x 947 (142) 7.4 : 7.6, 649 x 4118 (189) 7.9 : 7.4
+    // and not where they end one after the other: streamed outputs (4096 x 8192 25.8 : 26.1), INT8 and INT4 codes alone in blocks of
+    // three batches and more (4096 x 8192 21.4 : 21.8; FP6, with more work an element, 3768 x 6272 18.7 : 18.0), and codes alone in
+    // two batches with a second block on less than half of the CUs (3000 x 3000 10.6 : 10.9, FP6 10.6 : 11.0).
+    const bool alone = MODE != 0 && !XHAT;
+    const bool groups = n_blocks >= (!buf ? 160u : MODE >= 2 ? 80u : 104u) && !streamed &&
+                        !(alone && (nb == 2 ? n_blocks > 256 && n_blocks < 384 : nb > 2 && MODE != 3));
+    kernel<<<grid, block, 0, stream>>>(X, T, I, ldx, t, c, alpha, qmax, a, b, codes, xhat, zc, state, groups, ncc, nb, ncc * nrc,
                                        matrix_stride);
     return hipGetLastError();
 }

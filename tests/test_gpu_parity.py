@@ -2241,9 +2241,11 @@ def test_random_shapes_w4a4_fp6(cq):
         assert np.array_equal(bits16(host(Y)), bits16(Y_ref))
 
 
-# one column chunk, 32 rows a block: 64 blocks, which add to the launch's word, and 65, 80 and 107, which add in 16 groups of equal
-# and of different sizes first; 3 chunks in one launch of a batch
-@pytest.mark.parametrize("T,I", [(2048, 512), (2049, 512), (2560, 509), (3400, 512), (1100, 1300)])
+# one column chunk, 32 rows a block: 64 blocks, which add to the launch's word, and 65, 80 and 107, where the analysis kernel adds in
+# 16 groups of equal and of different sizes first; 79, 80, 103 and 104, off the vector layout 159 and 160, where the others begin
+# to; and of 64 rows 266 and 391, of 96 rows 344, where codes alone do and do not
+@pytest.mark.parametrize("T,I", [(2048, 512), (2049, 512), (2560, 509), (3400, 512), (1100, 1300), (2528, 512), (2560, 512), (3296, 512),
+                                 (3328, 512), (5088, 509), (5120, 509), (17000, 512), (25000, 512), (33000, 512)])
 def test_counts_of_launches_on_either_side_of_the_grouped_adds(cq, T, I):
     say("grouped adds: %dx%d" % (T, I))
     X = outliers(T, I, seed=T + I)
@@ -2254,6 +2256,8 @@ def test_counts_of_launches_on_either_side_of_the_grouped_adds(cq, T, I):
         assert int(cq.crossquant_kernel_count(Xg, t, c, alpha, bits)) == ref["Z"]
         assert int(cq.crossquant_quantize(Xg, t, c, alpha, bits, want_xhat=False)[4]) == ref["Z"]
         assert int(cq.crossquant_quantize(Xg, t, c, alpha, bits)[4]) == ref["Z"]
+        if bits == 4 and I % 128 == 0:
+            assert int(cq.crossquant_quantize_fp6(Xg, t, c, alpha)[4]) == ref["Z"]
         counters = cq.crossquant_kernel_analysis(Xg, t, c, alpha, bits)[1]
         assert int(counters[0]) == ref["Z"]
         assert int(counters[1]) == int((host(c)[None, :] >= host(t)[:, None]).sum())
