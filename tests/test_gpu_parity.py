@@ -2263,6 +2263,29 @@ def test_counts_of_launches_on_either_side_of_the_grouped_adds(cq, T, I):
         assert int(counters[1]) == int((host(c)[None, :] >= host(t)[:, None]).sum())
 
 
+@pytest.mark.parametrize("T,I", [(1, 8), (33, 512), (65, 520), (100, 24), (2049, 1024)])
+def test_counts_of_a_last_block_with_missing_rows(cq, T, I):
+    """The count-only kernel works on copies of the last row, under its factor, in place of rows past the end: an ordinary
+    last row, one of zeros and one whose quotients lie on the tie."""
+    import torch
+    say("missing rows: %dx%d" % (T, I))
+    X = outliers(T, I, seed=T + I)
+    for last in ("as it is", "zero", "on the tie"):
+        Xl, (t, c) = X.copy(), oracle.absmax(X)
+        t, c = t.copy(), c.copy()
+        if last == "zero":
+            Xl[-1], t[-1] = 0, 0
+        if last == "on the tie":                             # alpha = 1: x / (t / 127) = 1/2
+            Xl[-1], t[-1], c[:] = 0.5, 127.0, 1.0
+        for alpha in (0.15, 1.0):
+            a, b = torch.full((T + 1,), 7.0, device="cuda"), torch.full((I + 1,), 7.0, device="cuda")
+            z = cq.crossquant_kernel_count(gpu(Xl), gpu(t), gpu(c), alpha, 8, row_scale=a[:T], col_scale=b[:I])
+            ref = oracle.quantize(Xl, t, c, alpha, 8)
+            assert int(z) == ref["Z"], (last, alpha)
+            assert np.array_equal(bits32(host(a[:T])), bits32(ref["a"])) and np.array_equal(bits32(host(b[:I])), bits32(ref["b"]))
+            assert float(a[T]) == 7.0 and float(b[I]) == 7.0
+
+
 @pytest.mark.parametrize("T", [1, 3, 4, 5, 8, 9, 31, 33, 64, 65])
 @pytest.mark.parametrize("I,ldx", [(8, 8), (504, 512), (520, 520), (4096, 4104), (4104, 4104), (8192, 8192), (8200, 8200)])
 def test_absmax_of_few_tokens(cq, T, I, ldx):
