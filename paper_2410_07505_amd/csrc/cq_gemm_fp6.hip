@@ -468,13 +468,16 @@ gemm_f6_ring_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ r
 // 8 waves = WM x WN wave tiles of 16 MT tokens x 64 channels times WK shares of the contraction, whose partial sums
 // meet in LDS.  A step is 128 WK elements; a slot holds [WK][(TM + TN) / 32 row blocks][two fragments along K].  Bound, as
 // there, by what a CU takes in from its L2, and for a decode step by the weights' way from HBM.
+// MU: the first activation tiles of a wave, which alone hold tokens (T <= 16 in tiles of 32, half of whose partial sums would change
+// hands for nothing: 1 x 384 x 2728 5.7 -> 5.5 us, 16 x 512 x 1024 6.0 -> 5.8).
 // ---------------------------------------------------------------------------------------------------------------
-template <int MT, int WM, int WN, int WK, int S, bool ONCE>
+template <int MT, int WM, int WN, int WK, int S, bool ONCE, int MU>
 __global__ void __launch_bounds__(64 * kSplitWaves)
 gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ row_scale,
                       const uint8_t* __restrict__ qw6, const float* __restrict__ w_scale, int T, int I, int O,
                       uint16_t* __restrict__ Y, int64_t ldy, int32_t* __restrict__ acc_debug, int tiles_m, int total) {
     static_assert(WM * WN * WK == kSplitWaves && MT % 2 == 0, "8 waves, whole row blocks");
+    static_assert(MU == MT || (MU < MT && WM == 1), "the first tiles of the block's rows");
     constexpr int NT = 4, TM = 16 * MT * WM, TN = 64 * WN;
     constexpr int kRbA = TM / 32, kRb = (TM + TN) / 32, kPair = 2 * kFragBytes;
     constexpr int kSlot = WK * kRb * kPair, kRequests = kSlot / 1024;
@@ -530,7 +533,7 @@ gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__
                            lds + min(wave * N + n, kRequests - 1) * 1024);
         };
         struct Frags {
-            frag6 a[MT], b[NT];
+            frag6 a[MU], b[NT];
         };
         const int share_base = wk * kRb * kPair;
         auto read = [&](Frags& f, int slot) {
@@ -538,18 +541,18 @@ gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__
 #pragma unroll
             for (int ni = 0; ni < NT; ++ni) f.b[ni] = read_tile(s, kRbA + 2 * wn, ni, fl);
 #pragma unroll
-            for (int mi = 0; mi < MT; ++mi) f.a[mi] = read_tile(s, wm * MT / 2, mi, fl);
+            for (int mi = 0; mi < MU; ++mi) f.a[mi] = read_tile(s, wm * MT / 2, mi, fl);
         };
-        v4f acc[MT][NT];
+        v4f acc[MU][NT];
 #pragma unroll
-        for (int mi = 0; mi < MT; ++mi)
+        for (int mi = 0; mi < MU; ++mi)
 #pragma unroll
             for (int ni = 0; ni < NT; ++ni) acc[mi][ni] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 
         // The scales first, held until the end.  (Behind the first requests, or a few steps before the end, the waits for
         // requests become waits for more of them: FP6 32 x 5120 x 20480 15.5 us, 15.8 and 17.3.  The fence keeps the loads here.)
-        TileScales<MT, NT, WK> scales;
-        tile_scales<MT, NT, WN, WK>(scales, row_scale, w_scale, T, O, m0, n0, w, wk, lane);
+        TileScales<MU, NT, WK> scales;
+        tile_scales<MU, NT, WN, WK>(scales, row_scale, w_scale, T, O, m0, n0, w, wk, lane);
         asm volatile("" ::: "memory");
         request_first();
 #pragma unroll
@@ -575,7 +578,7 @@ gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__
             __builtin_amdgcn_sched_barrier(0);
             if (FULL || kt + 1 < nk) read(nxt, next_slot);
 #pragma unroll
-            for (int mi = 0; mi < MT; ++mi)
+            for (int mi = 0; mi < MU; ++mi)
 #pragma unroll
                 for (int ni = 0; ni < NT; ++ni) acc[mi][ni] = mfma6(cur.a[mi], cur.b[ni], acc[mi][ni]);
             __builtin_amdgcn_sched_barrier(0);
@@ -597,26 +600,26 @@ gemm_f6_staged_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__
             if (kt + 1 < nk) step(no{}, kt + 1, f1, f0);
         }
         __syncthreads();                                                 // the ring is free: it holds the partial sums now
-        sum_and_store<MT, NT, WM, WN, WK>(acc, lds, scales, w, wk, lane, T, O, Y, ldy, acc_debug, m0, n0, true);
+        sum_and_store<MU, NT, WM, WN, WK>(acc, lds, scales, w, wk, lane, T, O, Y, ldy, acc_debug, m0, n0, true);
         __syncthreads();
     }
 }
 
-template <int MT, int WM, int WN, int WK, int S, bool ONCE = false>
+template <int MT, int WM, int WN, int WK, int S, bool ONCE = false, int MU = MT>
 hipError_t launch_f6_staged(const uint8_t* qx6, const float* row_scale, const uint8_t* qw6, const float* w_scale, int T, int I,
                             int O, uint16_t* Y, int64_t ldy, int32_t* acc_debug, hipStream_t stream) {
     constexpr int TM = 16 * MT * WM, TN = 64 * WN;
-    constexpr int kRing = S * WK * (TM + TN) / 32 * 2 * kFragBytes, kParts = kPartsBytes<MT, 4, WM, WN, WK>;
+    constexpr int kRing = S * WK * (TM + TN) / 32 * 2 * kFragBytes, kParts = kPartsBytes<MU, 4, WM, WN, WK>;
     constexpr int kLds = kRing > kParts ? kRing : kParts;
     static_assert(kLds <= 160 * 1024, "LDS budget of a gfx950 CU");
     const int tiles_m = (T + TM - 1) / TM;
     const int64_t total = (int64_t)tiles_m * ((O + TN - 1) / TN);
     if (total >= (int64_t)1 << 31) return hipErrorInvalidValue;
     static std::atomic<uint64_t> allowed{0};
-    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_f6_staged_kernel<MT, WM, WN, WK, S, ONCE>), kLds, allowed);
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_f6_staged_kernel<MT, WM, WN, WK, S, ONCE, MU>), kLds, allowed);
     if (e != hipSuccess) return e;
     const int64_t blocks = std::min<int64_t>((total + kXcds - 1) / kXcds * kXcds, (int64_t)1 << 20);
-    gemm_f6_staged_kernel<MT, WM, WN, WK, S, ONCE><<<dim3((unsigned)blocks), dim3(64 * kSplitWaves), kLds, stream>>>(
+    gemm_f6_staged_kernel<MT, WM, WN, WK, S, ONCE, MU><<<dim3((unsigned)blocks), dim3(64 * kSplitWaves), kLds, stream>>>(
         qx6, row_scale, qw6, w_scale, T, I, O, Y, ldy, acc_debug, tiles_m, (int)total);
     return hipGetLastError();
 }
@@ -1027,7 +1030,9 @@ hipError_t launch_w4a4_linear(const void* qx6, const float* row_scale, const voi
             return once ? launch_f6_staged<2, 2, 2, 2, 4, true>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream)
                         : launch_f6_staged<2, 2, 2, 2, 4>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
         case 2: return launch_f6_staged<2, 2, 1, 4, 3>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
-        case 3: return launch_f6_staged<2, 1, 1, 8, 2>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
+        case 3:
+            return T <= 16 ? launch_f6_staged<2, 1, 1, 8, 2, false, 1>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream)
+                           : launch_f6_staged<2, 1, 1, 8, 2>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, acc_debug, stream);
         default: break;
     }
     const bool stream_y = !y_stays_cached(T, O);
