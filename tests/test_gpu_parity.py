@@ -1472,8 +1472,9 @@ def test_linear_on_either_side_of_the_line_between_its_kernels(cq, T, I, O, kern
     assert len(names) == 1 and "gemm_i8_" + kernel in names[0]
 
 
-# Outputs that tiles of 256 x 32 nt cover in one round of 256 CUs, for each nt, ragged on both edges and not; I: one to five steps
-@pytest.mark.parametrize("I", [128, 256, 384, 512, 640])
+# Outputs that tiles of 256 x 32 nt cover in one round of 256 CUs, for each nt, ragged on both edges and not; I: one to eight steps, and
+# the 32 of a real layer, where some sums pass 2^24 and are rounded to binary32
+@pytest.mark.parametrize("I", [128, 256, 384, 512, 640, 768, 896, 1024, 4096])
 @pytest.mark.parametrize("T,O,nt", [(1000, 8600, 5), (1024, 11008, 6), (2048, 8456, 9), (1900, 10000, 10), (4096, 5120, 10), (2040, 11256, 11)])
 def test_linear_in_one_round_of_tiles_of_another_width(cq, T, O, nt, I):
     import torch
@@ -1481,18 +1482,20 @@ def test_linear_in_one_round_of_tiles_of_another_width(cq, T, O, nt, I):
     g = torch.Generator(device="cuda").manual_seed(T + I)
     qx = torch.randint(-127, 128, (T, I), generator=g, device="cuda", dtype=torch.int8)
     qw = torch.randint(-127, 128, (O, I), generator=g, device="cuda", dtype=torch.int8)
+    qx[2:40], qw[2:60] = qx[2:40].abs() | 64, qw[2:60].abs() | 64        # large sums of all residues
     qx[1], qw[1] = 127, -127                                 # the largest sums
     a, s = torch.rand(T, generator=g, device="cuda") * 1e-2, torch.rand(O, generator=g, device="cuda") * 1e-3
     buf = torch.full((T + 2, O + 8), 7.0, device="cuda", dtype=torch.float16)
     Y = buf[1:T + 1, :O]
     run = lambda: cq.crossquant_w8a8_linear(qx, a, qw, s, Y=Y)
     run()
-    acc = (qx.double() @ qw.double().t().contiguous()).float()          # exact: integers below 2^24
-    want = ((acc * a[:, None]) * s[None, :]).half()
+    acc = (qx.double() @ qw.double().t().contiguous()).int()            # exact: below 2^53
+    assert I < 4096 or bool((acc.float().double() != acc.double()).any())
+    want = ((acc.float() * a[:, None]) * s[None, :]).half()
     assert torch.equal(Y.contiguous().view(torch.int16), want.view(torch.int16))
     assert bool((buf[0] == 7.0).all() and (buf[-1] == 7.0).all() and (buf[:, O:] == 7.0).all())
     Y_acc, acc_out = cq.crossquant_w8a8_linear(qx, a, qw, s, want_acc=True)      # another kernel
-    assert torch.equal(acc_out.float(), acc) and torch.equal(Y_acc.view(torch.int16), want.view(torch.int16))
+    assert torch.equal(acc_out, acc) and torch.equal(Y_acc.view(torch.int16), want.view(torch.int16))
     names = launched(cq, run)
     assert len(names) == 1 and "gemm_i8_wide_kernelILi%dE" % nt in names[0]
 
@@ -1713,6 +1716,14 @@ def test_end_to_end_full_config_sampled(cq, name):
     # every output equals its own accumulator through the epilogue (checked on the GPU tensors)
     y_from_acc = ((acc.to(torch.float32) * a[:, None]) * s[None, :]).to(torch.float16)
     assert torch.equal(y_from_acc.view(torch.int16), Y.view(torch.int16))
+    # without the raw accumulators, as a layer runs it: C2 then goes to another kernel
+    run = lambda: cq.crossquant_w8a8_linear(codes, a, qw, s, Y=Y)
+    want = Y.clone()
+    Y.fill_(7)
+    run()
+    assert torch.equal(Y.view(torch.int16), want.view(torch.int16))
+    names = launched(cq, run)
+    assert len(names) == 1 and ("gemm_i8_wide_kernelILi11E" if name == "C2" else "gemm_i8_") in names[0]
 
 
 # ----------------------------------------------------------------------------- quantize inside the GEMM's activation load
@@ -1966,6 +1977,30 @@ def test_w4a4_linear_fp6(cq, T, I, O):
     assert np.array_equal(bits16(host(Y)), bits16(Y_ref))
     Y8, _ = cq.crossquant_w8a8_linear(gpu(qx), gpu(a), gpu(qw), gpu(s))          # the integer path agrees
     assert np.array_equal(bits16(host(Y8)), bits16(host(Y)))
+
+
+@pytest.mark.parametrize("T", [1, 5, 15, 16, 17])
+@pytest.mark.parametrize("I,O", [(128, 8), (1152, 72), (2304, 4096), (8192, 136)])
+def test_w4a4_linear_of_at_most_16_tokens(cq, T, I, O):
+    """Such calls leave the second half of every 32-token tile out.  Against exact products, with guarded rows and columns, with and without
+    the raw accumulators, and which instance it is."""
+    import torch
+    say("w4a4 linear of few tokens: %dx%dx%d" % (T, I, O))
+    g = torch.Generator(device="cuda").manual_seed(T + I)
+    qx = torch.randint(-7, 8, (T, I), generator=g, device="cuda", dtype=torch.int8)
+    qw = torch.randint(-7, 8, (O, I), generator=g, device="cuda", dtype=torch.int8)
+    a, s = torch.rand(T, generator=g, device="cuda") * 1e-2, torch.rand(O, generator=g, device="cuda") * 1e-1
+    px, pw = cq.crossquant_pack_fp6(qx), cq.crossquant_pack_fp6_weights(qw)
+    buf = torch.full((T + 2, O + 8), 7.0, device="cuda", dtype=torch.float16)
+    run = lambda: cq.crossquant_w4a4_linear(px, a, pw, s, T, I, O, Y=buf[1:T + 1, :O])
+    run()
+    acc = (qx.double() @ qw.double().t().contiguous()).int()
+    want = ((acc.float() * a[:, None]) * s[None, :]).half()
+    assert torch.equal(buf[1:T + 1, :O].contiguous().view(torch.int16), want.view(torch.int16))
+    assert bool((buf[0] == 7.0).all() and (buf[-1] == 7.0).all() and (buf[:, O:] == 7.0).all())
+    Y_acc, acc_out = cq.crossquant_w4a4_linear(px, a, pw, s, T, I, O, want_acc=True)
+    assert torch.equal(acc_out, acc) and torch.equal(Y_acc.view(torch.int16), want.view(torch.int16))
+    assert ("gemm_f6_staged_kernelILi2ELi1ELi1ELi8ELi2ELb0ELi%dE" % (1 if T <= 16 else 2)) in launched(cq, run)[0]
 
 
 # Contractions around the point where a tile has its first steps that ask for nothing (five to eight steps), with a partly
