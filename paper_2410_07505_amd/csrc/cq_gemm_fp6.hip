@@ -663,7 +663,7 @@ gemm_f6_wide_kernel(const uint8_t* __restrict__ qx6, const float* __restrict__ r
     constexpr int F = NT / 4, P = NT % 4 / 2;                // groups of 64 channels a wave has to itself, and shares
     constexpr int WTN = 16 * NT, BNW = 2 * WTN, kPair = 2 * kFragBytes;
     constexpr int kSets = NT < 12 ? 4 : 3;                   // weight tiles in registers: read kSets - 1 ahead (12: no room for more)
-        constexpr bool kDeep = NT < 10;                          // the operands' tiles in kSlots slots each, requested kSlots - 1 steps ahead
+    constexpr bool kDeep = NT < 10;                          // the operands' tiles in kSlots slots each, requested kSlots - 1 steps ahead
     constexpr int kSlots = NT == 4 ? 4 : 3, kSlotsA = kDeep ? kSlots : 2;
     constexpr int kTileA = 8 * kPair, kTileB = NT * kPair, kReq = (8 + NT) * 3;  // LDS bytes; 1 KiB requests
     constexpr int N = (kReq + 7) / 8;                        // ... of a wave at most: ids wave, wave + 8, ...
@@ -991,9 +991,9 @@ hipError_t launch_w4a4_linear(const void* qx6, const float* row_scale, const voi
     const uint8_t* qx = static_cast<const uint8_t*>(qx6);
     const uint8_t* qw = static_cast<const uint8_t*>(qw6);
     // Small tiles: the kind with the fewest rounds of tiles over the CUs times rows (TM + TN) a CU takes in per step, of equal
-    // ones the larger tile.  Measured at I = 4096 (us; ring first, then 32 x 64, 64 x 64, 64 x 128, 128 x 128): 32 x 4096 27 : 8.5
-    // 8.7 12.1 16; 256 x 4096 27 : 15.5 9.3 12.9 17.2; 512 x 4096 27 : 28.8 17.0 13.4 17.5; 1024 x 4096 28 : 57 32.0 25.5 19.2;
-    // 2048 x 4096 (two rounds of the last) 31 : 122 77 53 39; and 32 x 5120 x 20480 34.7 : 21.8 20.6 15.8 19.0.
+    // ones the larger tile.  Measured at I = 4096 (us; ring first, then 32 x 64, 64 x 64, 64 x 128, 128 x 128): 32 x 4096 26 : 7.7
+    // 8.6 10.9 14.1; 256 x 4096 26 : 14.9 9.1 11.5 14.6; 512 x 4096 27 : 28 16.8 12.3 15.5; 1024 x 4096 28 : 57 32 24.0 18.1;
+    // 2048 x 4096 (two rounds of the last) 31 : 123 76 48 34; and 32 x 5120 x 20480 32 : 21.7 21.0 15.5 17.3.
     static const int kinds[4][2] = {{128, 128}, {64, 128}, {64, 64}, {32, 64}};
     int64_t cost = INT64_MAX;
     int kind = -1;
@@ -1006,19 +1006,22 @@ hipError_t launch_w4a4_linear(const void* qx6, const float* row_scale, const voi
         }
     }
     // Taken where they are faster than the ring's rounds of 256 x 256 tiles, in that unit times the contraction (100000 are about
-    // 1 us): up to 192 always, beyond with the fixed part of larger tiles or more rounds.  At the line, us, small tiles : ring: 512 x
-    // 128 x 4096 6.3 : 6.8 (192); 1024 x I x 4096 (256) 9.3 : 7.4 at I = 128, 9.9 : 9.2 at 512, 10.9 : 11.8 at 1024, 19.2 : 28.1 at 4096;
-    // 60 x I x 33024 (384) 12.5 : 9.4 at 512, 20.0 : 18.0 at 2048, 59.7 : 55.2 at 8192; 16 x I x 98304 (576, two rounds of the
-    // ring) 17.0 : 17.8 at 512, 58 : 68 at 4096; 128 x I x 81920 (768) 27.8 : 19.1 at 512, 73 : 81 at 4096.
+    // 1 us): up to 192 always, beyond with the fixed part of larger tiles or more rounds.  Around the line, us, small tiles : ring: 512 x
+    // 128 x 4096 5.7 : 7.1 (192); 1024 x I x 4096 (256) 7.3 : 7.6 at I = 128, 8.1 : 9.3 at 512, 9.3 : 12.1 at 1024, 17.7 : 28.5 at 4096;
+    // 60 x I x 33024 (384) 10.0 : 9.0 at 512, 18.0 : 18.0 at 2048, 57 : 52 at 8192; 16 x I x 98304 (576, two rounds of the
+    // ring) 16.1 : 17.9 at 512, 57 : 74 at 4096; 128 x I x 81920 (768) 21.3 : 19.5 at 512, 66 : 76 at 4096.  The 930 was fitted to
+    // earlier forms of the small tiles, so the line lies on the ring's side.
     const int64_t rounds = (total + n_cu - 1) / n_cu;
     const int64_t ring_time = rounds * ((int64_t)500 * I + 110000) - (int64_t)100 * I;
-    // One round of 256 x 128 tiles (w4a4_wide_tile) is ahead of two rounds of 128 x 128 at every contraction, of one of them at short ones:
-    // 1000 x I x 4096, 128 x 128 : 256 x 128 : ring, 7.2 : 6.1 : 7.6 us at I = 128, 8.0 : 7.9 : 9.5 at 512, 8.7 : 8.8 : 10.7 at 768, 9.3 : 9.7 : 12.0
-    // at 1024, 19.4 : 24.2 : 29.7 at 4096.  From I = 640 on such calls keep the line above: the kernel on its short side is pinned there.
+    // One round of 256 x 128 tiles (w4a4_wide_tile) is ahead of two rounds of 128 x 128 at every contraction, and of one of them at short
+    // ones; the ring is behind both then.  128 x 128 : 256 x 128 : ring, us: 1000 x I x 4096 7.3 : 6.2 : 7.6 at I = 128, 8.0 : 7.7 : 9.3 at 512, 8.5 :
+    // 8.25 : 9.9 at 640, 8.5 : 8.7 : 10.6 at 768, 9.0 : 9.2 : 11.2 at 896, 17.7 : 22.5 : 28.6 at 4096; 500 x I x 8192 8.4 : 8.2 : 10.0 at 640, 8.5 : 8.6 :
+    // 10.6 at 768; 2000 x I x 2048 8.4 : 8.2 : 9.9 and 8.5 : 8.6 : 10.6.
     const int cu_blocks = n_cu >= kXcds ? n_cu / kXcds * kXcds : kXcds;      // the larger tiles: one block per CU, a multiple of the XCDs
     int wide = acc_debug ? 0 : w4a4_wide_tile(T, I, O, cu_blocks);
-    if (wide == 4 && cost <= 256 && I >= 640) wide = 0;
-    if (cost > 192 && (wide == 4 || cost * (I + 930) >= ring_time)) kind = -1;
+    const bool one_round = wide == 4 && cost <= 256;                         // of either
+    if (one_round && I > 640) wide = 0;
+    if (cost > 192 && (wide == 4 || (!one_round && cost * (I + 930) >= ring_time))) kind = -1;
     // weights that one row of tiles reads once and that no cache keeps: see launch_w8a8_staged (32 x 8192 x 28672 33.9 -> 32.2
     // us, 64 x 8192 x 28672 35.3 -> 34.1)
     const bool once = kind >= 0 && T <= kinds[kind][0] && (int64_t)O * I / 4 * 3 > (int64_t)128 << 20;
@@ -1036,7 +1039,7 @@ hipError_t launch_w4a4_linear(const void* qx6, const float* row_scale, const voi
         default: break;
     }
     const bool stream_y = !y_stays_cached(T, O);
-    switch (wide) {                                          // (one round of the first two is at most 25 MiB of Y)
+    switch (wide) {                                          // (one round of the first two is at most 24 MiB of Y)
         case 4: return launch_f6_wide<4, false>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, cu_blocks, stream);
         case 6: return launch_f6_wide<6, false>(qx, row_scale, qw, w_scale, T, I, O, Y, ldy, cu_blocks, stream);
         case 10:

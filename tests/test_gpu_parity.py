@@ -2053,7 +2053,8 @@ def test_w4a4_linear_tiles_that_split_the_contraction(cq, T, O, I):
     assert np.array_equal(bits16(host(Y)), bits16(Y_ref))
 
 
-@pytest.mark.parametrize("T,I,O,kernel", [(1000, 640, 4088, "ring_kernelILb0"),        # a round of 128 x 128 tiles or of 256 x 256
+@pytest.mark.parametrize("T,I,O,kernel", [(1000, 640, 4088, "wide_kernelILi4E"),       # a round of 128 x 128 tiles or of 256 x 128
+                                          (1000, 768, 4088, "staged_kernelILi4E"),
                                           (1000, 1024, 4088, "staged_kernelILi4E"),
                                           (505, 128, 4088, "staged_kernelILi2ELi2ELi2E"),
                                           (60, 2048, 33024, "ring_kernelILb0"),        # two rounds of 64 x 128, or 129 tiles
