@@ -60,8 +60,9 @@ typedef enum {
  *    with ldx % 8 == 0 and I % 8 == 0 is the layout the loads are made for; any other takes unaligned
  *    16-byte loads).
  * t: out, float[T].  c: out, float[I].  Both are exact (a maximum of binary16 values).
- * The maxima are accumulated with atomics, so t and c are cleared first, inside the call.  That is
- * done by the one launch itself: its first blocks store the
+ * At most 64 rows of at most 8192 columns of the layout the loads are made for: every maximum is formed in one
+ * place and stored.  Otherwise the maxima are accumulated with atomics, so t and c are cleared first, inside the call.
+ * That is done by the one launch itself: its first blocks store the
  * zeros and the others wait for them (a bounded wait on a counter in library-owned device memory, one
  * per stream handle as for crossquant_quantize's zero count; other layouts have 16 counters of their own, so that
  * their calls take none of those) before their atomics.  Calls captured

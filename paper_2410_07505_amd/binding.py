@@ -556,10 +556,9 @@ def crossquant_kernel_analysis(X: torch.Tensor, t: torch.Tensor, c: torch.Tensor
                                col_scale: torch.Tensor = None, counters: torch.Tensor = None,
                                work_vectors: bool = True):
     """"Remove Kernel" matrix (float16 [T][I] or None) and a three-element int64 tensor
-    {kernel size, #{c_j >= t_i}, #{B~_ij < B_ij}}.  row_scale / col_scale receive the scale factors
-    (allocated here when not given); work_vectors=False passes NULL for both instead."""
-    if (counters is not None and (xrk is not None or not want_xrk)
-            and (row_scale is not None or col_scale is not None or not work_vectors)):
+    {kernel size, #{c_j >= t_i}, #{B~_ij < B_ij}}.  row_scale / col_scale: optional buffers that receive the scale factors;
+    the library needs none, and work_vectors makes no difference."""
+    if counters is not None and (xrk is not None or not want_xrk):
         status = _fast.kernel_analysis(X, t, c, alpha, bits, xrk, row_scale, col_scale, counters)
         if status != _NOT_PLAIN:
             _check(status)
@@ -569,9 +568,6 @@ def crossquant_kernel_analysis(X: torch.Tensor, t: torch.Tensor, c: torch.Tensor
     dev = X.device
     if xrk is None and want_xrk:
         xrk = torch.empty((T, I), dtype=torch.float16, device=dev)
-    if work_vectors and row_scale is None and col_scale is None:
-        row_scale = torch.empty(T, dtype=torch.float32, device=dev)
-        col_scale = torch.empty(I, dtype=torch.float32, device=dev)
     if counters is None:
         counters = torch.empty(3, dtype=torch.int64, device=dev)
     _buf(t, torch.float32, (T,), "t", X)

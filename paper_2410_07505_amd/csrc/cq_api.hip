@@ -1,6 +1,6 @@
 // C-ABI entry points: argument validation on the host, then kernel launches on the caller's
 // stream.  No allocation and no host synchronisation.  The library does hold a little process-wide
-// state, all of it behind these calls: the table that gives every stream handle a slot of device-side
+// state, all of it behind these calls: the tables that give every stream handle slots of device-side
 // accumulators (cq_slots.hip: the quantize and analysis kernels' count words, the counters of the absmax
 // launch that clears for itself, with the values they reach kept on the host, the barrier words of the
 // single-read kernel and its poll limit), the device addresses of those, and one flag per kernel and device
@@ -179,7 +179,7 @@ int crossquant_kernel_analysis_static(const void* X, int64_t T, int64_t I, int64
                                       float alpha, int bits, void* xrk, unsigned long long* counters, void* stream) {
     if (!t || !c || !counters) return CQ_ERR_NULL;
     if (int s = check_matrix(X, T, I, ldx)) return s;
-    if (T > CQ_ANALYSIS_STATIC_MAX || I > CQ_ANALYSIS_STATIC_MAX) return CQ_ERR_SHAPE;
+    if (T > CQ_ANALYSIS_STATIC_MAX || I > CQ_ANALYSIS_STATIC_MAX) return CQ_ERR_SHAPE;      // its contract; the kernel takes more
     if (bits != 4 && bits != 8) return CQ_ERR_BITS;
     if (!(alpha >= 0.0f && alpha <= 1.0f)) return CQ_ERR_ALPHA;
     if (!aligned(t, 4) || !aligned(c, 4) || !aligned(xrk, 2) || !aligned(counters, 8)) return CQ_ERR_ALIGN;

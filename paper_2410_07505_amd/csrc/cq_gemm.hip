@@ -425,17 +425,20 @@ hipError_t launch_w8a8_linear(const int8_t* qx, const float* row_scale, const in
                          al16(acc_debug) && ldy < ((int64_t)1 << 22);
     // The smaller tiles of cq_gemm_staged.hip where they take less time by what both were measured to take: in the unit of
     // w8a8_staged_time a round of half tiles here 336 I + 164000, one of whole tiles 500 I + 300000 (the latter is compared only
-    // with small tiles for few tokens and more than 32768 channels).  At the line, us, small tiles : ring:
-    //   64 x 128 tiles   512 x 512 x 4096 7.4 : 6.3, 512 x 1024 x 4096 8.4 : 8.4, 512 x 2048 x 4096 10.6 : 13.0, 512 x 4096 x 4096 15.6 : 22.4
-    //   128 x 128 tiles  1024 x 512 x 4096 9.2 : 7.0, 1024 x 2048 x 4096 14.7 : 13.6, 1024 x 4096 x 4096 23.0 : 24.0, 512 x 8192 x
-    //                    5120 33.6 : 40.3, 128 x 8192 x 28672 54.2 : 64.1, 256 x 4096 x 11008 21.1 : 22.8, 1024 x 11008 x 4096 50.4 : 57.6
-    //   whole tiles      60 x 1024 x 49152 17.3 : 15.6, 60 x 2048 x 49152 26.9 : 25.6, 60 x 8192 x 49152 88 : 102, 16 x 512 x 98304
-    //                    13.8 : 17.0
+    // with small tiles for few tokens and more than 32768 channels).  Around the line, us, small tiles : ring:
+    //   64 x 128 tiles   512 x 512 x 4096 7.4 : 6.8, 512 x 1024 x 4096 8.1 : 8.7, 512 x 2048 x 4096 10.2 : 13.5, 512 x 4096 x 4096 14.6 : 23.3
+    //   128 x 128 tiles  1024 x 512 x 4096 8.1 : 7.2, 1024 x 1024 x 4096 9.8 : 9.8, 1024 x 2048 x 4096 13.4 : 14.8, 1024 x 4096 x 4096 21.7 : 25.9,
+    //                    512 x 8192 x 5120 31.1 : 42.2, 256 x 4096 x 11008 19.2 : 23.8, 1024 x 11008 x 4096 47.1 : 61.2, but 128 x 8192 x 28672
+    //                    54.2 : 51.1
+    //   64 x 64 tiles, two rounds and more   60 x 1024 x 49152 18.2 : 16.1, 60 x 2048 x 49152 24.6 : 25.9, 60 x 8192 x 49152 83 : 92
+    //   32 x 64 tiles    16 x 512 x 98304 13.3 : 17.3
+    // The times that the line compares were fitted to earlier forms of these kernels: it lies on the ring's side by about 1 us, which
+    // 512 x 1024 x 4096 and 1024 x 2048 x 4096 show.
     // (a constant line, 240 against the rounds times (TM + TN) of the small tiles, lost up to 40 % on either side of it)
     int64_t ring_time = (int64_t)((n_main + n_cu - 1) / n_cu) * ((int64_t)500 * I + 300000) + (n_main < total ? (int64_t)336 * I + 164000 : 0);
     // Tiles of another width where one round of them takes less than the rounds here: a round of whole tiles is 100, one of half
     // tiles 42 behind whole ones and 60 by itself (2048 x 4096 x O: O = 8448, 264 tiles, 68.5 us, of 288 columns 54.0; O = 11776, 368
-    // tiles, 73.5 against 114 for two rounds of 352).  One round is at most 46 MiB of Y, which stays in the caches as there.  Not for
+    // tiles, 73.5 against 114 for two rounds of 352).  One round is at most 44 MiB of Y, which stays in the caches as there.  Not for
     // few tokens, which were not measured, nor with the raw accumulators, which that kernel does not store.
     int wide_units = 0;
     const int ring_units = 100 * ((n_main + n_cu - 1) / n_cu) + (n_main < total ? (n_main ? 42 : 60) : 0);

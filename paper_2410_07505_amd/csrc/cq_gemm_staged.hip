@@ -39,7 +39,7 @@ __device__ __forceinline__ v4i load16_tail(const int8_t* row, int kb, int I) {
 // requested into it) and step kt + 1 has landed (its fragments are read while kt is multiplied): one barrier a step.
 // DMA: operands aligned to 16 bytes with I % 16 == 0 go straight to LDS; pieces past a row's end come from a zero
 // block.  Otherwise (I >= 16) they pass through registers, loaded unaligned two steps before they are stored: 512 x 2752 x
-// 4096 takes 13.8 us in the first form, 512 x 2756 x 4096 15.5 us in the second (whether rows start on a word or a byte makes
+// 4096 takes 13.7 us in the first form, 512 x 2756 x 4096 15.0 us in the second (whether rows start on a word or a byte makes
 // 1 us; with one step in registers, and the row's end dealt with in every step, which spilled, 19.9 us).
 // ONCE: the weights' requests are non-temporal.
 template <int MT, int NT, int WM, int WN, int WK, int S, bool DMA, bool ONCE>
@@ -267,11 +267,11 @@ gemm_i8_short_kernel(const int8_t* __restrict__ qx, const float* __restrict__ ro
 
 // Tile kinds by what a CU has to take in for one byte of the contraction of one tile (TM + TN rows).  The cost of a launch is the
 // rounds of tiles over the CUs times that; of equal ones the smaller tile is taken.  Measured at I = 4096 (us, best kind
-// first): 16 x 4096 5.5 (16 x 16), 6.3 (32 x 32), 8.0 (32 x 64); 64 x 4096 6.9 (32 x 32), 8.0 (32 x 64), 9.6 (64 x 64);
-// 64 x 11008 11.0 (64 x 64), 12.4 (32 x 64), 16.2 (32 x 32); 256 x 4096 10.1 (64 x 64), 11.8 (32 x 64), 14.1 (64 x 128);
-// 512 x 4096 15.5 (64 x 128), 18.2 (64 x 64), 20.8 (128 x 128); the rule picks the first of each.  Off the 16-byte layout
-// likewise: 128 x 2750 x 4090 9.6 (32 x 64), 11.7 (64 x 64), 15.1 (32 x 32); 509 x 2750 x 4090 17.8 (64 x 128), 18.9
-// (64 x 64), 21.0 (128 x 128); 1000 x 2750 x 4090 24.0 (128 x 128), 33.6 (64 x 128).
+// first): 16 x 4096 4.7 (16 x 16), 5.7 (32 x 32), 7.1 (32 x 64); 64 x 4096 7.1 (32 x 32), 7.2 (32 x 64), 9.1 (64 x 64);
+// 64 x 11008 11.6 (64 x 64), 12.7 (32 x 64), 16.6 (32 x 32); 256 x 4096 10.5 (64 x 64), 11.7 (32 x 64), 12.6 (64 x 128);
+// 512 x 4096 14.7 (64 x 128), 18.2 (128 x 128), 19.4 (64 x 64); the rule picks the first of each.  Off the 16-byte layout
+// likewise: 128 x 2750 x 4090 9.1 (32 x 64), 10.2 (64 x 64), 13.1 (32 x 32); 509 x 2750 x 4090 17.5 (64 x 128), 18.6
+// (64 x 64), 21.0 (128 x 128); 1000 x 2750 x 4090 24.7 (128 x 128), 34.2 (64 x 128).
 static const int kKinds[][2] = {{16, 16}, {32, 32}, {32, 64}, {64, 64}, {64, 128}, {128, 128}};
 constexpr int kNumKinds = 6;
 
@@ -295,9 +295,10 @@ static int best_kind(int T, int O, int n_cu, int64_t* cost) {
 
 // The time of the launch in the unit of the kinds' cost (one operand row and one byte of the contraction; 75000 of them are
 // about 1 us), with what a round of tiles takes besides: first requests, partial sums, stores.  Fitted to launches of 1 to 6
-// rounds with I from 128 to 8192, e.g. one round of 64 x 64 tiles 4.2 us + 1.45 us per 1024 bytes of I, of 64 x 128 6.0 + 2.4, of
-// 128 x 128 6.6 + 3.5.  More than 2048 tokens under 128 x 128 tiles are left to the ring: every XCD walks one column of
-// tiles there and fetches all the activations (4096 x 4096 x 1024 26.7 us against 24.3; 2048 x 4096 x 2048 23.7 : 24.3).
+// rounds with I from 128 to 8192; at that time one round of 64 x 64 tiles took 4.2 us + 1.45 us per 1024 bytes of I, of 64 x 128 6.0 + 2.4,
+// of 128 x 128 6.6 + 3.5.  Now, from 1024 to 4096 bytes, 4.4 + 1.6, 5.9 + 2.2 and 6.0 + 3.9.  More than 2048 tokens under 128 x 128 tiles
+// are left to the ring: every XCD walks one column of tiles there and fetches all the activations (4096 x 4096 x 1024 25.4 us against
+// 25.3; 2048 x 4096 x 2048 22.5 : 25.8).
 int64_t w8a8_staged_time(int T, int I, int O, int n_cu) {
     static const int kRound[kNumKinds] = {82000, 142000, 90000, 187000, 329000, 351000};
     int64_t cost = 0;
